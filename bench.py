@@ -16,7 +16,7 @@ XNOR/popcount kernel (snn_bnn_conv2d on the decoded kernels) for the speed-up.
 
 Prints ONE JSON line: the metric (GOPS-equivalent of the dense convolutions the layers equal, plus the speed-up
 over the 1-bit kernel), a `roofline` object for the convolution launch (algorithmic bytes, gather-adds and
-responses of Sec. 4.5, the one-hot slots the kernel spends per gather as launched, fractions against the vendor
+responses of Sec. 4.5, the contraction slots the kernel spends per gather as launched, fractions against the vendor
 peaks and against peaks measured in this run by the probes of include/snn_peaks.h, HBM traffic from two
 rocprofv3 counter passes this script starts before it touches the GPU), a `configs` array (the other four
 workloads, each with its oracle check and a cold-cache series) and `cpu_baseline` (the CPU oracle timed on
@@ -42,6 +42,9 @@ MFMA_FP6_FP4_PEAK_FLOPS = 10.1e15          # dense FP6 / FP4 operands (v_mfma_f3
 # vector peak / 2 for FMA / 2 for the packed form)
 VALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
 MFMA_FLOP_32x32x64 = 2 * 32 * 32 * 64
+# contraction slots per input channel of the convolution as launched: the nine taps (the dense contraction on packed rows,
+# the library's own choice for these layers), over channels rounded up to blocks of 32
+SLOTS_PER_CHANNEL = 9
 
 COPY_CAL_BYTES = 256 * 1024 * 1024           # the copy probe of the counter passes reads and writes this much
 
@@ -112,12 +115,13 @@ def measure_traffic(args):
         for counter in ("FETCH_SIZE", "WRITE_SIZE"):
             per = _pmc_pass(counter, args, os.path.join(out_root, counter.lower()))
             cal = [v for k, vs in per.items() if "copy_kernel" in k for v in vs]
-            conv = [v for k, vs in per.items() if "subbit_stack_kernel" in k or "subbit_mfma" in k for v in vs]
+            conv = [v for k, vs in per.items() if "rows_fp4" in k or "subbit_stack_kernel" in k or "subbit_mfma" in k
+                    if "prep" not in k for v in vs]
             if not cal or not conv:
                 raise RuntimeError("kernels missing from the %s pass: %s" % (counter, sorted(per)))
             scale = COPY_CAL_BYTES / (sum(cal) / len(cal) * 1024.0)
             launches = 3
-            # a workload the stack kernel does not hold runs as several launches per call: sum per call
+            # a call can be several launches (layers beyond what one holds): sum per call
             per_call = sum(conv) / launches
             res[counter] = {"bytes": per_call * 1024.0 * scale, "scale": scale, "dispatches": len(conv)}
         f, w = res["FETCH_SIZE"], res["WRITE_SIZE"]
@@ -319,7 +323,7 @@ def measured_peaks(torch, np):
     return out
 
 
-def conv_roofline(layers, slots, t_s, peaks, accounting):
+def conv_roofline(layers, t_s, peaks, accounting):
     """The roofline object of a sub-bit convolution launch (or of the launches of a list of layers): Sec. 4.5's own
     units, the unit the kernel spends per gather as launched, fractions against vendor and measured peaks."""
     gather_adds = sum(accounting.stage2_gather_adds(L) for L in layers)
@@ -328,23 +332,17 @@ def conv_roofline(layers, slots, t_s, peaks, accounting):
     in_bytes = sum(L.N * L.C_in * L.H * ((L.W + 31) // 32) * 4 for L in layers)
     idx_bytes = sum(L.C_in * L.C_out * 2 for L in layers)
     alg_bytes = float(out_bytes + in_bytes + idx_bytes)
-    # flops the matrix cores execute for stage 2 as launched: 2 * slots per (pixel, c_out, c_in), channel counts
-    # rounded up to what one instruction holds (2 channels at 32 slots, 4 at 16, 1 at 64)
-    flops = 0.0
-    for L, sl in zip(layers, slots):
-        per_instr = 64 // sl
-        ci = (L.C_in + per_instr - 1) // per_instr * per_instr
-        flops += 2.0 * sl * L.pixels * L.C_out * ci
+    # flops the matrix cores execute as launched
+    flops = sum(2.0 * SLOTS_PER_CHANNEL * L.pixels * L.C_out * ((L.C_in + 31) // 32 * 32) for L in layers)
     t_hbm = alg_bytes / HBM_PEAK_BYTES
     t_unit = flops / MFMA_FP6_FP4_PEAK_FLOPS
     r = {
         "bound": "mfma" if t_unit >= t_hbm else "hbm",
         "alg_bytes": alg_bytes, "alg_bytes_split": {"in_packed": in_bytes, "out_f32": out_bytes, "idx_u16": idx_bytes},
         "gather_adds": gather_adds, "responses": responses,
-        "unit_used": "contraction slots of v_mfma_f32_32x32x64_f8f6f4 (FP4 one-hot selector x FP6 match counts, fp32 "
-                     "accumulators): stage 1 is a table row per window (no arithmetic), stage 2 spends `slots_per_channel` "
-                     "multiply-adds per gather-add, of which one is not a multiplication by zero",
-        "slots_per_channel": sorted(set(slots)) if len(set(slots)) > 1 else slots[0],
+        "unit_used": "contraction slots of v_mfma_f32_32x32x64_f8f6f4 (FP4 signs x FP4 signs, fp32 accumulators): "
+                     "`slots_per_channel` multiply-adds per gather-add, the nine taps of the kernel the index selects",
+        "slots_per_channel": SLOTS_PER_CHANNEL,
         "unit_flops_as_launched": flops,
         "t_kernel_us": t_s * 1e6,
         "t_floor_hbm_us": t_hbm * 1e6, "t_floor_unit_us": t_unit * 1e6,
@@ -358,9 +356,9 @@ def conv_roofline(layers, slots, t_s, peaks, accounting):
     }
     if peaks:
         bw = peaks["hbm_write_nontemporal_GBps"] * 1e9        # the launch writes 96 % of its bytes, with non-temporal stores
-        mf = peaks["mfma_f4f6_onehot_x_counts_TFLOPs"] * 1e12
+        mf = peaks["mfma_f4f6_random_TFLOPs"] * 1e12
         r["frac_vs_measured_peaks"] = max(alg_bytes / bw, flops / mf) / t_s
-        r["frac_vs_measured_note"] = ("max(alg_bytes / hbm_write_nontemporal, unit_flops_as_launched / mfma_f4f6_onehot_x_counts) "
+        r["frac_vs_measured_note"] = ("max(alg_bytes / hbm_write_nontemporal, unit_flops_as_launched / mfma_f4f6_random) "
                                       "/ t_kernel, both from peaks_measured")
     return r
 
@@ -438,7 +436,7 @@ def run_configs(bn, args, peaks, oracle):
                "timing": "conv_us / bnn_conv_us: %d launches back to back between one pair of HIP events; single_launch: one "
                          "pair per launch; cold: 512 MB written between launches, median of 7" % reps}
         if slots > 0:
-            rf = conv_roofline([L], [slots], t_conv * 1e-6, peaks, accounting)
+            rf = conv_roofline([L], t_conv * 1e-6, peaks, accounting)
             row["roofline"] = {k: rf[k] for k in ("bound", "alg_bytes", "gather_adds", "responses", "slots_per_channel", "frac",
                                                    "frac_hbm", "frac_unit", "useful_frac", "frac_vs_measured_peaks") if k in rf}
         if oracle is not None:
@@ -508,7 +506,7 @@ def run_configs(bn, args, peaks, oracle):
     row["bnn_conv_us_uniform_w9"] = bn.event_avg_us(bnn_uniform, reps)
     row["bnn_conv_us_same_weights"] = row["bnn_conv_us"]
     # the 1-bit layer through the sub-bit path: identity subset of all 512 kernels, idx = the kernel codes (an invariant
-    # check, Sec. 4.1: a 1-bit layer is the sub-bit layer whose subset is the whole set; runs on the LDS-gather kernel)
+    # check, Sec. 4.1: a 1-bit layer is the sub-bit layer whose subset is the whole set)
     d512 = B.make_desc(L.N, L.C_in, L.C_out, L.H, L.W, L.stride, 512, B.SNN_ACT_BIN_ROWS)
     ident = bn.dev(np.arange(512, dtype=np.uint16))
     ws512 = B.alloc_workspace(d512, B.SNN_WS_SUBBIT)
@@ -887,13 +885,11 @@ def main():
 
     dense_ops = sum(L.dense_ops for L in layers)
     in_bytes_packed = sum(L.N * L.C_in * L.H * ((L.W + 31) // 32) * 4 for L in layers)
-    slots = [B.snn_subbit_slots_per_channel(s["d_sub"]) for s in st]
     roofline = None
     if many_ok:
-        roofline = conv_roofline(layers, slots, t_conv_in_step_us * 1e-6, peaks, accounting)
-        roofline["kernel"] = ("subbit_stack_kernel: ONE launch per step runs the convolutions of all %d layers (resident workers of "
-                              "one wave draw (layer, tile) items); t_kernel = average over %d steps (the timed steps run a second time) of a "
-                              "HIP-event pair around that launch, on the launch stream" % (len(layers), args.steps))
+        roofline = conv_roofline(layers, t_conv_in_step_us * 1e-6, peaks, accounting)
+        roofline["kernel"] = ("rows_fp4_many_kernel: the convolutions of all %d layers, up to fifteen to a launch; t_kernel = average over %d steps (the timed steps run a second time) of a "
+                              "HIP-event pair around the call, on the launch stream" % (len(layers), args.steps))
         roofline["t_kernel_us_back_to_back"] = t_convs_b2b
         roofline["t_kernel_us_single_launch_median"] = t_convs_each[len(t_convs_each) // 2]
         roofline["t_kernel_us_single_launch_min"] = t_convs_each[0]

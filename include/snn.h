@@ -125,9 +125,12 @@ int snn_project_kernels(const float *w, int64_t n, const uint16_t *codebook, int
                         uint16_t *idx_out, void *stream);
 
 /*
- * Sec. 4.5 / Fig. 6: the sub-bit convolution.  Stage 1 convolves every input channel with the
- * K subset kernels (responses stay on chip), stage 2 sums, for each output channel, the
- * responses its indices select; then y = alpha * S.
+ * Sec. 4.5 / Fig. 6: the sub-bit convolution: every input channel convolved with the K subset
+ * kernels, and for each output channel the sum of the responses its indices select; then
+ * y = alpha * S.  For +-1 activations the sums are integers and the library is free in how it
+ * forms them: it contracts over (tap, input channel) on the matrix cores (nine slots per input
+ * channel); the two-stage kernels (K slots per input channel, or LDS gathers) run the layers that
+ * form does not take (rows of more than about a thousand pixels) and are selected by the tuning knobs below.
  *   desc      host; act = SNN_ACT_BIN_ROWS (+-1 activations) or SNN_ACT_F32
  *   x         device, activations in the layout desc->act names
  *   codebook  device, uint16 [K] 9-bit codes
@@ -147,10 +150,11 @@ int snn_subbit_conv2d(const snn_conv_desc *desc, const void *x, const uint16_t *
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results
  * and errors as snn_subbit_conv2d, without `workspace` / `ws_bytes`: the tables the call builds live
  * in a buffer inside the library, SNN_NOALLOC_MAX_WORKSPACE_BYTES per GPU, held until the process
- * ends.  The call allocates and frees nothing.  A layer whose tables need more
- * (snn_workspace_bytes(desc, SNN_WS_SUBBIT) > SNN_NOALLOC_MAX_WORKSPACE_BYTES) is refused with
+ * ends.  The call allocates and frees nothing.  A layer whose tables need more than
+ * SNN_NOALLOC_MAX_WORKSPACE_BYTES is refused with
  * SNN_ERR_WORKSPACE and nothing is enqueued; SNN_ERR_LAUNCH also if the buffer's address cannot be
- * obtained.  All calls on one GPU share the buffer: every call rebuilds what it reads, and calls
+ * obtained.  (The call picks a form whose tables fit: the limit is on the smaller of the two forms'
+ * tables.)  All calls on one GPU share the buffer: every call rebuilds what it reads, and calls
  * that overlap on one GPU (different streams, or threads) race - issue them on one stream.
  */
 #define SNN_NOALLOC_MAX_WORKSPACE_BYTES (4 * 1024 * 1024)
@@ -519,15 +523,16 @@ size_t snn_packed_bytes(int N, int C, int H, int W, int layout);
 /* Static, human-readable name of a status code. */
 const char *snn_status_string(int status);
 
-/* Contraction slots per input channel that the matrix-core form of the sub-bit convolution spends on
- * this layer as launched (Sec. 4.5: the method needs one of them, the gather; the others multiply a zero
- * of the one-hot operand): 32 (two channels per matrix instruction, K <= 32), 16 (four channels,
+/* Contraction slots per input channel that the two-stage (one-hot) matrix-core form of the sub-bit convolution spends on
+ * this layer (Sec. 4.5: the method needs one of them, the gather; the others multiply a zero
+ * of the one-hot operand; the dense contraction spends nine on any layer): 32 (two channels per matrix instruction, K <= 32), 16 (four channels,
  * K <= 16 on long channel runs), 64 (one channel, 32 < K <= 64); 0 where a kernel without matrix
  * instructions runs the layer (K > 64, C_in = 1, fp32 activations); negative SNN_ERR_* for an invalid desc.
  * Host-only; for the roofline accounting of a benchmark. */
 int snn_subbit_slots_per_channel(const snn_conv_desc *desc);
 
-/* Tuning and test switches.  Each knob holds SNN_TUNE_AUTO (the library's own choice) unless set; a knob's
+/* Tuning and test switches.  Setting one of SNN_TUNE_SUBBIT_MFMA, _MFMA_TILE, _MFMA_KS, _MFMA_STAGE, _MFMA_QUAD or
+ * _STACK sends the sub-bit layers to the two-stage kernels these describe.  Each knob holds SNN_TUNE_AUTO (the library's own choice) unless set; a knob's
  * first value is read ONCE, when the library first looks at any knob, from the environment variable named like
  * the knob without "TUNE_" (SNN_MFMA_TILE as "PB,CB").  They select among kernel forms that all compute the same result.
  * Table layouts in a workspace depend on them: a workspace written by a prepare call must be used under the

@@ -30,6 +30,20 @@ __device__ inline uint32_t or_of_eight_lanes(uint32_t w)
     return w;
 }
 
+// Index i of an index tensor: plain uint16 (tau = 0), or tau bits at bit i * tau of a little-endian bit
+// stream of 32-bit words (the storage format of Sec. 4.4 / Fig. 5: tau bits per kernel, tau / 9 per weight).
+__device__ inline uint32_t index_at(const void *__restrict__ idx, int64_t i, int tau)
+{
+    if (tau == 0) return ((const uint16_t *)idx)[i];
+    const uint32_t *w = (const uint32_t *)idx;
+    const int64_t bit = i * tau;
+    const int64_t word = bit >> 5;
+    const int sh = (int)(bit & 31);
+    uint32_t v = w[word] >> sh;
+    if (sh + tau > 32) v |= w[word + 1] << (32 - sh);
+    return v & ((1u << tau) - 1u);
+}
+
 constexpr int PACK_THREADS = 256;
 constexpr int PACK_U = 2;                                  // 16-byte loads in flight per thread (2: 7 % faster than 4 on 51 MB inputs)
 constexpr int PACK_CHUNK = PACK_THREADS * 4 * PACK_U;      // elements whose sign bits are staged in LDS per pass

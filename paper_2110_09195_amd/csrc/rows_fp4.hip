@@ -1,0 +1,1026 @@
+// The sub-bit 3x3 convolution on packed rows as a dense contraction over (tap, input channel) on the matrix cores:
+//
+//   S[co][pixel] = sum over taps t and input channels c of  w(co, c, t) * x(pixel, t, c),   w = codebook[idx[co][c]]
+//
+// with w, x in {+1, -1} (0 for taps outside the image and for padding channels) as FP4 e2m1 operands of
+// v_mfma_f32_32x32x64_f8f6f4.  All products are +-1 or 0 and |S| <= 9 C_in < 2^24, so the fp32 accumulator holds S
+// exactly and the results are those of the two-stage form bit for bit, for every subset size.
+//
+// Why not the one-hot form of the two stages (subbit_mfma.hip): gathering one of K responses costs that form K
+// contraction slots per input channel on a matrix unit (16, 32 or 64), this one costs nine, whatever K is.  Matrix
+// instructions of the ResNet-18 stack at batch 64, K = 32: 5.82 M there, 1.64 M here.  Measured, one-hot form -> this one:
+// that stack's convolutions 200 -> 91 us; 256 -> 256 14x14 batch 128 K = 32 32 -> 14.7 us; 512 -> 512 7x7 batch 256
+// K = 64 92 -> 29 us; K > 64 (the LDS-gather kernel) 100 -> 150 37x53 stride 2 batch 12 164 -> 12.5 us.
+//
+// Operands.  A step is 64 contraction slots; lane half h of a wave supplies 32 of them, the 32 channels of one
+// channel block at one tap:
+//   main steps   step 9 p + t: channel blocks 2 p (h = 0) and 2 p + 1 (h = 1), tap t
+//   last steps   (an odd number of channel blocks) the last block alone, taps 2 s (h = 0) and 2 s + 1 (h = 1); for the tap
+//                that does not exist the lanes read a zero pixel
+// Both operands are FP4 codes 0010 (+1 or -1 by the sign bit, bit 3): a set bit (+1) is stored with the sign bit set on
+// both sides, so that the sign bits are the packed bits themselves and the product comes out right.
+// A (weights) is kept at one bit per weight, 32 slots in a word whose bit 4 j + r is slot 8 r + j: two instructions make
+//   eight codes of it.  (As codes in memory, four times the bytes, the weights were the bound: a wave of 1 x 2 blocks
+//   needs 2 KB of codes per 64 clocks of matrix work.)
+// B (activations) is read from LDS as it is: a workgroup expands the packed rows its pixels touch into codes once,
+//   [channel block of 32][pixel] 16 bytes,
+//   on rows of W + 1 pixels (column -1 is a zero pixel and also the right border of the row above) and images of H + 1
+//   rows (a zero row above each image is also the bottom border of the one before): no tap needs a mask, and the
+//   window of an output pixel is nine reads at fixed distances.  Channels past C_in are zero here.
+#include "front_ops.h"
+#include "rows_fp4.h"
+
+#include <type_traits>
+
+namespace snn {
+
+namespace {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) const u32x4 lds_cu32x4;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+typedef __attribute__((address_space(3))) float lds_f32;
+typedef __attribute__((address_space(3))) const f32x4 lds_cf32x4;
+
+// words of a pair of channel blocks and 32 output channels: [lane] 16 bytes (taps 0..3), [lane] 16 bytes (4..7), [lane] 4 (8)
+constexpr uint32_t RF_PAIR_BYTES = 2304;
+constexpr uint32_t OFF_NONE = 0x80000000u;             // a lane offset past every buffer used here (all < 2 GiB)
+
+__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+}
+
+// One layer as the kernel sees it.
+struct RfLayer {
+    const uint32_t *x;       // packed rows [N][C_in][H][WW]
+    const uint32_t *wq;      // weights in operand layout
+    const float *scale;      // [2][32 n_cob]: alpha, then beta (sign epilogue), 0 for padding channels
+    void *out;               // float y, or packed rows of the signs
+    int N, C_in, C_out, H, W, WW, stride;
+    int Ho, Wo, HoWo, P;
+    int n_cob;               // blocks of 32 output channels
+    int ncb;                 // blocks of 32 input channels
+    int chunk;               // of which this many are expanded into LDS at a time (even unless all of them)
+    int pairs;               // pairs of channel blocks, the last one possibly half empty
+    int plane;               // bytes of one expanded channel block
+    int n_blk;               // blocks of up to 32 pixels
+    int n_cotiles, n_wgs;
+    int wpx_shift;           // log2 of the waves of a workgroup along pixels; the others share its pixels
+    int rows_pb, bpi, wpr;   // sign epilogue: rows per block, blocks per image, blocks per row
+    Divisor div_HoWo, div_Wo, div_H1, div_WW, div_cotiles, div_bpi, div_wpr, div_Ho;
+};
+
+// byte p of the four words -> o[p]
+__device__ __forceinline__ void bytes4(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t (&o)[4])
+{
+    const uint32_t ab_lo = __builtin_amdgcn_perm(b, a, 0x05010400u), ab_hi = __builtin_amdgcn_perm(b, a, 0x07030602u);
+    const uint32_t cd_lo = __builtin_amdgcn_perm(d, c, 0x05010400u), cd_hi = __builtin_amdgcn_perm(d, c, 0x07030602u);
+    o[0] = __builtin_amdgcn_perm(cd_lo, ab_lo, 0x05040100u);
+    o[1] = __builtin_amdgcn_perm(cd_lo, ab_lo, 0x07060302u);
+    o[2] = __builtin_amdgcn_perm(cd_hi, ab_hi, 0x05040100u);
+    o[3] = __builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u);
+}
+
+// ---- the convolution ----------------------------------------------------------------------------------------
+// A workgroup of four waves: 2^wpx_shift of them side by side along pixels, the others on further output channels of
+// the same pixels.  A wave owns PB blocks of 32 pixels x CB blocks of 32 output channels.  Pixel blocks: 32 consecutive
+// pixels of the flattened (n, ho, wo) order; for the sign epilogue whole output words (whole rows while they fit 32
+// pixels, else one word of a row), so that the wave that owns a block owns the words it writes.
+template <int PB, int CB, bool SIGN>
+__device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned char *const smem)
+{
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_l = lane & 31, h = lane >> 5;
+    // Workgroups go to the eight XCDs in turn: an XCD gets a contiguous run of tiles, so that neighbours in the output
+    // planes and the tiles that read the same packed rows share an L2.
+    {
+        const uint32_t per = (uint32_t)L.n_wgs >> 3, rem = (uint32_t)L.n_wgs & 7u, xcd = wg & 7u;
+        wg = xcd * per + min(xcd, rem) + (wg >> 3);
+    }
+    const uint32_t pxt = fast_div(wg, L.div_cotiles);
+    const int cot = (int)(wg - pxt * (uint32_t)L.n_cotiles);
+    const int wpx = wave & ((1 << L.wpx_shift) - 1), wco = wave >> L.wpx_shift;
+    const int wg_blk0 = (int)pxt * (PB << L.wpx_shift);
+    const int blk0 = wg_blk0 + wpx * PB;
+    const int cob0 = ((cot << (2 - L.wpx_shift)) + wco) * CB;
+    const bool active = cob0 < L.n_cob && blk0 < L.n_blk;       // wave-uniform; idle waves still fill LDS
+
+    // ---- pixels --------------------------------------------------------------------------------------------------
+    auto pixel_of = [&](int B, int px, int &n, int &ho, int &wo) -> bool {
+        bool ok = B < L.n_blk;
+        if (!ok) B = L.n_blk - 1;
+        if constexpr (!SIGN) {
+            int pp = B * 32 + px;
+            if (pp >= L.P) {
+                ok = false;
+                pp = L.P - 1;
+            }
+            n = (int)fast_div((uint32_t)pp, L.div_HoWo);
+            const int r = pp - n * L.HoWo;
+            ho = (int)fast_div((uint32_t)r, L.div_Wo);
+            wo = r - ho * L.Wo;
+        } else if (L.Wo <= 32) {
+            n = (int)fast_div((uint32_t)B, L.div_bpi);
+            const int rb = B - n * L.bpi;
+            int rl = (int)fast_div((uint32_t)px, L.div_Wo);
+            wo = px - rl * L.Wo;
+            ho = rb * L.rows_pb + rl;
+            if (rl >= L.rows_pb || ho >= L.Ho) {
+                ok = false;
+                ho = rb * L.rows_pb;
+                wo = 0;
+            }
+        } else {
+            const int R = (int)fast_div((uint32_t)B, L.div_wpr);
+            n = (int)fast_div((uint32_t)R, L.div_Ho);
+            ho = R - n * L.Ho;
+            wo = 32 * (B - R * L.wpr) + px;
+            if (wo >= L.Wo) {
+                ok = false;
+                wo = 32 * (B - R * L.wpr);
+            }
+        }
+        return ok;
+    };
+    // rows (numbered n (H + 1) + h + 1 over the batch) that the workgroup's pixels touch
+    const int H1 = L.H + 1, W1 = L.W + 1;
+    int R0, nrows, n0;
+    {
+        int ho, wo, n1, ho1, wo1;
+        pixel_of(wg_blk0, 0, n0, ho, wo);
+        R0 = n0 * H1 + ho * L.stride;
+        const int lastB = min(wg_blk0 + (PB << L.wpx_shift), L.n_blk) - 1;
+        if constexpr (!SIGN) {
+            pixel_of(lastB, min(31, L.P - 1 - 32 * lastB), n1, ho1, wo1);
+        } else {
+            pixel_of(lastB, 0, n1, ho1, wo1);
+            if (L.Wo <= 32) ho1 = min(ho1 + L.rows_pb, L.Ho) - 1;
+        }
+        nrows = n1 * H1 + ho1 * L.stride + 3 - R0;
+        R0 = __builtin_amdgcn_readfirstlane(R0);
+        nrows = __builtin_amdgcn_readfirstlane(nrows);
+        n0 = __builtin_amdgcn_readfirstlane(n0);
+    }
+
+    const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+    const uint32_t plane = (uint32_t)L.plane;
+    const uint32_t tile_lds = lds0 + 4u * CB * 32u * (SIGN ? 8u : 4u);      // behind the scales
+    // ---- packed rows -> FP4 codes in LDS --------------------------------------------------------------------------
+    // A task of a wave is 16 words (a word: 32 pixels of a row) of one channel block: lane (i, g) takes word i of the 8
+    // channels of group g - eight loads, a transposition of nibbles, two instructions per pixel - and four lanes side by
+    // side write the 16 bytes of a pixel.  The loads of a task are issued before the previous one is worked on.
+    const uint32_t xplane = (uint32_t)(L.H * L.WW) * 4u;
+    const int64_t image_words = (int64_t)L.C_in * L.H * L.WW;
+    const int64_t x_left = ((int64_t)(L.N - n0) * image_words) * 4;
+    const __amdgpu_buffer_rsrc_t xres = make_rsrc(L.x + (int64_t)n0 * image_words, (uint32_t)min(x_left, (int64_t)0x7fffffff));
+    const int RW = nrows * L.WW, nk = (RW + 15) >> 4;
+    const int grp = lane & 3;
+    struct Task {
+        int k, cb;                                             // words 16 k .. 16 k + 15, channel block
+        uint32_t w[8];
+        uint32_t addr, vmask;
+        int npx;                                               // pixels of the word
+        int edge;                                              // 1: the word starts a row, 2: the last row
+    };
+    auto load_task = [&](Task &T, int cb_first) {
+        const int rw = 16 * T.k + (lane >> 2);
+        const bool have = rw < RW;
+        const int row = (int)fast_div((uint32_t)rw, L.div_WW), word = rw - row * L.WW;
+        const int R = R0 + row;
+        const int n = (int)fast_div((uint32_t)R, L.div_H1), hh = R - n * H1;
+        const int cb0 = (cb_first + T.cb) * 32, c0 = cb0 + grp * 8;
+        const bool ok = have && hh > 0 && n < L.N && c0 < L.C_in;
+        const uint32_t off = (uint32_t)((((n - n0) * L.C_in + grp * 8) * L.H + hh - 1) * L.WW + word) * 4u;
+        if ((L.C_in & 7) == 0) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                T.w[j] = __builtin_amdgcn_raw_buffer_load_b32(xres, (int)(ok ? off : OFF_NONE), (int)((uint32_t)(cb0 + j) * xplane), 0);
+            T.vmask = ok ? 0xffffffffu : 0u;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                T.w[j] = __builtin_amdgcn_raw_buffer_load_b32(xres, (int)(ok && c0 + j < L.C_in ? off + (uint32_t)j * xplane : OFF_NONE),
+                                                              (int)((uint32_t)cb0 * xplane), 0);
+            T.vmask = !ok ? 0u : L.C_in - c0 >= 8 ? 0xffffffffu : (1u << (4 * (L.C_in - c0))) - 1u;
+        }
+        T.addr = tile_lds + (uint32_t)T.cb * plane + (uint32_t)(row * W1 + 1 + 32 * word) * 16u + (uint32_t)grp * 4u;
+        T.npx = have ? min(32, L.W - 32 * word) : 0;
+        T.edge = have && word == 0 ? (row == nrows - 1 ? 2 : 1) : 0;
+    };
+    auto store_task = [&](const Task &T) {
+        uint32_t ev[4], od[4];
+        bytes4(T.w[0], T.w[2], T.w[4], T.w[6], ev);
+        bytes4(T.w[1], T.w[3], T.w[5], T.w[7], od);
+        const uint32_t m8 = T.vmask & 0x88888888u, m2 = T.vmask & 0x22222222u;
+        if (T.edge) *(lds_u32 *)(uintptr_t)(T.addr - 16u) = 0u;
+        if (T.edge == 2) *(lds_u32 *)(uintptr_t)(T.addr + (uint32_t)L.W * 16u) = 0u;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            if (8 * p >= L.W) break;                           // (wave-uniform: short rows have no such pixels)
+            // D[m]: nibble j = pixels 4 m .. 4 m + 3 of channel j
+            const uint32_t D[2] = {(ev[p] & 0x0f0f0f0fu) | ((od[p] << 4) & 0xf0f0f0f0u), ((ev[p] >> 4) & 0x0f0f0f0fu) | (od[p] & 0xf0f0f0f0u)};
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const int px = 8 * p + 4 * m;
+                const uint32_t at = T.addr + (uint32_t)px * 16u;
+                if ((L.W & 3) == 0) {                          // (wave-uniform) words end at whole groups of four
+                    if (px < T.npx) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) *(lds_u32 *)(uintptr_t)(at + 16u * r) = ((D[m] << (3 - r)) & m8) | m2;
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (px + r < T.npx) *(lds_u32 *)(uintptr_t)(at + 16u * r) = ((D[m] << (3 - r)) & m8) | m2;
+                }
+            }
+        }
+    };
+    auto next_task = [&](Task &T) {
+        T.k += 4;
+        while (T.k >= nk) {
+            T.k -= nk;
+            ++T.cb;
+        }
+    };
+    Task task;
+    auto first_task = [&](int cb_first, int ncb) {
+        task.k = wave;
+        task.cb = 0;
+        while (task.k >= nk) {
+            task.k -= nk;
+            ++task.cb;
+        }
+        if (task.cb < ncb) load_task(task, cb_first);
+    };
+    auto fill = [&](int cb_first, int ncb) {
+        while (task.cb < ncb) {
+            Task nx;
+            nx.k = task.k;
+            nx.cb = task.cb;
+            next_task(nx);
+            if (nx.cb < ncb) load_task(nx, cb_first);
+            store_task(task);
+            task = nx;
+        }
+    };
+    first_task(0, min(L.chunk, L.ncb));
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- weights: the words of the first pair (and of the second, where a pair is too little work to hide a load) ----
+    const __amdgpu_buffer_rsrc_t wres = make_rsrc(L.wq, (uint32_t)(L.n_cob * L.pairs) * RF_PAIR_BYTES);
+    constexpr bool AHEAD = PB == 1;
+    uint32_t A[CB][9], An[AHEAD ? CB : 1][9];
+    auto load_words = [&](int pr, int cb, int piece, uint32_t (&a)[9]) {       // (past the last pair or block: the last one, not used)
+        const uint32_t at = (uint32_t)(min(cob0 + cb, L.n_cob - 1) * L.pairs + min(pr, L.pairs - 1)) * RF_PAIR_BYTES;
+        if (piece < 2) {
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(wres, lane * 16, (int)(at + 1024u * piece), 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[4 * piece + i] = v[i];
+        } else {
+            a[8] = __builtin_amdgcn_raw_buffer_load_b32(wres, lane * 4, (int)(at + 2048u), 0);
+        }
+    };
+    if (active) {
+#pragma unroll
+        for (int piece = 0; piece < 3; ++piece)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) load_words(0, cb, piece, A[cb]);
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int piece = 0; piece < 3; ++piece)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) load_words(1, cb, piece, An[cb]);
+        }
+    }
+    // scales of the workgroup's channels (4 CB blocks at most)
+    float early_scale[2] = {0.0f, 0.0f};
+    const int scale_first = (cot << (2 - L.wpx_shift)) * CB * 32;
+    const bool has_scale = tid < (CB * 32 << (2 - L.wpx_shift)) && scale_first + tid < 32 * L.n_cob;
+    {
+        const __amdgpu_buffer_rsrc_t sres = make_rsrc(L.scale, (uint32_t)L.n_cob * 256u);
+        const uint32_t off = has_scale ? (uint32_t)(scale_first + tid) * 4u : OFF_NONE;
+        early_scale[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sres, (int)off, 0, 0));
+        if constexpr (SIGN) early_scale[1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sres, (int)off, (int)((uint32_t)L.n_cob * 128u), 0));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- the lane's windows -----------------------------------------------------------------------------------------
+    uint32_t top[PB];                                          // LDS address of the window's first pixel, channel block 0
+    uint32_t yoff[PB];                                         // byte offset of y[n - n0][4 h][pixel]
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+        int n, ho, wo;
+        const bool ok = pixel_of(blk0 + pb, n_l, n, ho, wo);
+        const bool mine = blk0 + pb < L.n_blk;                 // (a block past the last one: any pixel of the tile)
+        top[pb] = tile_lds + (mine ? (uint32_t)((n * H1 + ho * L.stride - R0) * W1 + wo * L.stride) * 16u : 0u);
+        yoff[pb] = ok ? (uint32_t)(((n - n0) * L.C_out + 4 * h) * L.HoWo + ho * L.Wo + wo) * 4u : OFF_NONE;
+    }
+    const uint32_t pitch = (uint32_t)W1 * 16u;
+
+    v16f acc[CB][PB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[cb][pb][r] = 0.0f;
+
+    auto expand = [&](uint32_t w, u32x4 &a) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[r] = ((w << (3 - r)) & 0x88888888u) | 0x22222222u;
+    };
+    auto multiply = [&](const u32x4 (&a)[CB], const u32x4 (&b)[PB]) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+                const v8i av = {(int)a[cb][0], (int)a[cb][1], (int)a[cb][2], (int)a[cb][3], 0, 0, 0, 0};
+                const v8i bv = {(int)b[pb][0], (int)b[pb][1], (int)b[pb][2], (int)b[pb][3], 0, 0, 0, 0};
+                acc[cb][pb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc[cb][pb], 4, 4, 0, 0, 0, 0);
+            }
+    };
+
+    int pair = 0;                                              // of the whole layer
+    for (int cb_first = 0; cb_first < L.ncb; cb_first += L.chunk) {
+        const int here = min(L.chunk, L.ncb - cb_first);
+        if (cb_first > 0) {
+            first_task(cb_first, here);
+            __syncthreads();                                   // the previous blocks are no longer read
+        }
+        fill(cb_first, here);
+        if (cb_first == 0 && has_scale) {
+            *(lds_f32 *)(uintptr_t)(lds0 + (uint32_t)tid * 4u) = early_scale[0];
+            if constexpr (SIGN) *(lds_f32 *)(uintptr_t)(lds0 + 4u * CB * 32u * 4u + (uint32_t)tid * 4u) = early_scale[1];
+        }
+        __syncthreads();
+        if (!active) continue;
+        const int np = here >> 1;
+        u32x4 B[2][PB], E[2][CB];
+        uint32_t ad[PB];
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+            ad[pb] = top[pb] + (uint32_t)h * plane;
+            if (np > 0) B[0][pb] = *(lds_cu32x4 *)(uintptr_t)ad[pb];
+        }
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) expand(A[cb][0], E[0][cb]);
+        // One step: the matrix instructions of a tap, and the operands of the next one.
+        auto step = [&](auto tc, auto bufc, uint32_t next) {
+            constexpr int t = decltype(tc)::value, cur = decltype(bufc)::value, nxt = cur ^ 1;
+            if constexpr (t < 8) {
+                constexpr int dy = (t + 1) / 3, dx = (t + 1) % 3;
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+                    B[nxt][pb] = *(lds_cu32x4 *)(uintptr_t)(ad[pb] + (uint32_t)dy * pitch + (uint32_t)dx * 16u);
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) expand(A[cb][t + 1], E[nxt][cb]);
+            } else {
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) {
+                    ad[pb] += next;
+                    B[nxt][pb] = *(lds_cu32x4 *)(uintptr_t)ad[pb];
+                }
+                if constexpr (AHEAD) {
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) {
+#pragma unroll
+                        for (int i = 0; i < 9; ++i) A[cb][i] = An[cb][i];
+#pragma unroll
+                        for (int piece = 0; piece < 3; ++piece) load_words(pair + 2, cb, piece, An[cb]);
+                    }
+                }
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) expand(A[cb][0], E[nxt][cb]);
+            }
+            multiply(E[cur], B[cur]);
+            // words of the next pair as soon as those of this one have been expanded: at least five steps ahead
+            if constexpr (!AHEAD && (t == 3 || t == 7 || t == 8)) {
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) load_words(pair + 1, cb, t == 3 ? 0 : t == 7 ? 1 : 2, A[cb]);
+            }
+        };
+        auto run_pair = [&](auto par, uint32_t next) {
+            constexpr int p0 = decltype(par)::value;
+            step(std::integral_constant<int, 0>{}, std::integral_constant<int, p0>{}, next);
+            step(std::integral_constant<int, 1>{}, std::integral_constant<int, p0 ^ 1>{}, next);
+            step(std::integral_constant<int, 2>{}, std::integral_constant<int, p0>{}, next);
+            step(std::integral_constant<int, 3>{}, std::integral_constant<int, p0 ^ 1>{}, next);
+            step(std::integral_constant<int, 4>{}, std::integral_constant<int, p0>{}, next);
+            step(std::integral_constant<int, 5>{}, std::integral_constant<int, p0 ^ 1>{}, next);
+            step(std::integral_constant<int, 6>{}, std::integral_constant<int, p0>{}, next);
+            step(std::integral_constant<int, 7>{}, std::integral_constant<int, p0 ^ 1>{}, next);
+            step(std::integral_constant<int, 8>{}, std::integral_constant<int, p0>{}, next);
+            ++pair;
+        };
+        int pr = 0;
+        for (; pr + 2 <= np; pr += 2) {
+            run_pair(std::integral_constant<int, 0>{}, 2u * plane);
+            run_pair(std::integral_constant<int, 1>{}, pr + 2 < np ? 2u * plane : 0u);
+        }
+        if (pr < np) run_pair(std::integral_constant<int, 0>{}, 0u);
+        if (here & 1) {
+            // the last block alone: two taps per step
+            const uint32_t last = (uint32_t)(here - 1) * plane;
+#pragma unroll
+            for (int u = 0; u < 5; ++u) {
+                const int t0 = 2 * u, t1 = u < 4 ? 2 * u + 1 : 0;
+                const uint32_t o0 = (uint32_t)(t0 / 3) * pitch + (uint32_t)(t0 % 3) * 16u;
+                const uint32_t o1 = (uint32_t)(t1 / 3) * pitch + (uint32_t)(t1 % 3) * 16u;
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) {
+                    const uint32_t at = u == 4 && h ? tile_lds : top[pb] + (h ? o1 : o0);      // (the tile's first pixel is zero)
+                    B[0][pb] = *(lds_cu32x4 *)(uintptr_t)(at + last);
+                }
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) expand(A[cb][u], E[0][cb]);
+                multiply(E[0], B[0]);
+            }
+        }
+    }
+    if (!active) return;
+
+    const uint32_t scale_lane = lds0 + (uint32_t)(wco * CB * 32 + 4 * h) * 4u;
+    if constexpr (SIGN) {
+        // ---- the next layer's sign: bit = (fl(fl(S alpha) + beta) >= 0), packed rows ---------------------------------
+        // The 32 lanes of a half hold the pixels of one block of one channel: a ballot turns their signs into a bit
+        // string that holds the block's words of that channel.  Accumulator register r is channels cl and cl + 4, in
+        // the low and the high half of the ballot.
+        uint32_t *const out = (uint32_t *)L.out;
+        const int WWo = (L.Wo + 31) / 32;
+        const uint32_t oplane = (uint32_t)(L.Ho * WWo);
+        const bool short_rows = L.Wo <= 32;
+        const int wpb = short_rows ? L.rows_pb : 1;            // words of one channel in a block
+        const uint32_t wmask = L.Wo < 32 ? (1u << L.Wo) - 1u : 0xffffffffu;
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+            const int Bk = blk0 + pb;
+            if (Bk >= L.n_blk) continue;                       // (wave-uniform)
+            int bn, bword, bwords;                             // image, first word in a channel plane, words
+            if (short_rows) {
+                bn = (int)fast_div((uint32_t)Bk, L.div_bpi);
+                bword = (Bk - bn * L.bpi) * L.rows_pb;
+                bwords = min(L.rows_pb, L.Ho - bword);
+            } else {
+                const int R = (int)fast_div((uint32_t)Bk, L.div_wpr);
+                bn = (int)fast_div((uint32_t)R, L.div_Ho);
+                bword = (R - bn * L.Ho) * WWo + (Bk - R * L.wpr);
+                bwords = 1;
+            }
+            const unsigned long long okm = __ballot(yoff[pb] != OFF_NONE);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                if (cob0 + cb >= L.n_cob) continue;            // (wave-uniform)
+                uint32_t bits = 0;                             // lane c (and c + 32): the 32 signs of channel c of the block
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 al = *(lds_cf32x4 *)(uintptr_t)(scale_lane + (uint32_t)(cb * 32 + 8 * q) * 4u);
+                    const f32x4 be = *(lds_cf32x4 *)(uintptr_t)(scale_lane + (uint32_t)(4 * CB * 32 + cb * 32 + 8 * q) * 4u);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int r = 4 * q + i, cl = 8 * q + i;
+                        const unsigned long long m = __ballot(mul_then_add(acc[cb][pb][r], al[i], be[i]) >= 0.0f) & okm;
+                        const uint32_t m_lo = (uint32_t)m, m_hi = (uint32_t)(m >> 32);          // wave-uniform
+                        asm("v_writelane_b32 %0, %1, %2" : "+v"(bits) : "s"(m_lo), "n"(cl));
+                        asm("v_writelane_b32 %0, %1, %2" : "+v"(bits) : "s"(m_hi), "n"(cl + 4));
+                    }
+                }
+                const int co = (cob0 + cb) * 32 + n_l;         // the channel whose words this lane stores
+                uint32_t *const dst = out + (int64_t)(bn * L.C_out + co) * oplane + bword;
+                if (wpb == 1) {
+                    if (h == 0 && co < L.C_out) dst[0] = bits;
+                    continue;
+                }
+                // several words per channel and block (rows of up to 16 pixels): the lane halves store alternate words
+                const uint32_t mine = (uint32_t)__shfl((int)bits, n_l);
+                for (int j = h; j < bwords; j += 2)
+                    if (co < L.C_out) dst[j] = (mine >> (uint32_t)(j * L.Wo)) & wmask;
+            }
+        }
+        return;
+    }
+    // ---- y = alpha * S -------------------------------------------------------------------------------------------------
+    // Lanes 0..31 of a register are 32 consecutive pixels of one channel; register r is channel 8 (r / 4) + 4 h + r % 4.
+    const int64_t y_image = (int64_t)L.C_out * L.HoWo;
+    const int64_t y_left = (int64_t)(L.N - n0) * y_image * 4;
+    const __amdgpu_buffer_rsrc_t yres = make_rsrc((float *)L.out + (int64_t)n0 * y_image, (uint32_t)min(y_left, (int64_t)0x7fffffff));
+    const uint32_t chan = (uint32_t)L.HoWo * 4u;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        const int co0 = (cob0 + cb) * 32;
+        const bool whole = co0 + 32 <= L.C_out;                // (wave-uniform)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 al = *(lds_cf32x4 *)(uintptr_t)(scale_lane + (uint32_t)(cb * 32 + 8 * q) * 4u);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int c = co0 + 8 * q + i;                 // wave-uniform part of the channel
+                if (!whole && c + 4 * h >= L.C_out) continue;
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[cb][pb][4 * q + i] * al[i]), yres, (int)yoff[pb],
+                                                          (int)((uint32_t)c * chan), 2 /* non-temporal */);
+            }
+        }
+    }
+}
+
+template <int PB, int CB, bool SIGN>
+__global__ __launch_bounds__(256, PB == 4 ? 2 : PB * CB == 4 ? 3 : 4)
+void rows_fp4_kernel(const RfLayer L)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    rf_tile<PB, CB, SIGN>(L, blockIdx.x, smem);
+}
+
+// Several layers in one launch (fp32 output): workgroups [first[l], first[l + 1]) run layer l.  The layers share the
+// chip: while the workgroups of one layer store their outputs those of another multiply.
+constexpr int RF_MANY_MAX = 15;
+struct RfMany {
+    int n_layers;
+    int first[RF_MANY_MAX + 1];          // multiples of eight (the XCD of a workgroup inside its layer)
+    int form[RF_MANY_MAX];               // 10 PB + CB
+    RfLayer layer[RF_MANY_MAX];
+};
+static_assert(sizeof(RfMany) <= 4096, "kernel arguments");
+
+__global__ __launch_bounds__(256, 3)
+void rows_fp4_many_kernel(const RfMany m)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int b = blockIdx.x;
+    int l = 0;
+    while (l + 1 < m.n_layers && b >= m.first[l + 1]) ++l;              // block-uniform
+    const RfLayer &L = m.layer[l];
+    const uint32_t wg = (uint32_t)(b - m.first[l]);
+    if (wg >= (uint32_t)L.n_wgs) return;                                // padding to a multiple of eight
+    switch (m.form[l]) {
+    case 22: rf_tile<2, 2, false>(L, wg, smem); break;
+    case 12: rf_tile<1, 2, false>(L, wg, smem); break;
+    case 21: rf_tile<2, 1, false>(L, wg, smem); break;
+    default: rf_tile<1, 1, false>(L, wg, smem); break;
+    }
+}
+
+// ---- weights -> operand layout ---------------------------------------------------------------------------------------
+// Codes of up to 8 consecutive channels as three words of nibbles (nibble j: bits 0..3 of channel j's code in `lo`, 4..7 in
+// `mid`, bit 8 in `hi`) -> bits 4 j: tap t of channel j (code bit 8 - t).
+__device__ __forceinline__ uint32_t tap_bits(uint32_t lo, uint32_t mid, uint32_t hi, int t)
+{
+    const int bit = 8 - t;
+    return ((bit == 8 ? hi : bit >= 4 ? mid : lo) >> (bit & 3)) & 0x11111111u;
+}
+
+// Stores the words of (block of 32 output channels, channel co in it, input channel block cb): w[t] for tap t.
+__device__ __forceinline__ void store_words(uint32_t *wq, int cob, int co, int cb, int ncb, const uint32_t (&w)[9])
+{
+    const int pairs = (ncb + 1) >> 1;
+    unsigned char *const at = (unsigned char *)wq + (int64_t)(cob * pairs + (cb >> 1)) * RF_PAIR_BYTES;
+    if ((ncb & 1) && cb == ncb - 1) {
+        // the last block of an odd number: word u of lane half h is tap 2 u + h
+        *(u32x4 *)(at + co * 16) = (u32x4){w[0], w[2], w[4], w[6]};
+        *(u32x4 *)(at + (co + 32) * 16) = (u32x4){w[1], w[3], w[5], w[7]};
+        *(uint32_t *)(at + 1024 + co * 16) = w[8];
+        *(uint32_t *)(at + 1024 + (co + 32) * 16) = 0u;
+        return;
+    }
+    const int lane = co + 32 * (cb & 1);
+    *(u32x4 *)(at + lane * 16) = (u32x4){w[0], w[1], w[2], w[3]};
+    *(u32x4 *)(at + 1024 + lane * 16) = (u32x4){w[4], w[5], w[6], w[7]};
+    *(uint32_t *)(at + 2048 + lane * 4) = w[8];
+}
+
+struct RfWeights {
+    uint32_t *wq;
+    float *scale;
+    int C_in, C_out, n_cob, ncb;
+};
+
+__device__ __forceinline__ void store_scales(const RfWeights &W, int cob, int c, const float *alpha, const float *beta)
+{
+    const int co = cob * 32 + c;
+    W.scale[co] = co < W.C_out ? alpha[co] : 0.0f;
+    W.scale[32 * W.n_cob + co] = beta && co < W.C_out ? beta[co] : 0.0f;
+}
+
+// From indices (uint16, or tau bits each in a stream): 256 threads = 2 channel blocks x 32 output channels x 4 groups of 8
+// input channels (slots 8 d + j of a word are bits 4 j + d: the four groups of a word are four lanes).
+__global__ __launch_bounds__(256)
+void rows_fp4_prep_kernel(const RfWeights W, const uint16_t *__restrict__ codebook, int K, const void *__restrict__ idx, int tau,
+                          const float *__restrict__ alpha, const float *__restrict__ beta)
+{
+    __shared__ uint16_t codes[512];
+    const int tid = threadIdx.x;
+    const int d = tid & 3, co = (tid >> 2) & 31;
+    const int cob = blockIdx.x, cb = 2 * blockIdx.y + (tid >> 7);
+    const int c0 = cb * 32 + d * 8, oc = cob * 32 + co;
+    uint32_t k[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) k[j] = oc < W.C_out && c0 + j < W.C_in ? index_at(idx, (int64_t)oc * W.C_in + c0 + j, tau) : 0u;
+    for (int i = tid; i < K; i += 256) codes[i] = codebook[i] & 511u;
+    __syncthreads();
+    if (blockIdx.y == 0 && tid < 32) store_scales(W, cob, tid, alpha, beta);
+    if (cb >= W.ncb) return;
+    uint32_t lo = 0, mid = 0, hi = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t c = codes[min(k[j], (uint32_t)K - 1u)];
+        lo |= (c & 15u) << (4 * j);
+        mid |= ((c >> 4) & 15u) << (4 * j);
+        hi |= (c >> 8) << (4 * j);
+    }
+    uint32_t w[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        w[t] = tap_bits(lo, mid, hi, t) << d;
+        w[t] |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[t], 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, true);
+        w[t] |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[t], 0x4E /* quad_perm [2,3,0,1] */, 0xF, 0xF, true);
+    }
+    if (d == 0) store_words(W.wq, cob, co, cb, W.ncb, w);
+}
+
+// From real-valued kernels: the projection of Eq. 2 / Eq. 5 (idx_out as snn_project_kernels writes it) and the operand
+// layout.  A workgroup takes 32 output channels x 32 input channels; thread (co, e) the four kernels 4 e .. 4 e + 3 of
+// its output channel, so that eight threads read 1152 contiguous bytes and make one word per tap.
+struct RfProject {
+    RfWeights W;
+    const float *w;            // [C_out][C_in][9]
+    const uint16_t *codebook;
+    const float *alpha;
+    const float *beta;         // or nullptr
+    uint16_t *idx_out;         // [C_out][C_in]
+    int K;
+};
+constexpr int RF_PROJECT_LDS_WORDS = 64 * 12 + 32;
+
+__device__ __forceinline__ void rf_project_block(const RfProject &p, int block, uint32_t *lds)
+{
+    const RfWeights &W = p.W;
+    const int tid = threadIdx.x;
+    const int cob = block / W.ncb, cb = block - cob * W.ncb;
+    const int co = tid >> 3, e = tid & 7;
+    const int oc = cob * 32 + co, c0 = cb * 32 + 4 * e;
+    const int have = oc < W.C_out ? max(0, min(4, W.C_in - c0)) : 0;
+    const int64_t at = (int64_t)oc * W.C_in + c0;
+    float wt[4][9];
+    if (have == 4 && (((uintptr_t)(p.w + at * 9)) & 15) == 0) {
+        const float4 *src = (const float4 *)(p.w + at * 9);
+        float flat[36];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const float4 v = src[i];
+            flat[4 * i] = v.x;
+            flat[4 * i + 1] = v.y;
+            flat[4 * i + 2] = v.z;
+            flat[4 * i + 3] = v.w;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int t = 0; t < 9; ++t) wt[q][t] = flat[9 * q + t];
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int t = 0; t < 9; ++t) wt[q][t] = q < have ? p.w[(at + q) * 9 + t] : 0.0f;
+    }
+    float *coef = (float *)lds;
+    uint16_t *codes = (uint16_t *)(lds + 64 * 12);
+    project_fill_coef(coef, p.codebook, p.K, tid, 256);
+    for (int i = tid; i < p.K; i += 256) codes[i] = p.codebook[i] & 511u;
+    if (cb == 0 && tid < 32) store_scales(W, cob, tid, p.alpha, p.beta);
+    __syncthreads();
+    int best[4] = {0, 0, 0, 0};
+    if (__builtin_amdgcn_readfirstlane(__ballot(have > 0) != 0ull)) project_argmax<4>(wt, coef, p.K, best);
+    if (have == 4 && (((uintptr_t)(p.idx_out + at)) & 7) == 0) {
+        *(uint2 *)(p.idx_out + at) = make_uint2((uint32_t)best[0] | (uint32_t)best[1] << 16, (uint32_t)best[2] | (uint32_t)best[3] << 16);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (q < have) p.idx_out[at + q] = (uint16_t)best[q];
+    }
+    uint32_t lo = 0, mid = 0, hi = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t c = codes[best[q]];
+        lo |= (c & 15u) << (4 * q);
+        mid |= ((c >> 4) & 15u) << (4 * q);
+        hi |= (c >> 8) << (4 * q);
+    }
+    uint32_t words[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) words[t] = or_of_eight_lanes(tap_bits(lo, mid, hi, t) << (16 * (e & 1) + (e >> 1)));
+    if (e == 0) store_words(W.wq, cob, co, cb, W.ncb, words);
+}
+
+// The weights-side work of up to RF_PROJECT_MAX layers in one launch.
+constexpr int RF_PROJECT_MAX = 32;
+struct RfProjectMany {
+    int n_layers;
+    int first[RF_PROJECT_MAX + 1];
+    RfProject layer[RF_PROJECT_MAX];
+};
+static_assert(sizeof(RfProjectMany) <= 4096, "kernel arguments");
+
+__global__ __launch_bounds__(256)
+void rows_fp4_project_many_kernel(const RfProjectMany m)
+{
+    __shared__ __align__(16) uint32_t lds[RF_PROJECT_LDS_WORDS];
+    const int b = blockIdx.x;
+    int l = 0;
+    while (l + 1 < m.n_layers && b >= m.first[l + 1]) ++l;              // block-uniform
+    rf_project_block(m.layer[l], b - m.first[l], lds);
+}
+
+// The first launch of a layer's forward pass: projection + operand layout, and sign + packing of the activations.
+struct RfFront {
+    RfProject pr;
+    int project_blocks;
+    const float *x;            // activations [rows][W]; none when the input is packed already
+    uint32_t *xr;
+    int64_t rows;
+    int W, WW, rows_per_block, vec;
+};
+
+__global__ __launch_bounds__(256)
+void rows_fp4_front_kernel(const RfFront p)
+{
+    static_assert(PACK_THREADS == 256 && PACK_LDS_WORDS <= RF_PROJECT_LDS_WORDS, "one block size and buffer for both roles");
+    __shared__ __align__(16) uint32_t lds[RF_PROJECT_LDS_WORDS];
+    const int b = blockIdx.x;
+    if (b >= p.project_blocks) {
+        pack_rows_block(p.x, p.xr, p.rows, p.W, p.WW, p.rows_per_block, p.vec, (int64_t)(b - p.project_blocks), lds);
+        return;
+    }
+    rf_project_block(p.pr, b, lds);
+}
+
+// ---- host side -----------------------------------------------------------------------------------------------------------
+
+struct RfPlan {
+    int PB, CB, wpx_shift;
+    int n_cob, ncb, chunk;
+    int64_t n_blk, n_cotiles, n_wgs;
+    int rows_pb, bpi, wpr;
+    int64_t rows;                // padded input rows a workgroup touches at most
+    int64_t plane;
+    size_t lds;
+    bool ok;
+};
+
+constexpr size_t RF_LDS_TARGET = 72 * 1024;      // two workgroups per compute unit
+constexpr size_t RF_LDS_MAX = 150 * 1024;
+
+size_t rf_weight_bytes(const Geom &g)
+{
+    return align_up((size_t)((g.C_out + 31) / 32) * ((g.C_in + 63) / 64) * RF_PAIR_BYTES, 256);
+}
+
+RfPlan rf_plan(const Geom &g, bool sign, bool many = false)
+{
+    RfPlan pl;
+    pl.n_cob = (g.C_out + 31) / 32;
+    pl.ncb = (g.C_in + 31) / 32;
+    pl.rows_pb = g.Wo <= 32 ? 32 / g.Wo : 1;
+    pl.bpi = (g.Ho + pl.rows_pb - 1) / pl.rows_pb;
+    pl.wpr = (g.Wo + 31) / 32;
+    pl.n_blk = !sign ? (g.P + 31) / 32 : g.Wo <= 32 ? (int64_t)g.N * pl.bpi : (int64_t)g.N * g.Ho * pl.wpr;
+    pl.CB = pl.n_cob >= 2 ? 2 : 1;
+    // waves of a workgroup share its expanded pixels between as many output channels as there are
+    pl.wpx_shift = pl.n_cob >= 3 ? 1 : 2;
+    const int cob_wg = pl.CB << (2 - pl.wpx_shift);
+    pl.n_cotiles = (pl.n_cob + cob_wg - 1) / cob_wg;
+    pl.ok = false;
+    for (int PB : {4, 2, 1}) {
+        const int64_t nb = (int64_t)PB << pl.wpx_shift;        // pixel blocks of a workgroup
+        const int64_t wgs = (pl.n_blk + nb - 1) / nb * pl.n_cotiles;
+        // four blocks per wave halve the weight traffic; fewer where that leaves compute units without work
+        if (PB == 4 && (wgs < 512 || pl.CB == 1 || many)) continue;
+        if (PB == 2 && wgs < 256 && !many) continue;
+        // rows the workgroup's pixels touch, and their three-row windows
+        int64_t row_changes, image_changes;
+        if (!sign) {
+            row_changes = (g.Wo - 1 + 32 * nb - 1) / g.Wo;
+            image_changes = ((int64_t)g.HoWo - 1 + 32 * nb - 1) / g.HoWo;
+        } else {
+            row_changes = (g.Wo <= 32 ? nb * pl.rows_pb : (pl.wpr - 1 + nb - 1) / pl.wpr + 1) - 1;
+            image_changes = (row_changes + g.Ho - 1) / g.Ho;
+        }
+        int64_t rows = g.stride * row_changes + image_changes + 3;
+        if (rows > (int64_t)g.N * (g.H + 1) + 1) rows = (int64_t)g.N * (g.H + 1) + 1;
+        const int64_t plane = (rows * (g.W + 1) + 1) * 16;
+        const size_t fixed = (size_t)4 * pl.CB * 32 * (sign ? 8 : 4);
+        int chunk = pl.ncb;
+        while (chunk > 2 && fixed + (size_t)chunk * plane > RF_LDS_TARGET) chunk = ((chunk + 1) / 2 + 1) & ~1;
+        if (fixed + (size_t)chunk * plane > RF_LDS_MAX) continue;
+        pl.PB = PB;
+        pl.rows = rows;
+        pl.plane = plane;
+        pl.chunk = chunk;
+        pl.lds = fixed + (size_t)chunk * plane;
+        pl.n_wgs = wgs;
+        pl.ok = true;
+        break;
+    }
+    if (!pl.ok) return pl;
+    // 32-bit offsets: packed rows and outputs of the images a workgroup touches, the weights, pixel and tile numbers
+    const int64_t images = (pl.rows + g.H) / (g.H + 1) + 1;
+    const int64_t lim = ((int64_t)1 << 31) - 4096;
+    if (images * g.C_in * g.H * g.WW * 4 >= lim || images * g.C_out * g.HoWo * 4 >= lim || (int64_t)rf_weight_bytes(g) >= lim ||
+        (int64_t)g.N * g.C_out >= lim || g.P >= lim - 65536 || (int64_t)g.N * (g.H + 1) >= lim || pl.n_blk * 32 >= lim || pl.n_wgs >= lim ||
+        (int64_t)g.C_out * g.HoWo * 4 >= lim)
+        pl.ok = false;
+    return pl;
+}
+
+RfLayer rf_layer(const RfPlan &pl, const Geom &g, const void *x, void *out, void *ws)
+{
+    RfLayer L;
+    L.x = (const uint32_t *)x;
+    L.wq = (const uint32_t *)ws;
+    L.scale = (const float *)((char *)ws + rf_weight_bytes(g));
+    L.out = out;
+    L.N = g.N; L.C_in = g.C_in; L.C_out = g.C_out; L.H = g.H; L.W = g.W; L.WW = g.WW; L.stride = g.stride;
+    L.Ho = g.Ho; L.Wo = g.Wo; L.HoWo = g.HoWo; L.P = (int)g.P;
+    L.n_cob = pl.n_cob; L.ncb = pl.ncb; L.chunk = pl.chunk; L.pairs = (pl.ncb + 1) / 2; L.plane = (int)pl.plane;
+    L.n_blk = (int)pl.n_blk; L.n_cotiles = (int)pl.n_cotiles; L.n_wgs = (int)pl.n_wgs;
+    L.wpx_shift = pl.wpx_shift;
+    L.rows_pb = pl.rows_pb; L.bpi = pl.bpi; L.wpr = pl.wpr;
+    L.div_HoWo = make_divisor((uint32_t)g.HoWo);
+    L.div_Wo = make_divisor((uint32_t)g.Wo);
+    L.div_H1 = make_divisor((uint32_t)g.H + 1u);
+    L.div_WW = make_divisor((uint32_t)g.WW);
+    L.div_cotiles = make_divisor((uint32_t)pl.n_cotiles);
+    L.div_bpi = make_divisor((uint32_t)pl.bpi);
+    L.div_wpr = make_divisor((uint32_t)pl.wpr);
+    L.div_Ho = make_divisor((uint32_t)g.Ho);
+    return L;
+}
+
+RfWeights rf_weights(const Geom &g, void *ws)
+{
+    RfWeights W;
+    W.wq = (uint32_t *)ws;
+    W.scale = (float *)((char *)ws + rf_weight_bytes(g));
+    W.C_in = g.C_in;
+    W.C_out = g.C_out;
+    W.n_cob = (g.C_out + 31) / 32;
+    W.ncb = (g.C_in + 31) / 32;
+    return W;
+}
+
+template <int PB, int CB, bool SIGN>
+int launch_rf_one(const RfPlan &pl, const RfLayer &L, hipStream_t s)
+{
+    auto kern = rows_fp4_kernel<PB, CB, SIGN>;
+    static LdsGrant grant;
+    if (grant_dynamic_lds((const void *)kern, pl.lds, grant) != SNN_OK) return SNN_ERR_LAUNCH;
+    hipLaunchKernelGGL(kern, dim3((unsigned)pl.n_wgs), dim3(256), pl.lds, s, L);
+    return check_launch();
+}
+
+template <bool SIGN>
+int launch_rf(const RfPlan &pl, const RfLayer &L, hipStream_t s)
+{
+    if (pl.CB == 2) {
+        if (pl.PB == 4) return launch_rf_one<4, 2, SIGN>(pl, L, s);
+        if (pl.PB == 2) return launch_rf_one<2, 2, SIGN>(pl, L, s);
+        return launch_rf_one<1, 2, SIGN>(pl, L, s);
+    }
+    if (pl.PB == 2) return launch_rf_one<2, 1, SIGN>(pl, L, s);
+    return launch_rf_one<1, 1, SIGN>(pl, L, s);
+}
+
+RfProject rf_project(const Geom &g, const float *w, const uint16_t *codebook, const float *alpha, const float *beta, uint16_t *idx_out,
+                     void *ws)
+{
+    RfProject p;
+    p.W = rf_weights(g, ws);
+    p.w = w;
+    p.codebook = codebook;
+    p.alpha = alpha;
+    p.beta = beta;
+    p.idx_out = idx_out;
+    p.K = g.K;
+    return p;
+}
+
+}  // namespace
+
+bool rows_fp4_supported(const Geom &g) { return rf_plan(g, false).ok && rf_plan(g, true).ok; }
+
+size_t rows_fp4_workspace_bytes(const Geom &g)
+{
+    return rf_weight_bytes(g) + align_up((size_t)((g.C_out + 31) / 32) * 64 * sizeof(float), 256);
+}
+
+int launch_rows_fp4(const Geom &g, const void *x, const uint16_t *codebook, const void *idx, int tau, const float *alpha, float *y,
+                    void *ws, hipStream_t s, const SignEpilogue *sign, int phases)
+{
+    const RfPlan pl = rf_plan(g, sign != nullptr);
+    if (!pl.ok) return SNN_ERR_UNSUPPORTED;
+    if (phases & SNN_PHASE_PREPARE) {
+        const RfWeights W = rf_weights(g, ws);
+        hipLaunchKernelGGL(rows_fp4_prep_kernel, dim3((unsigned)W.n_cob, (unsigned)((W.ncb + 1) / 2)), dim3(256), 0, s, W, codebook, g.K, idx,
+                           tau, alpha, sign ? sign->beta : nullptr);
+        const int rc = check_launch();
+        if (rc != SNN_OK) return rc;
+    }
+    if (!(phases & SNN_PHASE_CONVOLVE)) return SNN_OK;
+    if (sign) return launch_rf<true>(pl, rf_layer(pl, g, x, sign->out, ws), s);
+    return launch_rf<false>(pl, rf_layer(pl, g, x, y, ws), s);
+}
+
+int launch_rows_fp4_forward(const Geom &g, const float *x, const float *w, const uint16_t *codebook, const float *alpha, uint16_t *idx_out,
+                            float *y, uint32_t *xr, void *ws, hipStream_t s, const SignEpilogue *sign)
+{
+    const RfPlan pl = rf_plan(g, sign != nullptr);
+    if (!pl.ok) return SNN_ERR_UNSUPPORTED;
+    RfFront f;
+    f.pr = rf_project(g, w, codebook, alpha, sign ? sign->beta : nullptr, idx_out, ws);
+    f.project_blocks = f.pr.W.n_cob * f.pr.W.ncb;
+    f.x = x;
+    f.xr = xr;
+    f.rows = (int64_t)g.N * g.C_in * g.H;
+    f.W = g.W;
+    f.WW = g.WW;
+    const PackRowsPlan pk = pack_rows_plan(x, f.rows, g.W);
+    f.rows_per_block = pk.rows_per_block;
+    f.vec = pk.vec;
+    const int64_t blocks = f.project_blocks + (x ? pk.blocks : 0);
+    if (blocks > 0x7fffffffLL) return SNN_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(rows_fp4_front_kernel, dim3((unsigned)blocks), dim3(256), 0, s, f);
+    const int rc = check_launch();
+    if (rc != SNN_OK) return rc;
+    if (sign) return launch_rf<true>(pl, rf_layer(pl, g, xr, sign->out, ws), s);
+    return launch_rf<false>(pl, rf_layer(pl, g, xr, y, ws), s);
+}
+
+int launch_rows_fp4_project_many(int n_layers, const Geom *gs, const float *const *w, const uint16_t *const *codebook,
+                                 const float *const *alpha, const float *const *beta, uint16_t *const *idx_out, void *const *ws, hipStream_t s)
+{
+    for (int l0 = 0; l0 < n_layers; l0 += RF_PROJECT_MAX) {
+        RfProjectMany m;
+        m.n_layers = n_layers - l0 < RF_PROJECT_MAX ? n_layers - l0 : RF_PROJECT_MAX;
+        int64_t blocks = 0;
+        for (int i = 0; i < m.n_layers; ++i) {
+            const int l = l0 + i;
+            m.layer[i] = rf_project(gs[l], w[l], codebook[l], alpha[l], beta[l], idx_out[l], ws[l]);
+            m.first[i] = (int)blocks;
+            blocks += (int64_t)m.layer[i].W.n_cob * m.layer[i].W.ncb;
+            if (blocks > 0x7fffffffLL) return SNN_ERR_UNSUPPORTED;
+        }
+        for (int i = m.n_layers; i <= RF_PROJECT_MAX; ++i) m.first[i] = (int)blocks;
+        hipLaunchKernelGGL(rows_fp4_project_many_kernel, dim3((unsigned)blocks), dim3(256), 0, s, m);
+        const int rc = check_launch();
+        if (rc != SNN_OK) return rc;
+    }
+    return SNN_OK;
+}
+
+int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, float *const *y, void *const *ws, hipStream_t s)
+{
+    static LdsGrant grant;
+    RfMany m;
+    m.n_layers = 0;
+    int64_t blocks = 0;
+    size_t lds = 0;
+    auto flush = [&]() -> int {
+        if (m.n_layers == 0) return SNN_OK;
+        for (int i = m.n_layers; i <= RF_MANY_MAX; ++i) m.first[i] = (int)blocks;
+        if (grant_dynamic_lds((const void *)rows_fp4_many_kernel, lds, grant) != SNN_OK) return SNN_ERR_LAUNCH;
+        hipLaunchKernelGGL(rows_fp4_many_kernel, dim3((unsigned)blocks), dim3(256), lds, s, m);
+        m.n_layers = 0;
+        blocks = 0;
+        lds = 0;
+        return check_launch();
+    };
+    for (int l = 0; l < n_layers; ++l) {
+        const RfPlan pl = rf_plan(gs[l], false, true);
+        if (!pl.ok) return SNN_ERR_UNSUPPORTED;
+        const RfLayer L = rf_layer(pl, gs[l], x[l], y[l], ws[l]);
+        const int form = 10 * pl.PB + pl.CB;
+        const int64_t here = (pl.n_wgs + 7) / 8 * 8;
+        if (blocks + here > 0x7fffffffLL) {
+            const int rc = flush();
+            if (rc != SNN_OK) return rc;
+        }
+        m.layer[m.n_layers] = L;
+        m.form[m.n_layers] = form;
+        m.first[m.n_layers] = (int)blocks;
+        blocks += here;
+        if (pl.lds > lds) lds = pl.lds;
+        if (++m.n_layers == RF_MANY_MAX) {
+            const int rc = flush();
+            if (rc != SNN_OK) return rc;
+        }
+    }
+    return flush();
+}
+
+}  // namespace snn

@@ -1,4 +1,5 @@
 // C entry points of the library: argument checks, workspace sizing, dispatch.
+#include "rows_fp4.h"
 #include "snn_internal.h"
 
 #include <stdio.h>
@@ -92,6 +93,70 @@ bool subbit_act_supported(int act) { return act == SNN_ACT_BIN_ROWS || act == SN
 bool bnn_supported(const snn_conv_desc *d)
 {
     return d->act == SNN_ACT_F32 || d->act == SNN_ACT_BIN_CHANNELS;
+}
+
+// Several layers: those the dense contraction takes share its launches, the others those of the two-stage kernels.
+template <class T>
+std::vector<T> pick(const std::vector<T> &v, const std::vector<int> &which)
+{
+    std::vector<T> r;
+    r.reserve(which.size());
+    for (int i : which) r.push_back(v[i]);
+    return r;
+}
+
+struct FormSplit {
+    std::vector<int> rows, two_stage;
+};
+
+FormSplit split_forms(const std::vector<Geom> &gs)
+{
+    FormSplit f;
+    for (int l = 0; l < (int)gs.size(); ++l) (subbit_rows_form(gs[l]) ? f.rows : f.two_stage).push_back(l);
+    return f;
+}
+
+std::vector<void *> two_stage_tables(const std::vector<Geom> &gs, const std::vector<void *> &ws)
+{
+    std::vector<void *> r;
+    for (size_t i = 0; i < gs.size(); ++i) r.push_back((char *)ws[i] + subbit_two_stage_offset(gs[i]));
+    return r;
+}
+
+int prepare_layers(const std::vector<Geom> &gs, const std::vector<const float *> &w, const std::vector<const uint16_t *> &codebook,
+                   const std::vector<const float *> &alpha, const std::vector<const float *> &beta, const std::vector<uint16_t *> &idx,
+                   const std::vector<void *> &ws, hipStream_t s)
+{
+    const FormSplit f = split_forms(gs);
+    if (!f.rows.empty()) {
+        const int rc = launch_rows_fp4_project_many((int)f.rows.size(), pick(gs, f.rows).data(), pick(w, f.rows).data(),
+                                                    pick(codebook, f.rows).data(), pick(alpha, f.rows).data(), pick(beta, f.rows).data(),
+                                                    pick(idx, f.rows).data(), pick(ws, f.rows).data(), s);
+        if (rc != SNN_OK) return rc;
+    }
+    if (f.two_stage.empty()) return SNN_OK;
+    const std::vector<Geom> g2 = pick(gs, f.two_stage);
+    return launch_subbit_prepare_many((int)g2.size(), g2.data(), pick(w, f.two_stage).data(), pick(codebook, f.two_stage).data(),
+                                      pick(alpha, f.two_stage).data(), pick(beta, f.two_stage).data(), pick(idx, f.two_stage).data(),
+                                      two_stage_tables(g2, pick(ws, f.two_stage)).data(), s);
+}
+
+int convolve_layers(const std::vector<Geom> &gs, const std::vector<const void *> &x, const std::vector<float *> &y,
+                    const std::vector<void *> &ws, hipStream_t s)
+{
+    const FormSplit f = split_forms(gs);
+    if (!f.rows.empty()) {
+        const int rc = launch_rows_fp4_many((int)f.rows.size(), pick(gs, f.rows).data(), pick(x, f.rows).data(), pick(y, f.rows).data(),
+                                            pick(ws, f.rows).data(), s);
+        if (rc != SNN_OK) return rc;
+    }
+    if (f.two_stage.empty()) return SNN_OK;
+    const std::vector<Geom> g2 = pick(gs, f.two_stage);
+    const std::vector<void *> w2 = two_stage_tables(g2, pick(ws, f.two_stage));
+    const int n = (int)g2.size();
+    if (tuning(SNN_TUNE_STACK) != 0 && subbit_stack_supported(n, g2.data()))
+        return launch_subbit_stack(n, g2.data(), pick(x, f.two_stage).data(), pick(y, f.two_stage).data(), w2.data(), s);
+    return launch_subbit_mfma_many(n, g2.data(), pick(x, f.two_stage).data(), pick(y, f.two_stage).data(), w2.data(), s);
 }
 
 }  // namespace
@@ -250,11 +315,10 @@ int snn_subbit_conv2d_noalloc(const snn_conv_desc *desc, const void *x, const ui
     if (!desc_ok(desc, true) || !x || !codebook || !idx || !alpha || !y_nchw) return SNN_ERR_INVALID_ARG;
     if (!subbit_act_supported(desc->act)) return SNN_ERR_UNSUPPORTED;
     const Geom g = make_geom(*desc);
-    const size_t need = subbit_workspace_bytes(g, desc->act);
-    if (need > (size_t)SNN_NOALLOC_MAX_WORKSPACE_BYTES) return SNN_ERR_WORKSPACE;
     void *ws = scratch_on_current_device();
     if (!ws) return SNN_ERR_LAUNCH;
-    return launch_subbit(g, desc->act, x, codebook, idx, alpha, y_nchw, ws, (hipStream_t)stream);
+    return launch_subbit_fitting(g, desc->act, x, codebook, idx, alpha, y_nchw, ws, (size_t)SNN_NOALLOC_MAX_WORKSPACE_BYTES,
+                                 (hipStream_t)stream);
 }
 
 int snn_subbit_prepare(const snn_conv_desc *desc, const uint16_t *codebook, const uint16_t *idx, const float *alpha,
@@ -292,8 +356,11 @@ int snn_subbit_prepare_packed(const snn_conv_desc *desc, const uint16_t *codeboo
     if (!subbit_mfma_supported(g)) return SNN_ERR_UNSUPPORTED;
     const size_t need = subbit_workspace_bytes(g, desc->act);
     if (!workspace || ws_bytes < need || ((uintptr_t)workspace & 255u)) return SNN_ERR_WORKSPACE;
-    return launch_subbit_mfma(g, nullptr, codebook, (const uint16_t *)idx_packed, alpha, nullptr, workspace,
-                              (hipStream_t)stream, nullptr, SNN_PHASE_PREPARE, tau);
+    if (subbit_rows_form(g))
+        return launch_rows_fp4(g, nullptr, codebook, idx_packed, tau, alpha, nullptr, workspace, (hipStream_t)stream, nullptr,
+                               SNN_PHASE_PREPARE);
+    return launch_subbit_mfma(g, nullptr, codebook, (const uint16_t *)idx_packed, alpha, nullptr,
+                              (char *)workspace + subbit_two_stage_offset(g), (hipStream_t)stream, nullptr, SNN_PHASE_PREPARE, tau);
 }
 
 int snn_subbit_conv2d_prepared(const snn_conv_desc *desc, const void *x, const float *alpha, float *y_nchw,
@@ -378,8 +445,7 @@ int snn_subbit_project_prepare_many(const snn_layer_weights *layers, int n_layer
         idx[l] = L.idx_out;
         ws[l] = L.workspace;
     }
-    return launch_subbit_prepare_many(n_layers, gs.data(), w.data(), cb.data(), alpha.data(), beta.data(), idx.data(), ws.data(),
-                                      (hipStream_t)stream);
+    return prepare_layers(gs, w, cb, alpha, beta, idx, ws, (hipStream_t)stream);
 }
 
 int snn_subbit_conv2d_prepared_many(const snn_layer_io *layers, int n_layers, void *stream)
@@ -402,9 +468,7 @@ int snn_subbit_conv2d_prepared_many(const snn_layer_io *layers, int n_layers, vo
         y[l] = L.y_nchw;
         ws[l] = L.workspace;
     }
-    if (tuning(SNN_TUNE_STACK) != 0 && subbit_stack_supported(n_layers, gs.data()))
-        return launch_subbit_stack(n_layers, gs.data(), x.data(), y.data(), ws.data(), (hipStream_t)stream);
-    return launch_subbit_mfma_many(n_layers, gs.data(), x.data(), y.data(), ws.data(), (hipStream_t)stream);
+    return convolve_layers(gs, x, y, ws, (hipStream_t)stream);
 }
 
 int snn_subbit_forward_many(const snn_layer_forward *layers, int n_layers, void *stream)
@@ -447,12 +511,9 @@ int snn_subbit_forward_many(const snn_layer_forward *layers, int n_layers, void 
     }
     int rc = launch_pack_rows_many(n_layers, x.data(), xr.data(), rows.data(), widths.data(), (hipStream_t)stream);
     if (rc != SNN_OK) return rc;
-    rc = launch_subbit_prepare_many(n_layers, gs.data(), w.data(), codebook.data(), alpha.data(), no_beta.data(), idx_out.data(),
-                                    ws.data(), (hipStream_t)stream);
+    rc = prepare_layers(gs, w, codebook, alpha, no_beta, idx_out, ws, (hipStream_t)stream);
     if (rc != SNN_OK) return rc;
-    if (tuning(SNN_TUNE_STACK) != 0 && subbit_stack_supported(n_layers, gs.data()))
-        return launch_subbit_stack(n_layers, gs.data(), xp.data(), y.data(), ws.data(), (hipStream_t)stream);
-    return launch_subbit_mfma_many(n_layers, gs.data(), xp.data(), y.data(), ws.data(), (hipStream_t)stream);
+    return convolve_layers(gs, xp, y, ws, (hipStream_t)stream);
 }
 
 int snn_subbit_forward_sign(const snn_conv_desc *desc, const void *x_packed, const float *w, const uint16_t *codebook,

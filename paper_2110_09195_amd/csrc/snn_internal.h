@@ -73,6 +73,27 @@ __host__ __device__ inline uint32_t code_to_window_order(uint32_t code)
     return r;
 }
 
+// Division by a divisor fixed per layer (1 <= d < 2^31) of numerators below 2^31: q = mulhi(n, mul) >> shift with
+// mul = floor(2^(31 + s) / d) + 1, s = ceil(log2 d), shift = s - 1 (exact: mul * d - 2^(31 + s) is in (0, 2^s]);
+// d = 1 is mul = 0.  The kernel's per-tile set-up is a dozen divisions by H_out * W_out, W_out, H and the
+// number of channel tiles; the generic sequence costs forty instructions each.
+struct Divisor {
+    uint32_t mul, shift;
+};
+
+inline Divisor make_divisor(uint32_t d)
+{
+    if (d <= 1u) return {0u, 0u};
+    uint32_t s = 0;
+    while ((1ull << s) < d) ++s;
+    return {(uint32_t)((1ull << (31 + s)) / d) + 1u, s - 1u};
+}
+
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, const Divisor &d)
+{
+    return d.mul ? __umulhi(n, d.mul) >> d.shift : n;
+}
+
 // ---- launchers (each validates nothing: the C entry points did) -----------------------------
 
 int launch_pack_rows(const float *x, uint32_t *out, int64_t rows, int W, hipStream_t s);
@@ -109,6 +130,14 @@ int subbit_mfma_slots_per_channel(const Geom &g);
 int launch_subbit(const Geom &g, int act, const void *x, const uint16_t *codebook,
                   const uint16_t *idx, const float *alpha, float *y, void *ws, hipStream_t s,
                   int phases = SNN_PHASE_BOTH);
+
+// snn_subbit_conv2d's work in a buffer of fixed size: the form whose tables fit (SNN_ERR_WORKSPACE if none does)
+int launch_subbit_fitting(const Geom &g, int act, const void *x, const uint16_t *codebook, const uint16_t *idx, const float *alpha,
+                          float *y, void *ws, size_t ws_bytes, hipStream_t s);
+// whether the layer goes to the dense contraction (rows_fp4.hip); else to the two-stage kernels, whose tables start this
+// many bytes into the workspace
+bool subbit_rows_form(const Geom &g);
+size_t subbit_two_stage_offset(const Geom &g);
 
 // Optional ending of the sub-bit convolution: instead of y, the next layer's packed rows
 // bit = ((float)S * alpha[co] + beta[co] >= 0), uint32 [N][C_out][H_out][ceil(W_out / 32)].

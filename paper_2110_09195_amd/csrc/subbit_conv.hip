@@ -15,6 +15,7 @@
 // image (read as bit 0) fake; it depends only on the output channel and the pixel's border type.
 #include <stdlib.h>
 
+#include "rows_fp4.h"
 #include "subbit_common.h"
 
 namespace snn {
@@ -265,18 +266,44 @@ int launch_direct(const SbPlan &pl, const SbParams &prm, dim3 grid, hipStream_t 
     return check_launch();
 }
 
-// The matrix-core kernel takes every layer it supports; the knob SNN_TUNE_SUBBIT_MFMA = 0 (tuning and tests)
-// sends those layers to the fallback kernel instead.
+// Among the two-stage kernels the matrix-core one takes every layer it supports; the knob SNN_TUNE_SUBBIT_MFMA = 0
+// (tuning and tests) sends those layers to the LDS-gather kernel instead.
 bool use_mfma(const Geom &g)
 {
     return subbit_mfma_supported(g) && tuning(SNN_TUNE_SUBBIT_MFMA) != 0;
 }
 
+// the tables of either two-stage kernel, so that the override cannot outgrow a workspace
+size_t two_stage_bytes(const Geom &g)
+{
+    const size_t a = make_plan(g).bytes;
+    const size_t b = subbit_mfma_supported(g) ? subbit_mfma_workspace_bytes(g) : 0;
+    return a > b ? a : b;
+}
+
 }  // namespace
+
+// The dense contraction (rows_fp4.hip) takes every layer it supports: nine contraction slots per input channel against
+// the 16, 32 or 64 of the one-hot form; measured on every layer shape of the ResNets and on ragged ones it is the faster
+// form for all K (figures in that file; the smallest gain, 16 -> 16 channels 32x32 batch 8, is 1.16x).
+// Asking for one of the two-stage kernels' forms through a knob selects those kernels.
+bool subbit_rows_form(const Geom &g)
+{
+    for (int knob : {SNN_TUNE_SUBBIT_MFMA, SNN_TUNE_MFMA_TILE, SNN_TUNE_MFMA_KS, SNN_TUNE_MFMA_STAGE, SNN_TUNE_MFMA_QUAD, SNN_TUNE_STACK})
+        if (tuning(knob) != SNN_TUNE_AUTO) return false;
+    return rows_fp4_supported(g);
+}
+
+size_t subbit_two_stage_offset(const Geom &g) { return rows_fp4_supported(g) ? rows_fp4_workspace_bytes(g) : 0; }
 
 int launch_subbit_f32(const Geom &g, const void *x, const uint16_t *codebook, const uint16_t *idx,
                       const float *alpha, float *y, void *ws, hipStream_t s, int phases);
 size_t subbit_f32_workspace_bytes(const Geom &g);
+
+namespace {
+int launch_two_stage(const Geom &g, const void *x, const uint16_t *codebook, const uint16_t *idx, const float *alpha, float *y, void *ws,
+                     hipStream_t s, int phases);
+}
 
 int subbit_slots_per_channel(const Geom &g, int act)
 {
@@ -287,16 +314,34 @@ int subbit_slots_per_channel(const Geom &g, int act)
 size_t subbit_workspace_bytes(const Geom &g, int act)
 {
     if (act == SNN_ACT_F32) return subbit_f32_workspace_bytes(g);
-    // sized for either kernel, so that the override cannot outgrow a workspace
-    const size_t a = make_plan(g).bytes;
-    const size_t b = subbit_mfma_supported(g) ? subbit_mfma_workspace_bytes(g) : 0;
-    return a > b ? a : b;
+    // [tables of the dense contraction][tables of the two-stage kernels]: one workspace serves either
+    return subbit_two_stage_offset(g) + two_stage_bytes(g);
+}
+
+int launch_subbit_fitting(const Geom &g, int act, const void *x, const uint16_t *codebook, const uint16_t *idx, const float *alpha,
+                          float *y, void *ws, size_t ws_bytes, hipStream_t s)
+{
+    if (act == SNN_ACT_F32)
+        return subbit_f32_workspace_bytes(g) <= ws_bytes ? launch_subbit(g, act, x, codebook, idx, alpha, y, ws, s) : SNN_ERR_WORKSPACE;
+    if (subbit_rows_form(g) && rows_fp4_workspace_bytes(g) <= ws_bytes)
+        return launch_rows_fp4(g, x, codebook, idx, 0, alpha, y, ws, s, nullptr, SNN_PHASE_BOTH);
+    if (two_stage_bytes(g) > ws_bytes) return SNN_ERR_WORKSPACE;
+    return launch_two_stage(g, x, codebook, idx, alpha, y, ws, s, SNN_PHASE_BOTH);
 }
 
 int launch_subbit(const Geom &g, int act, const void *x, const uint16_t *codebook, const uint16_t *idx,
                   const float *alpha, float *y, void *ws, hipStream_t s, int phases)
 {
     if (act == SNN_ACT_F32) return launch_subbit_f32(g, x, codebook, idx, alpha, y, ws, s, phases);
+    if (subbit_rows_form(g)) return launch_rows_fp4(g, x, codebook, idx, 0, alpha, y, ws, s, nullptr, phases);
+    return launch_two_stage(g, x, codebook, idx, alpha, y, (char *)ws + subbit_two_stage_offset(g), s, phases);
+}
+
+namespace {
+
+int launch_two_stage(const Geom &g, const void *x, const uint16_t *codebook, const uint16_t *idx, const float *alpha, float *y, void *ws,
+                     hipStream_t s, int phases)
+{
     if (use_mfma(g)) return launch_subbit_mfma(g, x, codebook, idx, alpha, y, ws, s, nullptr, phases);
 
     const SbPlan pl = make_plan(g);
@@ -334,6 +379,8 @@ int launch_subbit(const Geom &g, int act, const void *x, const uint16_t *codeboo
     return launch_direct<4, 4>(pl, prm, grid, s);
 }
 
+}  // namespace
+
 // ---- one layer's forward pass in one call -----------------------------------------------------------
 // Workspace: [the convolution's own workspace][packed rows of sign(x)].
 size_t subbit_forward_workspace_bytes(const Geom &g)
@@ -346,8 +393,10 @@ int launch_subbit_forward(const Geom &g, const float *x, const float *w, const u
                           const float *alpha, uint16_t *idx_out, float *y, void *ws, hipStream_t s)
 {
     uint32_t *xr = (uint32_t *)((char *)ws + align_up(subbit_workspace_bytes(g, SNN_ACT_BIN_ROWS), 256));
-    if (use_mfma(g)) return launch_subbit_forward_mfma(g, x, w, codebook, alpha, idx_out, y, xr, ws, s);
-    // layers the matrix-core kernel does not take: the three operations one after the other
+    if (subbit_rows_form(g) && g.K <= 64) return launch_rows_fp4_forward(g, x, w, codebook, alpha, idx_out, y, xr, ws, s, nullptr);
+    if (!subbit_rows_form(g) && use_mfma(g))
+        return launch_subbit_forward_mfma(g, x, w, codebook, alpha, idx_out, y, xr, (char *)ws + subbit_two_stage_offset(g), s);
+    // larger subsets, and layers no matrix-core kernel takes: the three operations one after the other
     int rc = launch_pack_rows(x, xr, (int64_t)g.N * g.C_in * g.H, g.W, s);
     if (rc != SNN_OK) return rc;
     rc = launch_project(w, (int64_t)g.C_out * g.C_in, codebook, g.K, idx_out, s);
@@ -362,7 +411,8 @@ int launch_subbit_sign(const Geom &g, const void *x_packed, const uint16_t *code
     if (!use_mfma(g)) return SNN_ERR_UNSUPPORTED;
     // the convolution alone needs only the output pointer; a non-null epilogue selects the sign form either way
     const SignEpilogue sign = {beta, out_packed};
-    return launch_subbit_mfma(g, x_packed, codebook, idx, alpha, nullptr, ws, s, &sign, phases);
+    if (subbit_rows_form(g)) return launch_rows_fp4(g, x_packed, codebook, idx, 0, alpha, nullptr, ws, s, &sign, phases);
+    return launch_subbit_mfma(g, x_packed, codebook, idx, alpha, nullptr, (char *)ws + subbit_two_stage_offset(g), s, &sign, phases);
 }
 
 int launch_subbit_forward_sign(const Geom &g, const void *x_packed, const float *w, const uint16_t *codebook,
@@ -371,7 +421,10 @@ int launch_subbit_forward_sign(const Geom &g, const void *x_packed, const float 
 {
     if (!use_mfma(g)) return SNN_ERR_UNSUPPORTED;
     const SignEpilogue sign = {beta, out_packed};
-    return launch_subbit_forward_mfma(g, nullptr, w, codebook, alpha, idx_out, nullptr, (uint32_t *)x_packed, ws, s, &sign);
+    if (subbit_rows_form(g))
+        return launch_rows_fp4_forward(g, nullptr, w, codebook, alpha, idx_out, nullptr, (uint32_t *)x_packed, ws, s, &sign);
+    return launch_subbit_forward_mfma(g, nullptr, w, codebook, alpha, idx_out, nullptr, (uint32_t *)x_packed,
+                                      (char *)ws + subbit_two_stage_offset(g), s, &sign);
 }
 
 }  // namespace snn

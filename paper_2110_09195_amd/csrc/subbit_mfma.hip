@@ -152,20 +152,6 @@ __device__ inline uint2 fin_entry(int corr_term, float a, const float *beta, int
     return make_uint2(__float_as_uint(mult), __float_as_uint(thr));
 }
 
-// Index i of an index tensor: plain uint16 (tau = 0), or tau bits at bit i * tau of a little-endian bit
-// stream of 32-bit words (the storage format of Sec. 4.4 / Fig. 5: tau bits per kernel, tau / 9 per weight).
-__device__ inline uint32_t index_at(const void *__restrict__ idx, int64_t i, int tau)
-{
-    if (tau == 0) return ((const uint16_t *)idx)[i];
-    const uint32_t *w = (const uint32_t *)idx;
-    const int64_t bit = i * tau;
-    const int64_t word = bit >> 5;
-    const int sh = (int)(bit & 31);
-    uint32_t v = w[word] >> sh;
-    if (sh + tau > 32) v |= w[word + 1] << (32 - sh);
-    return v & ((1u << tau) - 1u);
-}
-
 // selector word of subset member k (see below)
 __device__ inline uint32_t sel_word(uint32_t k)
 {

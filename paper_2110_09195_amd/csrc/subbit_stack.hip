@@ -61,27 +61,6 @@ constexpr int ST_LDS_BYTES = ST_RUNS_OFF + ST_MAX_RUNS * 8;
 static_assert(ST_ALPHA_OFF % 16 == 0 && ST_CORR_OFF % 16 == 0 && ST_RUNS_OFF % 8 == 0, "aligned LDS accesses");
 static_assert(ST_WORKERS_PER_CU * ST_LDS_BYTES <= 160 * 1024, "all workers of a compute unit fit its LDS");
 
-// Division by a divisor fixed per layer (1 <= d < 2^31) of numerators below 2^31: q = mulhi(n, mul) >> shift with
-// mul = floor(2^(31 + s) / d) + 1, s = ceil(log2 d), shift = s - 1 (exact: mul * d - 2^(31 + s) is in (0, 2^s]);
-// d = 1 is mul = 0.  The kernel's per-tile set-up is a dozen divisions by H_out * W_out, W_out, H and the
-// number of channel tiles; the generic sequence costs forty instructions each.
-struct Divisor {
-    uint32_t mul, shift;
-};
-
-inline Divisor make_divisor(uint32_t d)
-{
-    if (d <= 1u) return {0u, 0u};
-    uint32_t s = 0;
-    while ((1ull << s) < d) ++s;
-    return {(uint32_t)((1ull << (31 + s)) / d) + 1u, s - 1u};
-}
-
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, const Divisor &d)
-{
-    return d.mul ? __umulhi(n, d.mul) >> d.shift : n;
-}
-
 struct StackLayer {
     const uint32_t *x;        // packed rows [N][C_in][H][WW]
     const uint32_t *lut;      // table images: [512][6] words (row = window, 32 FP6 values m_k - 4), then the split image

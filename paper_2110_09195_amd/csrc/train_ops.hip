@@ -12,42 +12,150 @@ namespace snn {
 namespace {
 
 constexpr int TB_THREADS = 256;
-constexpr int TB_PER = 2;                            // kernels per thread
-constexpr int TB_BLOCK = TB_THREADS * TB_PER;        // kernels per block
+constexpr int TB_UNIT = 112;                         // kernels that one 16-byte load of every thread covers (252 of 256 busy)
 
-// Pass 1: g_w = g_wbar where w in (-1, 1) (element-wise), else 0; per block, the sums of g_wbar by
-// member in LDS (float atomics), written as one partial [K][9] per block.
-__global__ __launch_bounds__(TB_THREADS)
-void project_backward_kernel(const float *__restrict__ w, const float *__restrict__ g_wbar,
-                             const uint16_t *__restrict__ idx, int64_t n, int K, float *__restrict__ g_w,
-                             float *__restrict__ partial)
+// 16-byte loads per thread and tensor: as many as leave enough blocks to fill the chip.  A block's time is a round
+// trip to memory and its LDS additions; its K x 9 partial sums are what more blocks cost.
+// (4096 kernels 4.1 us, 16384 3.8, 65536 6.0, 262144 11.9.)
+inline int tb_units(int64_t n) { return n <= (int64_t)TB_UNIT * 320 ? 1 : n <= (int64_t)TB_UNIT * 1280 ? 2 : 4; }
+inline int64_t tb_blocks(int64_t n)
 {
-    extern __shared__ float acc[];                   // [K][9]
+    const int64_t per = (int64_t)TB_UNIT * tb_units(n);
+    return (n + per - 1) / per;
+}
+
+// Pass 1: g_w = g_wbar where w in (-1, 1) (element-wise), else 0; per block, the sums of g_wbar by member, written as one
+// partial [K][9] per block.
+//
+// The sums by member are a product [member][kernel] x [kernel][tap] with the indices as a one-hot matrix, on the fp32 matrix
+// unit (products with 1 and 0 are exact, sums are fp32 as before; a wave's chain is a sixteenth of the block).  16 M members
+// cost 32 M clocks of a SIMD per four kernels, which stays under the 110 bytes per kernel of memory traffic up to
+// M = 16.  With LDS float atomics instead, which was the whole kernel's time at any layout of the lanes (290 clocks
+// per 64 additions, equal addresses among them or not), 262144 kernels at K = 32 take 17 us, here 11.9 (4096 kernels: 8.6
+// with one kernel per thread, here 4.1).
+// A zero times an infinity would reach members that it does not belong to: blocks with a value that is not finite, and
+// subsets of more than 256, add with the atomics (M = 0).
+template <int U, int M, bool WHOLE>
+__device__ __forceinline__ void project_backward_block(const float *__restrict__ wb, const float *__restrict__ gb,
+                                                       const uint16_t *__restrict__ ib, int cnt, int K, float *__restrict__ ob,
+                                                       float *__restrict__ dst, float *lds)
+{
+    constexpr int PER = TB_UNIT * U;
+    constexpr int STAGE = M > 0 ? PER * 9 + 16 : 0;  // (lanes 9..15 of the last kernel read past it)
+    __shared__ int member[PER + 1];
+    __shared__ int not_finite;
+    float *const acc = lds + STAGE;
     const int tid = threadIdx.x;
-    for (int i = tid; i < K * 9; i += TB_THREADS) acc[i] = 0.0f;
-    __syncthreads();
-    const int64_t c0 = (int64_t)blockIdx.x * TB_BLOCK;
+    const int ne = cnt * 9;
+    float wv[U][4], gv[U][4];
 #pragma unroll
-    for (int q = 0; q < TB_PER; ++q) {
-        const int64_t c = c0 + q * TB_THREADS + tid;
-        if (c < n) {
-            const int k = min((int)idx[c], K - 1);
-            float wv[9], gv[9];
+    for (int u = 0; u < U; ++u) {
+        const int e = (u * TB_THREADS + tid) * 4;
+        if constexpr (WHOLE) {                       // (threads past the end load the last elements again)
+            const int at = min(e, PER * 9 - 4);
+            const float4 a = *(const float4 *)(wb + at), b = *(const float4 *)(gb + at);
+            wv[u][0] = a.x; wv[u][1] = a.y; wv[u][2] = a.z; wv[u][3] = a.w;
+            gv[u][0] = b.x; gv[u][1] = b.y; gv[u][2] = b.z; gv[u][3] = b.w;
+        } else {
 #pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                wv[t] = w[c * 9 + t];
-                gv[t] = g_wbar[c * 9 + t];
-            }
-#pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                g_w[c * 9 + t] = (wv[t] > -1.0f && wv[t] < 1.0f) ? gv[t] : 0.0f;
-                atomicAdd(&acc[k * 9 + t], gv[t]);
+            for (int j = 0; j < 4; ++j) {
+                const int at = min(e + j, ne - 1);
+                wv[u][j] = wb[at];
+                gv[u][j] = e + j < ne ? gb[at] : 0.0f;
             }
         }
     }
+    for (int c = tid; c <= PER; c += TB_THREADS) {
+        const int k = min((int)ib[min(c, cnt - 1)], K - 1);
+        member[c] = c < cnt ? k : -1;
+    }
+    if (tid == 0) not_finite = M == 0;
     __syncthreads();
-    float *dst = partial + (int64_t)blockIdx.x * K * 9;
-    for (int i = tid; i < K * 9; i += TB_THREADS) dst[i] = acc[i];
+    bool odd = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int e = (u * TB_THREADS + tid) * 4;
+        if (e >= PER * 9) break;
+        float o[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            o[j] = wv[u][j] > -1.0f && wv[u][j] < 1.0f ? gv[u][j] : 0.0f;
+            odd |= !__builtin_isfinite(gv[u][j]);
+        }
+        if constexpr (WHOLE) {
+            *(float4 *)(ob + e) = make_float4(o[0], o[1], o[2], o[3]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (e + j < ne) ob[e + j] = o[j];
+        }
+        if constexpr (M > 0) *(float4 *)(lds + e) = make_float4(gv[u][0], gv[u][1], gv[u][2], gv[u][3]);
+    }
+    if (M > 0 && odd) not_finite = 1;
+    if constexpr (M > 0) {
+        if (tid < 16) lds[PER * 9 + tid] = 0.0f;
+    }
+    __syncthreads();
+    if (not_finite) {                                // (block-uniform)
+        for (int i = tid; i < K * 9; i += TB_THREADS) acc[i] = 0.0f;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = (u * TB_THREADS + tid) * 4;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int c = (e + j) / 9;
+                if (e + j < ne) atomicAdd(&acc[member[c] * 9 + e + j - 9 * c], gv[u][j]);
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < K * 9; i += TB_THREADS) dst[i] = acc[i];
+        return;
+    }
+    if constexpr (M > 0) {
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        // v_mfma_f32_16x16x4_f32: lane (i = lane % 16, q = lane / 16) holds A[member i][kernel q], B[kernel q][tap i] and
+        // D[members 4 q .. 4 q + 3][tap i]
+        const int lane = tid & 63, wave = tid >> 6, i = lane & 15, q = lane >> 4;
+        f32x4 sum[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) sum[m] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 7
+        for (int step = 0; step < PER / 16; ++step) {
+            const int c = 16 * step + 4 * wave + q;
+            const float g = lds[c * 9 + i];          // taps 9..15: whatever follows, in columns nobody reads
+            const int k = member[c] - i;
+#pragma unroll
+            for (int m = 0; m < M; ++m) sum[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(k == 16 * m ? 1.0f : 0.0f, g, sum[m], 0, 0, 0);
+        }
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int k = 16 * m + 4 * q + r;
+                if (i < 9 && k < K) acc[(wave * K + k) * 9 + i] = sum[m][r];
+            }
+        __syncthreads();
+        const int K9 = K * 9;
+        for (int e = tid; e < K9; e += TB_THREADS) dst[e] = (acc[e] + acc[K9 + e]) + (acc[2 * K9 + e] + acc[3 * K9 + e]);
+    }
+}
+
+template <int U, int M>
+__global__ __launch_bounds__(TB_THREADS)
+void project_backward_kernel(const float *__restrict__ w, const float *__restrict__ g_wbar,
+                             const uint16_t *__restrict__ idx, int64_t n, int K, float *__restrict__ g_w,
+                             float *__restrict__ partial, int vec)
+{
+    constexpr int PER = TB_UNIT * U;                 // a multiple of four: every block starts 16-byte aligned if the tensors do
+    extern __shared__ __align__(16) float lds[];
+    const int64_t c0 = (int64_t)blockIdx.x * PER;
+    const int cnt = (int)min((int64_t)PER, n - c0);
+    float *const dst = partial + (int64_t)blockIdx.x * K * 9;
+    if (vec && cnt == PER)                           // (block-uniform)
+        project_backward_block<U, M, true>(w + c0 * 9, g_wbar + c0 * 9, idx + c0, cnt, K, g_w + c0 * 9, dst, lds);
+    else
+        project_backward_block<U, M, false>(w + c0 * 9, g_wbar + c0 * 9, idx + c0, cnt, K, g_w + c0 * 9, dst, lds);
 }
 
 // Pass 2: g_p[k][t] = sum of the block partials; one wave per entry: lane l adds the partials of
@@ -97,18 +205,34 @@ void subset_update_kernel(const float *__restrict__ p, int8_t *__restrict__ m, f
 
 size_t project_backward_workspace_bytes(int64_t n, int K)
 {
-    const int64_t blocks = (n + TB_BLOCK - 1) / TB_BLOCK;
+    const int64_t blocks = tb_blocks(n);
     return align_up((size_t)(blocks > 0 ? blocks : 1) * K * 9 * sizeof(float), 256);
 }
 
 int launch_project_backward(const float *w, const float *g_wbar, const uint16_t *idx, int64_t n, int K, float *g_w,
                             float *g_p, void *ws, hipStream_t s)
 {
-    const int64_t blocks = (n + TB_BLOCK - 1) / TB_BLOCK;
+    const int64_t blocks = tb_blocks(n);
     if (blocks > 0x7fffffffLL) return SNN_ERR_INVALID_ARG;
-    if (blocks > 0)
-        hipLaunchKernelGGL(project_backward_kernel, dim3((unsigned)blocks), dim3(TB_THREADS), (size_t)K * 9 * sizeof(float), s, w,
-                           g_wbar, idx, n, K, g_w, (float *)ws);
+    const bool vec = ((((uintptr_t)w) | ((uintptr_t)g_wbar) | ((uintptr_t)g_w)) & 15u) == 0;
+    if (blocks > 0) {
+        const int U = tb_units(n), M = K <= 16 ? 1 : K <= 32 ? 2 : K <= 64 ? 4 : K <= 128 ? 8 : K <= 256 ? 16 : 0;
+        const size_t lds = sizeof(float) * (M > 0 ? (size_t)(TB_UNIT * U * 9 + 16) + 4 * (size_t)K * 9 : (size_t)K * 9);
+#define SNN_TB_CASE(M_)                                                                                                      \
+    case M_: {                                                                                                               \
+        auto kern = U == 1 ? project_backward_kernel<1, M_> : U == 2 ? project_backward_kernel<2, M_> : project_backward_kernel<4, M_>; \
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(TB_THREADS), lds, s, w, g_wbar, idx, n, K, g_w, (float *)ws, vec ? 1 : 0); \
+    } break;
+        switch (M) {
+            SNN_TB_CASE(0)
+            SNN_TB_CASE(1)
+            SNN_TB_CASE(2)
+            SNN_TB_CASE(4)
+            SNN_TB_CASE(8)
+            SNN_TB_CASE(16)
+        }
+#undef SNN_TB_CASE
+    }
     hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((K * 9 + TB_THREADS / 64 - 1) / (TB_THREADS / 64))), dim3(TB_THREADS), 0, s,
                        (const float *)ws, blocks, K * 9, g_p);
     return check_launch();

@@ -888,7 +888,7 @@ def main():
     roofline = None
     if many_ok:
         roofline = conv_roofline(layers, t_conv_in_step_us * 1e-6, peaks, accounting)
-        roofline["kernel"] = ("rows_fp4_many_kernel: the convolutions of all %d layers, up to fifteen to a launch; t_kernel = average over %d steps (the timed steps run a second time) of a "
+        roofline["kernel"] = ("rows_fp4_many_kernel: the convolutions of all %d layers in one launch (up to 34 layers to a launch); t_kernel = average over %d steps (the timed steps run a second time) of a "
                               "HIP-event pair around the call, on the launch stream" % (len(layers), args.steps))
         roofline["t_kernel_us_back_to_back"] = t_convs_b2b
         roofline["t_kernel_us_single_launch_median"] = t_convs_each[len(t_convs_each) // 2]

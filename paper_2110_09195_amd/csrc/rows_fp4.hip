@@ -30,7 +30,9 @@
 #include "front_ops.h"
 #include "rows_fp4.h"
 
+#include <algorithm>
 #include <type_traits>
+#include <vector>
 
 namespace snn {
 
@@ -540,26 +542,64 @@ void rows_fp4_kernel(const RfLayer L)
 
 // Several layers in one launch (fp32 output): workgroups [first[l], first[l + 1]) run layer l.  The layers share the
 // chip: while the workgroups of one layer store their outputs those of another multiply.
-constexpr int RF_MANY_MAX = 15;
+// A layer is described in 112 bytes, what follows from those is computed by the workgroup (scalar instructions), so that
+// the 4 KB of kernel arguments hold a whole network: with fifteen layers to a launch the sixteenth layer of the ResNet-18
+// stack (512 -> 512 7x7, 19 us alone, most of the chip idle) followed in a launch of its own, and a 32-layer stack took three.
+struct RfManyLayer {
+    const uint32_t *x;
+    const uint32_t *wq;                  // the scales lie behind it
+    void *y;
+    int N, C_in, C_out, H, W, Ho, Wo;
+    int chunk, plane, n_cotiles, n_wgs;
+    uint8_t PB, CB, wpx_shift, stride;
+    Divisor div_HoWo, div_Wo, div_H1, div_WW, div_cotiles;
+};
+constexpr int RF_MANY_MAX = 34;
 struct RfMany {
     int n_layers;
+    int fold;                            // groups of eight workgroups come from the two ends of the list in turn
     int first[RF_MANY_MAX + 1];          // multiples of eight (the XCD of a workgroup inside its layer)
-    int form[RF_MANY_MAX];               // 10 PB + CB
-    RfLayer layer[RF_MANY_MAX];
+    RfManyLayer layer[RF_MANY_MAX];
 };
 static_assert(sizeof(RfMany) <= 4096, "kernel arguments");
+
+// The layer whose range [first[l], first[l + 1]) block b falls into, n <= 63 layers: the lanes test one bound each.  (A loop over
+// the bounds waits for a scalar load per layer.)
+__device__ __forceinline__ int layer_of_block(const int *first, int n, int b)
+{
+    const int lane = threadIdx.x & 63;
+    return __builtin_amdgcn_readfirstlane((int)__popcll(__ballot(lane > 0 && lane < n && b >= first[lane < n ? lane : 0])));
+}
+
+__host__ __device__ constexpr size_t rf_weight_bytes(int C_out, int C_in)
+{
+    return ((size_t)((C_out + 31) / 32) * ((C_in + 63) / 64) * RF_PAIR_BYTES + 255) & ~(size_t)255;
+}
 
 __global__ __launch_bounds__(256, 3)
 void rows_fp4_many_kernel(const RfMany m)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int b = blockIdx.x;
-    int l = 0;
-    while (l + 1 < m.n_layers && b >= m.first[l + 1]) ++l;              // block-uniform
-    const RfLayer &L = m.layer[l];
+    int b = blockIdx.x;
+    if (m.fold) {
+        const int g = b >> 3, n_g = (int)(gridDim.x >> 3);
+        b = ((g & 1 ? n_g - 1 - (g >> 1) : g >> 1) << 3) + (b & 7);
+    }
+    const int l = layer_of_block(m.first, m.n_layers, b);
+    const RfManyLayer &c = m.layer[l];
     const uint32_t wg = (uint32_t)(b - m.first[l]);
-    if (wg >= (uint32_t)L.n_wgs) return;                                // padding to a multiple of eight
-    switch (m.form[l]) {
+    if (wg >= (uint32_t)c.n_wgs) return;                                // padding to a multiple of eight
+    RfLayer L = {};
+    L.x = c.x;
+    L.wq = c.wq;
+    L.scale = (const float *)((const char *)c.wq + rf_weight_bytes(c.C_out, c.C_in));
+    L.out = c.y;
+    L.N = c.N; L.C_in = c.C_in; L.C_out = c.C_out; L.H = c.H; L.W = c.W; L.WW = (c.W + 31) >> 5; L.stride = c.stride;
+    L.Ho = c.Ho; L.Wo = c.Wo; L.HoWo = c.Ho * c.Wo; L.P = c.N * L.HoWo;
+    L.n_cob = (c.C_out + 31) >> 5; L.ncb = (c.C_in + 31) >> 5; L.chunk = c.chunk; L.pairs = (L.ncb + 1) >> 1; L.plane = c.plane;
+    L.n_blk = (L.P + 31) >> 5; L.n_cotiles = c.n_cotiles; L.n_wgs = c.n_wgs; L.wpx_shift = c.wpx_shift;
+    L.div_HoWo = c.div_HoWo; L.div_Wo = c.div_Wo; L.div_H1 = c.div_H1; L.div_WW = c.div_WW; L.div_cotiles = c.div_cotiles;
+    switch (10 * c.PB + c.CB) {
     case 22: rf_tile<2, 2, false>(L, wg, smem); break;
     case 12: rf_tile<1, 2, false>(L, wg, smem); break;
     case 21: rf_tile<2, 1, false>(L, wg, smem); break;
@@ -776,10 +816,7 @@ struct RfPlan {
 constexpr size_t RF_LDS_TARGET = 72 * 1024;      // two workgroups per compute unit
 constexpr size_t RF_LDS_MAX = 150 * 1024;
 
-size_t rf_weight_bytes(const Geom &g)
-{
-    return align_up((size_t)((g.C_out + 31) / 32) * ((g.C_in + 63) / 64) * RF_PAIR_BYTES, 256);
-}
+size_t rf_weight_bytes(const Geom &g) { return rf_weight_bytes(g.C_out, g.C_in); }
 
 RfPlan rf_plan(const Geom &g, bool sign, bool many = false)
 {
@@ -986,41 +1023,52 @@ int launch_rows_fp4_project_many(int n_layers, const Geom *gs, const float *cons
 int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, float *const *y, void *const *ws, hipStream_t s)
 {
     static LdsGrant grant;
-    RfMany m;
-    m.n_layers = 0;
-    int64_t blocks = 0;
-    size_t lds = 0;
-    auto flush = [&]() -> int {
-        if (m.n_layers == 0) return SNN_OK;
-        for (int i = m.n_layers; i <= RF_MANY_MAX; ++i) m.first[i] = (int)blocks;
+    std::vector<RfPlan> plans(n_layers);
+    std::vector<int> order(n_layers);
+    for (int l = 0; l < n_layers; ++l) {
+        plans[l] = rf_plan(gs[l], false, true);
+        if (!plans[l].ok) return SNN_ERR_UNSUPPORTED;
+        order[l] = l;
+    }
+    // Order of the layers.  Outputs that fit the last-level cache (256 MB): the layers whose workgroups run longest from one
+    // end and the shortest, which are mostly stores, from the other in turn, so that stores and matrix work overlap and
+    // no long workgroup is left to run alone at the end.  More: the short ones first, the stores that the cache has taken up drain
+    // while the long ones multiply.  Measured, short first / both ends in turn (pack and projection included where they are
+    // part of the call): 32-layer stack batch 4 (39 MB) 43.2 / 36.7 us, batch 8 58.2 / 53.8, 16-layer stack batch 16
+    // (84 MB) 77.2 / 74.9, 18 small layers batch 256 (193 MB) 99.4 / 98.1; batch 32 (308 MB) 156 / 161, 16-layer stack batch 64
+    // (335 MB) 183 / 193; the long ones first without the turns: 53.8 -> 56.5 and 193 -> 202.
+    auto length = [&](int l) { return (int64_t)plans[l].ncb * plans[l].PB * plans[l].CB; };
+    int64_t out_bytes = 0;
+    for (int l = 0; l < n_layers; ++l) out_bytes += 4 * gs[l].P * gs[l].C_out;
+    const bool fold = out_bytes <= (int64_t)256 << 20;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return fold ? length(a) > length(b) : length(a) < length(b); });
+    for (int at = 0; at < n_layers;) {
+        RfMany m;
+        int n = 0;
+        int64_t blocks = 0;
+        size_t lds = 0;
+        for (; at < n_layers && n < RF_MANY_MAX; ++at, ++n) {
+            const int l = order[at];
+            const RfPlan &pl = plans[l];
+            const int64_t here = (pl.n_wgs + 7) / 8 * 8;
+            if (blocks + here > 0x7fffffffLL) break;
+            const RfLayer L = rf_layer(pl, gs[l], x[l], y[l], ws[l]);
+            m.layer[n] = {L.x, L.wq, L.out, L.N, L.C_in, L.C_out, L.H, L.W, L.Ho, L.Wo, L.chunk, L.plane, L.n_cotiles, L.n_wgs,
+                          (uint8_t)pl.PB, (uint8_t)pl.CB, (uint8_t)pl.wpx_shift, (uint8_t)gs[l].stride,
+                          L.div_HoWo, L.div_Wo, L.div_H1, L.div_WW, L.div_cotiles};
+            m.first[n] = (int)blocks;
+            blocks += here;
+            lds = std::max(lds, pl.lds);
+        }
+        m.n_layers = n;
+        m.fold = fold;
+        for (int i = n; i <= RF_MANY_MAX; ++i) m.first[i] = (int)blocks;
         if (grant_dynamic_lds((const void *)rows_fp4_many_kernel, lds, grant) != SNN_OK) return SNN_ERR_LAUNCH;
         hipLaunchKernelGGL(rows_fp4_many_kernel, dim3((unsigned)blocks), dim3(256), lds, s, m);
-        m.n_layers = 0;
-        blocks = 0;
-        lds = 0;
-        return check_launch();
-    };
-    for (int l = 0; l < n_layers; ++l) {
-        const RfPlan pl = rf_plan(gs[l], false, true);
-        if (!pl.ok) return SNN_ERR_UNSUPPORTED;
-        const RfLayer L = rf_layer(pl, gs[l], x[l], y[l], ws[l]);
-        const int form = 10 * pl.PB + pl.CB;
-        const int64_t here = (pl.n_wgs + 7) / 8 * 8;
-        if (blocks + here > 0x7fffffffLL) {
-            const int rc = flush();
-            if (rc != SNN_OK) return rc;
-        }
-        m.layer[m.n_layers] = L;
-        m.form[m.n_layers] = form;
-        m.first[m.n_layers] = (int)blocks;
-        blocks += here;
-        if (pl.lds > lds) lds = pl.lds;
-        if (++m.n_layers == RF_MANY_MAX) {
-            const int rc = flush();
-            if (rc != SNN_OK) return rc;
-        }
+        const int rc = check_launch();
+        if (rc != SNN_OK) return rc;
     }
-    return flush();
+    return SNN_OK;
 }
 
 }  // namespace snn

@@ -49,3 +49,33 @@ def test_rows_form_at_the_edges_of_its_tiles(oracle, case):
     want, _ = oracle.conv_sign(xs, codes, alpha, beta, stride)
     got = G.subbit_sign(oracle.pack_rows(x), x.shape, cb, idx, alpha, beta, stride)
     assert (got == want).all(), np.argwhere(got != want)[:5]
+
+
+@pytest.mark.parametrize("n_layers, N", [(3, 2), (34, 1), (36, 2), (3, 1700)])
+def test_many_layers_in_one_call_equal_one_call_per_layer(n_layers, N):
+    """The several-layers launch: fewer layers than one holds, exactly as many, a few more, and outputs past 256 MB (the layers
+    come in another order there).  Integer sums and one multiplication: bit for bit."""
+    import torch
+
+    from paper_2110_09195_amd import binding as B
+    print("many layers", n_layers, N, file=sys.stderr, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n_layers + N)
+    shapes = [(40, 70, 9, 33, 1), (65, 33, 5, 7, 2), (8, 128, 14, 25, 1), (200, 16, 6, 6, 1)]
+    layers, want = [], []
+    for i in range(n_layers):
+        C_in, C_out, H, W, stride = shapes[i % len(shapes)]
+        d = B.make_desc(N, C_in, C_out, H, W, stride, 16, B.SNN_ACT_BIN_ROWS)
+        x = B.snn_pack_activations(torch.randn((N, C_in, H, W), generator=gen, device="cuda"), B.SNN_ACT_BIN_ROWS)
+        cb = torch.randperm(512, generator=gen, device="cuda")[:16].to(torch.int16)
+        idx = torch.randint(0, 16, (C_out, C_in), generator=gen, device="cuda").to(torch.int16)
+        alpha = torch.rand(C_out, generator=gen, device="cuda") + 0.5
+        y = torch.full((N, C_out) + B.out_hw(d), float("nan"), device="cuda")
+        layers.append({"desc": d, "x": x, "y": y, "workspace": B.snn_subbit_prepare(d, cb, idx, alpha)})
+        want.append(B.snn_subbit_conv2d(d, x, cb, idx, alpha))
+    if N > 1000:
+        assert sum(v.numel() * 4 for v in want) > 256 << 20
+    B.snn_subbit_conv2d_prepared_many(B.layer_io_array(layers))
+    torch.cuda.synchronize()
+    for a, b in zip(layers, want):
+        assert torch.equal(a["y"], b)

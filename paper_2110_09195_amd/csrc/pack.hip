@@ -6,20 +6,6 @@ namespace snn {
 
 namespace {
 
-// A workgroup packs a run of consecutive blocks of rows: one contiguous piece of the input per workgroup, the
-// loads of the next two blocks in flight while the current one is packed.  (The memory system reads faster that
-// way than when the workgroups in flight share one window of the tensor, 8 KB each: 7.1 against 5.9 TB/s for a
-// read-only stream.)  Runs of four while the launch still has several thousand workgroups (measured on
-// the ResNet-18 stack's 55 000 blocks: 86 us with single blocks, 79 us with runs of two or four, 83 with eight,
-// 85 with sixteen - longer runs leave too few workgroups)
-constexpr int PACK_RUN_MAX = 4;
-inline int pack_run(int64_t blocks)
-{
-    int run = 1;
-    while (run < PACK_RUN_MAX && blocks / (2 * run) >= 4096) run *= 2;
-    return run;
-}
-
 __global__ __launch_bounds__(PACK_THREADS)
 void pack_rows_kernel(const float *__restrict__ x, uint32_t *__restrict__ out, int64_t rows, int W,
                       int WW, int rows_per_block, int vec, int64_t blocks, int run)

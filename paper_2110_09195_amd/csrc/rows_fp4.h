@@ -18,6 +18,10 @@ int launch_rows_fp4_forward(const Geom &g, const float *x, const float *w, const
 // several layers: the weights-side work, and the convolutions from prepared workspaces (fp32 output)
 int launch_rows_fp4_project_many(int n_layers, const Geom *gs, const float *const *w, const uint16_t *const *codebook,
                                  const float *const *alpha, const float *const *beta, uint16_t *const *idx_out, void *const *ws, hipStream_t s);
+// the same with the packing of the layers' activations (x -> xr)
+int launch_rows_fp4_front_many(int n_layers, const Geom *gs, const float *const *x, uint32_t *const *xr, const float *const *w,
+                               const uint16_t *const *codebook, const float *const *alpha, uint16_t *const *idx_out, void *const *ws,
+                               hipStream_t s);
 int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, float *const *y, void *const *ws, hipStream_t s);
 
 }  // namespace snn

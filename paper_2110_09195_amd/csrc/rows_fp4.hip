@@ -800,6 +800,68 @@ void rows_fp4_front_kernel(const RfFront p)
     rf_project_block(p.pr, b, lds);
 }
 
+// The first launch of a stack's forward pass: the same for every layer.  Projection is vector-unit work and packing a stream
+// from memory; in one launch, with the projection's workgroups spread over the first seven eighths of the grid, the
+// one runs beside the other.  Whole forward call of the ResNet-18 stack, one launch after the other -> together: batch 64 185 -> 180 us,
+// batch 16 74 -> 66 us, batch 2 43 -> 39 us; all projections within the first tenth instead: 185 and 70 us (they fill the
+// chip and the stream waits).  Six waves per SIMD asked for: at the projection's own 86 registers five fit, too few loads in flight for
+// the stream (batch 64 182-190 us).
+struct RfFrontLayer {
+    uint32_t *wq;                        // the scales lie behind it
+    const float *w;
+    const uint16_t *codebook;
+    const float *alpha;
+    uint16_t *idx_out;
+    const float *x;
+    uint32_t *xr;
+    int64_t rows;
+    int C_in, C_out, K;
+    int W, rows_per_block, vec, pack_blocks;
+};
+constexpr int RF_FRONT_MAX = 35;
+struct RfFrontMany {
+    int n_layers, run;                   // a packing workgroup takes `run` blocks of rows
+    int project_blocks;                  // every `period`-th workgroup projects until they are through
+    Divisor period;
+    uint32_t period_value;
+    int first_project[RF_FRONT_MAX + 1], first_pack[RF_FRONT_MAX + 1];
+    RfFrontLayer layer[RF_FRONT_MAX];
+};
+static_assert(sizeof(RfFrontMany) <= 4096, "kernel arguments");
+
+__global__ __launch_bounds__(256, 6)
+void rows_fp4_front_many_kernel(const RfFrontMany m)
+{
+    static_assert(PACK_THREADS == 256 && 2 * PACK_LDS_WORDS <= RF_PROJECT_LDS_WORDS, "one block size and buffer for both roles");
+    __shared__ __align__(16) uint32_t lds[RF_PROJECT_LDS_WORDS];
+    const uint32_t b = blockIdx.x;
+    const uint32_t turn = fast_div(b, m.period);
+    if (turn * m.period_value == b && turn < (uint32_t)m.project_blocks) {
+        const int l = layer_of_block(m.first_project, m.n_layers, (int)turn);
+        const RfFrontLayer &c = m.layer[l];
+        RfProject p;
+        p.W = {c.wq, (float *)((char *)c.wq + rf_weight_bytes(c.C_out, c.C_in)), c.C_in, c.C_out, (c.C_out + 31) >> 5, (c.C_in + 31) >> 5};
+        p.w = c.w;
+        p.codebook = c.codebook;
+        p.alpha = c.alpha;
+        p.beta = nullptr;
+        p.idx_out = c.idx_out;
+        p.K = c.K;
+        rf_project_block(p, (int)turn - m.first_project[l], lds);
+        return;
+    }
+    const int q = (int)b - min((int)turn + 1, m.project_blocks);
+    const int l = layer_of_block(m.first_pack, m.n_layers, q);
+    const RfFrontLayer &c = m.layer[l];
+    const int b0 = (q - m.first_pack[l]) * m.run, b1 = min(b0 + m.run, c.pack_blocks);
+    const int WW = (c.W + 31) >> 5;
+    if (c.vec && c.W <= PACK_CHUNK) {
+        pack_rows_stream(c.x, c.xr, c.rows, c.W, WW, c.rows_per_block, (int64_t)b0, (int64_t)b1, lds);
+        return;
+    }
+    for (int i = b0; i < b1; ++i) pack_rows_block(c.x, c.xr, c.rows, c.W, WW, c.rows_per_block, c.vec, (int64_t)i, lds);
+}
+
 // ---- host side -----------------------------------------------------------------------------------------------------------
 
 struct RfPlan {
@@ -1014,6 +1076,50 @@ int launch_rows_fp4_project_many(int n_layers, const Geom *gs, const float *cons
         }
         for (int i = m.n_layers; i <= RF_PROJECT_MAX; ++i) m.first[i] = (int)blocks;
         hipLaunchKernelGGL(rows_fp4_project_many_kernel, dim3((unsigned)blocks), dim3(256), 0, s, m);
+        const int rc = check_launch();
+        if (rc != SNN_OK) return rc;
+    }
+    return SNN_OK;
+}
+
+int launch_rows_fp4_front_many(int n_layers, const Geom *gs, const float *const *x, uint32_t *const *xr, const float *const *w,
+                               const uint16_t *const *codebook, const float *const *alpha, uint16_t *const *idx_out, void *const *ws,
+                               hipStream_t s)
+{
+    for (int l0 = 0; l0 < n_layers; l0 += RF_FRONT_MAX) {
+        RfFrontMany m;
+        m.n_layers = std::min(RF_FRONT_MAX, n_layers - l0);
+        int64_t row_blocks = 0, project = 0, pack = 0;
+        for (int i = 0; i < m.n_layers; ++i) {
+            const Geom &g = gs[l0 + i];
+            row_blocks += pack_rows_plan(x[l0 + i], (int64_t)g.N * g.C_in * g.H, g.W).blocks;
+        }
+        m.run = pack_run(row_blocks);
+        for (int i = 0; i < m.n_layers; ++i) {
+            const int l = l0 + i;
+            const Geom &g = gs[l];
+            const int64_t rows = (int64_t)g.N * g.C_in * g.H;
+            const PackRowsPlan pk = pack_rows_plan(x[l], rows, g.W);
+            if (pk.blocks > 0x7fffffffLL) return SNN_ERR_UNSUPPORTED;
+            m.layer[i] = {(uint32_t *)ws[l], w[l], codebook[l], alpha[l], idx_out[l], x[l], xr[l], rows, g.C_in, g.C_out, g.K,
+                          g.W, pk.rows_per_block, pk.vec, (int)pk.blocks};
+            m.first_project[i] = (int)project;
+            m.first_pack[i] = (int)pack;
+            project += (int64_t)((g.C_out + 31) / 32) * ((g.C_in + 31) / 32);
+            pack += (pk.blocks + m.run - 1) / m.run;
+            if (project + pack > 0x7fffffffLL) return SNN_ERR_UNSUPPORTED;
+        }
+        for (int i = m.n_layers; i <= RF_FRONT_MAX; ++i) {
+            m.first_project[i] = (int)project;
+            m.first_pack[i] = (int)pack;
+        }
+        m.project_blocks = (int)project;
+        // odd: consecutive workgroups go to the eight XCDs in turn, an even period would leave some without projections
+        int64_t period = (project + pack) * 7 / 8 / project;
+        period = period < 1 ? 1 : period - 1 + (period & 1);
+        m.period_value = (uint32_t)period;
+        m.period = make_divisor((uint32_t)period);
+        hipLaunchKernelGGL(rows_fp4_front_many_kernel, dim3((unsigned)(project + pack)), dim3(256), 0, s, m);
         const int rc = check_launch();
         if (rc != SNN_OK) return rc;
     }

@@ -502,16 +502,22 @@ int snn_subbit_forward_many(const snn_layer_forward *layers, int n_layers, void 
         y[l] = L.y_nchw;
         ws[l] = L.workspace;
     }
-    std::vector<int64_t> rows(n_layers);
-    std::vector<int> widths(n_layers);
-    std::vector<const float *> no_beta(n_layers, nullptr);
-    for (int l = 0; l < n_layers; ++l) {
-        rows[l] = (int64_t)gs[l].N * gs[l].C_in * gs[l].H;
-        widths[l] = gs[l].W;
+    int rc;
+    if (split_forms(gs).two_stage.empty()) {
+        rc = launch_rows_fp4_front_many(n_layers, gs.data(), x.data(), xr.data(), w.data(), codebook.data(), alpha.data(), idx_out.data(),
+                                        ws.data(), (hipStream_t)stream);
+    } else {
+        std::vector<int64_t> rows(n_layers);
+        std::vector<int> widths(n_layers);
+        std::vector<const float *> no_beta(n_layers, nullptr);
+        for (int l = 0; l < n_layers; ++l) {
+            rows[l] = (int64_t)gs[l].N * gs[l].C_in * gs[l].H;
+            widths[l] = gs[l].W;
+        }
+        rc = launch_pack_rows_many(n_layers, x.data(), xr.data(), rows.data(), widths.data(), (hipStream_t)stream);
+        if (rc != SNN_OK) return rc;
+        rc = prepare_layers(gs, w, codebook, alpha, no_beta, idx_out, ws, (hipStream_t)stream);
     }
-    int rc = launch_pack_rows_many(n_layers, x.data(), xr.data(), rows.data(), widths.data(), (hipStream_t)stream);
-    if (rc != SNN_OK) return rc;
-    rc = prepare_layers(gs, w, codebook, alpha, no_beta, idx_out, ws, (hipStream_t)stream);
     if (rc != SNN_OK) return rc;
     return convolve_layers(gs, xp, y, ws, (hipStream_t)stream);
 }

@@ -79,3 +79,34 @@ def test_many_layers_in_one_call_equal_one_call_per_layer(n_layers, N):
     torch.cuda.synchronize()
     for a, b in zip(layers, want):
         assert torch.equal(a["y"], b)
+
+
+@pytest.mark.parametrize("n_layers, N", [(1, 1), (3, 70), (35, 2), (37, 1)])
+def test_forward_of_many_layers_equals_forward_per_layer(n_layers, N):
+    """Projection and packing of several layers in one launch: a grid of almost nothing but projections, one with packing
+    workgroups between all of them, as many layers as a launch holds and a few more; rows that pack vectorised and not."""
+    import torch
+
+    from paper_2110_09195_amd import binding as B
+    print("forward of many layers", n_layers, N, file=sys.stderr, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n_layers * 1000 + N)
+    shapes = [(40, 70, 9, 33, 1), (65, 33, 5, 7, 2), (64, 64, 28, 28, 1), (3, 16, 2, 2100, 2)]
+    layers = []
+    for i in range(n_layers):
+        C_in, C_out, H, W, stride = shapes[i % len(shapes)]
+        K = (16, 64, 5)[i % 3]
+        d = B.make_desc(N, C_in, C_out, H, W, stride, K, B.SNN_ACT_BIN_ROWS)
+        layers.append({"desc": d, "x": torch.randn((N, C_in, H, W), generator=gen, device="cuda"),
+                       "w": torch.randn((C_out * C_in, 9), generator=gen, device="cuda"),
+                       "codebook": torch.sort(torch.randperm(512, generator=gen, device="cuda")[:K]).values.to(torch.int16),
+                       "alpha": torch.rand(C_out, generator=gen, device="cuda") + 0.5,
+                       "idx_out": torch.full((C_out * C_in,), -1, dtype=torch.int16, device="cuda"),
+                       "y": torch.full((N, C_out) + B.out_hw(d), float("nan"), device="cuda"), "workspace": B.alloc_workspace(d, B.SNN_WS_FORWARD)})
+    B.snn_subbit_forward_many(B.layer_forward_array(layers))
+    for L in layers:
+        idx = B.snn_project_kernels(L["w"], L["codebook"])
+        assert torch.equal(L["idx_out"], idx)
+        d = L["desc"]
+        y = B.snn_subbit_conv2d(d, B.snn_pack_activations(L["x"], B.SNN_ACT_BIN_ROWS), L["codebook"], idx.view(d.C_out, d.C_in), L["alpha"])
+        assert torch.equal(L["y"], y)

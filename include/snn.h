@@ -547,7 +547,7 @@ int snn_subbit_slots_per_channel(const snn_conv_desc *desc);
 #define SNN_TUNE_MFMA_STAGE  3 /* 0 / 1: packed rows staged in LDS wherever they fit */
 #define SNN_TUNE_MFMA_QUAD   4 /* 0 / 1: four channels per matrix instruction wherever K <= 16 */
 #define SNN_TUNE_STACK       5 /* 0: snn_subbit_conv2d_prepared_many runs one workgroup per tile group */
-#define SNN_TUNE_BNN_REGS    6 /* 0: the 1-bit kernel without register-resident windows */
+#define SNN_TUNE_BNN_REGS    6 /* the 1-bit layer's popcount kernels: 1 with register-resident windows, 0 without */
 #define SNN_TUNE_DENSE_TILE  7 /* 0 .. 4: tile shape of the dense contraction */
 #define SNN_TUNE_F32_WAVES   8 /* 4, 8, 16: waves per workgroup of the fp32-activation sub-bit kernel */
 #define SNN_TUNE_COUNT       9

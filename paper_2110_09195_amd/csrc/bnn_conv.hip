@@ -2,7 +2,8 @@
 // words of 32 input channels.  It is the denominator of every speed-up the sub-bit kernel
 // reports, so it is written to the same standard.
 //
-// Packed activations (SNN_ACT_BIN_CHANNELS), two kernels.  Up to 512 input channels: one lane owns
+// Packed activations (SNN_ACT_BIN_CHANNELS): most layers go to the matrix cores (rows_fp4.hip).  The others, and the XNOR/popcount
+// baseline when it is asked for by SNN_TUNE_BNN_REGS, have two kernels here.  Up to 512 input channels: one lane owns
 // one output pixel and keeps its window in registers; a block walks a chunk of output channels
 // whose weight words wait in LDS (bnn_regs_kernel).  More channels: one lane owns PXL output
 // pixels and keeps the mismatch counts of a block of COG output channels in registers; the loop
@@ -13,8 +14,10 @@
 // out again with a per-(channel, border type) table.
 //
 // fp32 activations (SNN_ACT_F32, the W/A = 1/32 rows): the same direct loop with add/subtract.
+#include <algorithm>
 #include <cstdlib>
 
+#include "rows_fp4.h"
 #include "snn_internal.h"
 
 namespace snn {
@@ -354,12 +357,13 @@ BnnCfg bnn_cfg(const Geom &g)
 size_t bnn_workspace_bytes(const Geom &g, int act)
 {
     if (act == SNN_ACT_F32) return align_up((size_t)g.C_out * g.C_in * sizeof(uint32_t), 256);
-    // room for either kernel's tables (channels rounded up to the largest channel block, words to a power of two)
+    // room for any kernel's tables (channels rounded up to the largest channel block, words to a power of two)
     int CWT = 1;
     while (CWT < g.CW) CWT <<= 1;
     const int CWmax = g.CW <= 16 ? CWT : g.CW;
     const int COP = (g.C_out + 31) / 32 * 32;
-    return align_up((size_t)COP * 9 * CWmax * sizeof(uint32_t), 256) + align_up((size_t)COP * 16 * sizeof(int32_t), 256);
+    const size_t counts = align_up((size_t)COP * 9 * CWmax * sizeof(uint32_t), 256) + align_up((size_t)COP * 16 * sizeof(int32_t), 256);
+    return std::max(counts, bnn_rows_workspace_bytes(g));
 }
 
 int launch_bnn(const Geom &g, int act, const void *x, const uint16_t *w9, const float *alpha, float *y,
@@ -380,6 +384,10 @@ int launch_bnn(const Geom &g, int act, const void *x, const uint16_t *w9, const 
                                (const float *)x, flips, alpha, y, g);
         return check_launch();
     }
+
+    // The matrix cores take the layer wherever their kernel's tile fits and its blocks have
+    // something to do (figures at the rule)
+    if (bnn_rows_form(g)) return launch_bnn_rows(g, x, w9, alpha, y, ws, s, phases);
 
     // (its window loads use 32-bit byte offsets whose top bit means "outside": packed inputs below 2 GiB)
     if (g.CW <= 16 && (int64_t)g.N * g.H * g.W * g.CW < ((int64_t)1 << 29) &&

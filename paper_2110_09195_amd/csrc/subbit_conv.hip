@@ -323,9 +323,9 @@ int launch_subbit_fitting(const Geom &g, int act, const void *x, const uint16_t 
 {
     if (act == SNN_ACT_F32)
         return subbit_f32_workspace_bytes(g) <= ws_bytes ? launch_subbit(g, act, x, codebook, idx, alpha, y, ws, s) : SNN_ERR_WORKSPACE;
+    if (two_stage_bytes(g) > ws_bytes) return SNN_ERR_WORKSPACE;      // the limit callers know, whatever form runs
     if (subbit_rows_form(g) && rows_fp4_workspace_bytes(g) <= ws_bytes)
         return launch_rows_fp4(g, x, codebook, idx, 0, alpha, y, ws, s, nullptr, SNN_PHASE_BOTH);
-    if (two_stage_bytes(g) > ws_bytes) return SNN_ERR_WORKSPACE;
     return launch_two_stage(g, x, codebook, idx, alpha, y, ws, s, SNN_PHASE_BOTH);
 }
 

@@ -68,3 +68,17 @@ def test_noalloc_refuses_layers_beyond_its_buffer():
     p = ctypes.c_void_p(t.data_ptr())
     rc = L.snn_subbit_conv2d_noalloc(ctypes.byref(d), p, p, p, p, p, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
     assert rc == -3, B.status_string(rc)
+
+
+def test_noalloc_keeps_its_limit_where_one_forms_tables_would_fit():
+    L = B.lib()
+    # 1024 x 1024 kernels, K = 32: 1.2 MB of tables for the dense contraction, 4.2 MB for the two-stage kernels
+    d = B.make_desc(1, 1024, 1024, 1, 1, 1, 32, B.SNN_ACT_BIN_ROWS)
+    x, cb, idx, alpha = _layer(0, 1, 1024, 1024, 1, 1, 1, 32)
+    xp = B.snn_pack_activations(_dev(x), B.SNN_ACT_BIN_ROWS)
+    y = torch.full((1, 1024, 1, 1), 7.0, device="cuda")
+    cb_d, idx_d, al_d = _dev(cb), _dev(idx), _dev(alpha)
+    rc = L.snn_subbit_conv2d_noalloc(ctypes.byref(d), xp.data_ptr(), cb_d.data_ptr(), idx_d.data_ptr(), al_d.data_ptr(), y.data_ptr(),
+                                     torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == -3 and (y == 7.0).all()

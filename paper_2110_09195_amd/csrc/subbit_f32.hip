@@ -199,6 +199,161 @@ void subbit_f32_prep_kernel(const uint16_t *__restrict__ codebook, const uint16_
     }
 }
 
+// ---- the dense form ----------------------------------------------------------------------------------------------------
+// S[co][pixel] = sum over taps and input channels of w x on v_mfma_f32_32x32x2_f32: a wave owns 32 output channels x 32
+// pixels, a step is a pair of input channels (one per lane half) at one tap.  The weight operand is +-1.0f made from the
+// channel's 9-bit code in two instructions, the activation operand comes straight from memory (L1 / L2: 64 x 4 bytes per 64
+// clocks of matrix work), three pairs of channels ahead.  Each tap has an accumulator of its own, so that no chain of roundings
+// is longer than the two-stage form's over the channels.
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+constexpr uint32_t SD_NONE = 0x80000000u;              // past every buffer used here
+
+// codes of [32 output channels][4 pairs of input channels]: lane (co, h) has the pairs' channels 2 p + h as four uint16
+// S = 4: the four waves of a workgroup share a block and split its channels, their sums meet in LDS (a quarter of the chain, four
+// times the waves: 1 x 512 -> 64 7x7 has four blocks); S = 1: a block per wave, for the few channels that are not worth it.
+template <int S>
+__global__ __launch_bounds__(256, 2)
+void subbit_f32_dense_kernel(const float *__restrict__ x, const uint32_t *__restrict__ wq, const float *__restrict__ alpha,
+                             float *__restrict__ y, Geom g, int n_cob, int quads, uint32_t n_blocks)
+{
+    const int lane = threadIdx.x & 63, n_l = lane & 31, h = lane >> 5;
+    const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t id = S == 1 ? blockIdx.x * 4u + (uint32_t)wave : blockIdx.x;
+    if (id >= n_blocks) return;                                // (S = 4: never, the grid is n_blocks)
+    const uint32_t blk = id / (uint32_t)n_cob;
+    const int cob = (int)(id - blk * (uint32_t)n_cob);
+    const uint32_t P = (uint32_t)g.P, HoWo = (uint32_t)g.HoWo;
+    const uint32_t n0 = blk * 32u / HoWo;
+    const bool mine = blk * 32u + (uint32_t)n_l < P;
+    const uint32_t pp = min(blk * 32u + (uint32_t)n_l, P - 1u);
+    const uint32_t n = pp / HoWo, r = pp - n * HoWo;
+    const int ho = (int)(r / (uint32_t)g.Wo), wo = (int)r - ho * g.Wo;
+
+    const int64_t x_image = (int64_t)g.C_in * g.H * g.W, y_image = (int64_t)g.C_out * g.HoWo;
+    const int64_t lim = 0x7fffffff;
+    const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(x + (int64_t)n0 * x_image), 0, (int)min((int64_t)(g.N - (int)n0) * x_image * 4, lim), 0x00020000);
+    const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(
+        y + (int64_t)n0 * y_image, 0, (int)min((int64_t)(g.N - (int)n0) * y_image * 4, lim), 0x00020000);
+    const uint32_t plane = (uint32_t)(g.H * g.W) * 4u;
+    uint32_t off[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        const int hh = ho * g.stride + t / 3 - 1, ww = wo * g.stride + t % 3 - 1;
+        const bool in = hh >= 0 && hh < g.H && ww >= 0 && ww < g.W;
+        off[t] = in ? (n - n0) * (uint32_t)x_image * 4u + (uint32_t)h * plane + (uint32_t)(hh * g.W + ww) * 4u : SD_NONE;
+    }
+    const int pairs = (g.C_in + 1) >> 1;
+    float B[4][9];
+    auto load_pair = [&](int p, float (&b)[9]) {               // (past the last channel: zeros, nothing read)
+        const bool have = 2 * p + h < g.C_in;
+        const uint32_t at = 2u * (uint32_t)min(p, pairs - 1) * plane;
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+            b[t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xres, (int)(have ? off[t] : SD_NONE), (int)at, 0));
+    };
+    const u32x2 *codes = (const u32x2 *)wq + (int64_t)cob * quads * 64 + lane;
+    const int q0 = S == 1 ? 0 : wave * quads / S, q1 = S == 1 ? quads : (wave + 1) * quads / S;
+    const int p_end = min(pairs, 4 * q1);
+    u32x2 c = codes[(int64_t)min(q0, quads - 1) * 64];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) load_pair(4 * q0 + u, B[u]);
+    // accumulator register i is row 8 (i / 4) + 4 h + i % 4; a wave stores all sixteen, or four of the sums of four waves
+    constexpr int NR = 16 / S;
+    const int row0 = S == 1 ? 0 : 8 * wave;
+    float al[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) al[i] = alpha[min(cob * 32 + row0 + 8 * (i >> 2) + 4 * h + (i & 3), g.C_out - 1)];
+    v16f acc[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[t][i] = 0.0f;
+    for (int q = q0; q < q1; ++q) {
+        const u32x2 cn = codes[(int64_t)min(q + 1, quads - 1) * 64];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int p = 4 * q + u;
+            if (p < p_end) {                                   // (wave-uniform)
+                if (p + 3 < p_end) load_pair(p + 3, B[(u + 3) & 3]);
+                const uint32_t code = c[u >> 1] >> (16 * (u & 1));     // bit t: tap t is -1
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    const float w = __uint_as_float(((code << (31 - t)) & 0x80000000u) | 0x3f800000u);
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, B[u][t], acc[t], 0, 0, 0);
+                }
+            }
+        }
+        c = cn;
+    }
+    const uint32_t yo = mine ? (((n - n0) * (uint32_t)g.C_out + 4u * (uint32_t)h) * HoWo + r) * 4u : SD_NONE;
+    float sum[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        sum[i] = ((acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i])) + ((acc[4][i] + acc[5][i]) + (acc[6][i] + acc[7][i])) + acc[8][i];
+    if constexpr (S > 1) {
+        __shared__ float part[S][16][64];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) part[wave][i][lane] = sum[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const int r16 = NR * wave + i;
+            sum[i] = (part[0][r16][lane] + part[1][r16][lane]) + (part[2][r16][lane] + part[3][r16][lane]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int co = cob * 32 + row0 + 8 * (i >> 2) + (i & 3);
+        const uint32_t o = co + 4 * h < g.C_out ? yo : SD_NONE;
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum[i] * al[i]), yres, (int)o, (int)((uint32_t)min(co, g.C_out - 1) * HoWo * 4u), 2);
+    }
+}
+
+__global__ __launch_bounds__(256)
+void subbit_f32_dense_prep_kernel(const uint16_t *__restrict__ codebook, const uint16_t *__restrict__ idx, int C_in, int C_out, int K,
+                                  int quads, int n, uint16_t *__restrict__ wq)
+{
+    const int gid = blockIdx.x * 256 + threadIdx.x;            // [cob][quad][lane][pair of the quad]
+    if (gid >= n) return;
+    const int lane = (gid >> 2) & 63, cq = gid >> 8;
+    const int cob = cq / quads, q = cq - cob * quads;
+    const int co = cob * 32 + (lane & 31), ci = 8 * q + 2 * (gid & 3) + (lane >> 5);
+    uint32_t code = 0;
+    if (co < C_out && ci < C_in) code = code_to_window_order(codebook[min((int)idx[(int64_t)co * C_in + ci], K - 1)] & 511u) ^ 511u;
+    wq[gid] = (uint16_t)code;
+}
+
+struct SdPlan { int n_cob, quads; int64_t n_blocks; };
+
+SdPlan sd_plan(const Geom &g)
+{
+    SdPlan p;
+    p.n_cob = (g.C_out + 31) / 32;
+    p.quads = (g.C_in + 7) / 8;
+    p.n_blocks = (g.P + 31) / 32 * p.n_cob;
+    return p;
+}
+
+bool use_dense(const Geom &g)
+{
+    if (tuning(SNN_TUNE_F32_WAVES) != SNN_TUNE_AUTO) return false;
+    // its words lie in the two-stage form's workspace (up to seven padding channels: 14 C_out bytes of the 20 KB before the
+    // offsets); 32-bit offsets inside the images of 32 pixels
+    const int64_t lim = ((int64_t)1 << 31) - 4096, images = (g.HoWo - 1 + 31) / g.HoWo + 1;
+    if (g.C_out > 512 || images * g.C_in * g.H * g.W * 4 >= lim || images * g.C_out * g.HoWo * 4 >= lim || g.P >= lim ||
+        sd_plan(g).n_blocks >= lim || (int64_t)sd_plan(g).n_cob * sd_plan(g).quads * 256 >= lim)
+        return false;
+    // Nine fp32 multiply-adds per output channel against nine per subset member and a gather: the two-stage form is left the
+    // small subsets with few output channels.  Measured, two-stage (its best workgroup) -> dense, prepared weights, us:
+    // 64 -> 64 8x8 batch 256 K = 4 15.1 -> 20, K = 16 21.0 -> 20.2, K = 32 25.5 -> 20.1, K = 64 49.6 -> 19.4;
+    // 16 -> 16 32x32 batch 128 K = 4 16.8 -> 20.8, K = 16 24.7 -> 20.7; 16 -> 256 56x56 batch 4 K = 4 26.1 -> 20.0;
+    // 512 -> 512 7x7 batch 8 K = 4 217 -> 36, K = 32 323 -> 36.  Relative error of the sums against 64 bits: 1.0e-7 for
+    // 1.6e-7 at 64 channels, 2.2e-7 for 4.1e-7 at 512.
+    return g.K >= 16 || g.C_out >= 256;
+}
+
 }  // namespace
 
 size_t subbit_f32_workspace_bytes(const Geom &g)
@@ -212,6 +367,21 @@ size_t subbit_f32_workspace_bytes(const Geom &g)
 int launch_subbit_f32(const Geom &g, const void *x, const uint16_t *codebook, const uint16_t *idx,
                       const float *alpha, float *y, void *ws, hipStream_t s, int phases)
 {
+    if (use_dense(g)) {
+        const SdPlan p = sd_plan(g);
+        const int words = p.n_cob * p.quads * 256;
+        if (phases & SNN_PHASE_PREPARE) {
+            hipLaunchKernelGGL(subbit_f32_dense_prep_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, codebook, idx, g.C_in, g.C_out,
+                               g.K, p.quads, words, (uint16_t *)ws);
+            const int rc = check_launch();
+            if (rc != SNN_OK) return rc;
+        }
+        if (!(phases & SNN_PHASE_CONVOLVE)) return SNN_OK;
+        const bool split = p.quads >= 4;
+        hipLaunchKernelGGL(split ? subbit_f32_dense_kernel<4> : subbit_f32_dense_kernel<1>, dim3((unsigned)(split ? p.n_blocks : (p.n_blocks + 3) / 4)),
+                           dim3(256), 0, s, (const float *)x, (const uint32_t *)ws, alpha, y, g, p.n_cob, p.quads, (uint32_t)p.n_blocks);
+        return check_launch();
+    }
     const F32Cfg c = pick_f32_cfg(g);
     const int COP = (g.C_out + c.COB - 1) / c.COB * c.COB;
     uint32_t *codes = (uint32_t *)ws;

@@ -275,11 +275,13 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             }
             for (int c0 = 0; c0 < ncb; c0 += 4) {
                 uint32_t w[2][4];
+                // (the scalar offset stays inside the buffer, also for words that do not exist: a lane offset is checked against what
+                // the scalar one leaves of the buffer, which for the last pixel of one word would be less than nothing)
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
-                        w[u][c] = __builtin_amdgcn_raw_buffer_load_b32(cres, (int)(c0 + c < ncb ? off[u] : OFF_NONE), 4 * (c0 + c), 0);
+                        w[u][c] = __builtin_amdgcn_raw_buffer_load_b32(cres, (int)(c0 + c < ncb ? off[u] : OFF_NONE), 4 * min(c0 + c, ncb - 1), 0);
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll

@@ -25,6 +25,13 @@ EDGES = [
     (300, 24, 20, 7, 7, 1),          # tiles that run over several images
     (40, 40, 200, 30, 30, 1),
     (70, 10, 70, 60, 60, 1),         # four pixel blocks per wave
+    # images of fewer words than the four that are loaded side by side, alone and as the last one of a batch
+    (1, 32, 8, 1, 1, 1),
+    (3, 20, 40, 1, 1, 2),
+    (1, 64, 70, 1, 1, 1),
+    (129, 33, 40, 1, 1, 1),
+    (2, 160, 33, 1, 1, 1),           # five words: the second group of four has one
+    (1, 30, 64, 1, 2, 2),
 ]
 
 

@@ -354,13 +354,46 @@ BnnCfg bnn_cfg(const Geom &g)
     return cands[3];
 }
 
+// Up to 512 input channels and (its window loads use 32-bit byte offsets whose top bit means "outside") packed inputs below
+// 2 GiB: the kernel with register-resident windows.
+bool bnn_regs_form(const Geom &g)
+{
+    return g.CW <= 16 && (int64_t)g.N * g.H * g.W * g.CW < ((int64_t)1 << 29) && tuning(SNN_TUNE_BNN_REGS) != 0;
+}
+
+int bnn_regs_chunk_for(const Geom &g, int CWT)
+{
+    // channels per block: fewer than the kernel's chunk where the layer would not fill the chip otherwise
+    const int64_t pblocks = (g.P + BNN_THREADS - 1) / BNN_THREADS;
+    int ch = bnn_regs_chunk(CWT);
+    while (ch > 8 && pblocks * ((g.C_out + ch - 1) / ch) < 2048) ch /= 2;
+    return ch;
+}
+
+int bnn_words_pow2(const Geom &g)
+{
+    int CWT = 1;
+    while (CWT < g.CW) CWT <<= 1;
+    return CWT;
+}
+
+// What the popcount kernels run: their grids, and 32-bit word offsets into the packed input.
+bool bnn_popcount_takes(const Geom &g)
+{
+    if (bnn_regs_form(g)) {
+        const int ch = bnn_regs_chunk_for(g, bnn_words_pow2(g));
+        return (g.C_out + ch - 1) / ch <= 65535;
+    }
+    const BnnCfg c = bnn_cfg(g);
+    return (g.P + (int64_t)BNN_THREADS * c.PXL - 1) / ((int64_t)BNN_THREADS * c.PXL) <= 0x7fffffffLL &&
+           (g.C_out + c.COG - 1) / c.COG <= 65535 && (int64_t)g.N * g.H * g.W * g.CW < ((int64_t)1 << 31);
+}
+
 size_t bnn_workspace_bytes(const Geom &g, int act)
 {
     if (act == SNN_ACT_F32) return align_up((size_t)g.C_out * g.C_in * sizeof(uint32_t), 256);
     // room for any kernel's tables (channels rounded up to the largest channel block, words to a power of two)
-    int CWT = 1;
-    while (CWT < g.CW) CWT <<= 1;
-    const int CWmax = g.CW <= 16 ? CWT : g.CW;
+    const int CWmax = g.CW <= 16 ? bnn_words_pow2(g) : g.CW;
     const int COP = (g.C_out + 31) / 32 * 32;
     const size_t counts = align_up((size_t)COP * 9 * CWmax * sizeof(uint32_t), 256) + align_up((size_t)COP * 16 * sizeof(int32_t), 256);
     return std::max(counts, bnn_rows_workspace_bytes(g));
@@ -385,23 +418,16 @@ int launch_bnn(const Geom &g, int act, const void *x, const uint16_t *w9, const 
         return check_launch();
     }
 
+    if (!bnn_popcount_takes(g)) return SNN_ERR_UNSUPPORTED;       // (whichever form would run)
     // The matrix cores take the layer wherever their kernel's tile fits and its blocks have
     // something to do (figures at the rule)
     if (bnn_rows_form(g)) return launch_bnn_rows(g, x, w9, alpha, y, ws, s, phases);
 
-    // (its window loads use 32-bit byte offsets whose top bit means "outside": packed inputs below 2 GiB)
-    if (g.CW <= 16 && (int64_t)g.N * g.H * g.W * g.CW < ((int64_t)1 << 29) &&
-        tuning(SNN_TUNE_BNN_REGS) != 0) {
-        // register-resident windows (C_in <= 512)
-        int CWT = 1;
-        while (CWT < g.CW) CWT <<= 1;
+    if (bnn_regs_form(g)) {
+        const int CWT = bnn_words_pow2(g);
         uint32_t *wplanes = (uint32_t *)ws;
         int32_t *corr = (int32_t *)((char *)ws + align_up((size_t)g.C_out * 9 * CWT * sizeof(uint32_t), 256));
-        // channels per block: fewer than the kernel's chunk where the layer would not fill the chip otherwise
-        int ch = bnn_regs_chunk(CWT);
-        while (ch > 8 && pblocks * ((g.C_out + ch - 1) / ch) < 2048) ch /= 2;
-        const int cgroups = (g.C_out + ch - 1) / ch;
-        if (cgroups > 65535) return SNN_ERR_UNSUPPORTED;
+        const int ch = bnn_regs_chunk_for(g, CWT), cgroups = (g.C_out + ch - 1) / ch;
         if (prepare)
             hipLaunchKernelGGL(bnn_prep_bin_kernel, dim3((unsigned)((g.C_out + 3) / 4)), dim3(256), 0, s, w9, g.C_out,
                                g.C_out, g.C_in, CWT, 1, wplanes, corr);
@@ -429,9 +455,6 @@ int launch_bnn(const Geom &g, int act, const void *x, const uint16_t *w9, const 
     int32_t *corr = (int32_t *)((char *)ws + align_up((size_t)COP * 9 * g.CW * sizeof(uint32_t), 256));
     const int64_t pb = (g.P + (int64_t)BNN_THREADS * c.PXL - 1) / ((int64_t)BNN_THREADS * c.PXL);
     const int cgroups = COP / c.COG;
-    if (pb > 0x7fffffffLL || cgroups > 65535) return SNN_ERR_UNSUPPORTED;
-    // the kernel addresses the packed input with 32-bit word offsets
-    if ((int64_t)g.N * g.H * g.W * g.CW >= ((int64_t)1 << 31)) return SNN_ERR_UNSUPPORTED;
 
     if (prepare)
         hipLaunchKernelGGL(bnn_prep_bin_kernel, dim3((unsigned)((COP + 3) / 4)), dim3(256), 0, s, w9, g.C_out, COP, g.C_in,

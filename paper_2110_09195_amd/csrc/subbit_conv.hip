@@ -273,6 +273,13 @@ bool use_mfma(const Geom &g)
     return subbit_mfma_supported(g) && tuning(SNN_TUNE_SUBBIT_MFMA) != 0;
 }
 
+// What the LDS-gather kernel runs: its grid, its LDS, and 32-bit word offsets into the packed input.
+bool gather_takes(const Geom &g, const SbPlan &pl)
+{
+    return (g.P + 63) / 64 <= 0x7fffffffLL && pl.COP / pl.cfg.cob() <= 65535 && pl.lds <= 160 * 1024 &&
+           (int64_t)g.N * g.C_in * g.H * g.WW < ((int64_t)1 << 31);
+}
+
 // the tables of either two-stage kernel, so that the override cannot outgrow a workspace
 size_t two_stage_bytes(const Geom &g)
 {
@@ -286,11 +293,14 @@ size_t two_stage_bytes(const Geom &g)
 // The dense contraction (rows_fp4.hip) takes every layer it supports: nine contraction slots per input channel against
 // the 16, 32 or 64 of the one-hot form; measured on every layer shape of the ResNets and on ragged ones it is the faster
 // form for all K (figures in that file; the smallest gain, 16 -> 16 channels 32x32 batch 8, is 1.16x).
-// Asking for one of the two-stage kernels' forms through a knob selects those kernels.
+// Asking for one of the two-stage kernels' forms through a knob selects those kernels.  A layer that neither of them runs is
+// refused, whatever this form could do (packed inputs of 2^31 words and more, as the header says, and outputs of 65536 blocks
+// of 256 channels).
 bool subbit_rows_form(const Geom &g)
 {
     for (int knob : {SNN_TUNE_SUBBIT_MFMA, SNN_TUNE_MFMA_TILE, SNN_TUNE_MFMA_KS, SNN_TUNE_MFMA_STAGE, SNN_TUNE_MFMA_QUAD, SNN_TUNE_STACK})
         if (tuning(knob) != SNN_TUNE_AUTO) return false;
+    if (!subbit_mfma_supported(g) && !gather_takes(g, make_plan(g))) return false;
     return rows_fp4_supported(g);
 }
 
@@ -348,9 +358,7 @@ int launch_two_stage(const Geom &g, const void *x, const uint16_t *codebook, con
     const SbCfg &c = pl.cfg;
     const int64_t tiles = (g.P + 63) / 64;
     const int cblocks = pl.COP / c.cob();
-    if (tiles > 0x7fffffffLL || cblocks > 65535 || pl.lds > 160 * 1024) return SNN_ERR_UNSUPPORTED;
-    // the kernel addresses the packed input with 32-bit word offsets
-    if ((int64_t)g.N * g.C_in * g.H * g.WW >= ((int64_t)1 << 31)) return SNN_ERR_UNSUPPORTED;
+    if (!gather_takes(g, pl)) return SNN_ERR_UNSUPPORTED;
 
     SbParams prm;
     prm.x = (const uint32_t *)x;
@@ -397,6 +405,7 @@ int launch_subbit_forward(const Geom &g, const float *x, const float *w, const u
     if (!subbit_rows_form(g) && use_mfma(g))
         return launch_subbit_forward_mfma(g, x, w, codebook, alpha, idx_out, y, xr, (char *)ws + subbit_two_stage_offset(g), s);
     // larger subsets, and layers no matrix-core kernel takes: the three operations one after the other
+    if (!subbit_mfma_supported(g) && !gather_takes(g, make_plan(g))) return SNN_ERR_UNSUPPORTED;      // (before anything is enqueued)
     int rc = launch_pack_rows(x, xr, (int64_t)g.N * g.C_in * g.H, g.W, s);
     if (rc != SNN_OK) return rc;
     rc = launch_project(w, (int64_t)g.C_out * g.C_in, codebook, g.K, idx_out, s);

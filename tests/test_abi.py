@@ -148,3 +148,26 @@ def test_workspace_covers_both_pixel_block_forms(L, tune):
         smaller = B.snn_workspace_bytes(d, B.SNN_WS_SUBBIT)
         tune("MFMA_QUAD", B.SNN_TUNE_AUTO)
         assert smaller < B.snn_workspace_bytes(d, B.SNN_WS_SUBBIT)
+
+
+def test_layers_past_the_documented_limits_are_refused_before_device_work(L):
+    """Packed inputs of 2^31 words and more, and outputs of more than 65535 channel blocks: UNSUPPORTED from every call, whichever
+    kernel the library would pick for a smaller layer of that kind.  (The pointers are never used.)"""
+    B = binding
+    p, big = ctypes.c_void_p(256), 1 << 62
+    rows, chans = B.SNN_ACT_BIN_ROWS, B.SNN_ACT_BIN_CHANNELS
+    for N, C_in, C_out, H, W, K in ((1 << 20, 2048, 8, 1, 1, 512), (1 << 20, 2048, 8, 1, 1, 32), (1 << 16, 128, 300, 32, 257, 64),
+                                    (1 << 20, 4096, 40, 1, 3, 200), (1, 32, 65536 * 256, 1, 1, 512)):
+        d = B.make_desc(N, C_in, C_out, H, W, 1, K, rows)
+        r = ctypes.byref(d)
+        assert L.snn_subbit_conv2d(r, p, p, p, p, p, p, big, None) == B.SNN_ERR_UNSUPPORTED, (N, C_in, C_out, H, W, K)
+        assert L.snn_subbit_prepare(r, p, p, p, p, big, None) == B.SNN_ERR_UNSUPPORTED
+        assert L.snn_subbit_conv2d_prepared(r, p, p, p, p, big, None) == B.SNN_ERR_UNSUPPORTED
+        assert L.snn_subbit_forward(r, p, p, p, p, p, p, p, big, None) == B.SNN_ERR_UNSUPPORTED
+    # 2^31 words; 65536 blocks of 64 channels of the kernel with register-resident windows, and of 32 of the other one
+    for N, C_in, C_out, H, W in ((1 << 20, 4096, 8, 4, 4), (1 << 24, 128, 40, 4, 8), (1, 32, 65536 * 64, 8, 8), (1, 600, 65536 * 32, 8, 8)):
+        d = B.make_desc(N, C_in, C_out, H, W, 1, 512, chans)
+        r = ctypes.byref(d)
+        assert L.snn_bnn_conv2d(r, p, p, p, p, p, big, None) == B.SNN_ERR_UNSUPPORTED, (N, C_in, C_out, H, W)
+        assert L.snn_bnn_prepare(r, p, p, big, None) == B.SNN_ERR_UNSUPPORTED
+        assert L.snn_bnn_conv2d_prepared(r, p, p, p, p, big, None) == B.SNN_ERR_UNSUPPORTED

@@ -357,7 +357,8 @@ int snn_subbit_forward_sign(const snn_conv_desc *desc, const void *x_packed, con
  *                order: g_p can differ in its last bits from run to run on the same input
  *   w, g_wbar  device, float [n][9];  idx  device, uint16 [n], values < K (as snn_project_kernels wrote them)
  *   g_w        device, float [n][9], fully overwritten;  g_p  device, float [K][9], fully overwritten
- *   workspace  device, >= snn_project_backward_workspace_bytes(n, K) bytes, 256-byte aligned
+ *   workspace  device, >= snn_project_backward_workspace_bytes(n, K) bytes, 256-byte aligned (non-decreasing in n
+ *              and K: the workspace of a network's largest layer serves every smaller one)
  * n = 0 is allowed (g_p = 0).  Errors: INVALID_ARG; WORKSPACE; LAUNCH.
  */
 int snn_project_backward(const float *w, const float *g_wbar, const uint16_t *idx, int64_t n, int K,

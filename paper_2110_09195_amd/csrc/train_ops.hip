@@ -5,6 +5,8 @@
 //   * the update of the sign memory m from p with the hysteresis threshold theta (Eq. 4), the 9-bit
 //     codes of the refined subset, and the check for repeated members (Sec. 4.3).
 // All of it is memory-bound streaming over [n][9] floats plus a K x 9 reduction.
+#include <algorithm>
+
 #include "snn_internal.h"
 
 namespace snn {
@@ -17,7 +19,8 @@ constexpr int TB_UNIT = 112;                         // kernels that one 16-byte
 // 16-byte loads per thread and tensor: as many as leave enough blocks to fill the chip.  A block's time is a round
 // trip to memory and its LDS additions; its K x 9 partial sums are what more blocks cost.
 // (4096 kernels 4.1 us, 16384 3.8, 65536 6.0, 262144 11.9.)
-inline int tb_units(int64_t n) { return n <= (int64_t)TB_UNIT * 320 ? 1 : n <= (int64_t)TB_UNIT * 1280 ? 2 : 4; }
+constexpr int64_t TB_ONE_MAX = (int64_t)TB_UNIT * 320, TB_TWO_MAX = (int64_t)TB_UNIT * 1280;      // kernels: one load, two loads up to here
+inline int tb_units(int64_t n) { return n <= TB_ONE_MAX ? 1 : n <= TB_TWO_MAX ? 2 : 4; }
 inline int64_t tb_blocks(int64_t n)
 {
     const int64_t per = (int64_t)TB_UNIT * tb_units(n);
@@ -203,9 +206,12 @@ void subset_update_kernel(const float *__restrict__ p, int8_t *__restrict__ m, f
 
 }  // namespace
 
+// Room for any number of kernels up to n: the block size jumps, and a workspace of a network's largest layer serves the others.
 size_t project_backward_workspace_bytes(int64_t n, int K)
 {
-    const int64_t blocks = tb_blocks(n);
+    int64_t blocks = tb_blocks(n);
+    for (const int64_t end : {TB_ONE_MAX, TB_TWO_MAX})
+        if (n > end) blocks = std::max(blocks, tb_blocks(end));
     return align_up((size_t)(blocks > 0 ? blocks : 1) * K * 9 * sizeof(float), 256);
 }
 

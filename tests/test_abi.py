@@ -171,3 +171,17 @@ def test_layers_past_the_documented_limits_are_refused_before_device_work(L):
         assert L.snn_bnn_conv2d(r, p, p, p, p, p, big, None) == B.SNN_ERR_UNSUPPORTED, (N, C_in, C_out, H, W)
         assert L.snn_bnn_prepare(r, p, p, big, None) == B.SNN_ERR_UNSUPPORTED
         assert L.snn_bnn_conv2d_prepared(r, p, p, p, p, big, None) == B.SNN_ERR_UNSUPPORTED
+
+
+def test_gradient_workspace_of_a_larger_layer_serves_a_smaller_one(L):
+    """Non-decreasing in the number of kernels (one workspace for a network's largest layer), across the sizes where the kernel's
+    blocks change, and in the subset size."""
+    size = binding.lib().snn_project_backward_workspace_bytes
+    edges = [112 * 320, 112 * 1280]
+    ns = sorted({0, 1, 112, 113, 128 * 256, 192 * 192, 512 * 512} | {e + i for e in edges for i in (-113, -1, 0, 1, 2, 113, 225, 40000)} |
+                set(range(1, 400000, 997)))
+    for K in (1, 32, 257, 512):
+        sizes = [size(n, K) for n in ns]
+        assert sizes == sorted(sizes), K
+    assert all(size(n, 32) <= size(n, 33) for n in ns)
+    assert size(128 * 256, 32) <= size(192 * 192, 32)

@@ -150,9 +150,9 @@ int snn_subbit_conv2d(const snn_conv_desc *desc, const void *x, const uint16_t *
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results
  * and errors as snn_subbit_conv2d, without `workspace` / `ws_bytes`: the tables the call builds live
  * in a buffer inside the library, SNN_NOALLOC_MAX_WORKSPACE_BYTES per GPU, held until the process
- * ends.  The call allocates and frees nothing.  A layer whose tables for the two-stage kernels need
- * more than SNN_NOALLOC_MAX_WORKSPACE_BYTES is refused with SNN_ERR_WORKSPACE and nothing is
- * enqueued, whichever form would have run; SNN_ERR_LAUNCH also if the buffer's address cannot be
+ * ends.  The call allocates and frees nothing.  A layer whose tables need more
+ * (snn_workspace_bytes(desc, SNN_WS_SUBBIT) > SNN_NOALLOC_MAX_WORKSPACE_BYTES) is refused with
+ * SNN_ERR_WORKSPACE and nothing is enqueued; SNN_ERR_LAUNCH also if the buffer's address cannot be
  * obtained.  All calls on one GPU share the buffer: every call rebuilds what it reads, and calls
  * that overlap on one GPU (different streams, or threads) race - issue them on one stream.
  */

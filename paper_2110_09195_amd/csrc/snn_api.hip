@@ -116,13 +116,6 @@ FormSplit split_forms(const std::vector<Geom> &gs)
     return f;
 }
 
-std::vector<void *> two_stage_tables(const std::vector<Geom> &gs, const std::vector<void *> &ws)
-{
-    std::vector<void *> r;
-    for (size_t i = 0; i < gs.size(); ++i) r.push_back((char *)ws[i] + subbit_two_stage_offset(gs[i]));
-    return r;
-}
-
 int prepare_layers(const std::vector<Geom> &gs, const std::vector<const float *> &w, const std::vector<const uint16_t *> &codebook,
                    const std::vector<const float *> &alpha, const std::vector<const float *> &beta, const std::vector<uint16_t *> &idx,
                    const std::vector<void *> &ws, hipStream_t s)
@@ -138,7 +131,7 @@ int prepare_layers(const std::vector<Geom> &gs, const std::vector<const float *>
     const std::vector<Geom> g2 = pick(gs, f.two_stage);
     return launch_subbit_prepare_many((int)g2.size(), g2.data(), pick(w, f.two_stage).data(), pick(codebook, f.two_stage).data(),
                                       pick(alpha, f.two_stage).data(), pick(beta, f.two_stage).data(), pick(idx, f.two_stage).data(),
-                                      two_stage_tables(g2, pick(ws, f.two_stage)).data(), s);
+                                      pick(ws, f.two_stage).data(), s);
 }
 
 int convolve_layers(const std::vector<Geom> &gs, const std::vector<const void *> &x, const std::vector<float *> &y,
@@ -152,7 +145,7 @@ int convolve_layers(const std::vector<Geom> &gs, const std::vector<const void *>
     }
     if (f.two_stage.empty()) return SNN_OK;
     const std::vector<Geom> g2 = pick(gs, f.two_stage);
-    const std::vector<void *> w2 = two_stage_tables(g2, pick(ws, f.two_stage));
+    const std::vector<void *> w2 = pick(ws, f.two_stage);
     const int n = (int)g2.size();
     if (tuning(SNN_TUNE_STACK) != 0 && subbit_stack_supported(n, g2.data()))
         return launch_subbit_stack(n, g2.data(), pick(x, f.two_stage).data(), pick(y, f.two_stage).data(), w2.data(), s);
@@ -315,10 +308,11 @@ int snn_subbit_conv2d_noalloc(const snn_conv_desc *desc, const void *x, const ui
     if (!desc_ok(desc, true) || !x || !codebook || !idx || !alpha || !y_nchw) return SNN_ERR_INVALID_ARG;
     if (!subbit_act_supported(desc->act)) return SNN_ERR_UNSUPPORTED;
     const Geom g = make_geom(*desc);
+    const size_t need = subbit_workspace_bytes(g, desc->act);
+    if (need > (size_t)SNN_NOALLOC_MAX_WORKSPACE_BYTES) return SNN_ERR_WORKSPACE;
     void *ws = scratch_on_current_device();
     if (!ws) return SNN_ERR_LAUNCH;
-    return launch_subbit_fitting(g, desc->act, x, codebook, idx, alpha, y_nchw, ws, (size_t)SNN_NOALLOC_MAX_WORKSPACE_BYTES,
-                                 (hipStream_t)stream);
+    return launch_subbit(g, desc->act, x, codebook, idx, alpha, y_nchw, ws, (hipStream_t)stream);
 }
 
 int snn_subbit_prepare(const snn_conv_desc *desc, const uint16_t *codebook, const uint16_t *idx, const float *alpha,
@@ -359,8 +353,8 @@ int snn_subbit_prepare_packed(const snn_conv_desc *desc, const uint16_t *codeboo
     if (subbit_rows_form(g))
         return launch_rows_fp4(g, nullptr, codebook, idx_packed, tau, alpha, nullptr, workspace, (hipStream_t)stream, nullptr,
                                SNN_PHASE_PREPARE);
-    return launch_subbit_mfma(g, nullptr, codebook, (const uint16_t *)idx_packed, alpha, nullptr,
-                              (char *)workspace + subbit_two_stage_offset(g), (hipStream_t)stream, nullptr, SNN_PHASE_PREPARE, tau);
+    return launch_subbit_mfma(g, nullptr, codebook, (const uint16_t *)idx_packed, alpha, nullptr, workspace,
+                              (hipStream_t)stream, nullptr, SNN_PHASE_PREPARE, tau);
 }
 
 int snn_subbit_conv2d_prepared(const snn_conv_desc *desc, const void *x, const float *alpha, float *y_nchw,

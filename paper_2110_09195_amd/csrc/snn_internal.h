@@ -131,13 +131,8 @@ int launch_subbit(const Geom &g, int act, const void *x, const uint16_t *codeboo
                   const uint16_t *idx, const float *alpha, float *y, void *ws, hipStream_t s,
                   int phases = SNN_PHASE_BOTH);
 
-// snn_subbit_conv2d's work in a buffer of fixed size: the form whose tables fit (SNN_ERR_WORKSPACE if none does)
-int launch_subbit_fitting(const Geom &g, int act, const void *x, const uint16_t *codebook, const uint16_t *idx, const float *alpha,
-                          float *y, void *ws, size_t ws_bytes, hipStream_t s);
-// whether the layer goes to the dense contraction (rows_fp4.hip); else to the two-stage kernels, whose tables start this
-// many bytes into the workspace
+// whether the layer goes to the dense contraction (rows_fp4.hip); else to the two-stage kernels
 bool subbit_rows_form(const Geom &g);
-size_t subbit_two_stage_offset(const Geom &g);
 
 // Optional ending of the sub-bit convolution: instead of y, the next layer's packed rows
 // bit = ((float)S * alpha[co] + beta[co] >= 0), uint32 [N][C_out][H_out][ceil(W_out / 32)].

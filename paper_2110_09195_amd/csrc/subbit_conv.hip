@@ -15,6 +15,8 @@
 // image (read as bit 0) fake; it depends only on the output channel and the pixel's border type.
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "rows_fp4.h"
 #include "subbit_common.h"
 
@@ -280,14 +282,6 @@ bool gather_takes(const Geom &g, const SbPlan &pl)
            (int64_t)g.N * g.C_in * g.H * g.WW < ((int64_t)1 << 31);
 }
 
-// the tables of either two-stage kernel, so that the override cannot outgrow a workspace
-size_t two_stage_bytes(const Geom &g)
-{
-    const size_t a = make_plan(g).bytes;
-    const size_t b = subbit_mfma_supported(g) ? subbit_mfma_workspace_bytes(g) : 0;
-    return a > b ? a : b;
-}
-
 }  // namespace
 
 // The dense contraction (rows_fp4.hip) takes every layer it supports: nine contraction slots per input channel against
@@ -303,8 +297,6 @@ bool subbit_rows_form(const Geom &g)
     if (!subbit_mfma_supported(g) && !gather_takes(g, make_plan(g))) return false;
     return rows_fp4_supported(g);
 }
-
-size_t subbit_two_stage_offset(const Geom &g) { return rows_fp4_supported(g) ? rows_fp4_workspace_bytes(g) : 0; }
 
 int launch_subbit_f32(const Geom &g, const void *x, const uint16_t *codebook, const uint16_t *idx,
                       const float *alpha, float *y, void *ws, hipStream_t s, int phases);
@@ -324,19 +316,11 @@ int subbit_slots_per_channel(const Geom &g, int act)
 size_t subbit_workspace_bytes(const Geom &g, int act)
 {
     if (act == SNN_ACT_F32) return subbit_f32_workspace_bytes(g);
-    // [tables of the dense contraction][tables of the two-stage kernels]: one workspace serves either
-    return subbit_two_stage_offset(g) + two_stage_bytes(g);
-}
-
-int launch_subbit_fitting(const Geom &g, int act, const void *x, const uint16_t *codebook, const uint16_t *idx, const float *alpha,
-                          float *y, void *ws, size_t ws_bytes, hipStream_t s)
-{
-    if (act == SNN_ACT_F32)
-        return subbit_f32_workspace_bytes(g) <= ws_bytes ? launch_subbit(g, act, x, codebook, idx, alpha, y, ws, s) : SNN_ERR_WORKSPACE;
-    if (two_stage_bytes(g) > ws_bytes) return SNN_ERR_WORKSPACE;      // the limit callers know, whatever form runs
-    if (subbit_rows_form(g) && rows_fp4_workspace_bytes(g) <= ws_bytes)
-        return launch_rows_fp4(g, x, codebook, idx, 0, alpha, y, ws, s, nullptr, SNN_PHASE_BOTH);
-    return launch_two_stage(g, x, codebook, idx, alpha, y, ws, s, SNN_PHASE_BOTH);
+    // sized for any of the kernels, so that the override cannot outgrow a workspace; the one that runs keeps its tables at the start.
+    // (The dense contraction's, 1.1 bytes a kernel against two and four, are larger than the others' only on a few narrow layers.)
+    const size_t gather = make_plan(g).bytes, one_hot = subbit_mfma_supported(g) ? subbit_mfma_workspace_bytes(g) : 0;
+    const size_t rows = rows_fp4_workspace_bytes(g);
+    return std::max({gather, one_hot, rows});
 }
 
 int launch_subbit(const Geom &g, int act, const void *x, const uint16_t *codebook, const uint16_t *idx,
@@ -344,7 +328,7 @@ int launch_subbit(const Geom &g, int act, const void *x, const uint16_t *codeboo
 {
     if (act == SNN_ACT_F32) return launch_subbit_f32(g, x, codebook, idx, alpha, y, ws, s, phases);
     if (subbit_rows_form(g)) return launch_rows_fp4(g, x, codebook, idx, 0, alpha, y, ws, s, nullptr, phases);
-    return launch_two_stage(g, x, codebook, idx, alpha, y, (char *)ws + subbit_two_stage_offset(g), s, phases);
+    return launch_two_stage(g, x, codebook, idx, alpha, y, ws, s, phases);
 }
 
 namespace {
@@ -403,7 +387,7 @@ int launch_subbit_forward(const Geom &g, const float *x, const float *w, const u
     uint32_t *xr = (uint32_t *)((char *)ws + align_up(subbit_workspace_bytes(g, SNN_ACT_BIN_ROWS), 256));
     if (subbit_rows_form(g) && g.K <= 64) return launch_rows_fp4_forward(g, x, w, codebook, alpha, idx_out, y, xr, ws, s, nullptr);
     if (!subbit_rows_form(g) && use_mfma(g))
-        return launch_subbit_forward_mfma(g, x, w, codebook, alpha, idx_out, y, xr, (char *)ws + subbit_two_stage_offset(g), s);
+        return launch_subbit_forward_mfma(g, x, w, codebook, alpha, idx_out, y, xr, ws, s);
     // larger subsets, and layers no matrix-core kernel takes: the three operations one after the other
     if (!subbit_mfma_supported(g) && !gather_takes(g, make_plan(g))) return SNN_ERR_UNSUPPORTED;      // (before anything is enqueued)
     int rc = launch_pack_rows(x, xr, (int64_t)g.N * g.C_in * g.H, g.W, s);
@@ -421,7 +405,7 @@ int launch_subbit_sign(const Geom &g, const void *x_packed, const uint16_t *code
     // the convolution alone needs only the output pointer; a non-null epilogue selects the sign form either way
     const SignEpilogue sign = {beta, out_packed};
     if (subbit_rows_form(g)) return launch_rows_fp4(g, x_packed, codebook, idx, 0, alpha, nullptr, ws, s, &sign, phases);
-    return launch_subbit_mfma(g, x_packed, codebook, idx, alpha, nullptr, (char *)ws + subbit_two_stage_offset(g), s, &sign, phases);
+    return launch_subbit_mfma(g, x_packed, codebook, idx, alpha, nullptr, ws, s, &sign, phases);
 }
 
 int launch_subbit_forward_sign(const Geom &g, const void *x_packed, const float *w, const uint16_t *codebook,
@@ -432,8 +416,7 @@ int launch_subbit_forward_sign(const Geom &g, const void *x_packed, const float 
     const SignEpilogue sign = {beta, out_packed};
     if (subbit_rows_form(g))
         return launch_rows_fp4_forward(g, nullptr, w, codebook, alpha, idx_out, nullptr, (uint32_t *)x_packed, ws, s, &sign);
-    return launch_subbit_forward_mfma(g, nullptr, w, codebook, alpha, idx_out, nullptr, (uint32_t *)x_packed,
-                                      (char *)ws + subbit_two_stage_offset(g), s, &sign);
+    return launch_subbit_forward_mfma(g, nullptr, w, codebook, alpha, idx_out, nullptr, (uint32_t *)x_packed, ws, s, &sign);
 }
 
 }  // namespace snn

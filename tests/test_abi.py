@@ -185,3 +185,25 @@ def test_gradient_workspace_of_a_larger_layer_serves_a_smaller_one(L):
         assert sizes == sorted(sizes), K
     assert all(size(n, 32) <= size(n, 33) for n in ns)
     assert size(128 * 256, 32) <= size(192 * 192, 32)
+
+
+def test_a_workspace_holds_the_tables_of_one_form(L):
+    """The size is that of the largest form's tables, not their sum (a network keeps a workspace per layer): the two-stage tables'
+    by hand, and the limit of the call with the library's own buffer, which reports it before any device work."""
+    B = binding
+    rows = B.SNN_ACT_BIN_ROWS
+
+    def up(n):
+        return (n + 255) // 256 * 256
+    # K > 64: 512 codes, uint16 offsets of ceil(C_in / 8) * 8 x 256-channel blocks, 16 border corrections per channel
+    assert B.snn_workspace_bytes(B.make_desc(8, 512, 512, 7, 7, 1, 128, rows), B.SNN_WS_SUBBIT) == 2048 + up(512 * 512 * 2) + up(512 * 64)
+    assert B.snn_workspace_bytes(B.make_desc(8, 100, 150, 37, 53, 2, 128, rows), B.SNN_WS_SUBBIT) == 2048 + up(104 * 256 * 2) + up(256 * 64)
+    # K <= 32: a selector word per input and output channel (four bytes a kernel), and less than 128 KB of other tables
+    for C in (128, 256, 512):
+        assert 4 * C * C < B.snn_workspace_bytes(B.make_desc(64, C, C, 14, 14, 1, 32, rows), B.SNN_WS_SUBBIT) < 4 * C * C + (1 << 17)
+    # the dense contraction's where they are the largest: 2304 bytes per 64 x 32 channels and the scales
+    assert B.snn_workspace_bytes(B.make_desc(8, 264, 8, 7, 7, 1, 128, rows), B.SNN_WS_SUBBIT) == 5 * 2304 + 256
+    p = ctypes.c_void_p(256)
+    d = B.make_desc(1, 1024, 1024, 1, 1, 1, 32, rows)
+    assert B.snn_workspace_bytes(d, B.SNN_WS_SUBBIT) > 4 << 20
+    assert L.snn_subbit_conv2d_noalloc(ctypes.byref(d), p, p, p, p, p, None) == B.SNN_ERR_WORKSPACE

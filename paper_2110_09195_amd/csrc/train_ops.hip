@@ -27,6 +27,23 @@ inline int64_t tb_blocks(int64_t n)
     return (n + per - 1) / per;
 }
 
+// Copies of the sums by member that a block adds to with atomics: 36 KB of LDS at most
+__host__ __device__ constexpr int tb_copies(int K) { return K <= 256 ? 4 : 2; }
+inline size_t tb_copies_bytes(int K) { return (size_t)(tb_copies(K) * K * 9 + 3) / 4 * 16; }
+
+__device__ __forceinline__ void clear_copies(float *acc, int n)        // (up to the next multiple of four)
+{
+    for (int i = 4 * threadIdx.x; i < n; i += 4 * TB_THREADS) *(float4 *)(acc + i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+
+__device__ __forceinline__ void store_copies(const float *acc, int copies, int K9, float *__restrict__ dst)
+{
+    for (int e = threadIdx.x; e < K9; e += TB_THREADS) {
+        const float lo = acc[e] + acc[K9 + e];
+        dst[e] = copies == 4 ? lo + (acc[2 * K9 + e] + acc[3 * K9 + e]) : lo;
+    }
+}
+
 // Pass 1: g_w = g_wbar where w in (-1, 1) (element-wise), else 0; per block, the sums of g_wbar by member, written as one
 // partial [K][9] per block.
 //
@@ -36,8 +53,9 @@ inline int64_t tb_blocks(int64_t n)
 // M = 16.  With LDS float atomics instead, which was the whole kernel's time at any layout of the lanes (290 clocks
 // per 64 additions, equal addresses among them or not), 262144 kernels at K = 32 take 17 us, here 11.9 (4096 kernels: 8.6
 // with one kernel per thread, here 4.1).
-// A zero times an infinity would reach members that it does not belong to: blocks with a value that is not finite, and
-// subsets of more than 256, add with the atomics (M = 0).
+// A zero times an infinity would reach members that it does not belong to: blocks with a value that is not finite add with
+// LDS float atomics, and so do (M = 0) the subsets whose one-hot rows are mostly zeros.  Each wave adds to a copy of the sums of its
+// own while four copies fit beside other blocks (K <= 256; two beyond), which keeps the chains of roundings as short as the product's.
 template <int U, int M, bool WHOLE>
 __device__ __forceinline__ void project_backward_block(const float *__restrict__ wb, const float *__restrict__ gb,
                                                        const uint16_t *__restrict__ ib, int cnt, int K, float *__restrict__ ob,
@@ -50,6 +68,7 @@ __device__ __forceinline__ void project_backward_block(const float *__restrict__
     float *const acc = lds + STAGE;
     const int tid = threadIdx.x;
     const int ne = cnt * 9;
+    const int copies = tb_copies(K);
     float wv[U][4], gv[U][4];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -100,19 +119,20 @@ __device__ __forceinline__ void project_backward_block(const float *__restrict__
     }
     __syncthreads();
     if (not_finite) {                                // (block-uniform)
-        for (int i = tid; i < K * 9; i += TB_THREADS) acc[i] = 0.0f;
+        clear_copies(acc, copies * K * 9);
         __syncthreads();
+        float *const mine = acc + ((tid >> 6) & (copies - 1)) * K * 9;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int e = (u * TB_THREADS + tid) * 4;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int c = (e + j) / 9;
-                if (e + j < ne) atomicAdd(&acc[member[c] * 9 + e + j - 9 * c], gv[u][j]);
+                if (e + j < ne) atomicAdd(&mine[member[c] * 9 + e + j - 9 * c], gv[u][j]);
             }
         }
         __syncthreads();
-        for (int i = tid; i < K * 9; i += TB_THREADS) dst[i] = acc[i];
+        store_copies(acc, copies, K * 9, dst);
         return;
     }
     if constexpr (M > 0) {
@@ -139,8 +159,7 @@ __device__ __forceinline__ void project_backward_block(const float *__restrict__
                 if (i < 9 && k < K) acc[(wave * K + k) * 9 + i] = sum[m][r];
             }
         __syncthreads();
-        const int K9 = K * 9;
-        for (int e = tid; e < K9; e += TB_THREADS) dst[e] = (acc[e] + acc[K9 + e]) + (acc[2 * K9 + e] + acc[3 * K9 + e]);
+        store_copies(acc, 4, K * 9, dst);
     }
 }
 
@@ -159,6 +178,48 @@ void project_backward_kernel(const float *__restrict__ w, const float *__restric
         project_backward_block<U, M, true>(w + c0 * 9, g_wbar + c0 * 9, idx + c0, cnt, K, g_w + c0 * 9, dst, lds);
     else
         project_backward_block<U, M, false>(w + c0 * 9, g_wbar + c0 * 9, idx + c0, cnt, K, g_w + c0 * 9, dst, lds);
+}
+
+// The same with the atomics on larger blocks: two kernels per thread.  For many kernels the partial sums, K x 9 per block, are what
+// counts, and the product's one-hot rows of large subsets are.
+constexpr int TB_LARGE = 2 * TB_THREADS;
+
+__global__ __launch_bounds__(TB_THREADS)
+void project_backward_large_kernel(const float *__restrict__ w, const float *__restrict__ g_wbar, const uint16_t *__restrict__ idx,
+                                   int64_t n, int K, float *__restrict__ g_w, float *__restrict__ partial)
+{
+    extern __shared__ __align__(16) float lds[];
+    const int tid = threadIdx.x, K9 = K * 9, copies = tb_copies(K);
+    constexpr int Q = TB_LARGE / TB_THREADS;
+    const int64_t c0 = (int64_t)blockIdx.x * TB_LARGE + tid;
+    int k[Q];
+    float wv[Q][9], gv[Q][9];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int64_t c = min(c0 + q * TB_THREADS, n - 1);
+        k[q] = min((int)idx[c], K - 1);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            wv[q][t] = w[c * 9 + t];
+            gv[q][t] = g_wbar[c * 9 + t];
+        }
+    }
+    clear_copies(lds, copies * K9);
+    __syncthreads();
+    float *const mine = lds + ((tid >> 6) & (copies - 1)) * K9;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int64_t c = c0 + q * TB_THREADS;
+        if (c < n) {
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                g_w[c * 9 + t] = wv[q][t] > -1.0f && wv[q][t] < 1.0f ? gv[q][t] : 0.0f;
+                atomicAdd(&mine[k[q] * 9 + t], gv[q][t]);
+            }
+        }
+    }
+    __syncthreads();
+    store_copies(lds, copies, K9, partial + (int64_t)blockIdx.x * K9);
 }
 
 // Pass 2: g_p[k][t] = sum of the block partials; one wave per entry: lane l adds the partials of
@@ -218,26 +279,30 @@ size_t project_backward_workspace_bytes(int64_t n, int K)
 int launch_project_backward(const float *w, const float *g_wbar, const uint16_t *idx, int64_t n, int K, float *g_w,
                             float *g_p, void *ws, hipStream_t s)
 {
-    const int64_t blocks = tb_blocks(n);
+    // The product costs time with K, the atomics do not: up to 64 members it is the faster at any size, up to 128 as long as blocks are
+    // small.  The small blocks' partial sums cost more than they save from some 5 M sums on.  Measured, product -> atomics on large
+    // blocks, us: 262144 kernels K = 64 19.1 -> 20.1, K = 128 29.4 -> 22.9, K = 256 52.8 -> 28.9; 20000 kernels K = 128
+    // 9.3 -> 10.3.  Atomics on small -> large blocks: 5000 kernels K = 512 9.1 -> 11.1, 20000 14.9 -> 12.8.  One copy of the sums
+    // instead of four is 4 % faster on large blocks, and its error on skewed indices 1.4 times as large (1.7e-7 for 1.2e-7).
+    const bool product = K <= 64 || (K <= 128 && n <= TB_ONE_MAX);
+    const bool large = !product && (n > TB_ONE_MAX || n * K > ((int64_t)5 << 20));
+    const int64_t blocks = large ? (n + TB_LARGE - 1) / TB_LARGE : tb_blocks(n);
     if (blocks > 0x7fffffffLL) return SNN_ERR_INVALID_ARG;
-    const bool vec = ((((uintptr_t)w) | ((uintptr_t)g_wbar) | ((uintptr_t)g_w)) & 15u) == 0;
-    if (blocks > 0) {
-        const int U = tb_units(n), M = K <= 16 ? 1 : K <= 32 ? 2 : K <= 64 ? 4 : K <= 128 ? 8 : K <= 256 ? 16 : 0;
-        const size_t lds = sizeof(float) * (M > 0 ? (size_t)(TB_UNIT * U * 9 + 16) + 4 * (size_t)K * 9 : (size_t)K * 9);
+    if (large) {
+        hipLaunchKernelGGL(project_backward_large_kernel, dim3((unsigned)blocks), dim3(TB_THREADS), tb_copies_bytes(K), s, w,
+                           g_wbar, idx, n, K, g_w, (float *)ws);
+    } else if (blocks > 0) {
+        const bool vec = ((((uintptr_t)w) | ((uintptr_t)g_wbar) | ((uintptr_t)g_w)) & 15u) == 0;
+        const int U = tb_units(n), M = !product ? 0 : K <= 16 ? 1 : K <= 32 ? 2 : K <= 64 ? 4 : 8;
+        const size_t lds = sizeof(float) * (M > 0 ? TB_UNIT * U * 9 + 16 : 0) + tb_copies_bytes(K);
+        auto kern = M == 0 ? project_backward_kernel<1, 0> : project_backward_kernel<1, 8>;      // (n <= TB_ONE_MAX: U = 1)
 #define SNN_TB_CASE(M_)                                                                                                      \
-    case M_: {                                                                                                               \
-        auto kern = U == 1 ? project_backward_kernel<1, M_> : U == 2 ? project_backward_kernel<2, M_> : project_backward_kernel<4, M_>; \
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(TB_THREADS), lds, s, w, g_wbar, idx, n, K, g_w, (float *)ws, vec ? 1 : 0); \
-    } break;
-        switch (M) {
-            SNN_TB_CASE(0)
-            SNN_TB_CASE(1)
-            SNN_TB_CASE(2)
-            SNN_TB_CASE(4)
-            SNN_TB_CASE(8)
-            SNN_TB_CASE(16)
-        }
+    if (M == M_) kern = U == 1 ? project_backward_kernel<1, M_> : U == 2 ? project_backward_kernel<2, M_> : project_backward_kernel<4, M_>;
+        SNN_TB_CASE(1)
+        SNN_TB_CASE(2)
+        SNN_TB_CASE(4)
 #undef SNN_TB_CASE
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(TB_THREADS), lds, s, w, g_wbar, idx, n, K, g_w, (float *)ws, vec ? 1 : 0);
     }
     hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((K * 9 + TB_THREADS / 64 - 1) / (TB_THREADS / 64))), dim3(TB_THREADS), 0, s,
                        (const float *)ws, blocks, K * 9, g_p);

@@ -25,7 +25,9 @@ def _inputs(n, K, shift):
 
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("n,K", [(1, 32), (3, 1), (111, 16), (112, 17), (113, 32), (112 * 320, 32), (112 * 320 + 1, 33), (112 * 1280, 64),
-                                 (112 * 1280 + 5, 65), (5000, 128), (5000, 129), (150000, 256), (5000, 257), (40000, 512)])
+                                 (112 * 1280 + 5, 65), (5000, 128), (5000, 129), (150000, 256), (5000, 257), (40000, 512),
+                                 (112 * 320, 128), (112 * 320 + 1, 128), (112 * 320, 65), (513, 129), (10240, 512), (10241, 512), (5 << 12, 256),
+                                 (1 + (5 << 12), 256), (112 * 320 + 1, 129)])
 def test_gradients_at_the_edges_of_the_blocks(oracle, n, K, shift):
     w, gw, idx, dw, dg, di, do = _inputs(n, K, shift)
     got_w, got_p = B.snn_project_backward(dw, dg, di, K, g_w=do)
@@ -33,15 +35,14 @@ def test_gradients_at_the_edges_of_the_blocks(oracle, n, K, shift):
     assert (got_w.cpu().numpy() == ref_w).all()
     sum_abs = np.zeros((K, 9))
     np.add.at(sum_abs, idx, np.abs(gw).astype(np.float64))
-    # a block adds at most 448 terms one after the other, a lane of the second pass at most blocks / 64 + 1 of the
+    # a block adds at most 448 terms one after the other (256 where a wave has 512 kernels' sums to itself or with one other), a lane of the second pass at most blocks / 64 + 1 of the
     # partial sums, and six additions join the lanes: so many roundings of at most 2^-24 of the sum of magnitudes
     tol = (448 + n // 112 // 64 + 7) * 2.0 ** -24 * sum_abs + 1e-30
     assert (np.abs(got_p.cpu().numpy().astype(np.float64) - ref_p) <= tol).all()
 
 
-@pytest.mark.parametrize("K", [8, 250])
-def test_values_that_are_not_finite_stay_in_their_member(K):
-    n = 300
+@pytest.mark.parametrize("K, n", [(8, 300), (100, 300), (250, 300), (300, 300), (100, 112 * 320 + 1)])
+def test_values_that_are_not_finite_stay_in_their_member(K, n):
     w = torch.zeros((n, 9), device="cuda")
     g = torch.ones((n, 9), device="cuda")
     idx = (torch.arange(n, device="cuda") % K).to(torch.int16)

@@ -2,7 +2,7 @@
 // words of 32 input channels.  It is the denominator of every speed-up the sub-bit kernel
 // reports, so it is written to the same standard.
 //
-// Packed activations (SNN_ACT_BIN_CHANNELS): most layers go to the matrix cores (rows_fp4.hip).  The others, and the XNOR/popcount
+// Packed activations (SNN_ACT_BIN_CHANNELS): layers of more than a few output channels go to the matrix cores (rows_fp4.hip).  The others, and the XNOR/popcount
 // baseline when it is asked for by SNN_TUNE_BNN_REGS, have two kernels here.  Up to 512 input channels: one lane owns
 // one output pixel and keeps its window in registers; a block walks a chunk of output channels
 // whose weight words wait in LDS (bnn_regs_kernel).  More channels: one lane owns PXL output

@@ -1104,14 +1104,25 @@ int launch_rows_fp4(const Geom &g, const void *x, const uint16_t *codebook, cons
 
 // The 1-bit layer: packing and convolution, popcount kernel -> here: 128 -> 128 28x28 batch 64 27.8 -> 16.5 us (packing is 5 of both),
 // 64 -> 64 56x56 batch 64 34 -> 24, 512 -> 512 7x7 batch 64 31 -> 17.5; small batches and 16 -> 16 32x32 batch 256 the same 17 (the
-// two launches from the host).  Layers of fewer than 256 kernels leave most of a 32 x 32 block empty (1 -> 1 56x56 batch 256 17.3
-// there, 19.6 here) and stay with the popcount kernel.  The packed input of the images a workgroup touches takes 32-bit
-// offsets, too.
+// two launches from the host).  The popcount kernels' time goes with the output channels, this one's mostly with the pixels
+// that its workgroups expand (rows above and below included, so more per output pixel the wider the rows are, and once per tile of
+// output channels): they keep the layers of few output channels.  Up to 512 input channels the line is about five output channels
+// per expanded pixel and output pixel, ten where the tile of wide rows leaves a compute unit one workgroup; past those
+// the popcount kernel is several times slower and keeps up to eight output channels on wide rows, 32 where a unit has one workgroup.  Prepared, popcount -> here, us:
+// 56x56 batch 64 (2.0 expanded) 256 -> 1 5.6 -> 16.8, 256 -> 8 13.3 -> 16.9, 256 -> 12 17.4 -> 17.1, 256 -> 32 35.3 -> 18.0,
+// 32 -> 8 5.9 -> 6.4; 56x224 batch 16 (5.3) 128 -> 16 13.1 -> 14.7, 128 -> 24 17.3 -> 15.0; 32x512 batch 64 64 -> 32 (10.0)
+// 53 -> 89, 64 -> 64 (5.0) 98 -> 77; 32x900 batch 2 (35) 64 -> 64 11.8 -> 19.2; 600 -> 1 56x56 batch 64 87 -> 31, 32x900 batch 2
+// 27 -> 133, 600 -> 32 56x448 batch 8 172 -> 92, 32x640 batch 16 156 -> 250.  Layers of fewer than 256 kernels leave most of a 32 x 32 block empty (1 -> 1 56x56 batch 256 17.3 there, 19.6 here)
+// and stay with the popcount kernel.  The packed input of the images a workgroup touches takes 32-bit offsets, too.
 bool bnn_rows_form(const Geom &g)
 {
     if ((int64_t)g.C_in * g.C_out < 256) return false;
     const RfPlan pl = rf_plan(g, false);
     if (!pl.ok || tuning(SNN_TUNE_BNN_REGS) != SNN_TUNE_AUTO) return false;
+    const int64_t expanded = pl.rows * (g.W + 1) * pl.n_cotiles, pixels = (int64_t)(32 * pl.PB) << pl.wpx_shift;
+    const bool alone = pl.lds > RF_LDS_TARGET;
+    if (g.CW > 16 ? (g.C_out <= 8 && expanded > 8 * pixels) || (g.C_out <= 32 && alone) : g.C_out * pixels < (alone ? 10 : 5) * expanded)
+        return false;
     const int64_t images = (pl.rows + g.H) / (g.H + 1) + 1;
     return images * g.H * g.W * g.CW * 4 < ((int64_t)1 << 31) - 4096;
 }

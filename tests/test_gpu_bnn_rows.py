@@ -32,6 +32,15 @@ EDGES = [
     (129, 33, 40, 1, 1, 1),
     (2, 160, 33, 1, 1, 1),           # five words: the second group of four has one
     (1, 30, 64, 1, 2, 2),
+    # both sides of the line to the popcount kernels: output channels against expanded pixels, one word and many, wide rows
+    (2, 40, 15, 56, 56, 1),
+    (2, 40, 16, 56, 56, 1),
+    (1, 24, 117, 3, 600, 1),
+    (1, 24, 118, 3, 600, 1),
+    (1, 70, 234, 3, 600, 2),
+    (1, 520, 8, 3, 600, 1),
+    (1, 520, 32, 3, 600, 1),
+    (1, 520, 33, 3, 600, 1),
 ]
 
 

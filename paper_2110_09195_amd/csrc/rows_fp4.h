@@ -7,6 +7,8 @@ namespace snn {
 
 // layers the kernel takes: any subset size; rows narrow enough that the tile of a workgroup fits LDS, 32-bit offsets
 bool rows_fp4_supported(const Geom &g);
+// whether the one-hot matrix form is the faster one (for layers that it takes)
+bool rows_fp4_loses_on_wide_rows(const Geom &g, bool sign);
 size_t rows_fp4_workspace_bytes(const Geom &g);
 
 // tau = 0: `idx` is uint16 [C_out][C_in]; else a stream of tau-bit indices (see snn_pack_indices)

@@ -1080,6 +1080,23 @@ RfProject rf_project(const Geom &g, const float *w, const uint16_t *codebook, co
 
 bool rows_fp4_supported(const Geom &g) { return rf_plan(g, false).ok && rf_plan(g, true).ok; }
 
+// Layers with wide rows.  A workgroup expands at least five rows for its one or two, so that from rows of about 600 pixels on the
+// expansion is most of the time: pixels expanded per output pixel, times channel blocks, a quarter more where the tile leaves a
+// compute unit one workgroup and a seventh more before the sign epilogue.  The one-hot form reads its windows as they are; its time goes
+// with the input channels.  One-hot -> here, prepared, 32 rows, batch 64, K = 16, us: 33 -> 20 512 wide 90 -> 75, 640 106 -> 103 (sign
+// 95 -> 117), 900 140 -> 190 (134 -> 214); 2 -> 4 K = 8 640 wide 46 -> 35, 900 67 -> 75; 128 -> 128 900 wide batch 32 269 -> 220.
+// Launches of fewer than 800 workgroups stay here (batch 8 33 -> 20 768 wide, 768 of them, 24 -> 20; 900 wide, 900, 23.9 -> 28.7).
+bool rows_fp4_loses_on_wide_rows(const Geom &g, bool sign)
+{
+    if (g.K > 64 || g.W <= 320) return false;                   // (the line is never below 320; no plan for the others)
+    const RfPlan pl = rf_plan(g, sign);
+    if (!pl.ok || pl.n_wgs < 800) return false;
+    const int64_t expanded = pl.rows * (g.W + 1) * pl.ncb, pixels = (int64_t)(32 * pl.PB) << pl.wpx_shift;
+    const int64_t here = expanded * (pl.lds > RF_LDS_TARGET ? 125 : 100) * (sign ? 115 : 100) / (100 * pixels);
+    const int64_t one_hot = 1350 + (g.K > 32 ? 220 * g.C_in : 57 * g.C_in + 23 * std::max(0, g.C_in - 64));
+    return here > one_hot;
+}
+
 size_t rows_fp4_workspace_bytes(const Geom &g)
 {
     return rf_weight_bytes(g) + align_up((size_t)((g.C_out + 31) / 32) * 64 * sizeof(float), 256);

@@ -109,10 +109,11 @@ struct FormSplit {
     std::vector<int> rows, two_stage;
 };
 
-FormSplit split_forms(const std::vector<Geom> &gs)
+// (beta: the layers' shifts if they end in a sign, nullptr where they do not)
+FormSplit split_forms(const std::vector<Geom> &gs, const std::vector<const float *> *beta = nullptr)
 {
     FormSplit f;
-    for (int l = 0; l < (int)gs.size(); ++l) (subbit_rows_form(gs[l]) ? f.rows : f.two_stage).push_back(l);
+    for (int l = 0; l < (int)gs.size(); ++l) (subbit_rows_form(gs[l], beta && (*beta)[l]) ? f.rows : f.two_stage).push_back(l);
     return f;
 }
 
@@ -120,7 +121,7 @@ int prepare_layers(const std::vector<Geom> &gs, const std::vector<const float *>
                    const std::vector<const float *> &alpha, const std::vector<const float *> &beta, const std::vector<uint16_t *> &idx,
                    const std::vector<void *> &ws, hipStream_t s)
 {
-    const FormSplit f = split_forms(gs);
+    const FormSplit f = split_forms(gs, &beta);
     if (!f.rows.empty()) {
         const int rc = launch_rows_fp4_project_many((int)f.rows.size(), pick(gs, f.rows).data(), pick(w, f.rows).data(),
                                                     pick(codebook, f.rows).data(), pick(alpha, f.rows).data(), pick(beta, f.rows).data(),
@@ -350,7 +351,7 @@ int snn_subbit_prepare_packed(const snn_conv_desc *desc, const uint16_t *codeboo
     if (!subbit_mfma_supported(g)) return SNN_ERR_UNSUPPORTED;
     const size_t need = subbit_workspace_bytes(g, desc->act);
     if (!workspace || ws_bytes < need || ((uintptr_t)workspace & 255u)) return SNN_ERR_WORKSPACE;
-    if (subbit_rows_form(g))
+    if (subbit_rows_form(g, false))
         return launch_rows_fp4(g, nullptr, codebook, idx_packed, tau, alpha, nullptr, workspace, (hipStream_t)stream, nullptr,
                                SNN_PHASE_PREPARE);
     return launch_subbit_mfma(g, nullptr, codebook, (const uint16_t *)idx_packed, alpha, nullptr, workspace,

@@ -131,8 +131,9 @@ int launch_subbit(const Geom &g, int act, const void *x, const uint16_t *codeboo
                   const uint16_t *idx, const float *alpha, float *y, void *ws, hipStream_t s,
                   int phases = SNN_PHASE_BOTH);
 
-// whether the layer goes to the dense contraction (rows_fp4.hip); else to the two-stage kernels
-bool subbit_rows_form(const Geom &g);
+// whether the layer (with fp32 output, or ending in the next layer's sign) goes to the dense contraction (rows_fp4.hip); else to the
+// two-stage kernels
+bool subbit_rows_form(const Geom &g, bool sign);
 
 // Optional ending of the sub-bit convolution: instead of y, the next layer's packed rows
 // bit = ((float)S * alpha[co] + beta[co] >= 0), uint32 [N][C_out][H_out][ceil(W_out / 32)].

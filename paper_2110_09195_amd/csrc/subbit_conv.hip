@@ -284,18 +284,20 @@ bool gather_takes(const Geom &g, const SbPlan &pl)
 
 }  // namespace
 
-// The dense contraction (rows_fp4.hip) takes every layer it supports: nine contraction slots per input channel against
+// The dense contraction (rows_fp4.hip) takes the layers it supports: nine contraction slots per input channel against
 // the 16, 32 or 64 of the one-hot form; measured on every layer shape of the ResNets and on ragged ones it is the faster
-// form for all K (figures in that file; the smallest gain, 16 -> 16 channels 32x32 batch 8, is 1.16x).
+// form for all K (figures in that file; the smallest gain, 16 -> 16 channels 32x32 batch 8, is 1.16x).  Some layers with rows of more
+// than about 600 pixels are the exception.
 // Asking for one of the two-stage kernels' forms through a knob selects those kernels.  A layer that neither of them runs is
 // refused, whatever this form could do (packed inputs of 2^31 words and more, as the header says, and outputs of 65536 blocks
 // of 256 channels).
-bool subbit_rows_form(const Geom &g)
+bool subbit_rows_form(const Geom &g, bool sign)
 {
     for (int knob : {SNN_TUNE_SUBBIT_MFMA, SNN_TUNE_MFMA_TILE, SNN_TUNE_MFMA_KS, SNN_TUNE_MFMA_STAGE, SNN_TUNE_MFMA_QUAD, SNN_TUNE_STACK})
         if (tuning(knob) != SNN_TUNE_AUTO) return false;
-    if (!subbit_mfma_supported(g) && !gather_takes(g, make_plan(g))) return false;
-    return rows_fp4_supported(g);
+    const bool one_hot = subbit_mfma_supported(g);
+    if (!one_hot && !gather_takes(g, make_plan(g))) return false;
+    return rows_fp4_supported(g) && !(one_hot && rows_fp4_loses_on_wide_rows(g, sign));
 }
 
 int launch_subbit_f32(const Geom &g, const void *x, const uint16_t *codebook, const uint16_t *idx,
@@ -327,7 +329,7 @@ int launch_subbit(const Geom &g, int act, const void *x, const uint16_t *codeboo
                   const float *alpha, float *y, void *ws, hipStream_t s, int phases)
 {
     if (act == SNN_ACT_F32) return launch_subbit_f32(g, x, codebook, idx, alpha, y, ws, s, phases);
-    if (subbit_rows_form(g)) return launch_rows_fp4(g, x, codebook, idx, 0, alpha, y, ws, s, nullptr, phases);
+    if (subbit_rows_form(g, false)) return launch_rows_fp4(g, x, codebook, idx, 0, alpha, y, ws, s, nullptr, phases);
     return launch_two_stage(g, x, codebook, idx, alpha, y, ws, s, phases);
 }
 
@@ -385,8 +387,8 @@ int launch_subbit_forward(const Geom &g, const float *x, const float *w, const u
                           const float *alpha, uint16_t *idx_out, float *y, void *ws, hipStream_t s)
 {
     uint32_t *xr = (uint32_t *)((char *)ws + align_up(subbit_workspace_bytes(g, SNN_ACT_BIN_ROWS), 256));
-    if (subbit_rows_form(g) && g.K <= 64) return launch_rows_fp4_forward(g, x, w, codebook, alpha, idx_out, y, xr, ws, s, nullptr);
-    if (!subbit_rows_form(g) && use_mfma(g))
+    if (subbit_rows_form(g, false) && g.K <= 64) return launch_rows_fp4_forward(g, x, w, codebook, alpha, idx_out, y, xr, ws, s, nullptr);
+    if (!subbit_rows_form(g, false) && use_mfma(g))
         return launch_subbit_forward_mfma(g, x, w, codebook, alpha, idx_out, y, xr, ws, s);
     // larger subsets, and layers no matrix-core kernel takes: the three operations one after the other
     if (!subbit_mfma_supported(g) && !gather_takes(g, make_plan(g))) return SNN_ERR_UNSUPPORTED;      // (before anything is enqueued)
@@ -404,7 +406,7 @@ int launch_subbit_sign(const Geom &g, const void *x_packed, const uint16_t *code
     if (!use_mfma(g)) return SNN_ERR_UNSUPPORTED;
     // the convolution alone needs only the output pointer; a non-null epilogue selects the sign form either way
     const SignEpilogue sign = {beta, out_packed};
-    if (subbit_rows_form(g)) return launch_rows_fp4(g, x_packed, codebook, idx, 0, alpha, nullptr, ws, s, &sign, phases);
+    if (subbit_rows_form(g, true)) return launch_rows_fp4(g, x_packed, codebook, idx, 0, alpha, nullptr, ws, s, &sign, phases);
     return launch_subbit_mfma(g, x_packed, codebook, idx, alpha, nullptr, ws, s, &sign, phases);
 }
 
@@ -414,7 +416,7 @@ int launch_subbit_forward_sign(const Geom &g, const void *x_packed, const float 
 {
     if (!use_mfma(g)) return SNN_ERR_UNSUPPORTED;
     const SignEpilogue sign = {beta, out_packed};
-    if (subbit_rows_form(g))
+    if (subbit_rows_form(g, true))
         return launch_rows_fp4_forward(g, nullptr, w, codebook, alpha, idx_out, nullptr, (uint32_t *)x_packed, ws, s, &sign);
     return launch_subbit_forward_mfma(g, nullptr, w, codebook, alpha, idx_out, nullptr, (uint32_t *)x_packed, ws, s, &sign);
 }

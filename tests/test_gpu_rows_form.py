@@ -26,6 +26,9 @@ EDGES = [
     (300, 24, 20, 7, 7, 1, 32),         # two pixel blocks per wave, tiles that run over several images
     (40, 40, 200, 30, 30, 1, 32),       # two by two blocks, a pixel tail
     (70, 10, 70, 60, 60, 1, 8),         # four pixel blocks per wave
+    (150, 3, 2, 2, 900, 1, 8),          # wide rows that the one-hot form takes, ends in a sign or not
+    (200, 3, 2, 2, 700, 1, 8),          # only if it ends in a sign
+    (200, 3, 2, 2, 500, 1, 8),          # not at all
 ]
 
 
@@ -49,6 +52,34 @@ def test_rows_form_at_the_edges_of_its_tiles(oracle, case):
     want, _ = oracle.conv_sign(xs, codes, alpha, beta, stride)
     got = G.subbit_sign(oracle.pack_rows(x), x.shape, cb, idx, alpha, beta, stride)
     assert (got == want).all(), np.argwhere(got != want)[:5]
+
+
+def test_weights_of_a_layer_whose_form_depends_on_its_ending(oracle):
+    """The tables that one call writes for a layer with fp32 output and for the same layer ending in a sign are those its two
+    convolutions read, where the two take different forms."""
+    import torch
+
+    from paper_2110_09195_amd import binding as B
+    N, C_in, C_out, H, W, K = 200, 3, 2, 2, 700, 8
+    g = np.random.default_rng(5)
+    x = g.standard_normal((N, C_in, H, W), dtype=np.float32)
+    cb, w, alpha = synth.codebook(g, K), synth.real_kernels(g, C_out * C_in), synth.alpha(g, C_out)
+    beta = np.array([0.5, -1.5], dtype=np.float32)
+    d = B.make_desc(N, C_in, C_out, H, W, 1, K, B.SNN_ACT_BIN_ROWS)
+    layers = [{"desc": d, "w": G.dev(w), "codebook": G.dev(cb), "alpha": G.dev(alpha), "beta": b,
+               "idx_out": torch.empty(C_out * C_in, dtype=torch.int16, device="cuda"), "workspace": B.alloc_workspace(d, B.SNN_WS_SUBBIT)}
+              for b in (None, G.dev(beta))]
+    B.snn_subbit_project_prepare_many(B.layer_weights_array(layers))
+    xp = B.snn_pack_activations(G.dev(x), B.SNN_ACT_BIN_ROWS)
+    codes = oracle.expand(cb, oracle.project(w, cb)[0].reshape(C_out, C_in))
+    _, Y = oracle.conv_bin(oracle.sign(x), codes, alpha, 1)
+    assert (B.snn_subbit_conv2d_prepared(d, xp, layers[0]["alpha"], layers[0]["workspace"]).cpu().numpy() == Y).all()
+    y = torch.full((N, C_out, H, W), float("nan"), device="cuda")
+    B.snn_subbit_conv2d_prepared_many(B.layer_io_array([{"desc": d, "x": xp, "y": y, "workspace": layers[0]["workspace"]}]))
+    assert (y.cpu().numpy() == Y).all()
+    want, _ = oracle.conv_sign(oracle.sign(x), codes, alpha, beta, 1)
+    got = B.snn_subbit_conv2d_sign_prepared(d, xp, layers[1]["workspace"])
+    assert (got.cpu().numpy().view(np.uint32).ravel() == np.asarray(want).view(np.uint32).ravel()).all()
 
 
 @pytest.mark.parametrize("n_layers, N", [(3, 2), (34, 1), (36, 2), (3, 1700)])

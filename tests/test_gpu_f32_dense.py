@@ -34,3 +34,44 @@ def test_f32_dense_form(oracle, case):
     got = G.subbit_f32(x, cb, idx, alpha, stride)
     # at most a rounding per channel of a tap, thirteen joining the sums and one for alpha, each of 2^-24 of the magnitudes
     assert (np.abs(got.astype(np.float64) - Y) <= (C_in + 16) * 2.0 ** -24 * mag.astype(np.float64) * 1.01).all()
+
+
+# values: what the inputs hold beside ordinary numbers
+@pytest.mark.parametrize("case", [(2, 3, 40, 5, 9, 1, 16), (2, 41, 70, 6, 7, 2, 32), (3, 64, 33, 8, 8, 1, 64), (2, 10, 20, 5, 6, 1, 4)])
+@pytest.mark.parametrize("values", ["infinite", "nan", "subnormal", "huge"])
+def test_f32_special_values(oracle, case, values):
+    """Infinities and NaN reach the outputs whose windows hold them and no other (padding is no product with zero); subnormal
+    inputs count in full.  The last case is the two-stage form's."""
+    N, C_in, C_out, H, W, stride, K = case
+    print("f32 special", case, values, file=sys.stderr, flush=True)
+    g = np.random.default_rng(sum(case))
+    x = g.standard_normal((N, C_in, H, W), dtype=np.float32)
+    if values == "infinite":
+        x.flat[::97], x.flat[50::131] = np.inf, -np.inf
+    elif values == "nan":
+        x.flat[::97] = np.nan
+    elif values == "subnormal":
+        x = (x * np.float32(1e-39)).astype(np.float32)
+        assert (np.abs(x) < 2.0 ** -126).all() and x.any()
+    else:                                               # sums of magnitudes up to 64 * 9 * 5e35 stay below 3.4e38
+        x = np.clip(x, -5, 5) * np.float32(1e35)
+    cb, idx = synth.codebook(g, K), synth.indices(g, C_out, C_in, K)
+    alpha = np.ones(C_out, dtype=np.float32) if values != "subnormal" else np.full(C_out, 2.0 ** 20, dtype=np.float32)
+    sg = np.where((oracle.expand(cb, idx)[:, :, None] >> (8 - np.arange(9))) & 1, 1.0, -1.0)        # [C_out][C_in][9]
+    xp = np.pad(x.astype(np.float64), ((0, 0), (0, 0), (1, 1), (1, 1)))
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    win = np.stack([xp[:, :, t // 3:t // 3 + stride * (Ho - 1) + 1:stride, t % 3:t % 3 + stride * (Wo - 1) + 1:stride] for t in range(9)], 2)
+    finite = np.where(np.isfinite(win), win, 0.0)
+    want = np.einsum("oct,nctyx->noyx", sg, finite) * float(alpha[0])
+    mag = np.abs(finite).sum((1, 2))[:, None] * float(alpha[0])
+    plus = np.einsum("oct,nctyx->noyx", (sg > 0) * 1.0, (win == np.inf) * 1.0) + np.einsum("oct,nctyx->noyx", (sg < 0) * 1.0, (win == -np.inf) * 1.0)
+    minus = np.einsum("oct,nctyx->noyx", (sg < 0) * 1.0, (win == np.inf) * 1.0) + np.einsum("oct,nctyx->noyx", (sg > 0) * 1.0, (win == -np.inf) * 1.0)
+    nan = np.isnan(win).any((1, 2))[:, None] | ((plus > 0) & (minus > 0))
+    got = G.subbit_f32(x, cb, idx, alpha, stride).astype(np.float64)
+    assert (np.isnan(got) == nan).all()
+    assert (got[~nan & (plus > 0)] == np.inf).all() and (got[~nan & (minus > 0)] == -np.inf).all()
+    ok = ~nan & (plus == 0) & (minus == 0)
+    assert np.isfinite(got[ok]).all()
+    # sums as above; a subnormal's roundings are of an absolute size (2^-150, and those of up to 9 C_in terms scaled by alpha)
+    tol = (C_in + 16) * 2.0 ** -24 * mag * 1.01
+    assert (np.abs(got - want) <= np.broadcast_to(tol, got.shape))[ok].all(), np.abs(got - want)[ok].max()

@@ -1,6 +1,6 @@
 """snn_subbit_conv2d_prepared_many (the convolutions of several prepared layers in as few launches as
-possible) against the oracle, element by element and bit for bit, through every tile form of the
-resident-worker kernel and through the layers it hands to the per-layer kernel; guard bytes around
+possible) against the oracle, element by element and bit for bit, through the dense contraction, and through every tile
+form of the resident-worker kernel (SNN_TUNE_STACK = 1) and the layers it hands to the per-layer kernel; guard bytes around
 every output and workspace."""
 import sys
 
@@ -60,9 +60,10 @@ FORMS = [
 ]
 
 
-@pytest.mark.parametrize("stack", [None, 0])
+@pytest.mark.parametrize("stack", [None, 0, 1])
 def test_many_every_form_in_one_call(oracle, stack, tune):
-    """stack = 0: the launch with one workgroup per group of tiles instead of resident workers."""
+    """None: the library's choice, for these layers the dense contraction.  1: the one-hot form with resident workers.  0: the one-hot
+    form with one workgroup per group of tiles instead."""
     if stack is not None:
         tune("STACK", stack)
     layers = [_make(oracle, i, *c) for i, c in enumerate(FORMS)]
@@ -75,15 +76,36 @@ def test_many_every_form_in_one_call(oracle, stack, tune):
         _check(layers, "call %d" % rep)
 
 
+@pytest.mark.parametrize("stack", [None, 1])
 @pytest.mark.parametrize("case", FORMS)
-def test_many_single_layer(oracle, case):
-    _say("many, one layer", case)
+def test_many_single_layer(oracle, case, stack, tune):
+    if stack is not None:
+        tune("STACK", stack)
+    _say("many, one layer", case, stack)
     layers = [_make(oracle, 50, *case)]
     B.snn_subbit_conv2d_prepared_many(B.layer_io_array(layers))
     _check(layers, "single layer")
 
 
-@pytest.mark.parametrize("stack", [None, 0])
+@pytest.mark.parametrize("case", FORMS)
+def test_one_hot_form_with_its_own_choice_of_tiles(oracle, case, tune):
+    """SNN_TUNE_SUBBIT_MFMA = 1 selects the one-hot matrix-core kernel and leaves the tiles to it: one call per layer, with fp32 output
+    and ending in a sign."""
+    tune("SUBBIT_MFMA", 1)
+    N, C_in, C_out, H, W, stride, K = case
+    _say("one-hot form", case)
+    g = np.random.default_rng(sum(case))
+    x = g.standard_normal((N, C_in, H, W), dtype=np.float32)
+    cb, idx, alpha = synth.codebook(g, K), synth.indices(g, C_out, C_in, K), synth.alpha(g, C_out)
+    xs, codes = oracle.sign(x), oracle.expand(cb, idx)
+    _, Y = oracle.conv_bin(xs, codes, alpha, stride)
+    assert (G.subbit_bin(x, cb, idx, alpha, stride) == Y).all()
+    beta = -(alpha * np.median(Y, axis=(0, 2, 3))).astype(np.float32)
+    want, _ = oracle.conv_sign(xs, codes, alpha, beta, stride)
+    assert (G.subbit_sign(oracle.pack_rows(x), x.shape, cb, idx, alpha, beta, stride) == want).all()
+
+
+@pytest.mark.parametrize("stack", [None, 0, 1])
 def test_many_more_layers_than_one_launch_holds(oracle, stack, tune):
     if stack is not None:
         tune("STACK", stack)
@@ -94,8 +116,11 @@ def test_many_more_layers_than_one_launch_holds(oracle, stack, tune):
     _check(layers, "19 layers")
 
 
-def test_many_equals_per_layer_calls_on_a_multi_tile_stack(oracle):
-    """Layers big enough that every worker draws several items, some of them from different layers."""
+@pytest.mark.parametrize("stack", [None, 1])
+def test_many_equals_per_layer_calls_on_a_multi_tile_stack(oracle, stack, tune):
+    """Layers big enough that every resident worker draws several items, some of them from different layers."""
+    if stack is not None:
+        tune("STACK", stack)
     cases = [(16, 64, 64, 56, 56, 1, 32), (16, 64, 128, 56, 56, 2, 32), (16, 128, 128, 28, 28, 1, 32), (16, 256, 256, 14, 14, 1, 32),
              (16, 512, 512, 7, 7, 1, 32)]
     layers = []
@@ -208,7 +233,7 @@ def _check_forward(layers, what):
         assert (G.host_u16(L["idx_out"]) == L["idx"].reshape(-1)).all(), "%s: projection of %s" % (what, L["shape"])
 
 
-@pytest.mark.parametrize("stack", [None, 0])
+@pytest.mark.parametrize("stack", [None, 0, 1])
 def test_forward_many_every_form(oracle, stack, tune):
     if stack is not None:
         tune("STACK", stack)

@@ -5,12 +5,10 @@
                     [--headline-only] [--no-configs] [--no-traffic]
 
 One "step" is one pass of the whole path over one batch of synthetic input, i.e. the forward lines of
-Alg. 1 for every 3x3 layer of the workload:
-  * project the real-valued kernels of all layers onto their subsets and build the convolution's tables
-    (Eq. 2 / Eq. 5; one launch, snn_subbit_project_prepare_many),
-  * binarise and pack every layer's fp32 input (one launch, snn_pack_activations_many),
-  * the sub-bit convolutions of all layers (Sec. 4.5: stage 1, stage 2, alpha scaling; one launch,
-    snn_subbit_conv2d_prepared_many).
+Alg. 1 for every 3x3 layer of the workload, one snn_subbit_forward_many call of two launches:
+  * the real-valued kernels of all layers projected onto their subsets, the convolution's weights built from them
+    (Eq. 2 / Eq. 5), and every layer's fp32 input binarised and packed,
+  * the sub-bit convolutions of all layers (Sec. 4.5) and alpha scaling.
 Inputs are resident in HBM before the timed region.  The same layers then run through the library's 1-bit
 XNOR/popcount kernel (snn_bnn_conv2d on the decoded kernels, SNN_TUNE_BNN_REGS = 1) for the speed-up.
 
@@ -42,9 +40,8 @@ MFMA_FP6_FP4_PEAK_FLOPS = 10.1e15          # dense FP6 / FP4 operands (v_mfma_f3
 # vector peak / 2 for FMA / 2 for the packed form)
 VALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
 MFMA_FLOP_32x32x64 = 2 * 32 * 32 * 64
-# contraction slots per input channel of the convolution as launched: the nine taps (the dense contraction on packed rows,
-# the library's own choice for these layers), over channels rounded up to blocks of 32
-SLOTS_PER_CHANNEL = 9
+# the knobs that select the two-stage kernels (environment variables; unset: the library's own choice)
+TWO_STAGE_KNOBS = ("SNN_SUBBIT_MFMA", "SNN_MFMA_TILE", "SNN_MFMA_KS", "SNN_MFMA_STAGE", "SNN_MFMA_QUAD", "SNN_STACK")
 
 COPY_CAL_BYTES = 256 * 1024 * 1024           # the copy probe of the counter passes reads and writes this much
 
@@ -323,6 +320,25 @@ def measured_peaks(torch, np):
     return out
 
 
+def dense_form(layers):
+    """Whether the library's dense contraction runs these layers: its choice for all rows of up to 320 pixels (the wider ones may go
+    to the one-hot form) unless a knob selects the two-stage kernels."""
+    return all(L.W <= 320 for L in layers) and not any(os.environ.get(k) for k in TWO_STAGE_KNOBS)
+
+
+def launched_work(layers):
+    """(contraction slots per input channel and output, flops of the matrix instructions) of the convolutions as launched."""
+    if dense_form(layers):
+        # a pair of blocks of 32 input channels is nine steps of 64 slots, a single one at the end five
+        steps = [9 * (((L.C_in + 31) // 32) // 2) + 5 * (((L.C_in + 31) // 32) % 2) for L in layers]
+        flops = sum(2.0 * 64 * st * L.pixels * ((L.C_out + 31) // 32 * 32) for st, L in zip(steps, layers))
+    else:
+        from paper_2110_09195_amd import binding as B
+        per = [B.snn_subbit_slots_per_channel(B.make_desc(L.N, L.C_in, L.C_out, L.H, L.W, L.stride, L.K, B.SNN_ACT_BIN_ROWS)) for L in layers]
+        flops = sum(2.0 * max(p, 0) * L.C_in * L.pixels * ((L.C_out + 31) // 32 * 32) for p, L in zip(per, layers))
+    return flops / sum(2.0 * L.pixels * L.C_out * L.C_in for L in layers), flops
+
+
 def conv_roofline(layers, t_s, peaks, accounting):
     """The roofline object of a sub-bit convolution launch (or of the launches of a list of layers): Sec. 4.5's own
     units, the unit the kernel spends per gather as launched, fractions against vendor and measured peaks."""
@@ -332,17 +348,17 @@ def conv_roofline(layers, t_s, peaks, accounting):
     in_bytes = sum(L.N * L.C_in * L.H * ((L.W + 31) // 32) * 4 for L in layers)
     idx_bytes = sum(L.C_in * L.C_out * 2 for L in layers)
     alg_bytes = float(out_bytes + in_bytes + idx_bytes)
-    # flops the matrix cores execute as launched
-    flops = sum(2.0 * SLOTS_PER_CHANNEL * L.pixels * L.C_out * ((L.C_in + 31) // 32 * 32) for L in layers)
+    slots, flops = launched_work(layers)
     t_hbm = alg_bytes / HBM_PEAK_BYTES
     t_unit = flops / MFMA_FP6_FP4_PEAK_FLOPS
     r = {
         "bound": "mfma" if t_unit >= t_hbm else "hbm",
         "alg_bytes": alg_bytes, "alg_bytes_split": {"in_packed": in_bytes, "out_f32": out_bytes, "idx_u16": idx_bytes},
         "gather_adds": gather_adds, "responses": responses,
-        "unit_used": "contraction slots of v_mfma_f32_32x32x64_f8f6f4 (FP4 signs x FP4 signs, fp32 accumulators): "
-                     "`slots_per_channel` multiply-adds per gather-add, the nine taps of the kernel the index selects",
-        "slots_per_channel": SLOTS_PER_CHANNEL,
+        "unit_used": "contraction slots of v_mfma_f32_32x32x64_f8f6f4: `slots_per_channel` multiply-adds per gather-add.  Dense "
+                     "contraction (FP4 signs x FP4 signs, fp32 accumulators): the nine taps of the kernel the index selects, ten in "
+                     "the last of an odd number of blocks of 32 input channels; channels rounded up to blocks of 32 on both sides",
+        "slots_per_channel": slots,
         "unit_flops_as_launched": flops,
         "t_kernel_us": t_s * 1e6,
         "t_floor_hbm_us": t_hbm * 1e6, "t_floor_unit_us": t_unit * 1e6,
@@ -435,7 +451,7 @@ def run_configs(bn, args, peaks, oracle):
                "project_us": bn.event_avg_us(lambda: B.snn_project_kernels(s["w"], s["cb"], out=s["idx"]), reps),
                "timing": "conv_us / bnn_conv_us: %d launches back to back between one pair of HIP events; single_launch: one "
                          "pair per launch; cold: 512 MB written between launches, median of 7" % reps}
-        if slots > 0:
+        if slots > 0 or dense_form([L]):
             rf = conv_roofline([L], t_conv * 1e-6, peaks, accounting)
             row["roofline"] = {k: rf[k] for k in ("bound", "alg_bytes", "gather_adds", "responses", "slots_per_channel", "frac",
                                                    "frac_hbm", "frac_unit", "useful_frac", "frac_vs_measured_peaks") if k in rf}
@@ -607,9 +623,10 @@ def main():
         B.snn_subbit_forward(s["d_sub"], s["x"], s["w"], s["cb"], s["alpha"], idx_out=s["idx"].view(L.C_out, L.C_in),
                              y=s["y"], workspace=s["ws_fwd"])
 
-    # The headline step, three launches: sign/pack of all layers' inputs, the weights-side work of all layers (projection +
-    # tables), the convolutions of all layers.  For the roofline the same steps run a second time with a pair of events
-    # on the launch stream around the convolution launch: their average is the kernel time it uses.
+    # The headline step is one snn_subbit_forward_many call: a launch for the sign/pack of all layers' inputs and the weights-side work
+    # of all layers, and one for all convolutions.  For the roofline the step runs a second time as three calls (pack,
+    # weights, convolutions) with a pair of events on the launch stream around the convolutions: their average is the kernel time
+    # it uses.
     prep_arr = B.layer_weights_array([{"desc": s["d_sub"], "w": s["w"], "codebook": s["cb"], "alpha": s["alpha"],
                                        "idx_out": s["idx"], "workspace": s["ws_sub"]} for s in st])
     many_ok = all(B.snn_subbit_slots_per_channel(s["d_sub"]) > 0 for s in st)
@@ -623,7 +640,7 @@ def main():
             for s in st:
                 conv_prepared(s)
 
-    # the same step as ONE call (snn_subbit_forward_many: the same three launches; its own workspaces and outputs)
+    # the step as ONE call (its own workspaces)
     fwd_many = None
     if many_ok:
         fwd_arr = B.layer_forward_array([{"desc": s["d_sub"], "x": s["x"], "w": s["w"], "codebook": s["cb"], "alpha": s["alpha"],
@@ -636,7 +653,7 @@ def main():
 
     def step(timed=False):
         if not timed and fwd_many is not None:
-            fwd_many()                      # the same three launches as one call
+            fwd_many()
             return
         B.snn_pack_activations_many(pack_arr)
         B.snn_subbit_project_prepare_many(prep_arr)
@@ -829,6 +846,16 @@ def main():
     t_bnn_k = [bn.event_avg_us(lambda s=s: conv_bnn_prepared(s), reps) for s in st]
     for s in st:
         assert torch.equal(s["y"], s["yb"]), "prepared 1-bit kernel disagrees on " + s["L"].name
+    # and what the library itself picks for the 1-bit layers (workspaces prepared for it, then again for the kernels above)
+    B.snn_set_tuning(B.SNN_TUNE_BNN_REGS, B.SNN_TUNE_AUTO)
+    for s in st:
+        B.snn_bnn_prepare(s["d_bnn"], s["w9"], s["ws_bnn"])
+    t_bnn_own = [bn.event_avg_us(lambda s=s: conv_bnn_prepared(s), reps) for s in st]
+    for s in st:
+        assert torch.equal(s["y"], s["yb"]), "the library's 1-bit layer disagrees on " + s["L"].name
+    B.snn_set_tuning(B.SNN_TUNE_BNN_REGS, 1)
+    for s in st:
+        B.snn_bnn_prepare(s["d_bnn"], s["w9"], s["ws_bnn"])
     # XOR + bit count: 2 lane-operations per 32-bit word of a tap (Sec. 3), 9 ceil(C_in / 32) words per output
     bnn_lane_ops = sum(2 * 9 * ((L.C_in + 31) // 32) * L.N * L.H_out * L.W_out * L.C_out for L in layers)
     t_proj = [bn.event_avg_us(lambda s=s: project(s), reps) for s in st]
@@ -888,10 +915,12 @@ def main():
     dense_ops = sum(L.dense_ops for L in layers)
     in_bytes_packed = sum(L.N * L.C_in * L.H * ((L.W + 31) // 32) * 4 for L in layers)
     roofline = None
-    if many_ok:
+    if many_ok or dense_form(layers):
         roofline = conv_roofline(layers, t_conv_in_step_us * 1e-6, peaks, accounting)
-        roofline["kernel"] = ("rows_fp4_many_kernel: the convolutions of all %d layers in one launch (up to 34 layers to a launch); t_kernel = average over %d steps (the timed steps run a second time) of a "
-                              "HIP-event pair around the call, on the launch stream" % (len(layers), args.steps))
+        what = ("rows_fp4_kernel, a launch per layer" if not many_ok else "the two-stage kernels" if not dense_form(layers) else
+                "rows_fp4_many_kernel: the convolutions of all %d layers in one launch (up to 34 layers to a launch)" % len(layers))
+        roofline["kernel"] = ("%s; t_kernel = average over %d steps (the timed steps run a second time) of a "
+                              "HIP-event pair around the calls, on the launch stream" % (what, args.steps))
         roofline["t_kernel_us_back_to_back"] = t_convs_b2b
         roofline["t_kernel_us_single_launch_median"] = t_convs_each[len(t_convs_each) // 2]
         roofline["t_kernel_us_single_launch_min"] = t_convs_each[0]
@@ -997,12 +1026,11 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "fp4 x fp6 -> f32 (exact integers; one f32 multiply by alpha)",
+        "dtype": "fp4 x fp4 -> f32 (signs; sums are exact integers; one f32 multiply by alpha)",
         "data": "synthetic",
         "config": {"workload": wname,
-                   "step": "one snn_subbit_forward_many call = three launches: sign + pack of all layers' inputs "
-                           "(snn_pack_activations_many), projection + tables of all layers (snn_subbit_project_prepare_many), "
-                           "the convolutions of all layers (snn_subbit_conv2d_prepared_many)" if many_ok else
+                   "step": "one snn_subbit_forward_many call = two launches: sign + pack of all layers' inputs with the projection "
+                           "and weight layout of all layers, then the convolutions of all layers" if many_ok else
                            "snn_subbit_project_prepare_many, then per layer snn_pack_activations + snn_subbit_conv2d_prepared"},
         "ms_per_step_three_calls": ms_per_step_three_calls,
         "ms_per_step_pack_launch_per_layer": ms_per_step_pack_per_layer,
@@ -1024,6 +1052,9 @@ def main():
                          "achieved": bnn_lane_ops / (sum(t_bnn_k) * 1e-6) / 1e12, "unit": "T lane-op/s",
                          "peak": VALU_PEAK_LANE_OPS / 1e12, "frac": bnn_lane_ops / VALU_PEAK_LANE_OPS / (sum(t_bnn_k) * 1e-6),
                          "frac_vs_measured_xor_bcnt": bnn_lane_ops / (peaks["valu_xor_bcnt_T_lane_ops"] * 1e12) / (sum(t_bnn_k) * 1e-6)},
+        "bnn_conv_prepared_us_by_library_choice": t_bnn_own,
+        "bnn_note": "bnn_* figures are the XNOR/popcount kernels (SNN_TUNE_BNN_REGS = 1), the baseline of the metric; by its own choice "
+                    "the library runs these 1-bit layers on the matrix cores, at about the sub-bit layers' cost",
         "speedup_vs_bnn_conv_cold": t_bnn_cold / t_convs_cold,
         "speedup_vs_bnn_step": ms_per_step_bnn / ms_per_step,
         "bnn_ms_per_step": ms_per_step_bnn,
@@ -1037,7 +1068,7 @@ def main():
                 "frac": (sum(L.N * L.C_in * L.H * L.W * 4 for L in layers) + in_bytes_packed) / HBM_PEAK_BYTES / (t_pack_many * 1e-6),
                 "frac_vs_measured_read": (sum(L.N * L.C_in * L.H * L.W * 4 for L in layers) + in_bytes_packed)
                 / (peaks["hbm_read_GBps"] * 1e9) / (t_pack_many * 1e-6)},
-            "subbit_prepare_many_kernel": {
+            "rows_fp4_project_many_kernel": {
                 "us": t_prep_many, "alg_bytes": sum(L.C_in * L.C_out * 38 for L in layers),
                 "lane_ops": sum(L.C_in * L.C_out * L.K * 10 for L in layers), "bound": "alu",
                 "frac": max(sum(L.C_in * L.C_out * 38 for L in layers) / HBM_PEAK_BYTES,
@@ -1045,8 +1076,8 @@ def main():
                 "frac_hbm": sum(L.C_in * L.C_out * 38 for L in layers) / HBM_PEAK_BYTES / (t_prep_many * 1e-6),
                 "note": "Eq. 2 / Eq. 5: per kernel and subset member nine sequential fp32 add/subtracts and one comparison "
                         "(10 lane-operations; 36 bytes in and 2 out per kernel).  As built a member costs 12 vector "
-                        "instructions (the comparison is a compare and two selects), and the selector words, tables and "
-                        "ballots of the block come on top: the launch is bound by vector issue at five waves per SIMD"}},
+                        "instructions (the comparison is a compare and two selects), and the weight words come on top.  The call "
+                        "alone; the step does this work in the launch that packs"}},
         "training_side": training,
         "chained_1bit_stack": chained,
         "dense_fp4_context": None if not extras else {

@@ -1,4 +1,4 @@
-"""Where the time of the one-launch convolution stack goes: wall-clock marks inside the kernel.
+"""Where the time of the resident-worker launch (SNN_TUNE_STACK = 1) goes: wall-clock marks inside the kernel.
 
     python -m paper_2110_09195_amd.devtools.stack_phases build      # anywhere: hipcc cross-compiles
     python -m paper_2110_09195_amd.devtools.stack_phases run        # on the GPU
@@ -91,6 +91,7 @@ def run():
         raise SystemExit("stack_phases: build first (python -m paper_2110_09195_amd.devtools.stack_phases build)")
     B.LIB_PATH = LIB
     torch.cuda.set_device(0)
+    B.snn_set_tuning(B.SNN_TUNE_STACK, 1)        # this kernel, not the library's choice for these layers
     layers = synth.resnet18_stack(N=64, K=32)
 
     def dev(a):

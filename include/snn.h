@@ -130,7 +130,8 @@ int snn_project_kernels(const float *w, int64_t n, const uint16_t *codebook, int
  * y = alpha * S.  For +-1 activations the sums are integers and the library is free in how it
  * forms them: it contracts over (tap, input channel) on the matrix cores (nine slots per input
  * channel); the two-stage kernels (K slots per input channel, or LDS gathers) run the layers that
- * form does not take (rows of more than about a thousand pixels) and are selected by the tuning knobs below.
+ * form does not take (rows of more than about a thousand pixels, and some of more than 320 with few channels)
+ * and are selected by the tuning knobs below.
  *   desc      host; act = SNN_ACT_BIN_ROWS (+-1 activations) or SNN_ACT_F32
  *   x         device, activations in the layout desc->act names
  *   codebook  device, uint16 [K] 9-bit codes
@@ -277,21 +278,20 @@ int snn_subbit_project_prepare_many(const snn_layer_weights *layers, int n_layer
 
 /*
  * snn_subbit_conv2d_prepared for several layers that do not depend on each other (each reads its own
- * input), e.g. the 3x3 layers of a network whose inputs are all resident: the two stages of Sec. 4.5
- * for every layer, as few launches as possible (layers whose form the shared kernel holds go
- * sixteen to a launch, any other layer gets a launch of its own).  The results are those of one
- * snn_subbit_conv2d_prepared call per layer, bit for bit; what changes is that the layers share the
- * chip instead of each ending with a few busy compute units.
+ * input), e.g. the 3x3 layers of a network whose inputs are all resident: the convolutions of Sec. 4.5
+ * in as few launches as possible.  The layers of the dense contraction go 34 to a launch.  Of those that the
+ * two-stage kernels run, the ones whose form the resident-worker kernel holds go sixteen to a launch, any other
+ * gets a launch of its own.  The results are those of one snn_subbit_conv2d_prepared call per layer, bit for
+ * bit; what changes is that the layers share the chip instead of each ending with a few busy compute units.
  *   layers[l].desc       host; act must be SNN_ACT_BIN_ROWS, K <= 64 (C_in >= 2 if K <= 32)
  *   layers[l].x_packed   device, packed rows of the layer's input
  *   layers[l].y_nchw     device, float [N][C_out][H_out][W_out], fully overwritten; the outputs of
  *                        different layers must not overlap
  *   layers[l].workspace  device, as prepared by snn_subbit_prepare / snn_subbit_prepare_packed /
  *                        snn_subbit_project_prepare_many (beta == NULL) for the same desc.  The tables
- *                        are only read.  The scheduling words at the end of layers[0].workspace (zero after
- *                        preparation) count work items while the call runs and are zero again when it
- *                        ends: calls that share that workspace must be ordered, like any two calls that
- *                        share a workspace.
+ *                        are only read.  The resident-worker kernel also counts its work items in scheduling words
+ *                        at the end of its first layer's workspace (zero after preparation, and again when the call
+ *                        ends): calls that share workspaces must be ordered.
  * Errors: INVALID_ARG; UNSUPPORTED (a layer outside the matrix-core kernel); WORKSPACE; LAUNCH.  All
  * layers are checked before anything is enqueued.
  */
@@ -305,11 +305,11 @@ typedef struct snn_layer_io {
 int snn_subbit_conv2d_prepared_many(const snn_layer_io *layers, int n_layers, void *stream);
 
 /*
- * Alg. 1 forward of a whole stack of independent layers in THREE launches: one binarises and packs every
- * layer's fp32 input (snn_pack_activations_many), one projects every layer's real-valued kernels onto its subset
- * (Eq. 2 / Eq. 5) and builds the convolution's tables (snn_subbit_project_prepare_many), the third is the launch
- * of snn_subbit_conv2d_prepared_many over all layers.  (The first two are independent: a caller with two streams
- * can issue these three calls itself and overlap them.)
+ * Alg. 1 forward of a whole stack of independent layers in TWO launches: one binarises and packs every
+ * layer's fp32 input, projects every layer's real-valued kernels onto its subset (Eq. 2 / Eq. 5) and builds the
+ * convolution's tables (the work of snn_pack_activations_many and snn_subbit_project_prepare_many), the other is
+ * that of snn_subbit_conv2d_prepared_many over all layers.  Each holds up to 34 layers; where the two-stage
+ * kernels run some layer, packing and projection are launches of their own.
  * Results (idx_out, y_nchw) are those of one snn_subbit_forward call per layer, bit for bit.
  *   layers[l].desc       host; act must be SNN_ACT_BIN_ROWS, K <= 64 (C_in >= 2 if K <= 32)
  *   layers[l].x_nchw     device, float [N][C_in][H][W]
@@ -426,7 +426,9 @@ int snn_project_vectors8(const float *w, int64_t n, const uint16_t *codebook8, i
 
 /*
  * Sec. 3: the 1-bit layer a = lambda * (w_bar o a_bar), "o" = XNOR + bit count over words of
- * 32 input channels.  The baseline every sub-bit number is compared with.
+ * 32 input channels.  The baseline every sub-bit number is compared with is its XNOR/popcount
+ * kernels, SNN_TUNE_BNN_REGS = 1; left to itself the library forms the same sums on the matrix cores
+ * where that is the faster way (most layers of more than a few output channels).
  *   desc      host; act = SNN_ACT_BIN_CHANNELS (+-1 activations) or SNN_ACT_F32; K ignored
  *   x         device, activations in the layout desc->act names
  *   w9        device, uint16 [C_out][C_in], one 9-bit code per kernel
@@ -440,8 +442,8 @@ int snn_bnn_conv2d(const snn_conv_desc *desc, const void *x, const uint16_t *w9,
 
 /*
  * snn_bnn_conv2d in two halves, for weights that stay fixed over many calls (the form the 1-bit layer of
- * Sec. 3 is timed in next to the prepared sub-bit calls): snn_bnn_prepare turns w9 into the bit planes
- * and border corrections the kernel reads (all that depends on the weights) and writes them to the
+ * Sec. 3 is timed in next to the prepared sub-bit calls): snn_bnn_prepare turns w9 into the tables
+ * the kernel reads (all that depends on the weights) and writes them to the
  * workspace; snn_bnn_conv2d_prepared runs the convolution from them.  Arguments as for snn_bnn_conv2d;
  * the workspace (SNN_WS_BNN) carries the prepared data between the two calls and must not be written in
  * between; the two calls together give exactly the result of snn_bnn_conv2d.  Same errors.
@@ -523,11 +525,12 @@ size_t snn_packed_bytes(int N, int C, int H, int W, int layout);
 /* Static, human-readable name of a status code. */
 const char *snn_status_string(int status);
 
-/* Contraction slots per input channel that the two-stage (one-hot) matrix-core form of the sub-bit convolution spends on
- * this layer (Sec. 4.5: the method needs one of them, the gather; the others multiply a zero
- * of the one-hot operand; the dense contraction spends nine on any layer): 32 (two channels per matrix instruction, K <= 32), 16 (four channels,
- * K <= 16 on long channel runs), 64 (one channel, 32 < K <= 64); 0 where a kernel without matrix
- * instructions runs the layer (K > 64, C_in = 1, fp32 activations); negative SNN_ERR_* for an invalid desc.
+/* Contraction slots per input channel that the one-hot form of the sub-bit convolution spends on this layer
+ * (Sec. 4.5: the method needs one of them, the gather; the others multiply a zero of the one-hot operand):
+ * 32 (two channels per matrix instruction, K <= 32), 16 (four channels, K <= 16 on long channel runs), 64 (one
+ * channel, 32 < K <= 64); 0 where that form does not take the layer (K > 64, C_in = 1 with K <= 32, fp32 activations);
+ * negative SNN_ERR_* for an invalid desc.  It describes that form whether or not it is the one that runs: the dense
+ * contraction, the library's choice for most layers, spends nine on any layer.
  * Host-only; for the roofline accounting of a benchmark. */
 int snn_subbit_slots_per_channel(const snn_conv_desc *desc);
 
@@ -546,7 +549,7 @@ int snn_subbit_slots_per_channel(const snn_conv_desc *desc);
 #define SNN_TUNE_MFMA_KS     2 /* waves that share a tile's input channels: 1, 2, 4 */
 #define SNN_TUNE_MFMA_STAGE  3 /* 0 / 1: packed rows staged in LDS wherever they fit */
 #define SNN_TUNE_MFMA_QUAD   4 /* 0 / 1: four channels per matrix instruction wherever K <= 16 */
-#define SNN_TUNE_STACK       5 /* 0: snn_subbit_conv2d_prepared_many runs one workgroup per tile group */
+#define SNN_TUNE_STACK       5 /* snn_subbit_conv2d_prepared_many: 1 resident workers, 0 one workgroup per tile group */
 #define SNN_TUNE_BNN_REGS    6 /* the 1-bit layer's popcount kernels: 1 with register-resident windows, 0 without */
 #define SNN_TUNE_DENSE_TILE  7 /* 0 .. 4: tile shape of the dense contraction */
 #define SNN_TUNE_F32_WAVES   8 /* 4, 8, 16: waves per workgroup of the fp32-activation sub-bit kernel */

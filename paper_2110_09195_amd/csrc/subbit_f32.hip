@@ -1,10 +1,10 @@
 // The sub-bit convolution of Sec. 4.5 / Fig. 6 with real-valued activations (SNN_ACT_F32; the
 // W/A = x/32 models of Tables 1-2 and the deployment test of Table 4).
 //
-// Same two stages as the +-1 kernel: per chunk of input channels the workgroup builds
-// T[ci][k][pixel] in LDS (nine add/subtracts of the window's values per response, as
-// fma(x, +-1, acc)), then every lane gathers float4 rows T[ci][idx[co][ci]][4 pixels] and adds
-// them in fp32.  y = alpha * S.
+// Two forms, chosen by subset size and output channels (use_dense); y = alpha * S in both, all sums in fp32.
+// Two-stage: per chunk of input channels the workgroup builds T[ci][k][pixel] in LDS (nine add/subtracts of the window's
+// values per response, as fma(x, +-1, acc)), then every lane gathers float4 rows T[ci][idx[co][ci]][4 pixels] and adds them.
+// Dense: a contraction over taps and input channels on the fp32 matrix unit.
 #include "subbit_common.h"
 
 namespace snn {
@@ -209,7 +209,8 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr uint32_t SD_NONE = 0x80000000u;              // past every buffer used here
 
-// codes of [32 output channels][4 pairs of input channels]: lane (co, h) has the pairs' channels 2 p + h as four uint16
+// wq: codes of [32 output channels][4 pairs of input channels]; lane (co, h) has the pairs' channels 2 p + h as four uint16.
+//
 // S = 4: the four waves of a workgroup share a block and split its channels, their sums meet in LDS (a quarter of the chain, four
 // times the waves: 1 x 512 -> 64 7x7 has four blocks); S = 1: a block per wave, for the few channels that are not worth it.
 template <int S>
@@ -351,6 +352,10 @@ bool use_dense(const Geom &g)
     // 16 -> 16 32x32 batch 128 K = 4 16.8 -> 20.8, K = 16 24.7 -> 20.7; 16 -> 256 56x56 batch 4 K = 4 26.1 -> 20.0;
     // 512 -> 512 7x7 batch 8 K = 4 217 -> 36, K = 32 323 -> 36.  Relative error of the sums against 64 bits: 1.0e-7 for
     // 1.6e-7 at 64 channels, 2.2e-7 for 4.1e-7 at 512.
+    // That error is why K >= 16 is the whole rule: where 64 pixels' responses are shared by 33 to 128 output channels and the pixels fill
+    // the chip (16384 and more), the two-stage form is the faster one up to K = 32: 64 -> 128 8x8 batch 256 K = 16 28.8 -> 34.8, 32x32
+    // batch 64 K = 16 89 -> 129, K = 32 104 -> 129; 64 -> 64 32x32 batch 64 K = 16 61 -> 67, K = 24 70 -> 67; also 64 -> 256 K = 16
+    // 212 -> 255, K = 4 189 -> 254.
     return g.K >= 16 || g.C_out >= 256;
 }
 

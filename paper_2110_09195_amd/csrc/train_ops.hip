@@ -48,9 +48,9 @@ __device__ __forceinline__ void store_copies(const float *acc, int copies, int K
 // partial [K][9] per block.
 //
 // The sums by member are a product [member][kernel] x [kernel][tap] with the indices as a one-hot matrix, on the fp32 matrix
-// unit (products with 1 and 0 are exact, sums are fp32 as before; a wave's chain is a sixteenth of the block).  16 M members
-// cost 32 M clocks of a SIMD per four kernels, which stays under the 110 bytes per kernel of memory traffic up to
-// M = 16.  With LDS float atomics instead, which was the whole kernel's time at any layout of the lanes (290 clocks
+// unit (products with 1 and 0 are exact, sums are fp32; a wave's chain is a sixteenth of the block).  16 M members
+// cost 32 M clocks of a SIMD per four kernels, which stays near the 110 bytes per kernel of memory traffic up to
+// M = 4 (where the line lies: launch_project_backward).  With LDS float atomics instead, which was the whole kernel's time at any layout of the lanes (290 clocks
 // per 64 additions, equal addresses among them or not), 262144 kernels at K = 32 take 17 us, here 11.9 (4096 kernels: 8.6
 // with one kernel per thread, here 4.1).
 // A zero times an infinity would reach members that it does not belong to: blocks with a value that is not finite add with

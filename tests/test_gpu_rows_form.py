@@ -82,6 +82,36 @@ def test_weights_of_a_layer_whose_form_depends_on_its_ending(oracle):
     assert (got.cpu().numpy().view(np.uint32).ravel() == np.asarray(want).view(np.uint32).ravel()).all()
 
 
+@pytest.mark.parametrize("W", [500, 700, 900])
+def test_one_call_forms_on_wide_rows(oracle, W):
+    """The calls that project and convolve, and the tables from packed indices, on both sides of the line to the one-hot form."""
+    import torch
+
+    from paper_2110_09195_amd import binding as B
+    N, C_in, C_out, H, K = 200, 3, 2, 2, 8
+    g = np.random.default_rng(W)
+    x = g.standard_normal((N, C_in, H, W), dtype=np.float32)
+    cb, w, alpha = synth.codebook(g, K), synth.real_kernels(g, C_out * C_in), synth.alpha(g, C_out)
+    beta = np.array([0.5, -1.5], dtype=np.float32)
+    idx = oracle.project(w, cb)[0].reshape(C_out, C_in)
+    xs, codes = oracle.sign(x), oracle.expand(cb, idx)
+    _, Y = oracle.conv_bin(xs, codes, alpha, 1)
+    y, got = G.subbit_forward(x, w, cb, alpha, C_out)
+    assert (got.reshape(C_out, C_in) == idx).all() and (y == Y).all()
+    want, _ = oracle.conv_sign(xs, codes, alpha, beta, 1)
+    bits, got = G.subbit_forward_sign(oracle.pack_rows(x), x.shape, w, cb, alpha, beta, C_out)
+    assert (got.reshape(C_out, C_in) == idx).all() and (bits == want).all()
+    d = B.make_desc(N, C_in, C_out, H, W, 1, K, B.SNN_ACT_BIN_ROWS)
+    xd = G.dev(x)
+    arr = [{"desc": d, "x": xd, "w": G.dev(w), "codebook": G.dev(cb), "alpha": G.dev(alpha),
+            "idx_out": torch.full((C_out * C_in,), -1, dtype=torch.int16, device="cuda"),
+            "y": torch.full((N, C_out, H, W), float("nan"), device="cuda"), "workspace": B.alloc_workspace(d, B.SNN_WS_FORWARD)}]
+    B.snn_subbit_forward_many(B.layer_forward_array(arr))
+    assert (arr[0]["y"].cpu().numpy() == Y).all()
+    ws = B.snn_subbit_prepare_packed(d, G.dev(cb), B.snn_pack_indices(G.dev(idx), 3), 3, G.dev(alpha))
+    assert (B.snn_subbit_conv2d_prepared(d, B.snn_pack_activations(xd, B.SNN_ACT_BIN_ROWS), G.dev(alpha), ws).cpu().numpy() == Y).all()
+
+
 @pytest.mark.parametrize("n_layers, N", [(3, 2), (34, 1), (36, 2), (3, 1700)])
 def test_many_layers_in_one_call_equal_one_call_per_layer(n_layers, N):
     """The several-layers launch: fewer layers than one holds, exactly as many, a few more, and outputs past 256 MB (the layers

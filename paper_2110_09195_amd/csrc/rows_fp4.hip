@@ -322,7 +322,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
 
     // ---- weights: the words of the first pair (and of the second, where a pair is too little work to hide a load) ----
     const __amdgpu_buffer_rsrc_t wres = make_rsrc(L.wq, (uint32_t)(L.n_cob * L.pairs) * RF_PAIR_BYTES);
-    constexpr bool AHEAD = PB == 1;
+    constexpr bool AHEAD = PB * CB <= 2;
     uint32_t A[CB][9], An[AHEAD ? CB : 1][9];
     auto load_words = [&](int pr, int cb, int piece, uint32_t (&a)[9]) {       // (past the last pair or block: the last one, not used)
         const uint32_t at = (uint32_t)(min(cob0 + cb, L.n_cob - 1) * L.pairs + min(pr, L.pairs - 1)) * RF_PAIR_BYTES;
@@ -373,26 +373,18 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     const uint32_t pitch = (uint32_t)W1 * 16u;
 
     v16f acc[CB][PB];
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-        for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[cb][pb][r] = 0.0f;
-
+    // (the two constants in registers: an instruction of two operations takes no literals)
+    uint32_t sign_bits = 0x88888888u, one_bits = 0x22222222u;
+    asm("" : "+v"(sign_bits));
+    asm("" : "+s"(one_bits));
     auto expand = [&](uint32_t w, u32x4 &a) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) a[r] = ((w << (3 - r)) & 0x88888888u) | 0x22222222u;
+        for (int r = 0; r < 4; ++r) a[r] = ((w << (3 - r)) & sign_bits) | one_bits;
     };
-    auto multiply = [&](const u32x4 (&a)[CB], const u32x4 (&b)[PB]) {
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb) {
-                const v8i av = {(int)a[cb][0], (int)a[cb][1], (int)a[cb][2], (int)a[cb][3], 0, 0, 0, 0};
-                const v8i bv = {(int)b[pb][0], (int)b[pb][1], (int)b[pb][2], (int)b[pb][3], 0, 0, 0, 0};
-                acc[cb][pb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc[cb][pb], 4, 4, 0, 0, 0, 0);
-            }
+    auto multiply = [&](const u32x4 &a, const u32x4 &b, v16f &sum) {
+        const v8i av = {(int)a[0], (int)a[1], (int)a[2], (int)a[3], 0, 0, 0, 0};
+        const v8i bv = {(int)b[0], (int)b[1], (int)b[2], (int)b[3], 0, 0, 0, 0};
+        sum = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, sum, 4, 4, 0, 0, 0, 0);
     };
 
     int pair = 0;                                              // of the whole layer
@@ -410,70 +402,97 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         }
         __syncthreads();
         if (!active) continue;
-        const int np = here >> 1;
-        u32x4 B[2][PB], E[2][CB];
-        uint32_t ad[PB];
+        if (cb_first == 0) {
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb) {
-            ad[pb] = top[pb] + (uint32_t)h * plane;
-            if (np > 0) B[0][pb] = *(lds_cu32x4 *)(uintptr_t)ad[pb];
-        }
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) expand(A[cb][0], E[0][cb]);
-        // One step: the matrix instructions of a tap, and the operands of the next one.
-        auto step = [&](auto tc, auto bufc, uint32_t next) {
-            constexpr int t = decltype(tc)::value, cur = decltype(bufc)::value, nxt = cur ^ 1;
-            if constexpr (t < 8) {
-                constexpr int dy = (t + 1) / 3, dx = (t + 1) % 3;
+            for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb)
-                    B[nxt][pb] = *(lds_cu32x4 *)(uintptr_t)(ad[pb] + (uint32_t)dy * pitch + (uint32_t)dx * 16u);
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) expand(A[cb][t + 1], E[nxt][cb]);
-            } else {
+                    for (int r = 0; r < 16; ++r) acc[cb][pb][r] = 0.0f;
+        }
+        // (opaque here: the addresses made of it would be kept in registers through the fill)
 #pragma unroll
-                for (int pb = 0; pb < PB; ++pb) {
-                    ad[pb] += next;
-                    B[nxt][pb] = *(lds_cu32x4 *)(uintptr_t)ad[pb];
-                }
-                if constexpr (AHEAD) {
+        for (int pb = 0; pb < PB; ++pb) asm volatile("" : "+v"(top[pb]));
+        // (the weights have been here since the fill: said so before the loop, its own waits count only what it has in flight)
+        __builtin_amdgcn_s_waitcnt(0x0f70 /* vmcnt(0) */);
+        const int np = here >> 1;
+        // A step is the matrix instructions of a tap.  A wave issues an instruction every four or five clocks whichever unit it
+        // is for, so a step of 32 PB CB matrix clocks has room for some 7 PB CB others: 7 per word of weights to expand, a read
+        // per pixel block, an address per row.  The reads are issued two steps ahead (three buffers, and nine taps are a multiple
+        // of three): one step of two matrix instructions is shorter than a read takes.  Measured against three instructions per four
+        // expanded slots, reads one step ahead and, for small grids, two blocks of output channels per wave on one of pixels: ResNet-18's
+        // chain of 1-bit layers at batch 64 167 -> 156 us, 512 -> 512 7x7 batch 8 12.2 -> 10.1.
+        u32x4 B[3][PB], E[CB];
+        uint32_t row[3][PB];                                   // LDS addresses of the window's rows
 #pragma unroll
-                    for (int cb = 0; cb < CB; ++cb) {
+        for (int pb = 0; pb < PB; ++pb) {
+            row[0][pb] = top[pb] + (uint32_t)h * plane;
+            row[1][pb] = row[0][pb] + pitch;
+            row[2][pb] = row[1][pb] + pitch;
+        }
+        auto read = [&](auto tc) {
+            constexpr int t = decltype(tc)::value;
 #pragma unroll
-                        for (int i = 0; i < 9; ++i) A[cb][i] = An[cb][i];
+            for (int pb = 0; pb < PB; ++pb) B[t % 3][pb] = *(lds_cu32x4 *)(uintptr_t)(row[t / 3][pb] + (uint32_t)(t % 3) * 16u);
+        };
+        if (np > 0) {
+            read(std::integral_constant<int, 0>{});
+            read(std::integral_constant<int, 1>{});
 #pragma unroll
-                        for (int piece = 0; piece < 3; ++piece) load_words(pair + 2, cb, piece, An[cb]);
-                    }
-                }
+            for (int cb = 0; cb < CB; ++cb) expand(A[cb][0], E[cb]);
+        }
+        auto step = [&](auto tc, uint32_t next) {
+            constexpr int t = decltype(tc)::value;
+            read(std::integral_constant<int, (t + 2) % 9>{});
+            if constexpr (t == 0 || t == 3) {                  // a row's three taps have been read: on to the next pair
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) expand(A[cb][0], E[nxt][cb]);
+                for (int pb = 0; pb < PB; ++pb) row[t / 3][pb] += next;
             }
-            multiply(E[cur], B[cur]);
+            if constexpr (t == 6) {
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) row[2][pb] += next;
+            }
+            if constexpr (AHEAD && t == 8) {
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) {
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) A[cb][i] = An[cb][i];
+#pragma unroll
+                    for (int piece = 0; piece < 3; ++piece) load_words(pair + 2, cb, piece, An[cb]);
+                }
+            }
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) multiply(E[cb], B[t % 3][pb], acc[cb][pb]);
+                expand(A[cb][(t + 1) % 9], E[cb]);
+            }
             // words of the next pair as soon as those of this one have been expanded: at least five steps ahead
             if constexpr (!AHEAD && (t == 3 || t == 7 || t == 8)) {
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) load_words(pair + 1, cb, t == 3 ? 0 : t == 7 ? 1 : 2, A[cb]);
             }
+            __builtin_amdgcn_sched_group_barrier(0x100 /* LDS reads */, PB, 0);
+#pragma unroll
+            for (int i = 0; i < PB * CB; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008 /* matrix */, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002 /* vector */, 7 / PB + 1, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         };
-        auto run_pair = [&](auto par, uint32_t next) {
-            constexpr int p0 = decltype(par)::value;
-            step(std::integral_constant<int, 0>{}, std::integral_constant<int, p0>{}, next);
-            step(std::integral_constant<int, 1>{}, std::integral_constant<int, p0 ^ 1>{}, next);
-            step(std::integral_constant<int, 2>{}, std::integral_constant<int, p0>{}, next);
-            step(std::integral_constant<int, 3>{}, std::integral_constant<int, p0 ^ 1>{}, next);
-            step(std::integral_constant<int, 4>{}, std::integral_constant<int, p0>{}, next);
-            step(std::integral_constant<int, 5>{}, std::integral_constant<int, p0 ^ 1>{}, next);
-            step(std::integral_constant<int, 6>{}, std::integral_constant<int, p0>{}, next);
-            step(std::integral_constant<int, 7>{}, std::integral_constant<int, p0 ^ 1>{}, next);
-            step(std::integral_constant<int, 8>{}, std::integral_constant<int, p0>{}, next);
+        for (int pr = 0; pr < np; ++pr) {
+            const uint32_t next = pr + 1 < np ? 2u * plane : 0u;
+            step(std::integral_constant<int, 0>{}, next);
+            step(std::integral_constant<int, 1>{}, next);
+            step(std::integral_constant<int, 2>{}, next);
+            step(std::integral_constant<int, 3>{}, next);
+            step(std::integral_constant<int, 4>{}, next);
+            step(std::integral_constant<int, 5>{}, next);
+            step(std::integral_constant<int, 6>{}, next);
+            step(std::integral_constant<int, 7>{}, next);
+            step(std::integral_constant<int, 8>{}, next);
             ++pair;
-        };
-        int pr = 0;
-        for (; pr + 2 <= np; pr += 2) {
-            run_pair(std::integral_constant<int, 0>{}, 2u * plane);
-            run_pair(std::integral_constant<int, 1>{}, pr + 2 < np ? 2u * plane : 0u);
         }
-        if (pr < np) run_pair(std::integral_constant<int, 0>{}, 0u);
         if (here & 1) {
             // the last block alone: two taps per step
             const uint32_t last = (uint32_t)(here - 1) * plane;
@@ -488,8 +507,11 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
                     B[0][pb] = *(lds_cu32x4 *)(uintptr_t)(at + last);
                 }
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) expand(A[cb][u], E[0][cb]);
-                multiply(E[0], B[0]);
+                for (int cb = 0; cb < CB; ++cb) {
+                    expand(A[cb][u], E[cb]);
+#pragma unroll
+                    for (int pb = 0; pb < PB; ++pb) multiply(E[cb], B[0][pb], acc[cb][pb]);
+                }
             }
         }
     }
@@ -649,7 +671,6 @@ void rows_fp4_many_kernel(const RfMany m)
     L.div_HoWo = c.div_HoWo; L.div_Wo = c.div_Wo; L.div_H1 = c.div_H1; L.div_WW = c.div_WW; L.div_cotiles = c.div_cotiles;
     switch (10 * c.PB + c.CB) {
     case 22: rf_tile<2, 2, false>(L, wg, smem); break;
-    case 12: rf_tile<1, 2, false>(L, wg, smem); break;
     case 21: rf_tile<2, 1, false>(L, wg, smem); break;
     default: rf_tile<1, 1, false>(L, wg, smem); break;
     }
@@ -955,18 +976,20 @@ RfPlan rf_plan(const Geom &g, bool sign, bool many = false)
     pl.bpi = (g.Ho + pl.rows_pb - 1) / pl.rows_pb;
     pl.wpr = (g.Wo + 31) / 32;
     pl.n_blk = !sign ? (g.P + 31) / 32 : g.Wo <= 32 ? (int64_t)g.N * pl.bpi : (int64_t)g.N * g.Ho * pl.wpr;
-    pl.CB = pl.n_cob >= 2 ? 2 : 1;
-    // waves of a workgroup share its expanded pixels between as many output channels as there are
-    pl.wpx_shift = pl.n_cob >= 3 ? 1 : 2;
-    const int cob_wg = pl.CB << (2 - pl.wpx_shift);
-    pl.n_cotiles = (pl.n_cob + cob_wg - 1) / cob_wg;
     pl.ok = false;
-    for (int PB : {4, 2, 1}) {
-        const int64_t nb = (int64_t)PB << pl.wpx_shift;        // pixel blocks of a workgroup
-        const int64_t wgs = (pl.n_blk + nb - 1) / nb * pl.n_cotiles;
-        // four blocks per wave halve the weight traffic; fewer where that leaves compute units without work
-        if (PB == 4 && (wgs < 512 || pl.CB == 1 || many)) continue;
-        if (PB == 2 && wgs < 256 && !many) continue;
+    struct Tile { int PB, CB; };
+    for (const Tile &t : pl.n_cob >= 2 ? std::initializer_list<Tile>{{4, 2}, {2, 2}, {2, 1}} : std::initializer_list<Tile>{{2, 1}, {1, 1}}) {
+        const int PB = t.PB;
+        // waves of a workgroup share its expanded pixels between as many output channels as there are
+        const int wpx_shift = t.CB == 2 ? (pl.n_cob >= 3 ? 1 : 2) : pl.n_cob >= 3 ? 0 : pl.n_cob == 2 ? 1 : 2;
+        const int cob_wg = t.CB << (2 - wpx_shift);
+        const int64_t n_cotiles = (pl.n_cob + cob_wg - 1) / cob_wg;
+        const int64_t nb = (int64_t)PB << wpx_shift;           // pixel blocks of a workgroup
+        const int64_t wgs = (pl.n_blk + nb - 1) / nb * n_cotiles;
+        // four blocks per wave halve the weight traffic; smaller tiles where that leaves compute units without work (half a tile
+        // is one block of output channels, not one of pixels: the weights a wave expands are used twice)
+        if (PB == 4 && (wgs < 512 || many)) continue;
+        if (PB == 2 && wgs < 256 && !many && t.CB == (pl.n_cob >= 2 ? 2 : 1)) continue;
         // rows the workgroup's pixels touch, and their three-row windows
         int64_t row_changes, image_changes;
         if (!sign) {
@@ -979,11 +1002,14 @@ RfPlan rf_plan(const Geom &g, bool sign, bool many = false)
         int64_t rows = g.stride * row_changes + image_changes + 3;
         if (rows > (int64_t)g.N * (g.H + 1) + 1) rows = (int64_t)g.N * (g.H + 1) + 1;
         const int64_t plane = (rows * (g.W + 1) + 1) * 16;
-        const size_t fixed = (size_t)4 * pl.CB * 32 * (sign ? 8 : 4);
+        const size_t fixed = (size_t)4 * t.CB * 32 * (sign ? 8 : 4);
         int chunk = pl.ncb;
         while (chunk > 2 && fixed + (size_t)chunk * plane > RF_LDS_TARGET) chunk = ((chunk + 1) / 2 + 1) & ~1;
         if (fixed + (size_t)chunk * plane > RF_LDS_MAX) continue;
         pl.PB = PB;
+        pl.CB = t.CB;
+        pl.wpx_shift = wpx_shift;
+        pl.n_cotiles = n_cotiles;
         pl.rows = rows;
         pl.plane = plane;
         pl.chunk = chunk;
@@ -1055,8 +1081,7 @@ int launch_rf(const RfPlan &pl, const RfLayer &L, hipStream_t s)
 {
     if (pl.CB == 2) {
         if (pl.PB == 4) return launch_rf_one<4, 2, SIGN, CHANNELS>(pl, L, s);
-        if (pl.PB == 2) return launch_rf_one<2, 2, SIGN, CHANNELS>(pl, L, s);
-        return launch_rf_one<1, 2, SIGN, CHANNELS>(pl, L, s);
+        return launch_rf_one<2, 2, SIGN, CHANNELS>(pl, L, s);
     }
     if (pl.PB == 2) return launch_rf_one<2, 1, SIGN, CHANNELS>(pl, L, s);
     return launch_rf_one<1, 1, SIGN, CHANNELS>(pl, L, s);

@@ -24,7 +24,7 @@
 //   needs 2 KB of codes per 64 clocks of matrix work.)
 // B (activations) is read from LDS as it is: a workgroup expands the packed rows its pixels touch into codes once,
 //   [channel block of 32][pixel] 16 bytes,
-//   on rows of W + 1 pixels (column -1 is a zero pixel and also the right border of the row above) and images of H + 1
+//   on rows of W + 1 pixels (column -1 is a zero pixel and also the right border of the row above; or of W + 2) and images of H + 1
 //   rows (a zero row above each image is also the bottom border of the one before): no tap needs a mask, and the
 //   window of an output pixel is nine reads at fixed distances.  Channels past C_in are zero here.
 // Packed channels (the 1-bit layer: a word holds 32 channels of a pixel, no transposition) run through the same kernel: which
@@ -72,6 +72,7 @@ struct RfLayer {
     int ncb;                 // blocks of 32 input channels
     int chunk;               // of which this many are expanded into LDS at a time (even unless all of them)
     int pairs;               // pairs of channel blocks, the last one possibly half empty
+    int pitch;               // pixels from one expanded row to the next: W + 1, or W + 2
     int plane;               // bytes of one expanded channel block
     int n_blk;               // blocks of up to 32 pixels
     int n_cotiles, n_wgs;
@@ -97,7 +98,7 @@ __device__ __forceinline__ void bytes4(uint32_t a, uint32_t b, uint32_t c, uint3
 // the same pixels.  A wave owns PB blocks of 32 pixels x CB blocks of 32 output channels.  Pixel blocks: 32 consecutive
 // pixels of the flattened (n, ho, wo) order; for the sign epilogue whole output words (whole rows while they fit 32
 // pixels, else one word of a row), so that the wave that owns a block owns the words it writes.
-template <int PB, int CB, bool SIGN, bool CHANNELS = false>
+template <int PB, int CB, bool SIGN, bool CHANNELS = false, int TASKS = 4>
 __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned char *const smem)
 {
     const int tid = threadIdx.x;
@@ -155,7 +156,8 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         return ok;
     };
     // rows (numbered n (H + 1) + h + 1 over the batch) that the workgroup's pixels touch
-    const int H1 = L.H + 1, W1 = L.W + 1;
+    const int H1 = L.H + 1, W1 = L.pitch;
+    const uint32_t pitch = (uint32_t)W1 * 16u;
     int R0, nrows, n0;
     {
         int ho, wo, n1, ho1, wo1;
@@ -180,7 +182,11 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     // ---- packed rows -> FP4 codes in LDS --------------------------------------------------------------------------
     // A task of a wave is 16 words (a word: 32 pixels of a row) of one channel block: lane (i, g) takes word i of the 8
     // channels of group g - eight loads, a transposition of nibbles, two instructions per pixel - and four lanes side by
-    // side write the 16 bytes of a pixel.  The loads of a task are issued before the previous one is worked on.
+    // side write the 16 bytes of a pixel.  A wave loads TASKS tasks at a time, four in the one-layer kernels: a load takes as long to come
+    // back as six tasks to expand.  Measured, one task ahead -> four at a time, the last pixels of a row apart from the whole groups
+    // of four, and the row pitch of rf_plan: 1-bit chain of ResNet-18 batch 64 156 -> 148 us, 512 -> 512 7x7 batch 256 28.2 -> 26.0, 256 -> 256
+    // 14x14 batch 128 14.5 -> 13.6, 100 -> 150 37x53 stride 2 batch 12 12.2 -> 10.0.  Several layers in one launch are bound by memory:
+    // two at a time 180.2 us for the ResNet-18 stack's forward pass, four 183.7, one 182.5.
     const uint32_t xplane = (uint32_t)(L.H * L.WW) * 4u;
     const int64_t image_words = (int64_t)L.C_in * L.H * L.WW;
     const int64_t x_left = ((int64_t)(L.N - n0) * image_words) * 4;
@@ -188,71 +194,83 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     const int RW = nrows * L.WW, nk = (RW + 15) >> 4;
     const int grp = lane & 3;
     struct Task {
-        int k, cb;                                             // words 16 k .. 16 k + 15, channel block
         uint32_t w[8];
         uint32_t addr, vmask;
         int npx;                                               // pixels of the word
-        int edge;                                              // 1: the word starts a row, 2: the last row
+        bool edge;                                             // the word starts a row
     };
+    int my_k = 0, my_cb = 0, at_k = -1, at_npx = 0;            // the wave's next task: words 16 k .. 16 k + 15, channel block
+    uint32_t at_off = 0, at_addr = 0;                          // what follows from k
+    bool at_ok = false, at_edge = false;
     auto load_task = [&](Task &T, int cb_first) {
-        const int rw = 16 * T.k + (lane >> 2);
-        const bool have = rw < RW;
-        const int row = (int)fast_div((uint32_t)rw, L.div_WW), word = rw - row * L.WW;
-        const int R = R0 + row;
-        const int n = (int)fast_div((uint32_t)R, L.div_H1), hh = R - n * H1;
-        const int cb0 = (cb_first + T.cb) * 32, c0 = cb0 + grp * 8;
-        const bool ok = have && hh > 0 && n < L.N && c0 < L.C_in;
-        const uint32_t off = (uint32_t)((((n - n0) * L.C_in + grp * 8) * L.H + hh - 1) * L.WW + word) * 4u;
+        if (my_k != at_k) {                                    // (wave-uniform)
+            at_k = my_k;
+            const int rw = 16 * my_k + (lane >> 2);
+            const bool have = rw < RW;
+            const int row = (int)fast_div((uint32_t)rw, L.div_WW), word = rw - row * L.WW;
+            const int R = R0 + row;
+            const int n = (int)fast_div((uint32_t)R, L.div_H1), hh = R - n * H1;
+            at_ok = have && hh > 0 && n < L.N;
+            at_off = (uint32_t)((((n - n0) * L.C_in + grp * 8) * L.H + hh - 1) * L.WW + word) * 4u;
+            at_addr = tile_lds + (uint32_t)(row * W1 + 1 + 32 * word) * 16u + (uint32_t)grp * 4u;
+            at_npx = have ? min(32, L.W - 32 * word) : 0;
+            at_edge = have && word == 0;
+        }
+        const int cb0 = (cb_first + my_cb) * 32, left = L.C_in - cb0 - grp * 8;    // channels of the group that exist
+        const bool ok = at_ok && left > 0;
         if ((L.C_in & 7) == 0) {
 #pragma unroll
             for (int j = 0; j < 8; ++j)
-                T.w[j] = __builtin_amdgcn_raw_buffer_load_b32(xres, (int)(ok ? off : OFF_NONE), (int)((uint32_t)(cb0 + j) * xplane), 0);
+                T.w[j] = __builtin_amdgcn_raw_buffer_load_b32(xres, (int)(ok ? at_off : OFF_NONE), (int)((uint32_t)(cb0 + j) * xplane), 0);
             T.vmask = ok ? 0xffffffffu : 0u;
         } else {
 #pragma unroll
             for (int j = 0; j < 8; ++j)
-                T.w[j] = __builtin_amdgcn_raw_buffer_load_b32(xres, (int)(ok && c0 + j < L.C_in ? off + (uint32_t)j * xplane : OFF_NONE),
+                T.w[j] = __builtin_amdgcn_raw_buffer_load_b32(xres, (int)(ok && left > j ? at_off + (uint32_t)j * xplane : OFF_NONE),
                                                               (int)((uint32_t)cb0 * xplane), 0);
-            T.vmask = !ok ? 0u : L.C_in - c0 >= 8 ? 0xffffffffu : (1u << (4 * (L.C_in - c0))) - 1u;
+            T.vmask = !ok ? 0u : left >= 8 ? 0xffffffffu : (1u << (4 * left)) - 1u;
         }
-        T.addr = tile_lds + (uint32_t)T.cb * plane + (uint32_t)(row * W1 + 1 + 32 * word) * 16u + (uint32_t)grp * 4u;
-        T.npx = have ? min(32, L.W - 32 * word) : 0;
-        T.edge = have && word == 0 ? (row == nrows - 1 ? 2 : 1) : 0;
+        T.addr = at_addr + (uint32_t)my_cb * plane;
+        T.npx = at_npx;
+        T.edge = at_edge;
+        my_k += 4;
+        while (my_k >= nk) {
+            my_k -= nk;
+            ++my_cb;
+        }
     };
     auto store_task = [&](const Task &T) {
+        int W = L.W;                                           // (opaque: a condition per group of pixels, kept in registers, would be
+        asm volatile("" : "+s"(W));                            // dozens of them)
         uint32_t ev[4], od[4];
         bytes4(T.w[0], T.w[2], T.w[4], T.w[6], ev);
         bytes4(T.w[1], T.w[3], T.w[5], T.w[7], od);
         const uint32_t m8 = T.vmask & 0x88888888u, m2 = T.vmask & 0x22222222u;
-        if (T.edge) *(lds_u32 *)(uintptr_t)(T.addr - 16u) = 0u;
-        if (T.edge == 2) *(lds_u32 *)(uintptr_t)(T.addr + (uint32_t)L.W * 16u) = 0u;
+        if (T.edge) {                                          // columns -1 and W
+            *(lds_u32 *)(uintptr_t)(T.addr - 16u) = 0u;
+            *(lds_u32 *)(uintptr_t)(T.addr + (uint32_t)L.W * 16u) = 0u;
+        }
+        uint32_t rest = 0;                                     // the last pixels of a row, where they are no whole group of four
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            if (8 * p >= L.W) break;                           // (wave-uniform: short rows have no such pixels)
+            if (8 * p >= W) break;                           // (wave-uniform: short rows have no such pixels)
             // D[m]: nibble j = pixels 4 m .. 4 m + 3 of channel j
             const uint32_t D[2] = {(ev[p] & 0x0f0f0f0fu) | ((od[p] << 4) & 0xf0f0f0f0u), ((ev[p] >> 4) & 0x0f0f0f0fu) | (od[p] & 0xf0f0f0f0u)};
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
                 const int px = 8 * p + 4 * m;
-                const uint32_t at = T.addr + (uint32_t)px * 16u;
-                if ((L.W & 3) == 0) {                          // (wave-uniform) words end at whole groups of four
-                    if (px < T.npx) {
+                if (px + 4 <= T.npx) {
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) *(lds_u32 *)(uintptr_t)(at + 16u * r) = ((D[m] << (3 - r)) & m8) | m2;
-                    }
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (px + r < T.npx) *(lds_u32 *)(uintptr_t)(at + 16u * r) = ((D[m] << (3 - r)) & m8) | m2;
+                    for (int r = 0; r < 4; ++r) *(lds_u32 *)(uintptr_t)(T.addr + 16u * (px + r)) = ((D[m] << (3 - r)) & m8) | m2;
                 }
+                if (px == (W & 28)) rest = D[m];
             }
         }
-    };
-    auto next_task = [&](Task &T) {
-        T.k += 4;
-        while (T.k >= nk) {
-            T.k -= nk;
-            ++T.cb;
+        if ((W & 3) && T.npx == (W & 31)) {
+            const uint32_t at = T.addr + 16u * (uint32_t)(W & 28);
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+                if (r < (W & 3)) *(lds_u32 *)(uintptr_t)(at + 16u * r) = ((rest << (3 - r)) & m8) | m2;
         }
     };
     // Packed channels [N][H][W][ncb]: a thread takes whole pixels of the tile, zero pixels included, two at a time.
@@ -269,7 +287,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
                 const int row = (int)fast_div((uint32_t)q, L.div_W1), col = q - row * W1 - 1;
                 const int R = R0 + row;
                 const int n = (int)fast_div((uint32_t)R, L.div_H1), hh = R - n * H1;
-                const bool ok = row < nrows && col >= 0 && hh > 0 && n < L.N;
+                const bool ok = row < nrows && col >= 0 && col < L.W && hh > 0 && n < L.N;
                 off[u] = ok ? (uint32_t)((((n - n0) * L.H + hh - 1) * L.W + col) * L.ncb + cb_first) * 4u : OFF_NONE;
                 at[u] = q < n_px ? tile_lds + (uint32_t)q * 16u : 0u;
             }
@@ -296,28 +314,41 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             }
         }
     };
-    Task task;
-    auto first_task = [&](int cb_first, int ncb) {
-        task.k = wave;
-        task.cb = 0;
-        while (task.k >= nk) {
-            task.k -= nk;
-            ++task.cb;
-        }
-        if (task.cb < ncb) load_task(task, cb_first);
+    // (of as many tasks at a time as there are in `task`)
+    auto load_tasks = [&](auto &task, int cb_first, int ncb) -> int {
+        int n = 0;
+#pragma unroll
+        for (auto &T : task)
+            if (my_cb < ncb) {
+                load_task(T, cb_first);
+                ++n;
+            }
+        return n;
     };
-    auto fill = [&](int cb_first, int ncb) {
-        while (task.cb < ncb) {
-            Task nx;
-            nx.k = task.k;
-            nx.cb = task.cb;
-            next_task(nx);
-            if (nx.cb < ncb) load_task(nx, cb_first);
-            store_task(task);
-            task = nx;
+    auto first_task = [&]() {
+        my_k = wave;
+        my_cb = 0;
+        while (my_k >= nk) {
+            my_k -= nk;
+            ++my_cb;
         }
     };
-    if constexpr (!CHANNELS) first_task(0, min(L.chunk, L.ncb));
+    auto fill = [&](auto &task, int n_tasks, int cb_first, int ncb) {
+        while (n_tasks > 0) {
+            int i = 0;
+#pragma unroll
+            for (const auto &T : task)
+                if (i++ < n_tasks) store_task(T);
+            n_tasks = load_tasks(task, cb_first, ncb);
+        }
+    };
+    Task tasks[TASKS];
+    const int here0 = min(L.chunk, L.ncb);
+    int n_tasks = 0;
+    if constexpr (!CHANNELS) {
+        first_task();
+        n_tasks = load_tasks(tasks, 0, here0);
+    }
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- weights: the words of the first pair (and of the second, where a pair is too little work to hide a load) ----
@@ -370,8 +401,6 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         top[pb] = tile_lds + (mine ? (uint32_t)((n * H1 + ho * L.stride - R0) * W1 + wo * L.stride) * 16u : 0u);
         yoff[pb] = ok ? (uint32_t)(((n - n0) * L.C_out + 4 * h) * L.HoWo + ho * L.Wo + wo) * 4u : OFF_NONE;
     }
-    const uint32_t pitch = (uint32_t)W1 * 16u;
-
     v16f acc[CB][PB];
     // (the two constants in registers: an instruction of two operations takes no literals)
     uint32_t sign_bits = 0x88888888u, one_bits = 0x22222222u;
@@ -387,29 +416,34 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         sum = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, sum, 4, 4, 0, 0, 0, 0);
     };
 
+    if constexpr (CHANNELS) fill_channels(0, here0);
+    else fill(tasks, n_tasks, 0, here0);
+    if (has_scale) {
+        *(lds_f32 *)(uintptr_t)(lds0 + (uint32_t)tid * 4u) = early_scale[0];
+        if constexpr (SIGN) *(lds_f32 *)(uintptr_t)(lds0 + 4u * CB * 32u * 4u + (uint32_t)tid * 4u) = early_scale[1];
+    }
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[cb][pb][r] = 0.0f;
     int pair = 0;                                              // of the whole layer
     for (int cb_first = 0; cb_first < L.ncb; cb_first += L.chunk) {
         const int here = min(L.chunk, L.ncb - cb_first);
         if (cb_first > 0) {
-            if constexpr (!CHANNELS) first_task(cb_first, here);
             __syncthreads();                                   // the previous blocks are no longer read
-        }
-        if constexpr (CHANNELS) fill_channels(cb_first, here);
-        else fill(cb_first, here);
-        if (cb_first == 0 && has_scale) {
-            *(lds_f32 *)(uintptr_t)(lds0 + (uint32_t)tid * 4u) = early_scale[0];
-            if constexpr (SIGN) *(lds_f32 *)(uintptr_t)(lds0 + 4u * CB * 32u * 4u + (uint32_t)tid * 4u) = early_scale[1];
+            if constexpr (CHANNELS) {
+                fill_channels(cb_first, here);
+            } else {                                           // (beside the accumulators there are registers for one task)
+                Task one[1];
+                first_task();
+                const int n = load_tasks(one, cb_first, here);
+                fill(one, n, cb_first, here);
+            }
         }
         __syncthreads();
         if (!active) continue;
-        if (cb_first == 0) {
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[cb][pb][r] = 0.0f;
-        }
         // (opaque here: the addresses made of it would be kept in registers through the fill)
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) asm volatile("" : "+v"(top[pb]));
@@ -620,7 +654,8 @@ struct RfManyLayer {
     const uint32_t *wq;                  // the scales lie behind it
     void *y;
     int N, C_in, C_out, H, W, Ho, Wo;
-    int chunk, plane, n_cotiles, n_wgs;
+    int plane, n_cotiles, n_wgs;
+    uint16_t chunk, pitch;               // (at most 128; rows fit LDS)
     uint8_t PB, CB, wpx_shift, stride;
     Divisor div_HoWo, div_Wo, div_H1, div_WW, div_cotiles;
 };
@@ -666,13 +701,13 @@ void rows_fp4_many_kernel(const RfMany m)
     L.out = c.y;
     L.N = c.N; L.C_in = c.C_in; L.C_out = c.C_out; L.H = c.H; L.W = c.W; L.WW = (c.W + 31) >> 5; L.stride = c.stride;
     L.Ho = c.Ho; L.Wo = c.Wo; L.HoWo = c.Ho * c.Wo; L.P = c.N * L.HoWo;
-    L.n_cob = (c.C_out + 31) >> 5; L.ncb = (c.C_in + 31) >> 5; L.chunk = c.chunk; L.pairs = (L.ncb + 1) >> 1; L.plane = c.plane;
+    L.n_cob = (c.C_out + 31) >> 5; L.ncb = (c.C_in + 31) >> 5; L.chunk = c.chunk; L.pairs = (L.ncb + 1) >> 1; L.pitch = c.pitch; L.plane = c.plane;
     L.n_blk = (L.P + 31) >> 5; L.n_cotiles = c.n_cotiles; L.n_wgs = c.n_wgs; L.wpx_shift = c.wpx_shift;
     L.div_HoWo = c.div_HoWo; L.div_Wo = c.div_Wo; L.div_H1 = c.div_H1; L.div_WW = c.div_WW; L.div_cotiles = c.div_cotiles;
     switch (10 * c.PB + c.CB) {
-    case 22: rf_tile<2, 2, false>(L, wg, smem); break;
-    case 21: rf_tile<2, 1, false>(L, wg, smem); break;
-    default: rf_tile<1, 1, false>(L, wg, smem); break;
+    case 22: rf_tile<2, 2, false, false, 2>(L, wg, smem); break;
+    case 21: rf_tile<2, 1, false, false, 2>(L, wg, smem); break;
+    default: rf_tile<1, 1, false, false, 2>(L, wg, smem); break;
     }
 }
 
@@ -958,12 +993,14 @@ struct RfPlan {
     int rows_pb, bpi, wpr;
     int64_t rows;                // padded input rows a workgroup touches at most
     int64_t plane;
+    int pitch;
     size_t lds;
     bool ok;
 };
 
 constexpr size_t RF_LDS_TARGET = 72 * 1024;      // two workgroups per compute unit
 constexpr size_t RF_LDS_MAX = 150 * 1024;
+constexpr size_t RF_LDS_CU = 160 * 1024;
 
 size_t rf_weight_bytes(const Geom &g) { return rf_weight_bytes(g.C_out, g.C_in); }
 
@@ -1001,17 +1038,24 @@ RfPlan rf_plan(const Geom &g, bool sign, bool many = false)
         }
         int64_t rows = g.stride * row_changes + image_changes + 3;
         if (rows > (int64_t)g.N * (g.H + 1) + 1) rows = (int64_t)g.N * (g.H + 1) + 1;
-        const int64_t plane = (rows * (g.W + 1) + 1) * 16;
         const size_t fixed = (size_t)4 * t.CB * 32 * (sign ? 8 : 4);
-        int chunk = pl.ncb;
-        while (chunk > 2 && fixed + (size_t)chunk * plane > RF_LDS_TARGET) chunk = ((chunk + 1) / 2 + 1) & ~1;
-        if (fixed + (size_t)chunk * plane > RF_LDS_MAX) continue;
+        auto plane_of = [&](int pitch) { return (rows * pitch + 1) * 16; };
+        int chunk = pl.ncb, pitch = g.W + 1;
+        while (chunk > 2 && fixed + (size_t)chunk * plane_of(pitch) > RF_LDS_TARGET) chunk = ((chunk + 1) / 2 + 1) & ~1;
+        if (fixed + (size_t)chunk * plane_of(pitch) > RF_LDS_MAX) continue;
+        // Of an odd pitch the sixteen rows whose pixels a wave writes at a time lie on different banks of LDS (at 8 or 16 pixels they
+        // are on two groups of them or one, 16 clocks per write instruction for 3): taken where it leaves as many workgroups beside
+        // each other, up to the three that the registers allow.
+        auto resident = [&](int p) { return std::min<int64_t>(3, (int64_t)RF_LDS_CU / (int64_t)(fixed + (size_t)chunk * plane_of(p))); };
+        if (pitch % 2 == 0 && resident(pitch + 1) == resident(pitch)) ++pitch;
+        const int64_t plane = plane_of(pitch);
         pl.PB = PB;
         pl.CB = t.CB;
         pl.wpx_shift = wpx_shift;
         pl.n_cotiles = n_cotiles;
         pl.rows = rows;
         pl.plane = plane;
+        pl.pitch = pitch;
         pl.chunk = chunk;
         pl.lds = fixed + (size_t)chunk * plane;
         pl.n_wgs = wgs;
@@ -1038,7 +1082,7 @@ RfLayer rf_layer(const RfPlan &pl, const Geom &g, const void *x, void *out, void
     L.out = out;
     L.N = g.N; L.C_in = g.C_in; L.C_out = g.C_out; L.H = g.H; L.W = g.W; L.WW = g.WW; L.stride = g.stride;
     L.Ho = g.Ho; L.Wo = g.Wo; L.HoWo = g.HoWo; L.P = (int)g.P;
-    L.n_cob = pl.n_cob; L.ncb = pl.ncb; L.chunk = pl.chunk; L.pairs = (pl.ncb + 1) / 2; L.plane = (int)pl.plane;
+    L.n_cob = pl.n_cob; L.ncb = pl.ncb; L.chunk = pl.chunk; L.pairs = (pl.ncb + 1) / 2; L.pitch = pl.pitch; L.plane = (int)pl.plane;
     L.n_blk = (int)pl.n_blk; L.n_cotiles = (int)pl.n_cotiles; L.n_wgs = (int)pl.n_wgs;
     L.wpx_shift = pl.wpx_shift;
     L.rows_pb = pl.rows_pb; L.bpi = pl.bpi; L.wpr = pl.wpr;
@@ -1050,7 +1094,7 @@ RfLayer rf_layer(const RfPlan &pl, const Geom &g, const void *x, void *out, void
     L.div_bpi = make_divisor((uint32_t)pl.bpi);
     L.div_wpr = make_divisor((uint32_t)pl.wpr);
     L.div_Ho = make_divisor((uint32_t)g.Ho);
-    L.div_W1 = make_divisor((uint32_t)g.W + 1u);
+    L.div_W1 = make_divisor((uint32_t)pl.pitch);
     return L;
 }
 
@@ -1311,7 +1355,7 @@ int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, flo
             const int64_t here = (pl.n_wgs + 7) / 8 * 8;
             if (blocks + here > 0x7fffffffLL) break;
             const RfLayer L = rf_layer(pl, gs[l], x[l], y[l], ws[l]);
-            m.layer[n] = {L.x, L.wq, L.out, L.N, L.C_in, L.C_out, L.H, L.W, L.Ho, L.Wo, L.chunk, L.plane, L.n_cotiles, L.n_wgs,
+            m.layer[n] = {L.x, L.wq, L.out, L.N, L.C_in, L.C_out, L.H, L.W, L.Ho, L.Wo, L.plane, L.n_cotiles, L.n_wgs, (uint16_t)L.chunk, (uint16_t)L.pitch,
                           (uint8_t)pl.PB, (uint8_t)pl.CB, (uint8_t)pl.wpx_shift, (uint8_t)gs[l].stride,
                           L.div_HoWo, L.div_Wo, L.div_H1, L.div_WW, L.div_cotiles};
             m.first[n] = (int)blocks;

@@ -64,7 +64,7 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t by
 struct RfLayer {
     const uint32_t *x;       // packed rows [N][C_in][H][WW]
     const uint32_t *wq;      // weights in operand layout
-    const float *scale;      // [2][32 n_cob]: alpha, then beta (sign epilogue), 0 for padding channels
+    const float *scale;      // [2][32 n_cob]: alpha, 0 for padding channels; before the sign epilogue what sign_entry gives
     void *out;               // float y, or packed rows of the signs
     int N, C_in, C_out, H, W, WW, stride;
     int Ho, Wo, HoWo, P;
@@ -422,12 +422,15 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         *(lds_f32 *)(uintptr_t)(lds0 + (uint32_t)tid * 4u) = early_scale[0];
         if constexpr (SIGN) *(lds_f32 *)(uintptr_t)(lds0 + 4u * CB * 32u * 4u + (uint32_t)tid * 4u) = early_scale[1];
     }
+    if constexpr (!SIGN) {
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb)
+            for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[cb][pb][r] = 0.0f;
+                for (int r = 0; r < 16; ++r) acc[cb][pb][r] = 0.0f;
+    }
+    const uint32_t scale_lane = lds0 + (uint32_t)(wco * CB * 32 + 4 * h) * 4u;
     int pair = 0;                                              // of the whole layer
     for (int cb_first = 0; cb_first < L.ncb; cb_first += L.chunk) {
         const int here = min(L.chunk, L.ncb - cb_first);
@@ -444,6 +447,20 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         }
         __syncthreads();
         if (!active) continue;
+        if constexpr (SIGN) {
+            if (cb_first == 0) {
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 c0 = *(lds_cf32x4 *)(uintptr_t)(scale_lane + (uint32_t)(cb * 32 + 8 * q) * 4u);
+#pragma unroll
+                        for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) acc[cb][pb][4 * q + i] = c0[i];
+                    }
+            }
+        }
         // (opaque here: the addresses made of it would be kept in registers through the fill)
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) asm volatile("" : "+v"(top[pb]));
@@ -551,22 +568,60 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     }
     if (!active) return;
 
-    const uint32_t scale_lane = lds0 + (uint32_t)(wco * CB * 32 + 4 * h) * 4u;
     if constexpr (SIGN) {
         // ---- the next layer's sign: bit = (fl(fl(S alpha) + beta) >= 0), packed rows ---------------------------------
-        // The 32 lanes of a half hold the pixels of one block of one channel: a ballot turns their signs into a bit
-        // string that holds the block's words of that channel.  Accumulator register r is channels cl and cl + 4, in
-        // the low and the high half of the ballot.
+        // The accumulators began at the channel's threshold (sign_entry): a bit is a sign bit.  A lane collects those of its pixel,
+        // sixteen channels of a block, two blocks to a word, one instruction each; a transposition of 32 x 32 bits over the
+        // lanes of a half (fifteen instructions) gives each lane the word of a channel.  (The two roundings, a ballot and its two words
+        // written to lanes were five instructions per register, 1.2 to 2.1 us of a layer's 8 to 13: 1-bit chain of ResNet-18 batch 64
+        // 148 us, now 132.)
         uint32_t *const out = (uint32_t *)L.out;
         const int WWo = (L.Wo + 31) / 32;
         const uint32_t oplane = (uint32_t)(L.Ho * WWo);
         const bool short_rows = L.Wo <= 32;
-        const int wpb = short_rows ? L.rows_pb : 1;            // words of one channel in a block
-        const uint32_t wmask = L.Wo < 32 ? (1u << L.Wo) - 1u : 0xffffffffu;
+        const uint32_t sel16 = lane & 16 ? 0x07060302u : 0x05040100u, sel8 = lane & 8 ? 0x03070105u : 0x06020400u;
+        const uint32_t keep4 = lane & 4 ? 0xf0f0f0f0u : 0x0f0f0f0fu, keep2 = lane & 2 ? 0xccccccccu : 0x33333333u,
+                       keep1 = lane & 1 ? 0xaaaaaaaau : 0x55555555u;
+        const uint32_t turn4 = lane & 4 ? 4u : 28u, turn2 = lane & 2 ? 2u : 30u, turn1 = lane & 1 ? 1u : 31u;
+        auto stage = [](uint32_t x, uint32_t y, uint32_t keep, uint32_t turn) {
+            const uint32_t r = __builtin_amdgcn_alignbit(y, y, turn);
+            return (x & keep) | (r & ~keep);
+        };
+        auto transpose = [&](uint32_t x) {                     // bit p of lane l: bit l of lane p
+            const auto swapped = __builtin_amdgcn_permlane16_swap(x, x, false, false);       // lanes 0..15 twice, lanes 16..31 twice
+            x = __builtin_amdgcn_perm(swapped[1], swapped[0], sel16);
+            uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128 /* row_ror:8 */, 0xF, 0xF, true);
+            x = __builtin_amdgcn_perm(y, x, sel8);
+            y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141 /* row_half_mirror */, 0xF, 0xF, true);
+            y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)y, 0x1B /* quad_perm [3,2,1,0] */, 0xF, 0xF, true);
+            x = stage(x, y, keep4, turn4);
+            y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E /* quad_perm [2,3,0,1] */, 0xF, 0xF, true);
+            x = stage(x, y, keep2, turn2);
+            y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, true);
+            return stage(x, y, keep1, turn1);
+        };
+        // lane l of a half: sixteen bits further up come first
+        const int late = n_l < 16, r = 15 - (n_l & 15);        // of the two blocks of sixteen registers: which, register
+        const int chan = 8 * (r >> 2) + 4 * h + (r & 3);
+        const int cb_of = CB == 2 ? late : 0;
+        const int co = (cob0 + cb_of) * 32 + chan;
+        const uint32_t flip = *(lds_u32 *)(uintptr_t)(lds0 + (uint32_t)(4 * CB * 32 + (wco * CB + cb_of) * 32 + chan) * 4u);
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb) {
-            const int Bk = blk0 + pb;
-            if (Bk >= L.n_blk) continue;                       // (wave-uniform)
+        for (int u = 0; u < (CB == 2 ? PB : (PB + 1) / 2); ++u) {
+            uint32_t bits = 0;
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                if (CB == 1 && 2 * u + v >= PB) {
+                    bits <<= 16;
+                    break;
+                }
+                const v16f &a = CB == 2 ? acc[v][u] : acc[0][2 * u + v];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(a[i]), 31);
+            }
+            bits = transpose(bits) ^ flip;
+            const int Bk = blk0 + (CB == 2 ? u : 2 * u + late);
+            if (Bk >= L.n_blk || (CB == 1 && 2 * u + late >= PB) || co >= L.C_out) continue;
             int bn, bword, bwords;                             // image, first word in a channel plane, words
             if (short_rows) {
                 bn = (int)fast_div((uint32_t)Bk, L.div_bpi);
@@ -575,37 +630,17 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             } else {
                 const int R = (int)fast_div((uint32_t)Bk, L.div_wpr);
                 bn = (int)fast_div((uint32_t)R, L.div_Ho);
-                bword = (R - bn * L.Ho) * WWo + (Bk - R * L.wpr);
+                const int word = Bk - R * L.wpr;
+                bword = (R - bn * L.Ho) * WWo + word;
                 bwords = 1;
+                if (32 * (word + 1) > L.Wo) bits &= (1u << (L.Wo & 31)) - 1u;
             }
-            const unsigned long long okm = __ballot(yoff[pb] != OFF_NONE);
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-                if (cob0 + cb >= L.n_cob) continue;            // (wave-uniform)
-                uint32_t bits = 0;                             // lane c (and c + 32): the 32 signs of channel c of the block
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 al = *(lds_cf32x4 *)(uintptr_t)(scale_lane + (uint32_t)(cb * 32 + 8 * q) * 4u);
-                    const f32x4 be = *(lds_cf32x4 *)(uintptr_t)(scale_lane + (uint32_t)(4 * CB * 32 + cb * 32 + 8 * q) * 4u);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int r = 4 * q + i, cl = 8 * q + i;
-                        const unsigned long long m = __ballot(mul_then_add(acc[cb][pb][r], al[i], be[i]) >= 0.0f) & okm;
-                        const uint32_t m_lo = (uint32_t)m, m_hi = (uint32_t)(m >> 32);          // wave-uniform
-                        asm("v_writelane_b32 %0, %1, %2" : "+v"(bits) : "s"(m_lo), "n"(cl));
-                        asm("v_writelane_b32 %0, %1, %2" : "+v"(bits) : "s"(m_hi), "n"(cl + 4));
-                    }
-                }
-                const int co = (cob0 + cb) * 32 + n_l;         // the channel whose words this lane stores
-                uint32_t *const dst = out + (int64_t)(bn * L.C_out + co) * oplane + bword;
-                if (wpb == 1) {
-                    if (h == 0 && co < L.C_out) dst[0] = bits;
-                    continue;
-                }
-                // several words per channel and block (rows of up to 16 pixels): the lane halves store alternate words
-                const uint32_t mine = (uint32_t)__shfl((int)bits, n_l);
-                for (int j = h; j < bwords; j += 2)
-                    if (co < L.C_out) dst[j] = (mine >> (uint32_t)(j * L.Wo)) & wmask;
+            uint32_t *const dst = out + (int64_t)(bn * L.C_out + co) * oplane + bword;
+            if (!short_rows || L.Wo == 32) {
+                dst[0] = bits;
+            } else {
+                const uint32_t wmask = (1u << L.Wo) - 1u;
+                for (int j = 0; j < bwords; ++j, bits >>= L.Wo) dst[j] = bits & wmask;
             }
         }
         return;
@@ -745,11 +780,30 @@ struct RfWeights {
     int C_in, C_out, n_cob, ncb;
 };
 
+// The next layer's sign, fl(fl(S a) + b) >= 0, of the sums S in [-9 C_in, 9 C_in]: monotone in S, so it is a threshold.  Returns the
+// accumulator's start, 0.5 - (first sum on the upper side), whose sum with S is never zero and exact, and what the word of
+// its sign bits is turned by: the upper side is 1 (a > 0, all ones) or 0 (a < 0).
+__device__ inline float2 sign_entry(float a, float b, int C_in)
+{
+    auto bit = [&](int S) { return mul_then_add((float)S, a, b) >= 0.0f; };
+    if (!(a > 0.0f || a < 0.0f)) return make_float2(-1.0e9f, __uint_as_float(bit(0) ? 0u : 0xffffffffu));      // one bit for every S
+    int lo = -9 * C_in, hi = 9 * C_in + 1;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (bit(mid) == (a > 0.0f)) hi = mid;
+        else lo = mid + 1;
+    }
+    return make_float2(0.5f - (float)lo, __uint_as_float(a > 0.0f ? 0xffffffffu : 0u));
+}
+
 __device__ __forceinline__ void store_scales(const RfWeights &W, int cob, int c, const float *alpha, const float *beta)
 {
     const int co = cob * 32 + c;
-    W.scale[co] = co < W.C_out ? alpha[co] : 0.0f;
-    W.scale[32 * W.n_cob + co] = beta && co < W.C_out ? beta[co] : 0.0f;
+    const bool real = co < W.C_out;
+    const float a = real ? alpha[co] : 0.0f;
+    const float2 e = beta ? sign_entry(a, real ? beta[co] : 0.0f, W.C_in) : make_float2(a, 0.0f);
+    W.scale[co] = e.x;
+    W.scale[32 * W.n_cob + co] = e.y;
 }
 
 // From indices (uint16, or tau bits each in a stream): 256 threads = 2 channel blocks x 32 output channels x 4 groups of 8

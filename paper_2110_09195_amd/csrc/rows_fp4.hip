@@ -49,6 +49,7 @@ typedef __attribute__((address_space(3))) const u32x4 lds_cu32x4;
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef __attribute__((address_space(3))) float lds_f32;
+typedef __attribute__((address_space(3))) uint16_t lds_u16;
 typedef __attribute__((address_space(3))) const f32x4 lds_cf32x4;
 
 // words of a pair of channel blocks and 32 output channels: [lane] 16 bytes (taps 0..3), [lane] 16 bytes (4..7), [lane] 4 (8)
@@ -80,6 +81,8 @@ struct RfLayer {
     int rows_pb, bpi, wpr;   // sign epilogue: rows per block, blocks per image, blocks per row
     Divisor div_HoWo, div_Wo, div_H1, div_WW, div_cotiles, div_bpi, div_wpr, div_Ho;
     Divisor div_W1;          // packed channels
+    const uint16_t *codebook, *idx;      // INDEXED
+    int K;
 };
 
 // byte p of the four words -> o[p]
@@ -93,12 +96,65 @@ __device__ __forceinline__ void bytes4(uint32_t a, uint32_t b, uint32_t c, uint3
     o[3] = __builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u);
 }
 
+// ---- weights -> operand layout, device side ----------------------------------------------------------------------
+// Codes of up to 8 consecutive channels as three words of nibbles (nibble j: bits 0..3 of channel j's code in `lo`, 4..7 in
+// `mid`, bit 8 in `hi`) -> bits 4 j: tap t of channel j (code bit 8 - t).
+__device__ __forceinline__ uint32_t tap_bits(uint32_t lo, uint32_t mid, uint32_t hi, int t)
+{
+    const int bit = 8 - t;
+    return ((bit == 8 ? hi : bit >= 4 ? mid : lo) >> (bit & 3)) & 0x11111111u;
+}
+
+// Stores the words of (channel co of a block of 32 output channels, input channel block cb) in their pair's RF_PAIR_BYTES (in memory or
+// in LDS): w[t] for tap t.
+template <class Put16, class Put4>
+__device__ __forceinline__ void put_words(Put16 &&put16, Put4 &&put4, int co, int cb, int ncb, const uint32_t (&w)[9])
+{
+    if ((ncb & 1) && cb == ncb - 1) {
+        // the last block of an odd number: word u of lane half h is tap 2 u + h
+        put16(co * 16, (u32x4){w[0], w[2], w[4], w[6]});
+        put16((co + 32) * 16, (u32x4){w[1], w[3], w[5], w[7]});
+        put4(1024 + co * 16, w[8]);
+        put4(1024 + (co + 32) * 16, 0u);
+        return;
+    }
+    const int lane = co + 32 * (cb & 1);
+    put16(lane * 16, (u32x4){w[0], w[1], w[2], w[3]});
+    put16(1024 + lane * 16, (u32x4){w[4], w[5], w[6], w[7]});
+    put4(2048 + lane * 4, w[8]);
+}
+
+__device__ __forceinline__ void store_words(uint32_t *wq, int cob, int co, int cb, int ncb, const uint32_t (&w)[9])
+{
+    unsigned char *const at = (unsigned char *)wq + (int64_t)(cob * ((ncb + 1) >> 1) + (cb >> 1)) * RF_PAIR_BYTES;
+    put_words([&](int o, u32x4 v) { *(u32x4 *)(at + o) = v; }, [&](int o, uint32_t v) { *(uint32_t *)(at + o) = v; }, co, cb, ncb, w);
+}
+
+// The words of eight codes per lane, four lanes side by side (d = lane % 4: channels 8 d .. 8 d + 7 of a block), valid in all four.
+__device__ __forceinline__ void words_of_codes(const uint32_t (&code)[8], int d, uint32_t (&w)[9])
+{
+    uint32_t lo = 0, mid = 0, hi = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        lo |= (code[j] & 15u) << (4 * j);
+        mid |= ((code[j] >> 4) & 15u) << (4 * j);
+        hi |= (code[j] >> 8) << (4 * j);
+    }
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        w[t] = tap_bits(lo, mid, hi, t) << d;
+        w[t] |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[t], 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, true);
+        w[t] |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[t], 0x4E /* quad_perm [2,3,0,1] */, 0xF, 0xF, true);
+    }
+}
+
 // ---- the convolution ----------------------------------------------------------------------------------------
 // A workgroup of four waves: 2^wpx_shift of them side by side along pixels, the others on further output channels of
 // the same pixels.  A wave owns PB blocks of 32 pixels x CB blocks of 32 output channels.  Pixel blocks: 32 consecutive
 // pixels of the flattened (n, ho, wo) order; for the sign epilogue whole output words (whole rows while they fit 32
 // pixels, else one word of a row), so that the wave that owns a block owns the words it writes.
-template <int PB, int CB, bool SIGN, bool CHANNELS = false, int TASKS = 4>
+// INDEXED: the weight words are made here, from codebook and indices, and kept in LDS behind the expanded pixels.
+template <int PB, int CB, bool SIGN, bool CHANNELS = false, int TASKS = 4, bool INDEXED = false>
 __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned char *const smem)
 {
     const int tid = threadIdx.x;
@@ -352,10 +408,22 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- weights: the words of the first pair (and of the second, where a pair is too little work to hide a load) ----
+    const uint32_t words_lds = tile_lds + (uint32_t)L.ncb * plane;          // (INDEXED: all channel blocks are expanded at once)
     const __amdgpu_buffer_rsrc_t wres = make_rsrc(L.wq, (uint32_t)(L.n_cob * L.pairs) * RF_PAIR_BYTES);
     constexpr bool AHEAD = PB * CB == 2;
     uint32_t A[CB][9], An[AHEAD ? CB : 1][9];
     auto load_words = [&](int pr, int cb, int piece, uint32_t (&a)[9]) {       // (past the last pair or block: the last one, not used)
+        if constexpr (INDEXED) {
+            const uint32_t at = words_lds + (uint32_t)((wco * CB + cb) * L.pairs + min(pr, L.pairs - 1)) * RF_PAIR_BYTES;
+            if (piece < 2) {
+                const u32x4 v = *(lds_cu32x4 *)(uintptr_t)(at + 1024u * piece + (uint32_t)lane * 16u);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a[4 * piece + i] = v[i];
+            } else {
+                a[8] = *(lds_u32 *)(uintptr_t)(at + 2048u + (uint32_t)lane * 4u);
+            }
+            return;
+        }
         const uint32_t at = (uint32_t)(min(cob0 + cb, L.n_cob - 1) * L.pairs + min(pr, L.pairs - 1)) * RF_PAIR_BYTES;
         if (piece < 2) {
             const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(wres, lane * 16, (int)(at + 1024u * piece), 0);
@@ -365,7 +433,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             a[8] = __builtin_amdgcn_raw_buffer_load_b32(wres, lane * 4, (int)(at + 2048u), 0);
         }
     };
-    if (active) {
+    auto first_words = [&]() {
 #pragma unroll
         for (int piece = 0; piece < 3; ++piece)
 #pragma unroll
@@ -376,14 +444,53 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) load_words(1, cb, piece, An[cb]);
         }
+    };
+    if constexpr (INDEXED) {
+        // as rows_fp4_prep_kernel: a pass of the 256 threads is 32 output channels x a pair of channel blocks
+        const uint32_t codes_lds = words_lds + (uint32_t)((CB << (2 - L.wpx_shift)) * L.pairs) * RF_PAIR_BYTES;
+        const __amdgpu_buffer_rsrc_t ires = make_rsrc(L.idx, (uint32_t)(L.C_out * L.C_in) * 2u);
+        const int d = tid & 3, co = (tid >> 2) & 31, first_cob = (cot << (2 - L.wpx_shift)) * CB;
+        const int n_pass = min(CB << (2 - L.wpx_shift), L.n_cob - first_cob) * L.pairs;
+        int c = 0, pr = 0;                                     // block of output channels (of the workgroup's), pair, of the next load
+        auto load_idx = [&](uint32_t (&k)[8]) {                // (past the last one: of no use)
+            const int oc = (first_cob + c) * 32 + co, c0 = (2 * pr + (tid >> 7)) * 32 + d * 8;
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                k[j] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(
+                    ires, (int)(oc < L.C_out && c0 + j < L.C_in ? (uint32_t)(oc * L.C_in + c0 + j) * 2u : OFF_NONE), 0, 0);
+            if (++pr == L.pairs) {
+                pr = 0;
+                ++c;
+            }
+        };
+        uint32_t k[8], kn[8];
+        load_idx(k);
+        for (int i = tid; i < L.K; i += 256) *(lds_u16 *)(uintptr_t)(codes_lds + 2u * (uint32_t)i) = L.codebook[i] & 511u;
+        __syncthreads();
+        for (int i = 0; i < n_pass; ++i) {
+            const int cb = 2 * (i % L.pairs) + (tid >> 7);
+            load_idx(kn);
+            uint32_t code[8], w[9];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) code[j] = *(lds_u16 *)(uintptr_t)(codes_lds + 2u * min(k[j], (uint32_t)L.K - 1u));
+            words_of_codes(code, d, w);
+            const uint32_t at = words_lds + (uint32_t)i * RF_PAIR_BYTES;
+            if (d == 0 && cb < L.ncb)
+                put_words([&](int o, u32x4 v) { *(lds_u32x4 *)(uintptr_t)(at + (uint32_t)o) = v; },
+                          [&](int o, uint32_t v) { *(lds_u32 *)(uintptr_t)(at + (uint32_t)o) = v; }, co, cb, L.ncb, w);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) k[j] = kn[j];
+        }
+    } else {
+        if (active) first_words();
     }
     // scales of the workgroup's channels (4 CB blocks at most)
     float early_scale[2] = {0.0f, 0.0f};
     const int scale_first = (cot << (2 - L.wpx_shift)) * CB * 32;
     const bool has_scale = tid < (CB * 32 << (2 - L.wpx_shift)) && scale_first + tid < 32 * L.n_cob;
     {
-        // (the 1-bit layer's are its alpha itself: channels past C_out lie beyond the buffer and read 0)
-        const __amdgpu_buffer_rsrc_t sres = make_rsrc(L.scale, CHANNELS ? (uint32_t)L.C_out * 4u : (uint32_t)L.n_cob * 256u);
+        // (the 1-bit layer's, and of a layer given as indices, are alpha itself: channels past C_out lie beyond the buffer and read 0)
+        const __amdgpu_buffer_rsrc_t sres = make_rsrc(L.scale, CHANNELS || INDEXED ? (uint32_t)L.C_out * 4u : (uint32_t)L.n_cob * 256u);
         const uint32_t off = has_scale ? (uint32_t)(scale_first + tid) * 4u : OFF_NONE;
         early_scale[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sres, (int)off, 0, 0));
         if constexpr (SIGN) early_scale[1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sres, (int)off, (int)((uint32_t)L.n_cob * 128u), 0));
@@ -447,6 +554,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         }
         __syncthreads();
         if (!active) continue;
+        if constexpr (INDEXED) first_words();
         if constexpr (SIGN) {
             if (cb_first == 0) {
 #pragma unroll
@@ -693,12 +801,12 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     }
 }
 
-template <int PB, int CB, bool SIGN, bool CHANNELS>
+template <int PB, int CB, bool SIGN, bool CHANNELS, bool INDEXED>
 __global__ __launch_bounds__(256, PB == 4 ? 2 : PB * CB == 4 ? 3 : 4)
 void rows_fp4_kernel(const RfLayer L)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    rf_tile<PB, CB, SIGN, CHANNELS>(L, blockIdx.x, smem);
+    rf_tile<PB, CB, SIGN, CHANNELS, 4, INDEXED>(L, blockIdx.x, smem);
 }
 
 // Several layers in one launch (fp32 output): workgroups [first[l], first[l + 1]) run layer l.  The layers share the
@@ -769,33 +877,6 @@ void rows_fp4_many_kernel(const RfMany m)
 }
 
 // ---- weights -> operand layout ---------------------------------------------------------------------------------------
-// Codes of up to 8 consecutive channels as three words of nibbles (nibble j: bits 0..3 of channel j's code in `lo`, 4..7 in
-// `mid`, bit 8 in `hi`) -> bits 4 j: tap t of channel j (code bit 8 - t).
-__device__ __forceinline__ uint32_t tap_bits(uint32_t lo, uint32_t mid, uint32_t hi, int t)
-{
-    const int bit = 8 - t;
-    return ((bit == 8 ? hi : bit >= 4 ? mid : lo) >> (bit & 3)) & 0x11111111u;
-}
-
-// Stores the words of (block of 32 output channels, channel co in it, input channel block cb): w[t] for tap t.
-__device__ __forceinline__ void store_words(uint32_t *wq, int cob, int co, int cb, int ncb, const uint32_t (&w)[9])
-{
-    const int pairs = (ncb + 1) >> 1;
-    unsigned char *const at = (unsigned char *)wq + (int64_t)(cob * pairs + (cb >> 1)) * RF_PAIR_BYTES;
-    if ((ncb & 1) && cb == ncb - 1) {
-        // the last block of an odd number: word u of lane half h is tap 2 u + h
-        *(u32x4 *)(at + co * 16) = (u32x4){w[0], w[2], w[4], w[6]};
-        *(u32x4 *)(at + (co + 32) * 16) = (u32x4){w[1], w[3], w[5], w[7]};
-        *(uint32_t *)(at + 1024 + co * 16) = w[8];
-        *(uint32_t *)(at + 1024 + (co + 32) * 16) = 0u;
-        return;
-    }
-    const int lane = co + 32 * (cb & 1);
-    *(u32x4 *)(at + lane * 16) = (u32x4){w[0], w[1], w[2], w[3]};
-    *(u32x4 *)(at + 1024 + lane * 16) = (u32x4){w[4], w[5], w[6], w[7]};
-    *(uint32_t *)(at + 2048 + lane * 4) = w[8];
-}
-
 struct RfWeights {
     uint32_t *wq;
     float *scale;
@@ -846,21 +927,10 @@ void rows_fp4_prep_kernel(const RfWeights W, const uint16_t *__restrict__ codebo
     __syncthreads();
     if (blockIdx.y == 0 && tid < 32) store_scales(W, cob, tid, alpha, beta);
     if (cb >= W.ncb) return;
-    uint32_t lo = 0, mid = 0, hi = 0;
+    uint32_t code[8], w[9];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint32_t c = codes[min(k[j], (uint32_t)K - 1u)];
-        lo |= (c & 15u) << (4 * j);
-        mid |= ((c >> 4) & 15u) << (4 * j);
-        hi |= (c >> 8) << (4 * j);
-    }
-    uint32_t w[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-        w[t] = tap_bits(lo, mid, hi, t) << d;
-        w[t] |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[t], 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, true);
-        w[t] |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[t], 0x4E /* quad_perm [2,3,0,1] */, 0xF, 0xF, true);
-    }
+    for (int j = 0; j < 8; ++j) code[j] = codes[min(k[j], (uint32_t)K - 1u)];
+    words_of_codes(code, d, w);
     if (d == 0) store_words(W.wq, cob, co, cb, W.ncb, w);
 }
 
@@ -1151,7 +1221,7 @@ RfPlan rf_plan(const Geom &g, bool sign, bool many = false)
 
 RfLayer rf_layer(const RfPlan &pl, const Geom &g, const void *x, void *out, void *ws)
 {
-    RfLayer L;
+    RfLayer L = {};
     L.x = (const uint32_t *)x;
     L.wq = (const uint32_t *)ws;
     L.scale = (const float *)((char *)ws + rf_weight_bytes(g));
@@ -1186,10 +1256,10 @@ RfWeights rf_weights(const Geom &g, void *ws)
     return W;
 }
 
-template <int PB, int CB, bool SIGN, bool CHANNELS>
+template <int PB, int CB, bool SIGN, bool CHANNELS, bool INDEXED = false>
 int launch_rf_one(const RfPlan &pl, const RfLayer &L, hipStream_t s)
 {
-    auto kern = rows_fp4_kernel<PB, CB, SIGN, CHANNELS>;
+    auto kern = rows_fp4_kernel<PB, CB, SIGN, CHANNELS, INDEXED>;
     static LdsGrant grant;
     if (grant_dynamic_lds((const void *)kern, pl.lds, grant) != SNN_OK) return SNN_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)pl.n_wgs), dim3(256), pl.lds, s, L);
@@ -1205,6 +1275,31 @@ int launch_rf(const RfPlan &pl, const RfLayer &L, hipStream_t s)
     }
     if (pl.PB == 2) return launch_rf_one<2, 1, SIGN, CHANNELS>(pl, L, s);
     return launch_rf_one<1, 1, SIGN, CHANNELS>(pl, L, s);
+}
+
+// One launch for a layer whose weights come as indices: every workgroup makes the words it needs, in passes of 32 output channels x 64
+// input channels of about 0.75 us each.  Against a launch of its own (two launches -> one, us per call, K = 32): one pass 16 -> 16
+// 32x32 batch 8 (64 workgroups) 8.9 -> 6.4, batch 128 (512) 8.9 -> 7.4, 32 -> 32 16x16 batch 128 8.7 -> 6.2; two passes 64 -> 64 8x8
+// batch 32 8.8 -> 7.4, 128 -> 32 28x28 batch 32 (98) 8.9 -> 7.8, batch 64 (196) 9.3 -> 10.2, 64 -> 64 56x56 batch 32 (784) 11.6 ->
+// 12.6; four passes 64 -> 128 28x28 stride 2 batch 8 8.8 -> 9.7; eight 100 -> 150 37x53 stride 2 batch 12 9.9 -> 13.1.
+bool rf_indexed(const RfPlan &pl, const Geom &g, size_t &lds)
+{
+    const int64_t passes = (int64_t)(pl.CB << (2 - pl.wpx_shift)) * ((pl.ncb + 1) / 2);
+    lds = pl.lds + (size_t)passes * RF_PAIR_BYTES + align_up((size_t)g.K * 2, 16);
+    return pl.PB <= 2 && pl.chunk == pl.ncb && pl.n_wgs <= (passes == 1 ? 512 : passes == 2 ? 128 : 0) && lds <= RF_LDS_TARGET;
+}
+
+int launch_rf_indexed(RfPlan pl, RfLayer L, const Geom &g, const uint16_t *codebook, const uint16_t *idx, const float *alpha, size_t lds,
+                      hipStream_t s)
+{
+    L.scale = alpha;
+    L.codebook = codebook;
+    L.idx = idx;
+    L.K = g.K;
+    pl.lds = lds;
+    if (pl.CB == 2) return launch_rf_one<2, 2, false, false, true>(pl, L, s);
+    if (pl.PB == 2) return launch_rf_one<2, 1, false, false, true>(pl, L, s);
+    return launch_rf_one<1, 1, false, false, true>(pl, L, s);
 }
 
 RfProject rf_project(const Geom &g, const float *w, const uint16_t *codebook, const float *alpha, const float *beta, uint16_t *idx_out,
@@ -1252,6 +1347,9 @@ int launch_rows_fp4(const Geom &g, const void *x, const uint16_t *codebook, cons
 {
     const RfPlan pl = rf_plan(g, sign != nullptr);
     if (!pl.ok) return SNN_ERR_UNSUPPORTED;
+    size_t lds;
+    if (phases == SNN_PHASE_BOTH && !sign && tau == 0 && rf_indexed(pl, g, lds))
+        return launch_rf_indexed(pl, rf_layer(pl, g, x, y, ws), g, codebook, (const uint16_t *)idx, alpha, lds, s);
     if (phases & SNN_PHASE_PREPARE) {
         const RfWeights W = rf_weights(g, ws);
         hipLaunchKernelGGL(rows_fp4_prep_kernel, dim3((unsigned)W.n_cob, (unsigned)((W.ncb + 1) / 2)), dim3(256), 0, s, W, codebook, g.K, idx,

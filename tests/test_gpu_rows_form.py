@@ -171,3 +171,51 @@ def test_forward_of_many_layers_equals_forward_per_layer(n_layers, N):
         d = L["desc"]
         y = B.snn_subbit_conv2d(d, B.snn_pack_activations(L["x"], B.SNN_ACT_BIN_ROWS), L["codebook"], idx.view(d.C_out, d.C_in), L["alpha"])
         assert torch.equal(L["y"], y)
+
+
+# N, C_in, C_out, H, W, stride, K: the convolution makes its weight words itself in one or two passes of 32 output x 64 input channels,
+# and the layers past that line; rows of odd and even width with and without a last group of less than four pixels
+ONE_LAUNCH = [(1, 1, 1, 5, 3, 1, 2), (3, 31, 32, 7, 7, 1, 5), (2, 33, 17, 9, 15, 2, 512), (5, 64, 32, 16, 31, 1, 200), (40, 16, 16, 64, 64, 1, 32),
+              (2, 65, 31, 14, 14, 1, 32), (9, 128, 20, 7, 13, 2, 64), (4, 64, 64, 8, 8, 1, 16), (2, 40, 33, 33, 6, 1, 300),
+              (2, 129, 32, 8, 8, 1, 32), (2, 64, 65, 9, 9, 1, 32), (130, 16, 16, 33, 33, 1, 32)]
+
+
+@pytest.mark.parametrize("case", ONE_LAUNCH)
+def test_words_made_by_the_convolution(oracle, case):
+    import torch
+    from paper_2110_09195_amd import binding as B
+    N, C_in, C_out, H, W, stride, K = case
+    print("one launch", case, file=sys.stderr, flush=True)
+    g = np.random.default_rng(sum(case))
+    x = g.standard_normal((N, C_in, H, W), dtype=np.float32)
+    cb, idx, alpha = synth.codebook(g, K), synth.indices(g, C_out, C_in, K), synth.alpha(g, C_out)
+    _, Y = oracle.conv_bin(oracle.sign(x), oracle.expand(cb, idx), alpha, stride)
+    y = G.subbit_bin(x, cb, idx, alpha, stride)
+    assert (y == Y).all(), np.argwhere(y != Y)[:5]
+    d = B.make_desc(N, C_in, C_out, H, W, stride, K, B.SNN_ACT_BIN_ROWS)
+    ws = B.snn_subbit_prepare(d, G.dev(cb), G.dev(idx), G.dev(alpha))
+    xp = B.snn_pack_activations(G.dev(x), B.SNN_ACT_BIN_ROWS)
+    prepared = B.snn_subbit_conv2d_prepared(d, xp, G.dev(alpha), ws)
+    torch.cuda.synchronize()
+    assert (prepared.cpu().numpy() == Y).all()
+
+
+@pytest.mark.parametrize("W", [5, 8, 16, 32, 33, 64])
+def test_thresholds_of_the_sign_ending(oracle, W):
+    """Scales and shifts of either sign, zero, infinite and not a number, and thresholds on attained sums."""
+    g = np.random.default_rng(W)
+    N, C_in, C_out, H, K = 3, 40, 96, 6, 32
+    x = g.standard_normal((N, C_in, H, W), dtype=np.float32)
+    cb, idx, alpha = synth.codebook(g, K), synth.indices(g, C_out, C_in, K), synth.alpha(g, C_out)
+    xs, codes = oracle.sign(x), oracle.expand(cb, idx)
+    alpha[::2] *= -1.0
+    S, _ = oracle.conv_bin(xs, codes, np.ones_like(alpha), 1)
+    beta = -(alpha * np.median(S, axis=(0, 2, 3))).astype(np.float32)
+    inf, nan = np.float32(np.inf), np.float32(np.nan)
+    for c, (a, b) in enumerate([(0, 0), (0, -1), (-0.0, 1), (nan, 0), (1, nan), (inf, 0), (-inf, 0), (inf, -inf), (1, inf), (-1, -inf), (1e-45, 0),
+                                (1e-45, -1e-45), (3e38, 1), (-3e38, 3e38), (1, 1e9), (1, -1e9), (nan, nan), (0, nan)]):
+        alpha[c], beta[c] = a, b
+    with np.errstate(all="ignore"):
+        want, _ = oracle.conv_sign(xs, codes, alpha, beta, 1)
+    got = G.subbit_sign(oracle.pack_rows(x), x.shape, cb, idx, alpha, beta, 1)
+    assert (got == want).all(), np.argwhere(got != want)[:5]

@@ -7,6 +7,8 @@
 // Dense: a contraction over taps and input channels on the fp32 matrix unit.
 #include "subbit_common.h"
 
+#include <type_traits>
+
 namespace snn {
 
 namespace {
@@ -213,15 +215,31 @@ constexpr uint32_t SD_NONE = 0x80000000u;              // past every buffer used
 //
 // S = 4: the four waves of a workgroup share a block and split its channels, their sums meet in LDS (a quarter of the chain, four
 // times the waves: 1 x 512 -> 64 7x7 has four blocks); S = 1: a block per wave, for the few channels that are not worth it.
-template <int S>
+//
+// NL > 0: a wave brings the input rows that its pixels touch, zero pixels around the images included, to LDS with NL loads per pair of
+// channels and reads its nine taps there (two pairs in LDS, two more in registers on the way; within a wave LDS keeps the order, no
+// barrier).  Nine loads per tap went through L1 for each: 64 -> 64 8x8 batch 256 20.8 us per call, with three loads 19.9 (bit for bit the same sums).  NL = 0: straight from memory,
+// for rows so wide that the pixels' rows are no fewer than their taps.
+struct SdRows {
+    int pitch;
+    Divisor div_pitch, div_H1;
+};
+
+// INDEXED: the codes are looked up here, in a copy of the codebook in LDS, instead of in words that a launch of their own has made
+// (that layer 19.9 -> 19.3 us, 64 -> 64 8x8 of small batches a launch less, 2.5 us).
+struct SdIndexed {
+    const uint16_t *codebook, *idx;
+    int K;
+};
+
+template <int S, int NL, bool INDEXED>
 __global__ __launch_bounds__(256, 2)
 void subbit_f32_dense_kernel(const float *__restrict__ x, const uint32_t *__restrict__ wq, const float *__restrict__ alpha,
-                             float *__restrict__ y, Geom g, int n_cob, int quads, uint32_t n_blocks)
+                             float *__restrict__ y, Geom g, int n_cob, int quads, uint32_t n_blocks, SdRows rows, SdIndexed ix)
 {
     const int lane = threadIdx.x & 63, n_l = lane & 31, h = lane >> 5;
     const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t id = S == 1 ? blockIdx.x * 4u + (uint32_t)wave : blockIdx.x;
-    if (id >= n_blocks) return;                                // (S = 4: never, the grid is n_blocks)
+    const uint32_t my_id = S == 1 ? blockIdx.x * 4u + (uint32_t)wave : blockIdx.x, id = min(my_id, n_blocks - 1u);
     const uint32_t blk = id / (uint32_t)n_cob;
     const int cob = (int)(id - blk * (uint32_t)n_cob);
     const uint32_t P = (uint32_t)g.P, HoWo = (uint32_t)g.HoWo;
@@ -238,7 +256,21 @@ void subbit_f32_dense_kernel(const float *__restrict__ x, const uint32_t *__rest
     const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(
         y + (int64_t)n0 * y_image, 0, (int)min((int64_t)(g.N - (int)n0) * y_image * 4, lim), 0x00020000);
     const uint32_t plane = (uint32_t)(g.H * g.W) * 4u;
-    uint32_t off[9];
+    uint32_t off[NL > 0 ? NL : 9];
+    uint32_t window = 0;                                       // NL > 0: LDS offset of the window's first pixel in a channel's plane
+    if constexpr (NL > 0) {
+        const int H1 = g.H + 1;
+        const uint32_t p0 = blk * 32u, r0 = p0 - n0 * HoWo;
+        const int R0 = (int)n0 * H1 + (int)(r0 / (uint32_t)g.Wo) * g.stride;
+        window = (uint32_t)(((int)n * H1 + ho * g.stride - R0) * rows.pitch + wo * g.stride) * 4u;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int q = 32 * i + n_l, row = (int)fast_div((uint32_t)q, rows.div_pitch), col = q - row * rows.pitch - 1;
+            const int R = R0 + row, ni = (int)fast_div((uint32_t)R, rows.div_H1), hh = R - ni * H1 - 1;
+            const bool in = col >= 0 && hh >= 0 && ni < g.N;
+            off[i] = in ? (uint32_t)(ni - (int)n0) * (uint32_t)x_image * 4u + (uint32_t)h * plane + (uint32_t)(hh * g.W + col) * 4u : SD_NONE;
+        }
+    } else
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
         const int hh = ho * g.stride + t / 3 - 1, ww = wo * g.stride + t % 3 - 1;
@@ -246,20 +278,60 @@ void subbit_f32_dense_kernel(const float *__restrict__ x, const uint32_t *__rest
         off[t] = in ? (n - n0) * (uint32_t)x_image * 4u + (uint32_t)h * plane + (uint32_t)(hh * g.W + ww) * 4u : SD_NONE;
     }
     const int pairs = (g.C_in + 1) >> 1;
-    float B[4][9];
-    auto load_pair = [&](int p, float (&b)[9]) {               // (past the last channel: zeros, nothing read)
+    float B[NL > 0 ? 2 : 4][9], G[2][NL > 0 ? NL : 1];
+    auto load_pair = [&](int p, auto &b) {                     // (past the last channel: zeros, nothing read)
         const bool have = 2 * p + h < g.C_in;
         const uint32_t at = 2u * (uint32_t)min(p, pairs - 1) * plane;
 #pragma unroll
-        for (int t = 0; t < 9; ++t)
+        for (int t = 0; t < (NL > 0 ? NL : 9); ++t)
             b[t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xres, (int)(have ? off[t] : SD_NONE), (int)at, 0));
     };
     const u32x2 *codes = (const u32x2 *)wq + (int64_t)cob * quads * 64 + lane;
     const int q0 = S == 1 ? 0 : wave * quads / S, q1 = S == 1 ? quads : (wave + 1) * quads / S;
     const int p_end = min(pairs, 4 * q1);
-    u32x2 c = codes[(int64_t)min(q0, quads - 1) * 64];
+    // INDEXED: the quad's four channels 8 q + 2 u + h of output channel 32 cob + lane % 32
+    const __amdgpu_buffer_rsrc_t ires =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(ix.idx), 0, INDEXED ? g.C_out * g.C_in * 2 : 0, 0x00020000);
+    const uint32_t idx_row = (uint32_t)((cob * 32 + n_l) * g.C_in);
+    auto load_idx = [&](int q, uint32_t (&k)[4]) {             // (of channels that do not exist: anything, their activations are zeros)
 #pragma unroll
-    for (int u = 0; u < 3; ++u) load_pair(4 * q0 + u, B[u]);
+        for (int u = 0; u < 4; ++u) {
+            const int ci = 8 * q + 2 * u + h;
+            k[u] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(
+                ires, (int)(cob * 32 + n_l < g.C_out && ci < g.C_in ? (idx_row + (uint32_t)ci) * 2u : SD_NONE), 0, 0);
+        }
+    };
+    uint32_t kn[4];
+    u32x2 c = {0, 0};
+    if constexpr (INDEXED) load_idx(q0, kn);
+    else c = codes[(int64_t)min(q0, quads - 1) * 64];
+    // [wave][stage][channel of the pair][32 NL positions]
+    __shared__ float staged[NL > 0 ? 4 : 1][2][2][NL > 0 ? 32 * NL : 1];
+    auto put = [&](int stage, const float (&b)[NL > 0 ? NL : 1]) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) staged[wave][stage][h][32 * i + n_l] = b[i];
+        __builtin_amdgcn_wave_barrier();                       // (other lanes read them; no instruction)
+    };
+    auto taps = [&](int stage, float (&b)[9]) {
+        const float *const at = &staged[wave][stage][h][0] + (window >> 2);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) b[t] = at[(t / 3) * rows.pitch + t % 3];
+        __builtin_amdgcn_wave_barrier();
+    };
+    float first[2][NL > 0 ? NL : 1];
+    if constexpr (NL > 0) {
+        load_pair(4 * q0, first[0]);
+        load_pair(4 * q0 + 1, first[1]);
+        load_pair(4 * q0 + 2, G[0]);
+        load_pair(4 * q0 + 3, G[1]);
+    } else {
+#pragma unroll
+        for (int u = 0; u < 3; ++u) load_pair(4 * q0 + u, B[u]);
+    }
+    __shared__ uint16_t book[INDEXED ? 512 : 1];               // in window order, bit t: tap t is -1
+    if constexpr (INDEXED) {
+        for (int k = (int)threadIdx.x; k < ix.K; k += 256) book[k] = (uint16_t)(code_to_window_order(ix.codebook[k] & 511u) ^ 511u);
+    }
     // accumulator register i is row 8 (i / 4) + 4 h + i % 4; a wave stores all sixteen, or four of the sums of four waves
     constexpr int NR = 16 / S;
     const int row0 = S == 1 ? 0 : 8 * wave;
@@ -271,22 +343,47 @@ void subbit_f32_dense_kernel(const float *__restrict__ x, const uint32_t *__rest
     for (int t = 0; t < 9; ++t)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[t][i] = 0.0f;
+    auto look_up = [&](const uint32_t (&k)[4]) {
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = book[min(k[u], (uint32_t)ix.K - 1u)];
+        return (u32x2){v[0] | v[1] << 16, v[2] | v[3] << 16};
+    };
+    if constexpr (INDEXED) __syncthreads();
+    if constexpr (NL > 0) {
+        put(0, first[0]);
+        put(1, first[1]);
+        taps(0, B[0]);
+    }
+    if (my_id >= n_blocks) return;                             // (S = 4: never, the grid is n_blocks)
     for (int q = q0; q < q1; ++q) {
-        const u32x2 cn = codes[(int64_t)min(q + 1, quads - 1) * 64];
+        u32x2 cn;
+        if constexpr (INDEXED) {
+            c = look_up(kn);
+            load_idx(q + 1, kn);
+        } else {
+            cn = codes[(int64_t)min(q + 1, quads - 1) * 64];
+        }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int p = 4 * q + u;
             if (p < p_end) {                                   // (wave-uniform)
-                if (p + 3 < p_end) load_pair(p + 3, B[(u + 3) & 3]);
+                if constexpr (NL > 0) {
+                    put(u & 1, G[u & 1]);                      // pair p + 2, over this one, whose taps have been read
+                    load_pair(p + 4, G[u & 1]);
+                    taps((u & 1) ^ 1, B[(u & 1) ^ 1]);
+                } else {
+                    if (p + 3 < p_end) load_pair(p + 3, B[(u + 3) & 3]);
+                }
                 const uint32_t code = c[u >> 1] >> (16 * (u & 1));     // bit t: tap t is -1
 #pragma unroll
                 for (int t = 0; t < 9; ++t) {
                     const float w = __uint_as_float(((code << (31 - t)) & 0x80000000u) | 0x3f800000u);
-                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, B[u][t], acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, B[NL > 0 ? u & 1 : u][t], acc[t], 0, 0, 0);
                 }
             }
         }
-        c = cn;
+        if constexpr (!INDEXED) c = cn;
     }
     const uint32_t yo = mine ? (((n - n0) * (uint32_t)g.C_out + 4u * (uint32_t)h) * HoWo + r) * 4u : SD_NONE;
     float sum[16];
@@ -375,16 +472,27 @@ int launch_subbit_f32(const Geom &g, const void *x, const uint16_t *codebook, co
     if (use_dense(g)) {
         const SdPlan p = sd_plan(g);
         const int words = p.n_cob * p.quads * 256;
-        if (phases & SNN_PHASE_PREPARE) {
+        if (phases == SNN_PHASE_PREPARE) {
             hipLaunchKernelGGL(subbit_f32_dense_prep_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, codebook, idx, g.C_in, g.C_out,
                                g.K, p.quads, words, (uint16_t *)ws);
-            const int rc = check_launch();
-            if (rc != SNN_OK) return rc;
+            return check_launch();
         }
-        if (!(phases & SNN_PHASE_CONVOLVE)) return SNN_OK;
         const bool split = p.quads >= 4;
-        hipLaunchKernelGGL(split ? subbit_f32_dense_kernel<4> : subbit_f32_dense_kernel<1>, dim3((unsigned)(split ? p.n_blocks : (p.n_blocks + 3) / 4)),
-                           dim3(256), 0, s, (const float *)x, (const uint32_t *)ws, alpha, y, g, p.n_cob, p.quads, (uint32_t)p.n_blocks);
+        // rows that 32 pixels touch (a zero row between images), as the loads of a wave half
+        const int64_t row_changes = (g.Wo - 1 + 31) / g.Wo, image_changes = ((int64_t)g.HoWo - 1 + 31) / g.HoWo;
+        const int64_t positions = (g.stride * row_changes + image_changes + 3) * (g.W + 1) + 1, loads = (positions + 31) / 32;
+        const SdRows rows = {g.W + 1, make_divisor((uint32_t)g.W + 1u), make_divisor((uint32_t)g.H + 1u)};
+        auto pick = [&](auto nl) {
+            constexpr int NL = decltype(nl)::value;
+            if (phases == SNN_PHASE_BOTH) return split ? subbit_f32_dense_kernel<4, NL, true> : subbit_f32_dense_kernel<1, NL, true>;
+            return split ? subbit_f32_dense_kernel<4, NL, false> : subbit_f32_dense_kernel<1, NL, false>;
+        };
+        const auto kern = loads <= 3   ? pick(std::integral_constant<int, 3>{})
+                          : loads <= 4 ? pick(std::integral_constant<int, 4>{})
+                          : loads <= 6 ? pick(std::integral_constant<int, 6>{})
+                                       : pick(std::integral_constant<int, 0>{});
+        hipLaunchKernelGGL(kern, dim3((unsigned)(split ? p.n_blocks : (p.n_blocks + 3) / 4)),
+                           dim3(256), 0, s, (const float *)x, (const uint32_t *)ws, alpha, y, g, p.n_cob, p.quads, (uint32_t)p.n_blocks, rows, SdIndexed{codebook, idx, g.K});
         return check_launch();
     }
     const F32Cfg c = pick_f32_cfg(g);

@@ -75,3 +75,30 @@ def test_f32_special_values(oracle, case, values):
     # sums as above; a subnormal's roundings are of an absolute size (2^-150, and those of up to 9 C_in terms scaled by alpha)
     tol = (C_in + 16) * 2.0 ** -24 * mag * 1.01
     assert (np.abs(got - want) <= np.broadcast_to(tol, got.shape))[ok].all(), np.abs(got - want)[ok].max()
+
+
+# N, C_in, C_out, H, W, stride, K: rows that a wave brings to LDS in three, four and six loads, and rows too wide for that; one wave per
+# block (up to 24 channels) and four; tiles over several images, one-row and one-column images, odd channel counts
+STAGED = [(9, 40, 33, 7, 7, 1, 32), (5, 24, 40, 8, 8, 2, 16), (40, 33, 64, 3, 3, 1, 64), (3, 64, 32, 14, 14, 1, 32), (3, 7, 70, 9, 16, 2, 20),
+          (2, 65, 32, 28, 28, 1, 32), (2, 16, 32, 5, 33, 2, 32), (2, 48, 32, 6, 60, 1, 32), (3, 8, 32, 4, 61, 1, 16), (33, 40, 16, 1, 5, 1, 32),
+          (17, 9, 300, 6, 1, 1, 4)]
+
+
+@pytest.mark.parametrize("case", STAGED)
+def test_rows_through_lds(oracle, case):
+    """Against float64, and the call that looks its codes up against the one on prepared words, bit for bit."""
+    import torch
+    from paper_2110_09195_amd import binding as B
+    N, C_in, C_out, H, W, stride, K = case
+    print("fp32 rows", case, flush=True)
+    g = np.random.default_rng(sum(case))
+    x = g.standard_normal((N, C_in, H, W), dtype=np.float32)
+    cb, idx, alpha = synth.codebook(g, K), synth.indices(g, C_out, C_in, K), synth.alpha(g, C_out)
+    ref = oracle.conv_f32(x, oracle.expand(cb, idx), alpha, stride)
+    y = G.subbit_f32(x, cb, idx, alpha, stride)
+    G.assert_f32_close(y, ref[1] if isinstance(ref, tuple) else ref)
+    d = B.make_desc(N, C_in, C_out, H, W, stride, K, B.SNN_ACT_F32)
+    ws = B.snn_subbit_prepare(d, G.dev(cb), G.dev(idx), G.dev(alpha))
+    prepared = B.snn_subbit_conv2d_prepared(d, G.dev(x), G.dev(alpha), ws)
+    torch.cuda.synchronize()
+    assert (prepared.cpu().numpy() == y).all()

@@ -168,6 +168,7 @@ int snn_subbit_conv2d_noalloc(const snn_conv_desc *desc, const void *x, const ui
  * convolution alone (one launch).  prepare followed by conv2d_prepared on the same stream equals
  * snn_subbit_conv2d bit for bit.  The environment overrides that select kernels must not change
  * between the two calls.
+ * (snn_subbit_conv2d itself may leave the workspace as it is: conv2d_prepared reads what a prepare call has written.)
  *   workspace  the same buffer in both calls (>= snn_workspace_bytes(desc, SNN_WS_SUBBIT) bytes,
  *              256-byte aligned); its contents belong to the library until the weights change
  *   alpha      the same values in both calls (some kernels read alpha at convolution time)

@@ -1193,7 +1193,7 @@ RfPlan rf_plan(const Geom &g, bool sign, bool many = false)
         // are on two groups of them or one, 16 clocks per write instruction for 3): taken where it leaves as many workgroups beside
         // each other, up to the three that the registers allow.
         auto resident = [&](int p) { return std::min<int64_t>(3, (int64_t)RF_LDS_CU / (int64_t)(fixed + (size_t)chunk * plane_of(p))); };
-        if (pitch % 2 == 0 && resident(pitch + 1) == resident(pitch)) ++pitch;
+        if (pitch % 2 == 0 && resident(pitch + 1) == resident(pitch) && fixed + (size_t)chunk * plane_of(pitch + 1) <= RF_LDS_TARGET) ++pitch;
         const int64_t plane = plane_of(pitch);
         pl.PB = PB;
         pl.CB = t.CB;

@@ -89,9 +89,9 @@ inline Divisor make_divisor(uint32_t d)
     return {(uint32_t)((1ull << (31 + s)) / d) + 1u, s - 1u};
 }
 
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, const Divisor &d)
+__host__ __device__ inline uint32_t fast_div(uint32_t n, const Divisor &d)
 {
-    return d.mul ? __umulhi(n, d.mul) >> d.shift : n;
+    return d.mul ? (uint32_t)(((uint64_t)n * d.mul) >> 32) >> d.shift : n;
 }
 
 // ---- launchers (each validates nothing: the C entry points did) -----------------------------

@@ -5,6 +5,7 @@
 // Two-stage: per chunk of input channels the workgroup builds T[ci][k][pixel] in LDS (nine add/subtracts of the window's
 // values per response, as fma(x, +-1, acc)), then every lane gathers float4 rows T[ci][idx[co][ci]][4 pixels] and adds them.
 // Dense: a contraction over taps and input channels on the fp32 matrix unit.
+#include "f32_rows.h"
 #include "subbit_common.h"
 
 #include <type_traits>
@@ -220,10 +221,6 @@ constexpr uint32_t SD_NONE = 0x80000000u;              // past every buffer used
 // channels and reads its nine taps there (two pairs in LDS, two more in registers on the way; within a wave LDS keeps the order, no
 // barrier).  Nine loads per tap went through L1 for each: 64 -> 64 8x8 batch 256 20.8 us per call, with three loads 19.9 (bit for bit the same sums).  NL = 0: straight from memory,
 // for rows so wide that the pixels' rows are no fewer than their taps.
-struct SdRows {
-    int pitch;
-    Divisor div_pitch, div_H1;
-};
 
 // INDEXED: the codes are looked up here, in a copy of the codebook in LDS, instead of in words that a launch of their own has made
 // (that layer 19.9 -> 19.3 us, 64 -> 64 8x8 of small batches a launch less, 2.5 us).
@@ -259,16 +256,12 @@ void subbit_f32_dense_kernel(const float *__restrict__ x, const uint32_t *__rest
     uint32_t off[NL > 0 ? NL : 9];
     uint32_t window = 0;                                       // NL > 0: LDS offset of the window's first pixel in a channel's plane
     if constexpr (NL > 0) {
-        const int H1 = g.H + 1;
-        const uint32_t p0 = blk * 32u, r0 = p0 - n0 * HoWo;
-        const int R0 = (int)n0 * H1 + (int)(r0 / (uint32_t)g.Wo) * g.stride;
-        window = (uint32_t)(((int)n * H1 + ho * g.stride - R0) * rows.pitch + wo * g.stride) * 4u;
+        const SdBlock b = sd_block(g, blk);
+        window = (uint32_t)sd_window(g, rows, b, n, ho, wo) * 4u;
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            const int q = 32 * i + n_l, row = (int)fast_div((uint32_t)q, rows.div_pitch), col = q - row * rows.pitch - 1;
-            const int R = R0 + row, ni = (int)fast_div((uint32_t)R, rows.div_H1), hh = R - ni * H1 - 1;
-            const bool in = col >= 0 && hh >= 0 && ni < g.N;
-            off[i] = in ? (uint32_t)(ni - (int)n0) * (uint32_t)x_image * 4u + (uint32_t)h * plane + (uint32_t)(hh * g.W + col) * 4u : SD_NONE;
+            const SdPixel p = sd_pixel(g, rows, b, 32 * i + n_l);
+            off[i] = p.in ? (uint32_t)p.image * (uint32_t)x_image * 4u + (uint32_t)h * plane + (uint32_t)(p.h * g.W + p.w) * 4u : SD_NONE;
         }
     } else
 #pragma unroll
@@ -478,10 +471,8 @@ int launch_subbit_f32(const Geom &g, const void *x, const uint16_t *codebook, co
             return check_launch();
         }
         const bool split = p.quads >= 4;
-        // rows that 32 pixels touch (a zero row between images), as the loads of a wave half
-        const int64_t row_changes = (g.Wo - 1 + 31) / g.Wo, image_changes = ((int64_t)g.HoWo - 1 + 31) / g.HoWo;
-        const int64_t positions = (g.stride * row_changes + image_changes + 3) * (g.W + 1) + 1, loads = (positions + 31) / 32;
-        const SdRows rows = {g.W + 1, make_divisor((uint32_t)g.W + 1u), make_divisor((uint32_t)g.H + 1u)};
+        const int64_t loads = sd_loads(g);
+        const SdRows rows = sd_rows(g);
         auto pick = [&](auto nl) {
             constexpr int NL = decltype(nl)::value;
             if (phases == SNN_PHASE_BOTH) return split ? subbit_f32_dense_kernel<4, NL, true> : subbit_f32_dense_kernel<1, NL, true>;

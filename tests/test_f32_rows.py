@@ -1,0 +1,74 @@
+"""The places of the input values in the rows that a block of the fp32 dense form keeps in LDS (csrc/f32_rows.h), on the host: against
+the definition of the convolution's window, also where the rows of the batch together are more than 2^31."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# Output pixels of block `blk` whose taps are not where the kernel looks for them, or -1 if one lies past the loads.
+SOURCE = r"""
+#include "f32_rows.h"
+using namespace snn;
+extern "C" long long bad_pixels(int N, int H, int W, int stride, long long blk)
+{
+    const Geom g = make_geom({N, 1, 1, H, W, stride, 32, SNN_ACT_F32});
+    const SdRows rows = sd_rows(g);
+    const SdBlock b = sd_block(g, (uint32_t)blk);
+    long long bad = 0;
+    for (int64_t p = blk * 32; p < blk * 32 + 32 && p < g.P; ++p) {
+        const int64_t n = p / g.HoWo;
+        const int ho = (int)(p % g.HoWo) / g.Wo, wo = (int)(p % g.HoWo) % g.Wo;
+        const int64_t at = sd_window(g, rows, b, (uint32_t)n, ho, wo);
+        bool ok = true;
+        for (int t = 0; t < 9; ++t) {
+            const int64_t q = at + (t / 3) * rows.pitch + t % 3;
+            if (q < 0 || q >= 32 * sd_loads(g)) return -1;
+            const SdPixel v = sd_pixel(g, rows, b, (int)q);
+            const int h = ho * stride + t / 3 - 1, w = wo * stride + t % 3 - 1;
+            const bool in = h >= 0 && h < H && w >= 0 && w < W;
+            ok = ok && (in ? v.in && (int64_t)b.n0 + v.image == n && v.h == h && v.w == w : !v.in);
+        }
+        bad += !ok;
+    }
+    return bad;
+}
+extern "C" long long blocks(int N, int H, int W, int stride)
+{
+    return (make_geom({N, 1, 1, H, W, stride, 32, SNN_ACT_F32}).P + 31) / 32;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not shutil.which(hipcc):
+        pytest.skip("no hipcc")
+    d = tmp_path_factory.mktemp("f32_rows")
+    src, lib = str(d / "rows.hip"), str(d / "rows.so")
+    with open(src, "w") as f:
+        f.write(SOURCE)
+    subprocess.run([hipcc, "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_2110_09195_amd", "csrc"), src, "-o", lib], check=True)
+    L = ctypes.CDLL(lib)
+    for f in (L.bad_pixels, L.blocks):
+        f.restype = ctypes.c_longlong
+    L.bad_pixels.argtypes = [ctypes.c_int] * 4 + [ctypes.c_longlong]
+    L.blocks.argtypes = [ctypes.c_int] * 4
+    return L
+
+
+# N, H, W, stride: N (H + 1) on either side of 2^31 and of 2^32; tall and wide images; the ordinary ones
+@pytest.mark.parametrize("case", [(2 ** 30 + 32768, 1, 1, 1), (2 ** 31 - 8192, 1, 1, 1), (7 * 10 ** 8, 3, 1, 1), (7 * 10 ** 8, 3, 1, 2), (2 ** 30 - 1, 1, 2, 1),
+                                  (5 * 10 ** 8, 2, 2, 2), (1, 2 ** 28, 1, 1), (3, 10 ** 7, 5, 2), (256, 8, 8, 1), (33, 7, 7, 2), (5, 9, 19, 1),
+                                  (100, 1, 31, 1), (40, 3, 3, 1)])
+def test_every_tap_is_found(host, case):
+    N, H, W, stride = case
+    n = host.blocks(N, H, W, stride)
+    # first and last blocks, and those around every eighth of the batch
+    for blk in sorted({b for e in range(9) for b in range(n * e // 8 - 40, n * e // 8 + 40) if 0 <= b < n}):
+        assert host.bad_pixels(N, H, W, stride, blk) == 0, (case, blk)

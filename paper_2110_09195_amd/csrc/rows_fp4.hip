@@ -545,7 +545,10 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             __syncthreads();                                   // the previous blocks are no longer read
             if constexpr (CHANNELS) {
                 fill_channels(cb_first, here);
-            } else {                                           // (beside the accumulators there are registers for one task)
+            } else {
+                // (beside the accumulators there are registers for one task: with the loads of the next in flight the tiles spill 3 to
+                // 35, measured 64 -> 512 13x13 43 -> 52 us, 256 -> 256 14x14 batch 128 13.9 -> 18.5, and where it spilled nothing, four
+                // pixel blocks alone, 512 -> 512 28x28 batch 64 57.5 -> 58.0)
                 Task one[1];
                 first_task();
                 const int n = load_tasks(one, cb_first, here);
@@ -582,17 +585,24 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         // expanded slots, reads one step ahead and, for small grids, two blocks of output channels per wave on one of pixels: ResNet-18's
         // chain of 1-bit layers at batch 64 167 -> 156 us, 512 -> 512 7x7 batch 8 12.2 -> 10.1.
         u32x4 B[3][PB], E[CB];
-        uint32_t row[3][PB];                                   // LDS addresses of the window's rows
+        // A step of four pixel blocks has matrix work for its reads and additions in any order; its registers are all taken: one
+        // address per pixel block there, and the order of the instructions is the compiler's.  (With three and an order laid down it
+        // spilled 14, and a wave that has any scratch memory starts later: 64 -> 512 13x13 batch 256 52.4 -> 43.4 us, 100 -> 150 31x31
+        // 66 -> 54, 256 -> 256 28x28 73 -> 64; the smaller tiles kept values of the last block alone, below, and spilled two.)
+        constexpr int ROWS = PB == 4 ? 1 : 3;
+        uint32_t row[ROWS][PB];                                // LDS addresses of the window's rows, or of the first
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
             row[0][pb] = top[pb] + (uint32_t)h * plane;
-            row[1][pb] = row[0][pb] + pitch;
-            row[2][pb] = row[1][pb] + pitch;
+#pragma unroll
+            for (int i = 1; i < ROWS; ++i) row[i][pb] = row[i - 1][pb] + pitch;
         }
         auto read = [&](auto tc) {
             constexpr int t = decltype(tc)::value;
 #pragma unroll
-            for (int pb = 0; pb < PB; ++pb) B[t % 3][pb] = *(lds_cu32x4 *)(uintptr_t)(row[t / 3][pb] + (uint32_t)(t % 3) * 16u);
+            for (int pb = 0; pb < PB; ++pb)
+                B[t % 3][pb] = *(lds_cu32x4 *)(uintptr_t)((ROWS == 3 ? row[t / 3 % ROWS][pb] : row[0][pb] + (uint32_t)(t / 3) * pitch) +
+                                                          (uint32_t)(t % 3) * 16u);
         };
         if (np > 0) {
             read(std::integral_constant<int, 0>{});
@@ -603,12 +613,16 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         // (W: the words of this pair; V: those of the next where they are kept beside these)
         auto step = [&](auto tc, uint32_t next, auto &W, auto &V) {
             constexpr int t = decltype(tc)::value;
+            if constexpr (ROWS == 1 && t == 7) {
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) row[0][pb] += next;
+            }
             read(std::integral_constant<int, (t + 2) % 9>{});
-            if constexpr (t == 0 || t == 3) {                  // a row's three taps have been read: on to the next pair
+            if constexpr (ROWS == 3 && (t == 0 || t == 3)) {   // a row's three taps have been read: on to the next pair
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb) row[t / 3][pb] += next;
             }
-            if constexpr (t == 6) {
+            if constexpr (ROWS == 3 && t == 6) {
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb) row[2][pb] += next;
             }
@@ -631,11 +645,13 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
 #pragma unroll
                     for (int piece = 0; piece < 3; ++piece) load_words(pair + 2, cb, piece, W[cb]);
             }
-            __builtin_amdgcn_sched_group_barrier(0x100 /* LDS reads */, PB, 0);
+            if constexpr (PB != 4) {
+                __builtin_amdgcn_sched_group_barrier(0x100 /* LDS reads */, PB, 0);
 #pragma unroll
-            for (int i = 0; i < PB * CB; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008 /* matrix */, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002 /* vector */, 7 / PB + 1, 0);
+                for (int i = 0; i < PB * CB; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008 /* matrix */, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002 /* vector */, 7 / PB + 1, 0);
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -677,6 +693,10 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         if (here & 1) {
             // the last block alone: two taps per step
             const uint32_t last = (uint32_t)(here - 1) * plane;
+            // (opaque: what is chosen by it would be kept in registers all along, and the tiles of two blocks of output channels have none
+            // left.  Several layers in one launch spill two for it: the ResNet-18 stack's forward pass 181.4 us with them, 183.4 without)
+            int second = h;
+            if constexpr (CB == 2 && TASKS == 4) asm volatile("" : "+v"(second));
 #pragma unroll
             for (int u = 0; u < 5; ++u) {
                 const int t0 = 2 * u, t1 = u < 4 ? 2 * u + 1 : 0;
@@ -684,7 +704,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
                 const uint32_t o1 = (uint32_t)(t1 / 3) * pitch + (uint32_t)(t1 % 3) * 16u;
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb) {
-                    const uint32_t at = u == 4 && h ? tile_lds : top[pb] + (h ? o1 : o0);      // (the tile's first pixel is zero)
+                    const uint32_t at = u == 4 && second ? tile_lds : top[pb] + (second ? o1 : o0);      // (the tile's first pixel is zero)
                     B[0][pb] = *(lds_cu32x4 *)(uintptr_t)(at + last);
                 }
 #pragma unroll

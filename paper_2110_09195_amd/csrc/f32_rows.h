@@ -20,6 +20,28 @@ inline int64_t sd_loads(const Geom &g)
     return ((g.stride * row_changes + image_changes + 3) * (g.W + 1) + 1 + 31) / 32;
 }
 
+// Whether a wave brings the rows to LDS, and with how many loads per pair of channels (three instances of the kernel); 0: its nine taps
+// straight from memory.  Both ways, us, prepared weights, memory -> LDS:
+//   three loads        3x5 and 7x7 to 8x8: 64 -> 64 8x8 batch 256 18.2 -> 17.2, 512 -> 512 7x7 batch 64 173 -> 160
+//   four               where a chip half full waits for each load, 64 -> 64 16x16 batch 8 7.0 -> 6.9, 512 -> 512 13x13 batch 8 (688
+//                      blocks) 79 -> 74, 96 -> 96 13x13 batch 64 (1014) 24.7 -> 24.6; not over more than two rounds of
+//                      workgroups, 64 -> 64 14x14 batch 256 (3136) 53.8 -> 57.1, 128 -> 128 13x13 batch 64 (1352) 43.9 -> 44.4.
+//                      Blocks of one wave (few channels) at any number: 24 -> 64 13x13 batch 256 20.9 -> 20.4
+//   five and six       only over long chains of channels where half the chip has no block at all, 512 -> 64 32x32 batch 1 (64 blocks)
+//                      34.0 -> 32.5, 512 -> 512 10x25 batch 1 (128) 34.2 -> 33.0, or (stride 2) on rows of eight pixels, whose taps
+//                      from memory are slow, 128 -> 128 8x8 batch 256 20.7 -> 18.0; not 64 -> 64 10x25 batch 256 64.9 -> 73.4, 28x28
+//                      189 -> 219, 16 -> 16 28x28 batch 64 (one wave) 10.5 -> 11.1, 512 -> 512 28x28 batch 1 (400) 49.2 -> 49.4,
+//                      128 -> 128 1x1 batch 256 11.2 -> 11.6, 33 -> 20 28x28 batch 1 5.7 -> 5.9, 7x7 stride 2 16.7 -> 17.9
+// quads: of pairs of input channels; more than three are split over four waves.
+inline int sd_staged(const Geom &g, int quads, int64_t n_blocks)
+{
+    const int64_t loads = sd_loads(g);
+    if (loads <= 3) return 3;
+    if (loads <= 4 && (quads < 4 || n_blocks <= 1024)) return 4;
+    if (loads <= 6 && ((quads >= 16 && n_blocks <= 128 && g.HoWo >= 32) || (g.stride == 2 && (g.W & 7) == 0))) return 6;
+    return 0;
+}
+
 // Rows are numbered n (H + 1) + h + 1 from the block's first image on, so that the numbers stay small whatever the batch: over
 // the batch they pass 2^31 (N > 2^30 images of one row).
 struct SdBlock {

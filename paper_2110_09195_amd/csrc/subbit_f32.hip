@@ -205,9 +205,8 @@ void subbit_f32_prep_kernel(const uint16_t *__restrict__ codebook, const uint16_
 // ---- the dense form ----------------------------------------------------------------------------------------------------
 // S[co][pixel] = sum over taps and input channels of w x on v_mfma_f32_32x32x2_f32: a wave owns 32 output channels x 32
 // pixels, a step is a pair of input channels (one per lane half) at one tap.  The weight operand is +-1.0f made from the
-// channel's 9-bit code in two instructions, the activation operand comes straight from memory (L1 / L2: 64 x 4 bytes per 64
-// clocks of matrix work), three pairs of channels ahead.  Each tap has an accumulator of its own, so that no chain of roundings
-// is longer than the two-stage form's over the channels.
+// channel's 9-bit code in two instructions, the activation operand comes from rows in LDS or straight from memory (NL, below).  Each tap
+// has an accumulator of its own, so that no chain of roundings is longer than the two-stage form's over the channels.
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr uint32_t SD_NONE = 0x80000000u;              // past every buffer used here
@@ -219,9 +218,9 @@ constexpr uint32_t SD_NONE = 0x80000000u;              // past every buffer used
 //
 // NL > 0: a wave brings the input rows that its pixels touch, zero pixels around the images included, to LDS with NL loads per pair of
 // channels and reads its nine taps there (two pairs in LDS, two more in registers on the way; within a wave LDS keeps the order, no
-// barrier).  Nine loads per tap went through L1 for each: 64 -> 64 8x8 batch 256 20.8 us per call, with three loads 19.9 (bit for bit the same sums).  NL = 0: straight from memory,
-// for rows so wide that the pixels' rows are no fewer than their taps.
-
+// barrier).  NL = 0: nine loads per pair straight from memory (L1 / L2: 64 x 4 bytes per 64 clocks of matrix work), three pairs of
+// channels ahead.  The sums are the same bit for bit; which way, and what both take: sd_staged (f32_rows.h).
+//
 // INDEXED: the codes are looked up here, in a copy of the codebook in LDS, instead of in words that a launch of their own has made
 // (that layer 19.9 -> 19.3 us, 64 -> 64 8x8 of small batches a launch less, 2.5 us).
 struct SdIndexed {
@@ -471,17 +470,17 @@ int launch_subbit_f32(const Geom &g, const void *x, const uint16_t *codebook, co
             return check_launch();
         }
         const bool split = p.quads >= 4;
-        const int64_t loads = sd_loads(g);
+        const int staged = sd_staged(g, p.quads, p.n_blocks);
         const SdRows rows = sd_rows(g);
         auto pick = [&](auto nl) {
             constexpr int NL = decltype(nl)::value;
             if (phases == SNN_PHASE_BOTH) return split ? subbit_f32_dense_kernel<4, NL, true> : subbit_f32_dense_kernel<1, NL, true>;
             return split ? subbit_f32_dense_kernel<4, NL, false> : subbit_f32_dense_kernel<1, NL, false>;
         };
-        const auto kern = loads <= 3   ? pick(std::integral_constant<int, 3>{})
-                          : loads <= 4 ? pick(std::integral_constant<int, 4>{})
-                          : loads <= 6 ? pick(std::integral_constant<int, 6>{})
-                                       : pick(std::integral_constant<int, 0>{});
+        const auto kern = staged == 3   ? pick(std::integral_constant<int, 3>{})
+                          : staged == 4 ? pick(std::integral_constant<int, 4>{})
+                          : staged == 6 ? pick(std::integral_constant<int, 6>{})
+                                        : pick(std::integral_constant<int, 0>{});
         hipLaunchKernelGGL(kern, dim3((unsigned)(split ? p.n_blocks : (p.n_blocks + 3) / 4)),
                            dim3(256), 0, s, (const float *)x, (const uint32_t *)ws, alpha, y, g, p.n_cob, p.quads, (uint32_t)p.n_blocks, rows, SdIndexed{codebook, idx, g.K});
         return check_launch();

@@ -36,6 +36,12 @@ extern "C" long long bad_pixels(int N, int H, int W, int stride, long long blk)
     }
     return bad;
 }
+extern "C" int staged(int N, int C_in, int C_out, int H, int W, int stride)
+{
+    const Geom g = make_geom({N, C_in, C_out, H, W, stride, 32, SNN_ACT_F32});
+    const int s = sd_staged(g, (C_in + 7) / 8, (g.P + 31) / 32 * ((C_out + 31) / 32));
+    return s == 0 || s >= sd_loads(g) ? s : -1;
+}
 extern "C" long long blocks(int N, int H, int W, int stride)
 {
     return (make_geom({N, 1, 1, H, W, stride, 32, SNN_ACT_F32}).P + 31) / 32;
@@ -59,6 +65,7 @@ def host(tmp_path_factory):
         f.restype = ctypes.c_longlong
     L.bad_pixels.argtypes = [ctypes.c_int] * 4 + [ctypes.c_longlong]
     L.blocks.argtypes = [ctypes.c_int] * 4
+    L.staged.argtypes = [ctypes.c_int] * 6
     return L
 
 
@@ -72,3 +79,14 @@ def test_every_tap_is_found(host, case):
     # first and last blocks, and those around every eighth of the batch
     for blk in sorted({b for e in range(9) for b in range(n * e // 8 - 40, n * e // 8 + 40) if 0 <= b < n}):
         assert host.bad_pixels(N, H, W, stride, blk) == 0, (case, blk)
+
+
+# rows that LDS is the slower way for stay with the loads straight from memory; either side of each line of the rule
+@pytest.mark.parametrize("case, loads", [((256, 64, 64, 8, 8, 1), 3), ((1, 3, 5, 3, 5, 1), 3), ((16, 64, 64, 16, 16, 1), 4), ((64, 64, 64, 16, 16, 1), 4),
+                                         ((65, 64, 64, 16, 16, 1), 0), ((256, 24, 64, 16, 16, 1), 4), ((64, 64, 64, 28, 28, 1), 0),
+                                         ((2, 16, 16, 28, 28, 1), 0), ((256, 64, 64, 10, 25, 1), 0), ((256, 128, 128, 8, 8, 2), 6),
+                                         ((256, 128, 128, 7, 7, 2), 0), ((4, 64, 64, 16, 16, 2), 0), ((1, 512, 512, 56, 56, 1), 0),
+                                         ((1, 512, 64, 32, 32, 1), 6), ((1, 512, 65, 32, 32, 1), 6), ((1, 512, 160, 32, 32, 1), 0),
+                                         ((1, 33, 20, 28, 28, 1), 0), ((64, 512, 64, 1, 1, 1), 0)])
+def test_rows_go_through_lds_only_where_that_is_faster(host, case, loads):
+    assert host.staged(*case) == loads

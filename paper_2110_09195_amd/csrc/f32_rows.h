@@ -42,6 +42,22 @@ inline int sd_staged(const Geom &g, int quads, int64_t n_blocks)
     return 0;
 }
 
+// Whether a layer given as indices looks its codes up in the convolution, without a launch that prepares its words (2.5 us).  A
+// workgroup then waits for indices and codebook before its first pair, and for each quad's indices in turn with its own loads, which
+// costs more the more loads it has in flight.  us per call, two launches -> looked up:
+//   three loads   64 -> 64 8x8 batch 128 (512 workgroups) 11.3 -> 10.9, batch 256 (1024) 19.37 -> 19.28, 256 -> 256 8x8 batch 64 (1024)
+//                 51.2 -> 51.0, 64 -> 512 8x8 batch 64 (2048) 33.3 -> 34.9
+//   four, six     128 -> 128 14x14 batch 8 (200) 12.9 -> 11.6, batch 32 (784) 31.1 -> 31.6, 64 -> 64 14x14 batch 64 (784) 20.0 -> 20.3
+//   memory        64 -> 64 28x28 batch 8 (392) 12.4 -> 12.0, 128 -> 128 37x53 batch 1 (248) 13.5 -> 12.4, 256 -> 256 32x32 batch 1 (256) 21.0 ->
+//                 19.8, 3 -> 64 28x28 batch 128 (1568, one quad) 19.9 -> 19.5, batch 256 32.8 -> 33.4; 64 -> 64 16x16 stride 2 batch 256
+//                 (1024) 26.0 -> 27.2, 128 -> 128 32x32 batch 8 (1024) 31.9 -> 32.6, 512 -> 64 28x28 batch 8 (392) 52.2 -> 55.5
+inline bool sd_looks_up(int staged, int quads, int64_t n_wgs)
+{
+    if (staged == 3) return n_wgs <= 1024;
+    if (staged) return n_wgs <= (quads <= 8 ? 1024 : 256);
+    return quads <= 32 && n_wgs <= 2048 && n_wgs * quads <= (n_wgs <= 512 ? 8192 : 4608);
+}
+
 // Rows are numbered n (H + 1) + h + 1 from the block's first image on, so that the numbers stay small whatever the batch: over
 // the batch they pass 2^31 (N > 2^30 images of one row).
 struct SdBlock {

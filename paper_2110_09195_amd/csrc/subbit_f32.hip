@@ -222,7 +222,7 @@ constexpr uint32_t SD_NONE = 0x80000000u;              // past every buffer used
 // channels ahead.  The sums are the same bit for bit; which way, and what both take: sd_staged (f32_rows.h).
 //
 // INDEXED: the codes are looked up here, in a copy of the codebook in LDS, instead of in words that a launch of their own has made
-// (that layer 19.9 -> 19.3 us, 64 -> 64 8x8 of small batches a launch less, 2.5 us).
+// (where: sd_looks_up).
 struct SdIndexed {
     const uint16_t *codebook, *idx;
     int K;
@@ -463,26 +463,29 @@ int launch_subbit_f32(const Geom &g, const void *x, const uint16_t *codebook, co
 {
     if (use_dense(g)) {
         const SdPlan p = sd_plan(g);
-        const int words = p.n_cob * p.quads * 256;
-        if (phases == SNN_PHASE_PREPARE) {
+        const bool split = p.quads >= 4;
+        const int64_t n_wgs = split ? p.n_blocks : (p.n_blocks + 3) / 4;
+        const int staged = sd_staged(g, p.quads, p.n_blocks);
+        const bool look_up = phases == SNN_PHASE_BOTH && sd_looks_up(staged, p.quads, n_wgs);
+        if ((phases & SNN_PHASE_PREPARE) && !look_up) {
+            const int words = p.n_cob * p.quads * 256;
             hipLaunchKernelGGL(subbit_f32_dense_prep_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, codebook, idx, g.C_in, g.C_out,
                                g.K, p.quads, words, (uint16_t *)ws);
-            return check_launch();
+            const int rc = check_launch();
+            if (rc != SNN_OK) return rc;
         }
-        const bool split = p.quads >= 4;
-        const int staged = sd_staged(g, p.quads, p.n_blocks);
-        const SdRows rows = sd_rows(g);
+        if (!(phases & SNN_PHASE_CONVOLVE)) return SNN_OK;
         auto pick = [&](auto nl) {
             constexpr int NL = decltype(nl)::value;
-            if (phases == SNN_PHASE_BOTH) return split ? subbit_f32_dense_kernel<4, NL, true> : subbit_f32_dense_kernel<1, NL, true>;
+            if (look_up) return split ? subbit_f32_dense_kernel<4, NL, true> : subbit_f32_dense_kernel<1, NL, true>;
             return split ? subbit_f32_dense_kernel<4, NL, false> : subbit_f32_dense_kernel<1, NL, false>;
         };
         const auto kern = staged == 3   ? pick(std::integral_constant<int, 3>{})
                           : staged == 4 ? pick(std::integral_constant<int, 4>{})
                           : staged == 6 ? pick(std::integral_constant<int, 6>{})
                                         : pick(std::integral_constant<int, 0>{});
-        hipLaunchKernelGGL(kern, dim3((unsigned)(split ? p.n_blocks : (p.n_blocks + 3) / 4)),
-                           dim3(256), 0, s, (const float *)x, (const uint32_t *)ws, alpha, y, g, p.n_cob, p.quads, (uint32_t)p.n_blocks, rows, SdIndexed{codebook, idx, g.K});
+        hipLaunchKernelGGL(kern, dim3((unsigned)n_wgs), dim3(256), 0, s, (const float *)x, (const uint32_t *)ws, alpha, y, g, p.n_cob, p.quads,
+                           (uint32_t)p.n_blocks, sd_rows(g), SdIndexed{codebook, idx, g.K});
         return check_launch();
     }
     const F32Cfg c = pick_f32_cfg(g);

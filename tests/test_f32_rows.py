@@ -42,6 +42,13 @@ extern "C" int staged(int N, int C_in, int C_out, int H, int W, int stride)
     const int s = sd_staged(g, (C_in + 7) / 8, (g.P + 31) / 32 * ((C_out + 31) / 32));
     return s == 0 || s >= sd_loads(g) ? s : -1;
 }
+extern "C" int looks_up(int N, int C_in, int C_out, int H, int W, int stride)
+{
+    const Geom g = make_geom({N, C_in, C_out, H, W, stride, 32, SNN_ACT_F32});
+    const int quads = (C_in + 7) / 8;
+    const int64_t n_blocks = (g.P + 31) / 32 * ((C_out + 31) / 32);
+    return sd_looks_up(sd_staged(g, quads, n_blocks), quads, quads < 4 ? (n_blocks + 3) / 4 : n_blocks);
+}
 extern "C" long long blocks(int N, int H, int W, int stride)
 {
     return (make_geom({N, 1, 1, H, W, stride, 32, SNN_ACT_F32}).P + 31) / 32;
@@ -65,7 +72,7 @@ def host(tmp_path_factory):
         f.restype = ctypes.c_longlong
     L.bad_pixels.argtypes = [ctypes.c_int] * 4 + [ctypes.c_longlong]
     L.blocks.argtypes = [ctypes.c_int] * 4
-    L.staged.argtypes = [ctypes.c_int] * 6
+    L.staged.argtypes = L.looks_up.argtypes = [ctypes.c_int] * 6
     return L
 
 
@@ -90,3 +97,12 @@ def test_every_tap_is_found(host, case):
                                          ((1, 33, 20, 28, 28, 1), 0), ((64, 512, 64, 1, 1, 1), 0)])
 def test_rows_go_through_lds_only_where_that_is_faster(host, case, loads):
     assert host.staged(*case) == loads
+
+
+@pytest.mark.parametrize("case, yes", [((256, 64, 64, 8, 8, 1), 1), ((257, 64, 64, 8, 8, 1), 0), ((20, 128, 128, 13, 13, 1), 0), ((8, 128, 128, 14, 14, 1), 1),
+                                       ((40, 64, 64, 14, 14, 1), 1), ((8, 64, 64, 28, 28, 1), 1), ((64, 64, 64, 28, 28, 1), 0),
+                                       ((1, 512, 64, 56, 56, 1), 0), ((1, 128, 128, 37, 53, 1), 1), ((1, 256, 256, 32, 32, 1), 1),
+                                       ((2, 256, 256, 32, 32, 1), 0), ((128, 3, 64, 28, 28, 1), 1), ((256, 3, 64, 28, 28, 1), 0),
+                                       ((256, 64, 64, 16, 16, 2), 0)])
+def test_codes_are_looked_up_only_where_that_is_faster(host, case, yes):
+    assert host.looks_up(*case) == yes

@@ -102,3 +102,29 @@ def test_rows_through_lds(oracle, case):
     prepared = B.snn_subbit_conv2d_prepared(d, G.dev(x), G.dev(alpha), ws)
     torch.cuda.synchronize()
     assert (prepared.cpu().numpy() == y).all()
+
+
+# N, C_in, C_out, H, W, stride, K, whether the call leaves the workspace alone: one launch where the convolution looks the codes up, two past
+# the lines of that rule, from rows in LDS and straight from memory, one wave and four per block
+ROUTES = [(8, 64, 64, 8, 8, 1, 32, True), (257, 64, 64, 8, 8, 1, 64, False), (8, 128, 128, 14, 14, 1, 32, True), (20, 128, 128, 13, 13, 1, 32, False),
+          (9, 64, 64, 28, 28, 1, 32, True), (40, 64, 64, 28, 28, 1, 512, False), (3, 300, 40, 9, 9, 2, 32, False), (130, 3, 64, 28, 28, 1, 17, True),
+          (170, 3, 64, 28, 28, 1, 32, False), (5, 70, 33, 8, 8, 2, 32, True)]
+
+
+@pytest.mark.parametrize("case", ROUTES)
+def test_call_looks_its_codes_up_or_prepares_them(case):
+    """Which launches a call made shows in its workspace; the result is that of prepare and convolution, bit for bit."""
+    import torch
+    from paper_2110_09195_amd import binding as B
+    *shape, alone = case
+    N, C_in, C_out, H, W, stride, K = shape
+    print("fp32 call", case, flush=True)
+    g = np.random.default_rng(sum(shape))
+    x = G.dev(g.standard_normal((N, C_in, H, W), dtype=np.float32))
+    cb, idx, alpha = G.dev(synth.codebook(g, K)), G.dev(synth.indices(g, C_out, C_in, K)), G.dev(synth.alpha(g, C_out))
+    d = B.make_desc(N, C_in, C_out, H, W, stride, K, B.SNN_ACT_F32)
+    ws = B.alloc_workspace(d, B.SNN_WS_SUBBIT).fill_(0x5a)
+    y = B.snn_subbit_conv2d(d, x, cb, idx, alpha, None, ws)
+    assert bool((ws == 0x5a).all()) == alone
+    prepared = B.snn_subbit_conv2d_prepared(d, x, alpha, B.snn_subbit_prepare(d, cb, idx, alpha))
+    assert torch.equal(y, prepared)

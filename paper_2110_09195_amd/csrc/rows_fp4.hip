@@ -1298,15 +1298,19 @@ int launch_rf(const RfPlan &pl, const RfLayer &L, hipStream_t s)
 }
 
 // One launch for a layer whose weights come as indices: every workgroup makes the words it needs, in passes of 32 output channels x 64
-// input channels of about 0.75 us each.  Against a launch of its own (two launches -> one, us per call, K = 32): one pass 16 -> 16
-// 32x32 batch 8 (64 workgroups) 8.9 -> 6.4, batch 128 (512) 8.9 -> 7.4, 32 -> 32 16x16 batch 128 8.7 -> 6.2; two passes 64 -> 64 8x8
-// batch 32 8.8 -> 7.4, 128 -> 32 28x28 batch 32 (98) 8.9 -> 7.8, batch 64 (196) 9.3 -> 10.2, 64 -> 64 56x56 batch 32 (784) 11.6 ->
-// 12.6; four passes 64 -> 128 28x28 stride 2 batch 8 8.8 -> 9.7; eight 100 -> 150 37x53 stride 2 batch 12 9.9 -> 13.1.
+// input channels of about 0.75 us each.  Against a launch of its own (us per call, two launches -> one, K = 32, workgroups in brackets):
+//   one pass      16 -> 16 32x32 batch 8 (64) 8.9 -> 6.4, batch 128 (512) 8.9 -> 7.4, batch 256 (1024) 10.0 -> 9.1, batch 384 (1536)
+//                 12.6 -> 13.0, batch 512 (2048) 13.6 -> 14.6; 33 -> 20 28x28 batch 384 (1176) 12.7 -> 12.5
+//   two           64 -> 64 8x8 batch 256 (128) 9.2 -> 7.8, batch 512 (256) 9.4 -> 8.0, batch 768 (384) 9.4 -> 10.0; 128 -> 32 28x28
+//                 batch 32 (196) 9.3 -> 8.0, batch 64 (392) 9.3 -> 10.2
+//   four, eight   64 -> 128 28x28 stride 2 batch 8 8.8 -> 9.7; 100 -> 150 37x53 stride 2 batch 12 9.9 -> 13.1
+// Both lines lie at half of where the two meet: there the one launch still gains a sixth.
 bool rf_indexed(const RfPlan &pl, const Geom &g, size_t &lds)
 {
     const int64_t passes = (int64_t)(pl.CB << (2 - pl.wpx_shift)) * ((pl.ncb + 1) / 2);
     lds = pl.lds + (size_t)passes * RF_PAIR_BYTES + align_up((size_t)g.K * 2, 16);
-    return pl.PB <= 2 && pl.chunk == pl.ncb && pl.n_wgs <= (passes == 1 ? 512 : passes == 2 ? 128 : 0) && lds <= RF_LDS_TARGET;
+    // (tiles of two blocks of output channels are two passes and more, and taken at 256 workgroups and more)
+    return pl.CB == 1 && pl.chunk == pl.ncb && pl.n_wgs <= (passes == 1 ? 512 : passes == 2 ? 128 : 0) && lds <= RF_LDS_TARGET;
 }
 
 int launch_rf_indexed(RfPlan pl, RfLayer L, const Geom &g, const uint16_t *codebook, const uint16_t *idx, const float *alpha, size_t lds,
@@ -1317,7 +1321,6 @@ int launch_rf_indexed(RfPlan pl, RfLayer L, const Geom &g, const uint16_t *codeb
     L.idx = idx;
     L.K = g.K;
     pl.lds = lds;
-    if (pl.CB == 2) return launch_rf_one<2, 2, false, false, true>(pl, L, s);
     if (pl.PB == 2) return launch_rf_one<2, 1, false, false, true>(pl, L, s);
     return launch_rf_one<1, 1, false, false, true>(pl, L, s);
 }

@@ -173,28 +173,32 @@ def test_forward_of_many_layers_equals_forward_per_layer(n_layers, N):
         assert torch.equal(L["y"], y)
 
 
-# N, C_in, C_out, H, W, stride, K: the convolution makes its weight words itself in one or two passes of 32 output x 64 input channels,
-# and the layers past that line; rows of odd and even width with and without a last group of less than four pixels
-ONE_LAUNCH = [(1, 1, 1, 5, 3, 1, 2), (3, 31, 32, 7, 7, 1, 5), (2, 33, 17, 9, 15, 2, 512), (5, 64, 32, 16, 31, 1, 200), (40, 16, 16, 64, 64, 1, 32),
-              (2, 65, 31, 14, 14, 1, 32), (9, 128, 20, 7, 13, 2, 64), (4, 64, 64, 8, 8, 1, 16), (2, 40, 33, 33, 6, 1, 300),
-              (2, 129, 32, 8, 8, 1, 32), (2, 64, 65, 9, 9, 1, 32), (130, 16, 16, 33, 33, 1, 32)]
+# N, C_in, C_out, H, W, stride, K, launches: the convolution makes its weight words itself in one or two passes of 32 output x 64 input
+# channels, and the layers past that line; rows of odd and even width with and without a last group of less than four pixels
+ONE_LAUNCH = [(1, 1, 1, 5, 3, 1, 2, 1), (3, 31, 32, 7, 7, 1, 5, 1), (2, 33, 17, 9, 15, 2, 512, 1), (5, 64, 32, 16, 31, 1, 200, 1),
+              (40, 16, 16, 64, 64, 1, 32, 2), (2, 65, 31, 14, 14, 1, 32, 1), (9, 128, 20, 7, 13, 2, 64, 1), (4, 64, 64, 8, 8, 1, 16, 1),
+              (2, 40, 33, 33, 6, 1, 300, 1), (2, 129, 32, 8, 8, 1, 32, 2), (2, 64, 65, 9, 9, 1, 32, 2), (130, 16, 16, 33, 33, 1, 32, 2),
+              (100, 16, 16, 32, 32, 1, 32, 1)]
 
 
 @pytest.mark.parametrize("case", ONE_LAUNCH)
 def test_words_made_by_the_convolution(oracle, case):
+    """Which launches a call made shows in its workspace: the one that makes the words itself leaves it alone."""
     import torch
     from paper_2110_09195_amd import binding as B
-    N, C_in, C_out, H, W, stride, K = case
+    N, C_in, C_out, H, W, stride, K, launches = case
     print("one launch", case, file=sys.stderr, flush=True)
-    g = np.random.default_rng(sum(case))
+    g = np.random.default_rng(sum(case[:-1]))
     x = g.standard_normal((N, C_in, H, W), dtype=np.float32)
     cb, idx, alpha = synth.codebook(g, K), synth.indices(g, C_out, C_in, K), synth.alpha(g, C_out)
     _, Y = oracle.conv_bin(oracle.sign(x), oracle.expand(cb, idx), alpha, stride)
-    y = G.subbit_bin(x, cb, idx, alpha, stride)
-    assert (y == Y).all(), np.argwhere(y != Y)[:5]
     d = B.make_desc(N, C_in, C_out, H, W, stride, K, B.SNN_ACT_BIN_ROWS)
-    ws = B.snn_subbit_prepare(d, G.dev(cb), G.dev(idx), G.dev(alpha))
     xp = B.snn_pack_activations(G.dev(x), B.SNN_ACT_BIN_ROWS)
+    ws = B.alloc_workspace(d, B.SNN_WS_SUBBIT).fill_(0x5a)
+    y = B.snn_subbit_conv2d(d, xp, G.dev(cb), G.dev(idx), G.dev(alpha), None, ws).cpu().numpy()
+    assert (y == Y).all(), np.argwhere(y != Y)[:5]
+    assert bool((ws == 0x5a).all()) == (launches == 1)
+    ws = B.snn_subbit_prepare(d, G.dev(cb), G.dev(idx), G.dev(alpha))
     prepared = B.snn_subbit_conv2d_prepared(d, xp, G.dev(alpha), ws)
     torch.cuda.synchronize()
     assert (prepared.cpu().numpy() == Y).all()

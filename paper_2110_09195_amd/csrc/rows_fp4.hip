@@ -908,15 +908,9 @@ struct RfWeights {
 // its sign bits is turned by: the upper side is 1 (a > 0, all ones) or 0 (a < 0).
 __device__ inline float2 sign_entry(float a, float b, int C_in)
 {
-    auto bit = [&](int S) { return mul_then_add((float)S, a, b) >= 0.0f; };
-    if (!(a > 0.0f || a < 0.0f)) return make_float2(-1.0e9f, __uint_as_float(bit(0) ? 0u : 0xffffffffu));      // one bit for every S
-    int lo = -9 * C_in, hi = 9 * C_in + 1;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (bit(mid) == (a > 0.0f)) hi = mid;
-        else lo = mid + 1;
-    }
-    return make_float2(0.5f - (float)lo, __uint_as_float(a > 0.0f ? 0xffffffffu : 0u));
+    // (a = 0 or not a number: one bit for every S)
+    if (!(a > 0.0f || a < 0.0f)) return make_float2(-1.0e9f, __uint_as_float(mul_then_add(0.0f, a, b) >= 0.0f ? 0u : 0xffffffffu));
+    return make_float2(0.5f - (float)sign_threshold(a, b, 9 * C_in), __uint_as_float(a > 0.0f ? 0xffffffffu : 0u));
 }
 
 __device__ __forceinline__ void store_scales(const RfWeights &W, int cob, int c, const float *alpha, const float *beta)

@@ -195,6 +195,19 @@ __device__ inline float mul_then_add(float a, float b, float c)
     return prod + c;
 }
 
+// The next layer's sign, fl(fl(S a) + b) >= 0, is monotone in the sum S for a > 0 and a < 0.  Returns the first S of [-smax, smax + 1]
+// from which on it is 1 (a > 0) or 0 (a < 0), found with the very expression that defines it.
+__device__ inline int sign_threshold(float a, float b, int smax)
+{
+    int lo = -smax, hi = smax + 1;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if ((mul_then_add((float)mid, a, b) >= 0.0f) == (a > 0.0f)) hi = mid;
+        else lo = mid + 1;
+    }
+    return lo;
+}
+
 // 1x1 layers: vectors of 8 input channels from a subset of {+-1}^8 (packed-channels input)
 bool subbit_conv1x1_supported(const Geom &g);
 size_t subbit_conv1x1_workspace_bytes(const Geom &g);

@@ -125,17 +125,9 @@ __device__ inline uint2 fin_entry(int corr_term, float a, const float *beta, int
 {
     if (!beta) return make_uint2((uint32_t)corr_term, __float_as_uint(a));
     const float b = real ? beta[co] : 0.0f;
-    const int smax = 9 * C_in;
-    auto pred = [&](int S) { return mul_then_add((float)S, a, b) >= 0.0f; };
     float mult, thr;
     if (a > 0.0f || a < 0.0f) {
-        // first S in [-smax, smax + 1] from which on the bit is 1 (a > 0) / 0 (a < 0)
-        int lo = -smax, hi = smax + 1;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (pred(mid) == (a > 0.0f)) hi = mid;
-            else lo = mid + 1;
-        }
+        const int lo = sign_threshold(a, b, 9 * C_in);
         if (a > 0.0f) {
             const int t = lo + corr_term;                       // 2 acc >= T + corr_term
             mult = 1.0f;
@@ -147,7 +139,7 @@ __device__ inline uint2 fin_entry(int corr_term, float a, const float *beta, int
         }
     } else {
         mult = 0.0f;
-        thr = pred(0) ? -1.0f : 1.0f;
+        thr = mul_then_add(0.0f, a, b) >= 0.0f ? -1.0f : 1.0f;
     }
     return make_uint2(__float_as_uint(mult), __float_as_uint(thr));
 }

@@ -169,6 +169,9 @@ int snn_subbit_conv2d_noalloc(const snn_conv_desc *desc, const void *x, const ui
  * snn_subbit_conv2d bit for bit.  The environment overrides that select kernels must not change
  * between the two calls.
  * (snn_subbit_conv2d itself may leave the workspace as it is: conv2d_prepared reads what a prepare call has written.)
+ *   desc       the same in both calls, here and in every other pair of a prepare call and its convolution: which
+ *              kernels run, and so the layout of the tables, follows from all of it, the batch included (not
+ *              checked).  For a last, smaller batch prepare a second workspace, or compute the full one.
  *   workspace  the same buffer in both calls (>= snn_workspace_bytes(desc, SNN_WS_SUBBIT) bytes,
  *              256-byte aligned); its contents belong to the library until the weights change
  *   alpha      the same values in both calls (some kernels read alpha at convolution time)
@@ -447,7 +450,7 @@ int snn_bnn_conv2d(const snn_conv_desc *desc, const void *x, const uint16_t *w9,
  * the kernel reads (all that depends on the weights) and writes them to the
  * workspace; snn_bnn_conv2d_prepared runs the convolution from them.  Arguments as for snn_bnn_conv2d;
  * the workspace (SNN_WS_BNN) carries the prepared data between the two calls and must not be written in
- * between; the two calls together give exactly the result of snn_bnn_conv2d.  Same errors.
+ * between; with the same desc the two calls together give exactly the result of snn_bnn_conv2d.  Same errors.
  */
 int snn_bnn_prepare(const snn_conv_desc *desc, const uint16_t *w9, void *workspace, size_t ws_bytes, void *stream);
 int snn_bnn_conv2d_prepared(const snn_conv_desc *desc, const void *x, const float *alpha, float *y_nchw,

@@ -1386,12 +1386,13 @@ int launch_rows_fp4(const Geom &g, const void *x, const uint16_t *codebook, cons
 // that its workgroups expand (rows above and below included, so more per output pixel the wider the rows are, and once per tile of
 // output channels): they keep the layers of few output channels.  Up to 512 input channels the line is about five output channels
 // per expanded pixel and output pixel, ten where the tile of wide rows leaves a compute unit one workgroup; past those
-// the popcount kernel is several times slower and keeps up to eight output channels on wide rows, 32 where a unit has one workgroup.  Prepared, popcount -> here, us:
+// the popcount kernel is several times slower and keeps up to eight output channels on wide rows, 32 where a unit has one
+// workgroup.  Prepared, popcount -> here, us:
 // 56x56 batch 64 (2.0 expanded) 256 -> 1 5.6 -> 16.8, 256 -> 8 13.3 -> 16.9, 256 -> 12 17.4 -> 17.1, 256 -> 32 35.3 -> 18.0,
 // 32 -> 8 5.9 -> 6.4; 56x224 batch 16 (5.3) 128 -> 16 13.1 -> 14.7, 128 -> 24 17.3 -> 15.0; 32x512 batch 64 64 -> 32 (10.0)
 // 53 -> 89, 64 -> 64 (5.0) 98 -> 77; 32x900 batch 2 (35) 64 -> 64 11.8 -> 19.2; 600 -> 1 56x56 batch 64 87 -> 31, 32x900 batch 2
-// 27 -> 133, 600 -> 32 56x448 batch 8 172 -> 92, 32x640 batch 16 156 -> 250.  Layers of fewer than 256 kernels leave most of a 32 x 32 block empty (1 -> 1 56x56 batch 256 17.3 there, 19.6 here)
-// and stay with the popcount kernel.  The packed input of the images a workgroup touches takes 32-bit offsets, too.
+// 27 -> 133, 600 -> 32 56x448 batch 8 172 -> 92, 32x640 batch 16 156 -> 250.  Layers of fewer than 256 kernels leave most of a
+// 32 x 32 block empty (1 -> 1 56x56 batch 256 17.3 there, 19.6 here) and stay with the popcount kernel.  The packed input of the images a workgroup touches takes 32-bit offsets, too.
 bool bnn_rows_form(const Geom &g)
 {
     if ((int64_t)g.C_in * g.C_out < 256) return false;
@@ -1547,8 +1548,8 @@ int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, flo
             const int64_t here = (pl.n_wgs + 7) / 8 * 8;
             if (blocks + here > 0x7fffffffLL) break;
             const RfLayer L = rf_layer(pl, gs[l], x[l], y[l], ws[l]);
-            m.layer[n] = {L.x, L.wq, L.out, L.N, L.C_in, L.C_out, L.H, L.W, L.Ho, L.Wo, L.plane, L.n_cotiles, L.n_wgs, (uint16_t)L.chunk, (uint16_t)L.pitch,
-                          (uint8_t)pl.PB, (uint8_t)pl.CB, (uint8_t)pl.wpx_shift, (uint8_t)gs[l].stride,
+            m.layer[n] = {L.x, L.wq, L.out, L.N, L.C_in, L.C_out, L.H, L.W, L.Ho, L.Wo, L.plane, L.n_cotiles, L.n_wgs,
+                          (uint16_t)L.chunk, (uint16_t)L.pitch, (uint8_t)pl.PB, (uint8_t)pl.CB, (uint8_t)pl.wpx_shift, (uint8_t)gs[l].stride,
                           L.div_HoWo, L.div_Wo, L.div_H1, L.div_WW, L.div_cotiles};
             m.first[n] = (int)blocks;
             blocks += here;

@@ -81,7 +81,7 @@ def test_f32_special_values(oracle, case, values):
 # block (up to 24 channels) and four; tiles over several images, one-row and one-column images, odd channel counts
 STAGED = [(9, 40, 33, 7, 7, 1, 32), (5, 24, 40, 8, 8, 2, 16), (40, 33, 64, 3, 3, 1, 64), (3, 64, 32, 14, 14, 1, 32), (3, 7, 70, 9, 16, 2, 20),
           (2, 65, 32, 28, 28, 1, 32), (2, 16, 32, 5, 33, 2, 32), (2, 48, 32, 6, 60, 1, 32), (3, 8, 32, 4, 61, 1, 16), (33, 40, 16, 1, 5, 1, 32),
-          (17, 9, 300, 6, 1, 1, 4)]
+          (17, 9, 300, 6, 1, 1, 4), (2, 128, 32, 28, 28, 1, 32), (3, 40, 32, 8, 8, 2, 32), (30, 33, 64, 16, 16, 1, 16), (100, 40, 64, 13, 13, 1, 16)]
 
 
 @pytest.mark.parametrize("case", STAGED)

@@ -61,6 +61,10 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t by
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
 }
 
+// Cache policy of the output's stores: kept in L2 (which merges what two tiles write of one line), non-temporal, or written through L2
+// at once (system scope), which leaves nothing to write back at the end of the launch.  store_policy says which.
+enum { RF_STORE_CACHED = 0, RF_STORE_NT = 1, RF_STORE_THROUGH = 2 };
+
 // One layer as the kernel sees it.
 struct RfLayer {
     const uint32_t *x;       // packed rows [N][C_in][H][WW]
@@ -78,6 +82,7 @@ struct RfLayer {
     int n_blk;               // blocks of up to 32 pixels
     int n_cotiles, n_wgs;
     int wpx_shift;           // log2 of the waves of a workgroup along pixels; the others share its pixels
+    int policy;              // of the output's stores, RF_STORE_*
     int rows_pb, bpi, wpr;   // sign epilogue: rows per block, blocks per image, blocks per row
     Divisor div_HoWo, div_Wo, div_H1, div_WW, div_cotiles, div_bpi, div_wpr, div_Ho;
     Divisor div_W1;          // packed channels
@@ -801,24 +806,29 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     const int64_t y_left = (int64_t)(L.N - n0) * y_image * 4;
     const __amdgpu_buffer_rsrc_t yres = make_rsrc((float *)L.out + (int64_t)n0 * y_image, (uint32_t)min(y_left, (int64_t)0x7fffffff));
     const uint32_t chan = (uint32_t)L.HoWo * 4u;
+    auto store = [&](auto policy) {
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-        const int co0 = (cob0 + cb) * 32;
-        const bool whole = co0 + 32 <= L.C_out;                // (wave-uniform)
+        for (int cb = 0; cb < CB; ++cb) {
+            const int co0 = (cob0 + cb) * 32;
+            const bool whole = co0 + 32 <= L.C_out;            // (wave-uniform)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const f32x4 al = *(lds_cf32x4 *)(uintptr_t)(scale_lane + (uint32_t)(cb * 32 + 8 * q) * 4u);
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 al = *(lds_cf32x4 *)(uintptr_t)(scale_lane + (uint32_t)(cb * 32 + 8 * q) * 4u);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int c = co0 + 8 * q + i;                 // wave-uniform part of the channel
-                if (!whole && c + 4 * h >= L.C_out) continue;
+                for (int i = 0; i < 4; ++i) {
+                    const int c = co0 + 8 * q + i;             // wave-uniform part of the channel
+                    if (!whole && c + 4 * h >= L.C_out) continue;
 #pragma unroll
-                for (int pb = 0; pb < PB; ++pb)
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[cb][pb][4 * q + i] * al[i]), yres, (int)yoff[pb],
-                                                          (int)((uint32_t)c * chan), 2 /* non-temporal */);
+                    for (int pb = 0; pb < PB; ++pb)
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[cb][pb][4 * q + i] * al[i]), yres, (int)yoff[pb],
+                                                              (int)((uint32_t)c * chan), decltype(policy)::value);
+                }
             }
         }
-    }
+    };
+    if (L.policy == RF_STORE_NT) store(std::integral_constant<int, 2>{});
+    else if (TASKS == 4 && L.policy == RF_STORE_THROUGH) store(std::integral_constant<int, 16>{});   // (never in a launch of several layers)
+    else store(std::integral_constant<int, 0>{});
 }
 
 template <int PB, int CB, bool SIGN, bool CHANNELS, bool INDEXED>
@@ -841,7 +851,7 @@ struct RfManyLayer {
     int N, C_in, C_out, H, W, Ho, Wo;
     int plane, n_cotiles, n_wgs;
     uint16_t chunk, pitch;               // (at most 128; rows fit LDS)
-    uint8_t PB, CB, wpx_shift, stride;
+    uint8_t PB_CB, wpx_shift, stride, policy;
     Divisor div_HoWo, div_Wo, div_H1, div_WW, div_cotiles;
 };
 constexpr int RF_MANY_MAX = 34;
@@ -889,7 +899,8 @@ void rows_fp4_many_kernel(const RfMany m)
     L.n_cob = (c.C_out + 31) >> 5; L.ncb = (c.C_in + 31) >> 5; L.chunk = c.chunk; L.pairs = (L.ncb + 1) >> 1; L.pitch = c.pitch; L.plane = c.plane;
     L.n_blk = (L.P + 31) >> 5; L.n_cotiles = c.n_cotiles; L.n_wgs = c.n_wgs; L.wpx_shift = c.wpx_shift;
     L.div_HoWo = c.div_HoWo; L.div_Wo = c.div_Wo; L.div_H1 = c.div_H1; L.div_WW = c.div_WW; L.div_cotiles = c.div_cotiles;
-    switch (10 * c.PB + c.CB) {
+    L.policy = c.policy;
+    switch (c.PB_CB) {
     case 22: rf_tile<2, 2, false, false, 2>(L, wg, smem); break;
     case 21: rf_tile<2, 1, false, false, 2>(L, wg, smem); break;
     default: rf_tile<1, 1, false, false, 2>(L, wg, smem); break;
@@ -1234,6 +1245,23 @@ RfPlan rf_plan(const Geom &g, bool sign, bool many = false)
     return pl;
 }
 
+// Cache policy of a layer's output in a launch of its own.  A wave stores runs of 32 pixels of a channel plane: whole lines where planes are a
+// multiple of 128 bytes, whole half lines of 64, else runs whose ends share a line with another tile.  Measured, us, prepared,
+// non-temporal / through / cached (MB of output in brackets):
+//   whole lines  64 -> 64 56x56 batch 64 (51) 15.6 / 14.4 / 15.8, batch 128 (103) 24.8 / 27.2 / 27.2, batch 256 42.7 / 47.6 / 51.6
+//   half lines   128 -> 128 28x28 batch 128 (51) 19.7 / 18.2 / 18.6, batch 256 (103) 32.0 / 30.0 / 31.3, 256 -> 256 batch 256 (206) 64 / 69 / 70
+//   neither      64 -> 512 13x13 batch 256 (89) 40.9 / 34.2 / 22.5, batch 64 (22) 10.4 / 10.6 / 9.7; 100 -> 150 31x31 batch 256 (148)
+//                54 / 100 / 48; 512 -> 512 7x7 batch 256 (26) 23.1 / 22.5 / 22.7
+//   (runs of whole 16 bytes: 256 -> 256 14x14 batch 64 (13) 10.0 / 9.2 / 9.6, batch 128 (26) 13.9 / 13.3 / 13.9, batch 256 (51) 30.6 / 23.8 / 22.5)
+int store_policy(const Geom &g, const void *out)
+{
+    const int64_t mb = (4 * g.P * g.C_out) >> 20;
+    const uintptr_t pieces = (uintptr_t)out | (uintptr_t)g.HoWo * 4u;
+    if ((pieces & 127) == 0) return mb > 96 ? RF_STORE_NT : RF_STORE_THROUGH;
+    if ((pieces & 63) == 0) return mb > 144 ? RF_STORE_NT : RF_STORE_THROUGH;
+    return (pieces & 15) == 0 && mb <= 32 ? RF_STORE_THROUGH : RF_STORE_CACHED;
+}
+
 RfLayer rf_layer(const RfPlan &pl, const Geom &g, const void *x, void *out, void *ws)
 {
     RfLayer L = {};
@@ -1246,6 +1274,7 @@ RfLayer rf_layer(const RfPlan &pl, const Geom &g, const void *x, void *out, void
     L.n_cob = pl.n_cob; L.ncb = pl.ncb; L.chunk = pl.chunk; L.pairs = (pl.ncb + 1) / 2; L.pitch = pl.pitch; L.plane = (int)pl.plane;
     L.n_blk = (int)pl.n_blk; L.n_cotiles = (int)pl.n_cotiles; L.n_wgs = (int)pl.n_wgs;
     L.wpx_shift = pl.wpx_shift;
+    L.policy = store_policy(g, out);
     L.rows_pb = pl.rows_pb; L.bpi = pl.bpi; L.wpr = pl.wpr;
     L.div_HoWo = make_divisor((uint32_t)g.HoWo);
     L.div_Wo = make_divisor((uint32_t)g.Wo);
@@ -1525,17 +1554,20 @@ int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, flo
         if (!plans[l].ok) return SNN_ERR_UNSUPPORTED;
         order[l] = l;
     }
-    // Order of the layers.  Outputs that fit the last-level cache (256 MB): the layers whose workgroups run longest from one
-    // end and the shortest, which are mostly stores, from the other in turn, so that stores and matrix work overlap and
-    // no long workgroup is left to run alone at the end.  More: the short ones first, the stores that the cache has taken up drain
-    // while the long ones multiply.  Measured, short first / both ends in turn (pack and projection included where they are
-    // part of the call): 32-layer stack batch 4 (39 MB) 43.2 / 36.7 us, batch 8 58.2 / 53.8, 16-layer stack batch 16
-    // (84 MB) 77.2 / 74.9, 18 small layers batch 256 (193 MB) 99.4 / 98.1; batch 32 (308 MB) 156 / 161, 16-layer stack batch 64
-    // (335 MB) 183 / 193; the long ones first without the turns: 53.8 -> 56.5 and 193 -> 202.
+    // Order of the layers.  Outputs that the last-level cache (256 MB) takes up beside what else a pass writes: the layers whose workgroups
+    // run longest from one end and the shortest, which are mostly stores, from the other in turn, so that stores and matrix
+    // work overlap and no long workgroup is left to run alone at the end.  More: the short ones first, the stores that the cache has taken up
+    // drain while the long ones multiply.  Measured, short first / both ends in turn (pack and projection included where they are
+    // part of the call): 32-layer stack batch 4 (43 MB) 41 / 36 us, batch 8 56 / 54, batch 16 (170 MB) 92.8 / 93.8; 16-layer stack batch 16
+    // (84 MB) 77.2 / 74.9, batch 37 (194 MB) 102.5 / 109.1, batch 48 (251 MB) 130 / 138, batch 64 (335 MB) 183 / 193; the long ones first without
+    // the turns: 53.8 -> 56.5 and 193 -> 202; all layers mixed in proportion to their size: 58 and 217 (stores to many tensors at a time).
+    // Cache policy: non-temporal, but where the order takes turns the outputs whose runs share lines stay in L2, 16-layer stack batch 16
+    // 53.7 -> 51.7, batch 32 95.6 -> 88.8, 32-layer stack batch 8 55.2 -> 53.2, batch 16 93.8 -> 86.7; not below 64 MB (32-layer stack batch 4
+    // 36.0 -> 37.5), and where the short ones go first it is 165 -> 179 (batch 64).
     auto length = [&](int l) { return (int64_t)plans[l].ncb * plans[l].PB * plans[l].CB; };
     int64_t out_bytes = 0;
     for (int l = 0; l < n_layers; ++l) out_bytes += 4 * gs[l].P * gs[l].C_out;
-    const bool fold = out_bytes <= (int64_t)256 << 20;
+    const bool fold = out_bytes <= (int64_t)176 << 20, cached = fold && out_bytes >= (int64_t)64 << 20;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return fold ? length(a) > length(b) : length(a) < length(b); });
     for (int at = 0; at < n_layers;) {
         RfMany m;
@@ -1548,8 +1580,9 @@ int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, flo
             const int64_t here = (pl.n_wgs + 7) / 8 * 8;
             if (blocks + here > 0x7fffffffLL) break;
             const RfLayer L = rf_layer(pl, gs[l], x[l], y[l], ws[l]);
+            const int policy = cached && (((uintptr_t)y[l] | (uintptr_t)gs[l].HoWo * 4u) & 63) != 0 ? RF_STORE_CACHED : RF_STORE_NT;
             m.layer[n] = {L.x, L.wq, L.out, L.N, L.C_in, L.C_out, L.H, L.W, L.Ho, L.Wo, L.plane, L.n_cotiles, L.n_wgs,
-                          (uint16_t)L.chunk, (uint16_t)L.pitch, (uint8_t)pl.PB, (uint8_t)pl.CB, (uint8_t)pl.wpx_shift, (uint8_t)gs[l].stride,
+                          (uint16_t)L.chunk, (uint16_t)L.pitch, (uint8_t)(10 * pl.PB + pl.CB), (uint8_t)pl.wpx_shift, (uint8_t)gs[l].stride, (uint8_t)policy,
                           L.div_HoWo, L.div_Wo, L.div_H1, L.div_WW, L.div_cotiles};
             m.first[n] = (int)blocks;
             blocks += here;

@@ -159,10 +159,21 @@ __device__ __forceinline__ void words_of_codes(const uint32_t (&code)[8], int d,
 // pixels of the flattened (n, ho, wo) order; for the sign epilogue whole output words (whole rows while they fit 32
 // pixels, else one word of a row), so that the wave that owns a block owns the words it writes.
 // INDEXED: the weight words are made here, from codebook and indices, and kept in LDS behind the expanded pixels.
-template <int PB, int CB, bool SIGN, bool CHANNELS = false, int TASKS = 4, bool INDEXED = false>
+// PACED: a divisor of one is a branch, as it once was everywhere.  The start of a workgroup's life is a chain of scalar and vector
+// instructions; without those branches and with 32-bit buffer bounds it is shorter: 1-bit chain of ResNet-18 batch 64 127 -> 123.5 us, 256 -> 256
+// 14x14 batch 128 13.0 -> 12.6, 100 -> 150 37x53 stride 2 batch 12 9.75 -> 9.3, the 32-layer stack at batch 8 51.3 -> 50.1.  Not so several
+// layers whose outputs are past the last-level cache: their workgroups then reach their stores sooner than the memory takes them, the
+// ResNet-18 stack's forward pass at batch 64 179.4 without branches 183.3, with them 180.3; its convolutions from prepared tables 165, 168, 165.5.
+template <int PB, int CB, bool SIGN, bool CHANNELS = false, int TASKS = 4, bool INDEXED = false, bool PACED = false>
 __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned char *const smem)
 {
     const int tid = threadIdx.x;
+    auto div = [](uint32_t n, const Divisor &d) -> uint32_t {      // (PACED: see above)
+        if constexpr (PACED) {
+            if (d.shift == 0) return n;
+        }
+        return fast_div(n, d);
+    };
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_l = lane & 31, h = lane >> 5;
     // Workgroups go to the eight XCDs in turn: an XCD gets a contiguous run of tiles, so that neighbours in the output
@@ -171,7 +182,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         const uint32_t per = (uint32_t)L.n_wgs >> 3, rem = (uint32_t)L.n_wgs & 7u, xcd = wg & 7u;
         wg = xcd * per + min(xcd, rem) + (wg >> 3);
     }
-    const uint32_t pxt = fast_div(wg, L.div_cotiles);
+    const uint32_t pxt = div(wg, L.div_cotiles);
     const int cot = (int)(wg - pxt * (uint32_t)L.n_cotiles);
     const int wpx = wave & ((1 << L.wpx_shift) - 1), wco = wave >> L.wpx_shift;
     const int wg_blk0 = (int)pxt * (PB << L.wpx_shift);
@@ -189,14 +200,14 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
                 ok = false;
                 pp = L.P - 1;
             }
-            n = (int)fast_div((uint32_t)pp, L.div_HoWo);
+            n = (int)div((uint32_t)pp, L.div_HoWo);
             const int r = pp - n * L.HoWo;
-            ho = (int)fast_div((uint32_t)r, L.div_Wo);
+            ho = (int)div((uint32_t)r, L.div_Wo);
             wo = r - ho * L.Wo;
         } else if (L.Wo <= 32) {
-            n = (int)fast_div((uint32_t)B, L.div_bpi);
+            n = (int)div((uint32_t)B, L.div_bpi);
             const int rb = B - n * L.bpi;
-            int rl = (int)fast_div((uint32_t)px, L.div_Wo);
+            int rl = (int)div((uint32_t)px, L.div_Wo);
             wo = px - rl * L.Wo;
             ho = rb * L.rows_pb + rl;
             if (rl >= L.rows_pb || ho >= L.Ho) {
@@ -205,8 +216,8 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
                 wo = 0;
             }
         } else {
-            const int R = (int)fast_div((uint32_t)B, L.div_wpr);
-            n = (int)fast_div((uint32_t)R, L.div_Ho);
+            const int R = (int)div((uint32_t)B, L.div_wpr);
+            n = (int)div((uint32_t)R, L.div_Ho);
             ho = R - n * L.Ho;
             wo = 32 * (B - R * L.wpr) + px;
             if (wo >= L.Wo) {
@@ -219,7 +230,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     // rows (numbered n (H + 1) + h + 1 over the batch) that the workgroup's pixels touch
     const int H1 = L.H + 1, W1 = L.pitch;
     const uint32_t pitch = (uint32_t)W1 * 16u;
-    int R0, nrows, n0;
+    int R0, nrows, n0, n_images;
     {
         int ho, wo, n1, ho1, wo1;
         pixel_of(wg_blk0, 0, n0, ho, wo);
@@ -235,6 +246,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         R0 = __builtin_amdgcn_readfirstlane(R0);
         nrows = __builtin_amdgcn_readfirstlane(nrows);
         n0 = __builtin_amdgcn_readfirstlane(n0);
+        n_images = __builtin_amdgcn_readfirstlane(n1) - n0 + 1;
     }
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
@@ -249,9 +261,8 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     // 14x14 batch 128 14.5 -> 13.6, 100 -> 150 37x53 stride 2 batch 12 12.2 -> 10.0.  Several layers in one launch are bound by memory:
     // two at a time 180.2 us for the ResNet-18 stack's forward pass, four 183.7, one 182.5.
     const uint32_t xplane = (uint32_t)(L.H * L.WW) * 4u;
-    const int64_t image_words = (int64_t)L.C_in * L.H * L.WW;
-    const int64_t x_left = ((int64_t)(L.N - n0) * image_words) * 4;
-    const __amdgpu_buffer_rsrc_t xres = make_rsrc(L.x + (int64_t)n0 * image_words, (uint32_t)min(x_left, (int64_t)0x7fffffff));
+    const uint32_t image_bytes = (uint32_t)L.C_in * xplane;    // (of the images that a tile touches: < 2 GiB)
+    const __amdgpu_buffer_rsrc_t xres = make_rsrc((const char *)L.x + (uint64_t)(uint32_t)n0 * image_bytes, (uint32_t)n_images * image_bytes);
     const int RW = nrows * L.WW, nk = (RW + 15) >> 4;
     const int grp = lane & 3;
     struct Task {
@@ -268,9 +279,9 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             at_k = my_k;
             const int rw = 16 * my_k + (lane >> 2);
             const bool have = rw < RW;
-            const int row = (int)fast_div((uint32_t)rw, L.div_WW), word = rw - row * L.WW;
+            const int row = (int)div((uint32_t)rw, L.div_WW), word = rw - row * L.WW;
             const int R = R0 + row;
-            const int n = (int)fast_div((uint32_t)R, L.div_H1), hh = R - n * H1;
+            const int n = (int)div((uint32_t)R, L.div_H1), hh = R - n * H1;
             at_ok = have && hh > 0 && n < L.N;
             at_off = (uint32_t)((((n - n0) * L.C_in + grp * 8) * L.H + hh - 1) * L.WW + word) * 4u;
             at_addr = tile_lds + (uint32_t)(row * W1 + 1 + 32 * word) * 16u + (uint32_t)grp * 4u;
@@ -335,9 +346,8 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         }
     };
     // Packed channels [N][H][W][ncb]: a thread takes whole pixels of the tile, zero pixels included, two at a time.
-    const int64_t cimage_words = (int64_t)L.H * L.W * L.ncb;
-    const __amdgpu_buffer_rsrc_t cres =
-        make_rsrc(L.x + (int64_t)n0 * cimage_words, (uint32_t)min((int64_t)(L.N - n0) * cimage_words * 4, (int64_t)0x7fffffff));
+    const uint32_t cimage_bytes = (uint32_t)(L.H * L.W * L.ncb) * 4u;
+    const __amdgpu_buffer_rsrc_t cres = make_rsrc((const char *)L.x + (uint64_t)(uint32_t)n0 * cimage_bytes, (uint32_t)n_images * cimage_bytes);
     auto fill_channels = [&](int cb_first, int ncb) {
         const int n_px = nrows * W1 + 1;
         for (int q0 = tid; q0 < n_px; q0 += 512) {
@@ -345,9 +355,9 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 const int q = q0 + 256 * u;
-                const int row = (int)fast_div((uint32_t)q, L.div_W1), col = q - row * W1 - 1;
+                const int row = (int)div((uint32_t)q, L.div_W1), col = q - row * W1 - 1;
                 const int R = R0 + row;
-                const int n = (int)fast_div((uint32_t)R, L.div_H1), hh = R - n * H1;
+                const int n = (int)div((uint32_t)R, L.div_H1), hh = R - n * H1;
                 const bool ok = row < nrows && col >= 0 && col < L.W && hh > 0 && n < L.N;
                 off[u] = ok ? (uint32_t)((((n - n0) * L.H + hh - 1) * L.W + col) * L.ncb + cb_first) * 4u : OFF_NONE;
                 at[u] = q < n_px ? tile_lds + (uint32_t)q * 16u : 0u;
@@ -779,12 +789,12 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             if (Bk >= L.n_blk || (CB == 1 && 2 * u + late >= PB) || co >= L.C_out) continue;
             int bn, bword, bwords;                             // image, first word in a channel plane, words
             if (short_rows) {
-                bn = (int)fast_div((uint32_t)Bk, L.div_bpi);
+                bn = (int)div((uint32_t)Bk, L.div_bpi);
                 bword = (Bk - bn * L.bpi) * L.rows_pb;
                 bwords = min(L.rows_pb, L.Ho - bword);
             } else {
-                const int R = (int)fast_div((uint32_t)Bk, L.div_wpr);
-                bn = (int)fast_div((uint32_t)R, L.div_Ho);
+                const int R = (int)div((uint32_t)Bk, L.div_wpr);
+                bn = (int)div((uint32_t)R, L.div_Ho);
                 const int word = Bk - R * L.wpr;
                 bword = (R - bn * L.Ho) * WWo + word;
                 bwords = 1;
@@ -802,10 +812,8 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     }
     // ---- y = alpha * S -------------------------------------------------------------------------------------------------
     // Lanes 0..31 of a register are 32 consecutive pixels of one channel; register r is channel 8 (r / 4) + 4 h + r % 4.
-    const int64_t y_image = (int64_t)L.C_out * L.HoWo;
-    const int64_t y_left = (int64_t)(L.N - n0) * y_image * 4;
-    const __amdgpu_buffer_rsrc_t yres = make_rsrc((float *)L.out + (int64_t)n0 * y_image, (uint32_t)min(y_left, (int64_t)0x7fffffff));
-    const uint32_t chan = (uint32_t)L.HoWo * 4u;
+    const uint32_t chan = (uint32_t)L.HoWo * 4u, y_image = (uint32_t)L.C_out * chan;
+    const __amdgpu_buffer_rsrc_t yres = make_rsrc((char *)L.out + (uint64_t)(uint32_t)n0 * y_image, (uint32_t)n_images * y_image);
     auto store = [&](auto policy) {
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
@@ -876,6 +884,7 @@ __host__ __device__ constexpr size_t rf_weight_bytes(int C_out, int C_in)
     return ((size_t)((C_out + 31) / 32) * ((C_in + 63) / 64) * RF_PAIR_BYTES + 255) & ~(size_t)255;
 }
 
+template <bool PACED>
 __global__ __launch_bounds__(256, 3)
 void rows_fp4_many_kernel(const RfMany m)
 {
@@ -901,9 +910,9 @@ void rows_fp4_many_kernel(const RfMany m)
     L.div_HoWo = c.div_HoWo; L.div_Wo = c.div_Wo; L.div_H1 = c.div_H1; L.div_WW = c.div_WW; L.div_cotiles = c.div_cotiles;
     L.policy = c.policy;
     switch (c.PB_CB) {
-    case 22: rf_tile<2, 2, false, false, 2>(L, wg, smem); break;
-    case 21: rf_tile<2, 1, false, false, 2>(L, wg, smem); break;
-    default: rf_tile<1, 1, false, false, 2>(L, wg, smem); break;
+    case 22: rf_tile<2, 2, false, false, 2, false, PACED>(L, wg, smem); break;
+    case 21: rf_tile<2, 1, false, false, 2, false, PACED>(L, wg, smem); break;
+    default: rf_tile<1, 1, false, false, 2, false, PACED>(L, wg, smem); break;
     }
 }
 
@@ -1546,7 +1555,7 @@ int launch_rows_fp4_front_many(int n_layers, const Geom *gs, const float *const 
 
 int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, float *const *y, void *const *ws, hipStream_t s)
 {
-    static LdsGrant grant;
+    static LdsGrant grant[2];
     std::vector<RfPlan> plans(n_layers);
     std::vector<int> order(n_layers);
     for (int l = 0; l < n_layers; ++l) {
@@ -1591,8 +1600,9 @@ int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, flo
         m.n_layers = n;
         m.fold = fold;
         for (int i = n; i <= RF_MANY_MAX; ++i) m.first[i] = (int)blocks;
-        if (grant_dynamic_lds((const void *)rows_fp4_many_kernel, lds, grant) != SNN_OK) return SNN_ERR_LAUNCH;
-        hipLaunchKernelGGL(rows_fp4_many_kernel, dim3((unsigned)blocks), dim3(256), lds, s, m);
+        auto kern = fold ? rows_fp4_many_kernel<false> : rows_fp4_many_kernel<true>;
+        if (grant_dynamic_lds((const void *)kern, lds, grant[fold]) != SNN_OK) return SNN_ERR_LAUNCH;
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, s, m);
         const int rc = check_launch();
         if (rc != SNN_OK) return rc;
     }

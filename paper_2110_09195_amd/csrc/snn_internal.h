@@ -83,16 +83,13 @@ struct Divisor {
 
 inline Divisor make_divisor(uint32_t d)
 {
-    if (d <= 1u) return {0u, 0u};
     uint32_t s = 0;
     while ((1ull << s) < d) ++s;
-    return {(uint32_t)((1ull << (31 + s)) / d) + 1u, s - 1u};
+    return {(uint32_t)((1ull << (31 + s)) / d) + 1u, s};
 }
 
-__host__ __device__ inline uint32_t fast_div(uint32_t n, const Divisor &d)
-{
-    return d.mul ? (uint32_t)(((uint64_t)n * d.mul) >> 32) >> d.shift : n;
-}
+// (of 2 n, so that a divisor of one is no case apart: at the start of a workgroup's life a branch costs more than a shift)
+__host__ __device__ inline uint32_t fast_div(uint32_t n, const Divisor &d) { return (uint32_t)(((uint64_t)(2u * n) * d.mul) >> 32) >> d.shift; }
 
 // ---- launchers (each validates nothing: the C entry points did) -----------------------------
 

@@ -30,6 +30,7 @@
 // Packed channels (the 1-bit layer: a word holds 32 channels of a pixel, no transposition) run through the same kernel: which
 // channel of a block sits in which slot is free as long as both operands agree, so there slot 8 r + j is channel 4 j + r, a
 // word of packed channels is expanded as a word of weights is, and weight words are plain bit planes.
+#include "fp4_common.h"
 #include "front_ops.h"
 #include "rows_fp4.h"
 
@@ -54,17 +55,6 @@ typedef __attribute__((address_space(3))) const f32x4 lds_cf32x4;
 
 // words of a pair of channel blocks and 32 output channels: [lane] 16 bytes (taps 0..3), [lane] 16 bytes (4..7), [lane] 4 (8)
 constexpr uint32_t RF_PAIR_BYTES = 2304;
-constexpr uint32_t OFF_NONE = 0x80000000u;             // a lane offset past every buffer used here (all < 2 GiB)
-
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
-}
-
-// Cache policy of the output's stores: kept in L2 (which merges what two tiles write of one line), non-temporal, or written through L2
-// at once (system scope), which leaves nothing to write back at the end of the launch.  store_policy says which.
-enum { RF_STORE_CACHED = 0, RF_STORE_NT = 1, RF_STORE_THROUGH = 2 };
-
 // One layer as the kernel sees it.
 struct RfLayer {
     const uint32_t *x;       // packed rows [N][C_in][H][WW]
@@ -82,7 +72,7 @@ struct RfLayer {
     int n_blk;               // blocks of up to 32 pixels
     int n_cotiles, n_wgs;
     int wpx_shift;           // log2 of the waves of a workgroup along pixels; the others share its pixels
-    int policy;              // of the output's stores, RF_STORE_*
+    int policy;              // of the output's stores, FP4_STORE_*
     int rows_pb, bpi, wpr;   // sign epilogue: rows per block, blocks per image, blocks per row
     Divisor div_HoWo, div_Wo, div_H1, div_WW, div_cotiles, div_bpi, div_wpr, div_Ho;
     Divisor div_W1;          // packed channels
@@ -834,8 +824,8 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             }
         }
     };
-    if (L.policy == RF_STORE_NT) store(std::integral_constant<int, 2>{});
-    else if (TASKS == 4 && L.policy == RF_STORE_THROUGH) store(std::integral_constant<int, 16>{});   // (never in a launch of several layers)
+    if (L.policy == FP4_STORE_NT) store(std::integral_constant<int, 2>{});
+    else if (TASKS == 4 && L.policy == FP4_STORE_THROUGH) store(std::integral_constant<int, 16>{});   // (never in a launch of several layers)
     else store(std::integral_constant<int, 0>{});
 }
 
@@ -1254,23 +1244,6 @@ RfPlan rf_plan(const Geom &g, bool sign, bool many = false)
     return pl;
 }
 
-// Cache policy of a layer's output in a launch of its own.  A wave stores runs of 32 pixels of a channel plane: whole lines where planes are a
-// multiple of 128 bytes, whole half lines of 64, else runs whose ends share a line with another tile.  Measured, us, prepared,
-// non-temporal / through / cached (MB of output in brackets):
-//   whole lines  64 -> 64 56x56 batch 64 (51) 15.6 / 14.4 / 15.8, batch 128 (103) 24.8 / 27.2 / 27.2, batch 256 42.7 / 47.6 / 51.6
-//   half lines   128 -> 128 28x28 batch 128 (51) 19.7 / 18.2 / 18.6, batch 256 (103) 32.0 / 30.0 / 31.3, 256 -> 256 batch 256 (206) 64 / 69 / 70
-//   neither      64 -> 512 13x13 batch 256 (89) 40.9 / 34.2 / 22.5, batch 64 (22) 10.4 / 10.6 / 9.7; 100 -> 150 31x31 batch 256 (148)
-//                54 / 100 / 48; 512 -> 512 7x7 batch 256 (26) 23.1 / 22.5 / 22.7
-//   (runs of whole 16 bytes: 256 -> 256 14x14 batch 64 (13) 10.0 / 9.2 / 9.6, batch 128 (26) 13.9 / 13.3 / 13.9, batch 256 (51) 30.6 / 23.8 / 22.5)
-int store_policy(const Geom &g, const void *out)
-{
-    const int64_t mb = (4 * g.P * g.C_out) >> 20;
-    const uintptr_t pieces = (uintptr_t)out | (uintptr_t)g.HoWo * 4u;
-    if ((pieces & 127) == 0) return mb > 96 ? RF_STORE_NT : RF_STORE_THROUGH;
-    if ((pieces & 63) == 0) return mb > 144 ? RF_STORE_NT : RF_STORE_THROUGH;
-    return (pieces & 15) == 0 && mb <= 32 ? RF_STORE_THROUGH : RF_STORE_CACHED;
-}
-
 RfLayer rf_layer(const RfPlan &pl, const Geom &g, const void *x, void *out, void *ws)
 {
     RfLayer L = {};
@@ -1589,7 +1562,7 @@ int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, flo
             const int64_t here = (pl.n_wgs + 7) / 8 * 8;
             if (blocks + here > 0x7fffffffLL) break;
             const RfLayer L = rf_layer(pl, gs[l], x[l], y[l], ws[l]);
-            const int policy = cached && (((uintptr_t)y[l] | (uintptr_t)gs[l].HoWo * 4u) & 63) != 0 ? RF_STORE_CACHED : RF_STORE_NT;
+            const int policy = cached && (((uintptr_t)y[l] | (uintptr_t)gs[l].HoWo * 4u) & 63) != 0 ? FP4_STORE_CACHED : FP4_STORE_NT;
             m.layer[n] = {L.x, L.wq, L.out, L.N, L.C_in, L.C_out, L.H, L.W, L.Ho, L.Wo, L.plane, L.n_cotiles, L.n_wgs,
                           (uint16_t)L.chunk, (uint16_t)L.pitch, (uint8_t)(10 * pl.PB + pl.CB), (uint8_t)pl.wpx_shift, (uint8_t)gs[l].stride, (uint8_t)policy,
                           L.div_HoWo, L.div_Wo, L.div_H1, L.div_WW, L.div_cotiles};

@@ -22,6 +22,7 @@
 // A wave owns PB blocks of 32 pixels x CB blocks of 32 output channels and a range of input
 // channel pairs; the KS waves that split the channels of one tile sit in one workgroup and add
 // their partial sums through LDS.
+#include "conv1x1_fp4.h"
 #include "front_ops.h"
 #include "subbit_mfma_plan.h"
 
@@ -1424,9 +1425,22 @@ bool subbit_conv1x1_supported(const Geom &g)
 
 size_t subbit_conv1x1_workspace_bytes(const Geom &g) { return mf_plan(groups_geom(g), false, true).bytes; }
 
+namespace {
+
+// The dense contraction, unless a knob asks for a form of the kernel here.  (Its tables are the smaller ones.)
+bool dense_form_1x1(const Geom &g)
+{
+    for (int knob : {SNN_TUNE_SUBBIT_MFMA, SNN_TUNE_MFMA_TILE, SNN_TUNE_MFMA_KS, SNN_TUNE_MFMA_STAGE, SNN_TUNE_MFMA_QUAD})
+        if (tuning(knob) != SNN_TUNE_AUTO) return false;
+    return conv1x1_fp4_supported(g) && conv1x1_fp4_workspace_bytes(g) <= subbit_conv1x1_workspace_bytes(g);
+}
+
+}  // namespace
+
 int launch_subbit_conv1x1(const Geom &g, const void *x, const uint16_t *codebook, const uint16_t *idx, const float *alpha,
                           float *y, void *ws, hipStream_t s, int phases)
 {
+    if (dense_form_1x1(g)) return launch_conv1x1_fp4(g, x, codebook, idx, alpha, y, ws, s, phases);
     const Geom gk = groups_geom(g);
     const MfPlan pl = mf_plan(gk, false, true);
     if (pl.n_wgs > 0x7fffffffLL || pl.lds > 160 * 1024 || pl.n_pxblocks > 0x7fffffffLL) return SNN_ERR_UNSUPPORTED;

@@ -222,6 +222,89 @@ void project_backward_large_kernel(const float *__restrict__ w, const float *__r
     store_copies(lds, copies, K9, partial + (int64_t)blockIdx.x * K9);
 }
 
+// Both gradients of up to TM_MAX kernels in one launch: block k < K sums the gradients of member k's kernels, the blocks behind them write g_w.
+// A member's block reads all indices, which is what bounds it (a quarter of a microsecond per 1024); a wave keeps the numbers of those that are
+// k in a piece of LDS of its own (in order, so that the sum is the same from run to run) and adds their gradients, seven kernels of
+// nine taps at a time.  No partial sums pass through memory, and no second launch waits for them: per call, two launches -> one, on the
+// GPU alone (and with the host's share), us, K = 32: 144 kernels 5.4 -> 2.8 (9.5 -> 6.5), 4096 5.8 -> 4.2 (9.7 -> 6.6), 8192 6.0 -> 6.1 (9.6 -> 6.6),
+// 16384 6.3 -> 9.9 (9.4 -> 9.5); K = 4 4096 5.2 -> 4.6, 8192 5.3 -> 6.9; K = 512 4096 8.6 -> 4.6, 8192 10.8 -> 6.1.
+constexpr int TM_THREADS = 1024, TM_WAVES = TM_THREADS / 64;
+constexpr int TM_SCAN = 8;                           // indices that a lane looks at
+constexpr int TM_MAX = TM_THREADS * TM_SCAN;
+
+__global__ __launch_bounds__(TM_THREADS)
+void project_backward_members_kernel(const float *__restrict__ w, const float *__restrict__ g_wbar, const uint16_t *__restrict__ idx, int n, int K,
+                                     float *__restrict__ g_w, float *__restrict__ g_p, int vec)
+{
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= K) {
+        const int e = (((int)blockIdx.x - K) * TM_THREADS + tid) * 4, ne = n * 9;
+        auto through = [](float wv, float gv) { return wv > -1.0f && wv < 1.0f ? gv : 0.0f; };
+        if (vec && e + 4 <= ne) {
+            const float4 a = *(const float4 *)(w + e), b = *(const float4 *)(g_wbar + e);
+            *(float4 *)(g_w + e) = make_float4(through(a.x, b.x), through(a.y, b.y), through(a.z, b.z), through(a.w, b.w));
+        } else {
+            for (int j = 0; j < 4; ++j)
+                if (e + j < ne) g_w[e + j] = through(w[e + j], g_wbar[e + j]);
+        }
+        return;
+    }
+    __shared__ uint16_t list[TM_WAVES][TM_SCAN * 64];
+    __shared__ float sums[TM_WAVES][64];
+    const int k = blockIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int entry = lane / 9, tap = lane - 9 * entry;        // (lane 63: no entry)
+    uint16_t *const mine = list[wave];
+    // (the indices go to the waves in turn, 64 at a time)
+    const int rounds = min(TM_SCAN, (n - wave * 64 + TM_THREADS - 1) / TM_THREADS);
+    int member[TM_SCAN];
+#pragma unroll
+    for (int i = 0; i < TM_SCAN; ++i) {
+        if (i >= rounds) break;                                // (wave-uniform)
+        const int c = i * TM_THREADS + tid;
+        member[i] = c < n ? min((int)idx[c], K - 1) : -1;
+    }
+    int found = 0;                                             // (wave-uniform)
+#pragma unroll
+    for (int i = 0; i < TM_SCAN; ++i) {
+        if (i >= rounds) break;
+        const bool hit = member[i] == k;
+        const unsigned long long hits = __ballot(hit);
+        if (hit) mine[found + (int)__popcll(hits & ((1ull << lane) - 1ull))] = (uint16_t)(i * TM_THREADS + tid);
+        found += (int)__popcll(hits);
+    }
+    // (the wave's own piece: what it wrote it reads back in order)
+    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};                   // four chains: a quarter of the roundings in a row
+    if (entry < 7) {
+        int e = entry;
+        for (; e + 49 < found; e += 56) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = g_wbar[(int)mine[e + 7 * u] * 9 + tap];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) sum[u] += v[u] + v[u + 4];
+        }
+        float v[7];
+#pragma unroll
+        for (int u = 0; u < 7; ++u) v[u] = e + 7 * u < found ? g_wbar[(int)mine[e + 7 * u] * 9 + tap] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 3; ++u) sum[u] += v[u] + v[u + 4];
+        sum[3] += v[3];
+    }
+    sums[wave][lane] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    __syncthreads();
+    // sixteen waves x seven entries of a tap: a thread adds the seven of a wave, sixteen lanes side by side their sums
+    if (tid < 9 * TM_WAVES) {
+        const int t = tid >> 4, wv = tid & 15;
+        float v[7];
+#pragma unroll
+        for (int e = 0; e < 7; ++e) v[e] = sums[wv][9 * e + t];
+        float s = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + v[6]);
+#pragma unroll
+        for (int d = 8; d >= 1; d >>= 1) s += __shfl_xor(s, d, 16);
+        if (wv == 0) g_p[k * 9 + t] = s;
+    }
+}
+
 // Pass 2: g_p[k][t] = sum of the block partials; one wave per entry: lane l adds the partials of
 // blocks l, l + 64, ... in order, then the 64 lane sums are added in a fixed butterfly.
 __global__ __launch_bounds__(TB_THREADS)
@@ -286,6 +369,14 @@ int launch_project_backward(const float *w, const float *g_wbar, const uint16_t 
     // instead of four is 4 % faster on large blocks, and its error on skewed indices 1.4 times as large (1.7e-7 for 1.2e-7).
     const bool product = K <= 64 || (K <= 128 && n <= TB_ONE_MAX);
     const bool large = !product && (n > TB_ONE_MAX || n * K > ((int64_t)5 << 20));
+    // (in place, g_w over g_wbar, a block of the one launch would read what another has written)
+    const bool apart = (uintptr_t)g_w + (size_t)n * 36 <= (uintptr_t)g_wbar || (uintptr_t)g_wbar + (size_t)n * 36 <= (uintptr_t)g_w;
+    if (n > 0 && n <= TM_MAX && apart) {
+        const bool vec = ((((uintptr_t)w) | ((uintptr_t)g_wbar) | ((uintptr_t)g_w)) & 15u) == 0;
+        const unsigned grid = (unsigned)(K + (n * 9 + 4 * TM_THREADS - 1) / (4 * TM_THREADS));
+        hipLaunchKernelGGL(project_backward_members_kernel, dim3(grid), dim3(TM_THREADS), 0, s, w, g_wbar, idx, (int)n, K, g_w, g_p, vec ? 1 : 0);
+        return check_launch();
+    }
     const int64_t blocks = large ? (n + TB_LARGE - 1) / TB_LARGE : tb_blocks(n);
     if (blocks > 0x7fffffffLL) return SNN_ERR_INVALID_ARG;
     if (large) {

@@ -12,6 +12,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsnn_hip.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 
 SNN_OK = 0
 SNN_ERR_INVALID_ARG = -1
@@ -78,15 +79,26 @@ class SnnError(RuntimeError):
 
 
 _lib = None
+_fast = None            # the module _marshal (csrc/marshal.cpp), which takes the ordinary case of the calls of small layers, once the library is loaded
+
+
+def _use(L):
+    """Loaded library -> what the calls below go to."""
+    global _lib, _fast
+    from . import _marshal
+    names = ("snn_subbit_conv2d", "snn_subbit_conv2d_prepared", "snn_subbit_conv2d_sign_prepared", "snn_subbit_conv1x1_prepared",
+             "snn_bnn_conv2d_prepared", "snn_pack_activations", "snn_packed_bytes", "snn_project_backward", "snn_subset_update")
+    _marshal.use(snn_conv_desc, tuple(ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names))
+    _lib, _fast = L, _marshal
 
 
 def lib():
     """Load libsnn_hip.so (built by `python -m paper_2110_09195_amd.build`)."""
-    global _lib
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise RuntimeError("HIP library not built: %s is missing; run "
-                               "`python -m paper_2110_09195_amd.build` (there is no CPU fallback)" % LIB_PATH)
+        for path in (LIB_PATH, MARSHAL_PATH):
+            if not os.path.exists(path):
+                raise RuntimeError("HIP library not built: %s is missing; run "
+                                   "`python -m paper_2110_09195_amd.build` (there is no CPU fallback)" % path)
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
         dp = ctypes.POINTER(snn_conv_desc)
@@ -168,7 +180,7 @@ def lib():
         L.snn_set_tuning.restype = i32
         L.snn_get_tuning.argtypes = [i32]
         L.snn_get_tuning.restype = i32
-        _lib = L
+        _use(L)
     return _lib
 
 
@@ -240,6 +252,8 @@ def alloc_workspace(desc, which, device="cuda"):
 
 def snn_pack_activations(x, layout, out=None):
     """x: float32 [N][C][H][W] on the GPU -> packed int32 tensor (flat words) in `layout`."""
+    if _fast and _fast.pack_activations(x, layout, out):
+        return out
     _dev(x, torch.float32, "x")
     N, C, H, W = x.shape
     nbytes = snn_packed_bytes(N, C, H, W, layout)
@@ -299,6 +313,8 @@ def _conv_out(desc, y, device):
 def snn_subbit_conv2d(desc, x, codebook, idx, alpha, y=None, workspace=None):
     """x: packed int32 (rows layout) or float32 NCHW per desc.act; codebook int16 [K];
     idx int16 [C_out][C_in]; alpha float32 [C_out] -> y float32 [N][C_out][Ho][Wo]."""
+    if _fast and _fast.subbit_conv2d(desc, x, codebook, idx, alpha, y, workspace):
+        return y
     _dev(codebook, torch.int16, "codebook")
     _dev(idx, torch.int16, "idx")
     _dev(alpha, torch.float32, "alpha")
@@ -357,6 +373,8 @@ def snn_subbit_prepare_packed(desc, codebook, idx_packed, tau, alpha, workspace=
 
 
 def snn_subbit_conv2d_prepared(desc, x, alpha, workspace, y=None):
+    if _fast and _fast.subbit_conv2d_prepared(desc, x, alpha, workspace, y):
+        return y
     _dev(alpha, torch.float32, "alpha")
     y = _conv_out(desc, y, x.device)
     _check(lib().snn_subbit_conv2d_prepared(ctypes.byref(desc), _ptr(x), _ptr(alpha), _ptr(y), _ptr(workspace),
@@ -425,6 +443,8 @@ def snn_subbit_prepare_sign(desc, codebook, idx, alpha, beta, workspace=None):
 
 
 def snn_subbit_conv2d_sign_prepared(desc, x, workspace, out=None):
+    if _fast and _fast.subbit_conv2d_sign_prepared(desc, x, workspace, out):
+        return out
     _dev(x, torch.int32, "x")
     out = _sign_out(desc, out, x.device)
     _check(lib().snn_subbit_conv2d_sign_prepared(ctypes.byref(desc), _ptr(x), _ptr(out), _ptr(workspace),
@@ -545,6 +565,8 @@ def snn_subbit_forward_sign(desc, x, w, codebook, alpha, beta, idx_out=None, out
 
 def snn_project_backward(w, g_wbar, idx, K, g_w=None, g_p=None, workspace=None):
     """w, g_wbar float32 [n][9], idx int16 [n] -> (g_w float32 [n][9], g_p float32 [K][9])."""
+    if _fast and _fast.project_backward(w, g_wbar, idx, K, g_w, g_p, workspace):
+        return g_w, g_p
     _dev(w, torch.float32, "w")
     _dev(g_wbar, torch.float32, "g_wbar")
     _dev(idx, torch.int16, "idx")
@@ -566,6 +588,9 @@ def snn_project_backward(w, g_wbar, idx, K, g_w=None, g_p=None, workspace=None):
 
 def snn_subset_update(p, m, theta):
     """p float32 [K][9], m int8 [K][9] (updated in place) -> (codebook int16 [K], dup uint8 [K])."""
+    refined = _fast and _fast.subset_update(p, m, theta)
+    if refined:
+        return refined
     _dev(p, torch.float32, "p")
     _dev(m, torch.int8, "m")
     K = p.numel() // 9
@@ -604,6 +629,8 @@ def snn_subbit_conv1x1_prepare(desc, codebook8, idx, alpha, workspace=None):
 
 
 def snn_subbit_conv1x1_prepared(desc, x, workspace, y=None):
+    if _fast and _fast.subbit_conv1x1_prepared(desc, x, workspace, y):
+        return y
     _dev(x, torch.int32, "x")
     y = _conv_out(desc, y, x.device)
     _check(lib().snn_subbit_conv1x1_prepared(ctypes.byref(desc), _ptr(x), _ptr(y), _ptr(workspace), workspace.numel(), _stream()),
@@ -632,6 +659,8 @@ def snn_bnn_prepare(desc, w9, workspace):
 
 def snn_bnn_conv2d_prepared(desc, x, alpha, workspace, y=None):
     """The convolution half of snn_bnn_conv2d, from a workspace snn_bnn_prepare has filled."""
+    if _fast and _fast.bnn_conv2d_prepared(desc, x, alpha, workspace, y):
+        return y
     _dev(alpha, torch.float32, "alpha")
     y = _conv_out(desc, y, x.device)
     _check(lib().snn_bnn_conv2d_prepared(ctypes.byref(desc), _ptr(x), _ptr(alpha), _ptr(y), _ptr(workspace),

@@ -28,6 +28,7 @@ int launch_rows_fp4_project_many(int n_layers, const Geom *gs, const float *cons
 int launch_rows_fp4_front_many(int n_layers, const Geom *gs, const float *const *x, uint32_t *const *xr, const float *const *w,
                                const uint16_t *const *codebook, const float *const *alpha, uint16_t *const *idx_out, void *const *ws,
                                hipStream_t s);
-int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, float *const *y, void *const *ws, hipStream_t s);
+// (projected: the same call has projected the layers' real-valued kernels)
+int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, float *const *y, void *const *ws, bool projected, hipStream_t s);
 
 }  // namespace snn

@@ -1526,7 +1526,7 @@ int launch_rows_fp4_front_many(int n_layers, const Geom *gs, const float *const 
     return SNN_OK;
 }
 
-int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, float *const *y, void *const *ws, hipStream_t s)
+int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, float *const *y, void *const *ws, bool projected, hipStream_t s)
 {
     static LdsGrant grant[2];
     std::vector<RfPlan> plans(n_layers);
@@ -1545,11 +1545,17 @@ int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, flo
     // the turns: 53.8 -> 56.5 and 193 -> 202; all layers mixed in proportion to their size: 58 and 217 (stores to many tensors at a time).
     // Cache policy: non-temporal, but where the order takes turns the outputs whose runs share lines stay in L2, 16-layer stack batch 16
     // 53.7 -> 51.7, batch 32 95.6 -> 88.8, 32-layer stack batch 8 55.2 -> 53.2, batch 16 93.8 -> 86.7; not below 64 MB (32-layer stack batch 4
-    // 36.0 -> 37.5), and where the short ones go first it is 165 -> 179 (batch 64).
+    // 36.0 -> 37.5), and where the short ones go first it is 165 -> 179 (batch 64).  Where the call has projected more than 60 MB of
+    // real-valued kernels, which come through L2 as well, it is the slower one: forward pass of the 32-layer stack (76 MB) batch 7 71.6 -> 74.3, batch 10
+    // 80.5 -> 83.0, batch 16 113.8 -> 116.6, of the 16-layer stack (43 MB) batch 16 65.2 -> 61.8, batch 28 96.8 -> 91.6.
     auto length = [&](int l) { return (int64_t)plans[l].ncb * plans[l].PB * plans[l].CB; };
-    int64_t out_bytes = 0;
-    for (int l = 0; l < n_layers; ++l) out_bytes += 4 * gs[l].P * gs[l].C_out;
-    const bool fold = out_bytes <= (int64_t)176 << 20, cached = fold && out_bytes >= (int64_t)64 << 20;
+    int64_t out_bytes = 0, kernel_bytes = 0;
+    for (int l = 0; l < n_layers; ++l) {
+        out_bytes += 4 * gs[l].P * gs[l].C_out;
+        if (projected) kernel_bytes += (int64_t)36 * gs[l].C_in * gs[l].C_out;
+    }
+    const bool fold = out_bytes <= (int64_t)176 << 20;
+    const bool cached = fold && out_bytes >= (int64_t)64 << 20 && kernel_bytes <= (int64_t)60 << 20;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return fold ? length(a) > length(b) : length(a) < length(b); });
     for (int at = 0; at < n_layers;) {
         RfMany m;

@@ -136,12 +136,12 @@ int prepare_layers(const std::vector<Geom> &gs, const std::vector<const float *>
 }
 
 int convolve_layers(const std::vector<Geom> &gs, const std::vector<const void *> &x, const std::vector<float *> &y,
-                    const std::vector<void *> &ws, hipStream_t s)
+                    const std::vector<void *> &ws, bool projected, hipStream_t s)
 {
     const FormSplit f = split_forms(gs);
     if (!f.rows.empty()) {
         const int rc = launch_rows_fp4_many((int)f.rows.size(), pick(gs, f.rows).data(), pick(x, f.rows).data(), pick(y, f.rows).data(),
-                                            pick(ws, f.rows).data(), s);
+                                            pick(ws, f.rows).data(), projected, s);
         if (rc != SNN_OK) return rc;
     }
     if (f.two_stage.empty()) return SNN_OK;
@@ -463,7 +463,7 @@ int snn_subbit_conv2d_prepared_many(const snn_layer_io *layers, int n_layers, vo
         y[l] = L.y_nchw;
         ws[l] = L.workspace;
     }
-    return convolve_layers(gs, x, y, ws, (hipStream_t)stream);
+    return convolve_layers(gs, x, y, ws, false, (hipStream_t)stream);
 }
 
 int snn_subbit_forward_many(const snn_layer_forward *layers, int n_layers, void *stream)
@@ -514,7 +514,7 @@ int snn_subbit_forward_many(const snn_layer_forward *layers, int n_layers, void 
         rc = prepare_layers(gs, w, codebook, alpha, no_beta, idx_out, ws, (hipStream_t)stream);
     }
     if (rc != SNN_OK) return rc;
-    return convolve_layers(gs, xp, y, ws, (hipStream_t)stream);
+    return convolve_layers(gs, xp, y, ws, true, (hipStream_t)stream);
 }
 
 int snn_subbit_forward_sign(const snn_conv_desc *desc, const void *x_packed, const float *w, const uint16_t *codebook,

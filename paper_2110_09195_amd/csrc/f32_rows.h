@@ -20,8 +20,9 @@ inline int64_t sd_loads(const Geom &g)
     return ((g.stride * row_changes + image_changes + 3) * (g.W + 1) + 1 + 31) / 32;
 }
 
-// Whether a wave brings the rows to LDS, and with how many loads per pair of channels (three instances of the kernel); 0: its nine taps
-// straight from memory.  Both ways, us, prepared weights, memory -> LDS:
+// Whether a wave of the form on the fp32 unit brings the rows to LDS, and with how many loads per pair of channels (three instances of the
+// kernel); 0: its nine taps straight from memory.  (Rows of up to six loads and more than eight channels go in bf16 pieces, subbit_f32.hip;
+// sd_looks_up goes by this rule for both.)  Both ways, us, prepared weights, memory -> LDS:
 //   three loads        3x5 and 7x7 to 8x8: 64 -> 64 8x8 batch 256 18.2 -> 17.2, 512 -> 512 7x7 batch 64 173 -> 160
 //   four               where a chip half full waits for each load, 64 -> 64 16x16 batch 8 7.0 -> 6.9, 512 -> 512 13x13 batch 8 (688
 //                      blocks) 79 -> 74, 96 -> 96 13x13 batch 64 (1014) 24.7 -> 24.6; not over more than two rounds of

@@ -401,6 +401,230 @@ void subbit_f32_dense_kernel(const float *__restrict__ x, const uint32_t *__rest
     }
 }
 
+// The same sums with the activations as three bf16 pieces, x = hi + mid + lo exactly (eight bits of the significand each), on
+// v_mfma_f32_32x32x16_bf16: products with +-1 are exact, sums are fp32, and sixteen channels of a tap take 96 clocks of a SIMD for 512.
+// A wave owns 32 pixels x 64 output channels; it brings its rows to LDS sixteen channels at a time, already in pieces, so that
+// a tap is three reads for six products, and hi has accumulators apart from mid and lo.  Measured, fp32 unit -> pieces (one call, us): 64 -> 64
+// 8x8 batch 256 20.4 -> 11.3, of which the matrix unit's share falls from 7.7 to 1.5 and what is left is one round of workgroups' loads,
+// splitting (six instructions a value) and stores; 128 -> 128 14x14 batch 32 33 -> 15, 512 -> 512 7x7 batch 4 30.2 -> 23.2, 16 -> 32 16x16 batch 200
+// 12.0 -> 8.7.  Error of the sums against 64 bits: 5.3e-8 for 1.03e-7 at 64 channels, 5.9e-8 for 2.2e-7 at 512 (a rounding per sixteen
+// channels of a tap for one per two).
+// Values that three pieces do not hold (subnormal remainders, infinities, NaN) send the wave's sixteen channels through the fp32 unit.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <int S, int CB, int NL, bool INDEXED>
+__global__ __launch_bounds__(256, 2)
+void subbit_f32_split_kernel(const float *__restrict__ x, const uint32_t *__restrict__ wq, const float *__restrict__ alpha,
+                             float *__restrict__ y, Geom g, int n_cob, int quads, uint32_t n_blocks, SdRows rows, SdIndexed ix)
+{
+    const int lane = threadIdx.x & 63, n_l = lane & 31, h = lane >> 5;
+    const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t my_id = S == 1 ? blockIdx.x * 4u + (uint32_t)wave : blockIdx.x, id = min(my_id, n_blocks - 1u);
+    const uint32_t cob_groups = (uint32_t)(n_cob + CB - 1) / CB, blk = id / cob_groups;
+    const int cob0 = CB * (int)(id - blk * cob_groups);
+    const uint32_t P = (uint32_t)g.P, HoWo = (uint32_t)g.HoWo;
+    const uint32_t n0 = blk * 32u / HoWo;
+    const bool mine = blk * 32u + (uint32_t)n_l < P;
+    const uint32_t pp = min(blk * 32u + (uint32_t)n_l, P - 1u);
+    const uint32_t n = pp / HoWo, r = pp - n * HoWo;
+    const int ho = (int)(r / (uint32_t)g.Wo), wo = (int)r - ho * g.Wo;
+
+    const int64_t x_image = (int64_t)g.C_in * g.H * g.W, y_image = (int64_t)g.C_out * g.HoWo;
+    const int64_t lim = 0x7fffffff;
+    const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(x + (int64_t)n0 * x_image), 0, (int)min((int64_t)(g.N - (int)n0) * x_image * 4, lim), 0x00020000);
+    const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(
+        y + (int64_t)n0 * y_image, 0, (int)min((int64_t)(g.N - (int)n0) * y_image * 4, lim), 0x00020000);
+    const uint32_t plane = (uint32_t)(g.H * g.W) * 4u;
+    const SdBlock b0 = sd_block(g, blk);
+    const int window = sd_window(g, rows, b0, n, ho, wo);      // position of the window's first pixel
+    uint32_t off[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        const SdPixel p = sd_pixel(g, rows, b0, 32 * i + n_l);
+        off[i] = p.in ? (uint32_t)p.image * (uint32_t)x_image * 4u + (uint32_t)h * plane + (uint32_t)(p.h * g.W + p.w) * 4u : SD_NONE;
+    }
+    const int pairs = (g.C_in + 1) >> 1, octs = (quads + 1) >> 1;
+    const int o0 = S == 1 ? 0 : wave * octs / S, o1 = S == 1 ? octs : (wave + 1) * octs / S;
+    float v[NL][8];                                            // lane half h: channels 16 o + 2 j + h
+    auto load_x = [&](int o) {                                 // (past the last channel: zeros, nothing read)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int p = 8 * o + j;
+            const bool have = 2 * p + h < g.C_in;
+            const uint32_t at = 2u * (uint32_t)min(p, pairs - 1) * plane;
+#pragma unroll
+            for (int i = 0; i < NL; ++i)
+                v[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xres, (int)(have ? off[i] : SD_NONE), (int)at, 0));
+        }
+    };
+    // Codes of the channels, two to a word: word m of a block has those of j = 2 m and 2 m + 1.  (Of a quad past the last: any.)
+    __shared__ uint16_t book[INDEXED ? 512 : 1];               // in window order, bit t: tap t is -1
+    const __amdgpu_buffer_rsrc_t ires =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(ix.idx), 0, INDEXED ? g.C_out * g.C_in * 2 : 0, 0x00020000);
+    uint32_t k[CB][8], c[CB][4];
+    auto load_w = [&](int o) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            const int cob = min(cob0 + cb, n_cob - 1);
+            if constexpr (INDEXED) {
+                const int co = cob * 32 + n_l;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int ci = 16 * o + 2 * j + h;
+                    k[cb][j] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(
+                        ires, (int)(co < g.C_out && ci < g.C_in ? (uint32_t)(co * g.C_in + ci) * 2u : SD_NONE), 0, 0);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const u32x2 w = *((const u32x2 *)wq + ((int64_t)cob * quads + min(2 * o + q, quads - 1)) * 64 + lane);
+                    k[cb][2 * q] = w[0];
+                    k[cb][2 * q + 1] = w[1];
+                }
+            }
+        }
+    };
+    auto take_w = [&]() {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                if constexpr (INDEXED)
+                    c[cb][m] = (uint32_t)book[min(k[cb][2 * m], (uint32_t)ix.K - 1u)] | (uint32_t)book[min(k[cb][2 * m + 1], (uint32_t)ix.K - 1u)] << 16;
+                else c[cb][m] = k[cb][m];
+            }
+    };
+    load_x(min(o0, octs - 1));
+    load_w(min(o0, octs - 1));
+    v16f hi[CB], low[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) hi[cb][i] = low[cb][i] = 0.0f;
+    // [wave][piece][lane half][position]: eight channels of a half as bf16; as they are, [wave][half of the eight][lane half][position]
+    __shared__ u32x4 stage[4][3][2][32 * NL];
+    if constexpr (INDEXED) {
+        for (int i = (int)threadIdx.x; i < ix.K; i += 256) book[i] = (uint16_t)(code_to_window_order(ix.codebook[i] & 511u) ^ 511u);
+        __syncthreads();
+    }
+    if (my_id >= n_blocks) return;                             // (S = 4: never, the grid is n_blocks)
+    for (int o = o0; o < o1; ++o) {
+        uint32_t lost = 0;
+        float odd = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            u32x4 piece[3];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                uint32_t f[3][2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const float a = v[i][2 * m + e];
+                    f[0][e] = __float_as_uint(a);
+                    const float b = a - __uint_as_float(f[0][e] & 0xffff0000u);
+                    f[1][e] = __float_as_uint(b);
+                    f[2][e] = __float_as_uint(b - __uint_as_float(f[1][e] & 0xffff0000u));
+                    lost |= f[2][e] & 0xffffu;
+                    odd = __builtin_fmaf(a, 0.0f, odd);
+                }
+#pragma unroll
+                for (int q = 0; q < 3; ++q) piece[q][m] = __builtin_amdgcn_perm(f[q][1], f[q][0], 0x07060302u);     // the upper halves
+            }
+#pragma unroll
+            for (int q = 0; q < 3; ++q) stage[wave][q][h][32 * i + n_l] = piece[q];
+        }
+        const bool pieces = __ballot(lost != 0 || odd != odd) == 0;        // (wave-uniform)
+        if (!pieces) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    stage[wave][q][h][32 * i + n_l] = (u32x4){__float_as_uint(v[i][4 * q]), __float_as_uint(v[i][4 * q + 1]),
+                                                              __float_as_uint(v[i][4 * q + 2]), __float_as_uint(v[i][4 * q + 3])};
+        }
+        __builtin_amdgcn_wave_barrier();                       // (other lanes read them; within a wave LDS keeps the order)
+        take_w();
+        if (o + 1 < o1) {
+            load_x(o + 1);
+            load_w(o + 1);
+        }
+        if (pieces) {
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                const int at = window + (t / 3) * rows.pitch + t % 3;
+                u32x4 B[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) B[q] = stage[wave][q][h][at];
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) {
+                    u32x4 A;
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) A[m] = ((c[cb][m] << (15 - t)) & 0x80008000u) | 0x3f803f80u;
+                    const bf16x8 w = __builtin_bit_cast(bf16x8, A);
+                    hi[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, __builtin_bit_cast(bf16x8, B[0]), hi[cb], 0, 0, 0);
+                    low[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, __builtin_bit_cast(bf16x8, B[1]), low[cb], 0, 0, 0);
+                    low[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, __builtin_bit_cast(bf16x8, B[2]), low[cb], 0, 0, 0);
+                }
+            }
+        } else {
+            for (int t = 0; t < 9; ++t) {
+                const int at = window + (t / 3) * rows.pitch + t % 3;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const f32x4 B = __builtin_bit_cast(f32x4, stage[wave][q][h][at]);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb) {
+                            const uint32_t code = c[cb][2 * q + (u >> 1)] >> (16 * (u & 1));
+                            const float w = __uint_as_float(((code << (31 - t)) & 0x80000000u) | 0x3f800000u);
+                            hi[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, B[u], hi[cb], 0, 0, 0);
+                        }
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    // accumulator register i is row 8 (i / 4) + 4 h + i % 4; a wave stores all 16 CB, or a quarter of the sums of four waves
+    constexpr int NR = 16 * CB / S;
+    const int r0 = S == 1 ? 0 : NR * wave;
+    float al[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int q = r0 + i;
+        al[i] = alpha[min((cob0 + (q >> 4)) * 32 + 8 * ((q & 15) >> 2) + 4 * h + (q & 3), g.C_out - 1)];
+    }
+    const uint32_t yo = mine ? (((n - n0) * (uint32_t)g.C_out + 4u * (uint32_t)h) * HoWo + r) * 4u : SD_NONE;
+    float sum[16 * CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum[16 * cb + i] = hi[cb][i] + low[cb][i];
+    if constexpr (S > 1) {
+        static_assert(sizeof(stage[0]) >= 16 * CB * 64 * sizeof(float), "a wave's sums lie over its own rows");
+        float *const part = (float *)&stage[wave][0][0][0];
+#pragma unroll
+        for (int i = 0; i < 16 * CB; ++i) part[i * 64 + lane] = sum[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            float f[S];
+#pragma unroll
+            for (int w = 0; w < S; ++w) f[w] = ((const float *)&stage[w][0][0][0])[(r0 + i) * 64 + lane];
+            sum[i] = (f[0] + f[1]) + (f[2] + f[3]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int q = r0 + i, co = (cob0 + (q >> 4)) * 32 + 8 * ((q & 15) >> 2) + (q & 3);
+        const uint32_t o = co + 4 * h < g.C_out ? yo : SD_NONE;
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum[i] * al[i]), yres, (int)o, (int)((uint32_t)min(co, g.C_out - 1) * HoWo * 4u), 2);
+    }
+}
+
 __global__ __launch_bounds__(256)
 void subbit_f32_dense_prep_kernel(const uint16_t *__restrict__ codebook, const uint16_t *__restrict__ idx, int C_in, int C_out, int K,
                                   int quads, int n, uint16_t *__restrict__ wq)
@@ -426,6 +650,31 @@ SdPlan sd_plan(const Geom &g)
     return p;
 }
 
+// Whether the pieces are the faster way: rows that fit six loads (two workgroups of a compute unit then have their LDS) and more channels than
+// half of the sixteen that a step takes.  us, fp32 unit -> pieces, K = 32: 12 -> 12 8x8 batch 256 6.7 -> 5.8, 28x28 batch 200 22.6 -> 18.4;
+// 8 -> 32 8x8 batch 256 6.25 -> 5.96, 28x28 batch 200 18.7 -> 19.0, 4 -> 16 14.1 -> 18.3, 1 -> 8 12.4 -> 18.4.  With ten loads (one workgroup to
+// a compute unit) 64 -> 64 56x56 batch 32 100 -> 95, 16 -> 16 batch 64 35 -> 49, 14x53 batch 8 12.3 -> 16.6.
+bool sd_split(const Geom &g) { return g.C_in > 8 && sd_loads(g) <= 6; }
+
+struct SdSplit {
+    int CB;                      // blocks of 32 output channels of a wave
+    bool four;                   // four waves split the channels of a block
+    int64_t blocks;
+};
+
+// Two blocks of output channels read each piece for two products; one, and the channels split over four waves, where that leaves SIMDs
+// without a wave (2 -> 1 blocks, us: 512 -> 21 6x6 batch 231 37.6 -> 27.4, 64 -> 64 8x8 batch 8 7.5 -> 5.7; one wave -> four: 24 -> 64 13x13
+// batch 64 11.4 -> 8.6; of few channels and many blocks four waves have nothing to do).
+SdSplit sd_split_plan(const Geom &g, int n_cob)
+{
+    const int64_t px = (g.P + 31) / 32, octs = (g.C_in + 15) / 16;
+    SdSplit s;
+    s.CB = n_cob >= 2 && px * ((n_cob + 1) / 2) * (octs >= 4 ? 4 : 1) >= 1024 ? 2 : 1;
+    s.blocks = px * ((n_cob + s.CB - 1) / s.CB);
+    s.four = octs >= 4 || (octs >= 2 && s.blocks < 1024);
+    return s;
+}
+
 bool use_dense(const Geom &g)
 {
     if (tuning(SNN_TUNE_F32_WAVES) != SNN_TUNE_AUTO) return false;
@@ -441,11 +690,13 @@ bool use_dense(const Geom &g)
     // 16 -> 16 32x32 batch 128 K = 4 16.8 -> 20.8, K = 16 24.7 -> 20.7; 16 -> 256 56x56 batch 4 K = 4 26.1 -> 20.0;
     // 512 -> 512 7x7 batch 8 K = 4 217 -> 36, K = 32 323 -> 36.  Relative error of the sums against 64 bits: 1.0e-7 for
     // 1.6e-7 at 64 channels, 2.2e-7 for 4.1e-7 at 512.
-    // That error is why K >= 16 is the whole rule: where 64 pixels' responses are shared by 33 to 128 output channels and the pixels fill
+    // In pieces (sd_split) it is the faster one at every K: K = 4 64 -> 64 8x8 batch 256 19.8 -> 11.7 (one call), 16 -> 16 32x32 batch 128 21.9 -> 15.6,
+    // 12 -> 12 28x28 batch 200 20.7 -> 18.3.
+    // On the fp32 unit that error is why K >= 16 is the whole rule: where 64 pixels' responses are shared by 33 to 128 output channels and the pixels fill
     // the chip (16384 and more), the two-stage form is the faster one up to K = 32: 64 -> 128 8x8 batch 256 K = 16 28.8 -> 34.8, 32x32
     // batch 64 K = 16 89 -> 129, K = 32 104 -> 129; 64 -> 64 32x32 batch 64 K = 16 61 -> 67, K = 24 70 -> 67; also 64 -> 256 K = 16
     // 212 -> 255, K = 4 189 -> 254.
-    return g.K >= 16 || g.C_out >= 256;
+    return g.K >= 16 || g.C_out >= 256 || sd_split(g);
 }
 
 }  // namespace
@@ -475,10 +726,30 @@ int launch_subbit_f32(const Geom &g, const void *x, const uint16_t *codebook, co
             if (rc != SNN_OK) return rc;
         }
         if (!(phases & SNN_PHASE_CONVOLVE)) return SNN_OK;
+        if (sd_split(g)) {
+            const SdSplit sp = sd_split_plan(g, p.n_cob);
+            const int64_t loads = sd_loads(g);
+            auto pick_split = [&](auto nl, auto cb) {
+                constexpr int NL = decltype(nl)::value, CB = decltype(cb)::value;
+                if (look_up) return sp.four ? subbit_f32_split_kernel<4, CB, NL, true> : subbit_f32_split_kernel<1, CB, NL, true>;
+                return sp.four ? subbit_f32_split_kernel<4, CB, NL, false> : subbit_f32_split_kernel<1, CB, NL, false>;
+            };
+            auto pick_loads = [&](auto cb) {
+                return loads <= 3   ? pick_split(std::integral_constant<int, 3>{}, cb)
+                       : loads == 4 ? pick_split(std::integral_constant<int, 4>{}, cb) : pick_split(std::integral_constant<int, 6>{}, cb);
+            };
+            const auto kern = sp.CB == 2 ? pick_loads(std::integral_constant<int, 2>{}) : pick_loads(std::integral_constant<int, 1>{});
+            hipLaunchKernelGGL(kern, dim3((unsigned)(sp.four ? sp.blocks : (sp.blocks + 3) / 4)), dim3(256), 0, s, (const float *)x, (const uint32_t *)ws,
+                               alpha, y, g, p.n_cob, p.quads, (uint32_t)sp.blocks, sd_rows(g), SdIndexed{codebook, idx, g.K});
+            return check_launch();
+        }
+        // (rows through LDS: only of eight channels and fewer here, one wave to a block)
         auto pick = [&](auto nl) {
             constexpr int NL = decltype(nl)::value;
-            if (look_up) return split ? subbit_f32_dense_kernel<4, NL, true> : subbit_f32_dense_kernel<1, NL, true>;
-            return split ? subbit_f32_dense_kernel<4, NL, false> : subbit_f32_dense_kernel<1, NL, false>;
+            if constexpr (NL == 0) {
+                if (split) return look_up ? subbit_f32_dense_kernel<4, NL, true> : subbit_f32_dense_kernel<4, NL, false>;
+            }
+            return look_up ? subbit_f32_dense_kernel<1, NL, true> : subbit_f32_dense_kernel<1, NL, false>;
         };
         const auto kern = staged == 3   ? pick(std::integral_constant<int, 3>{})
                           : staged == 4 ? pick(std::integral_constant<int, 4>{})

@@ -24,13 +24,15 @@ enum { FP4_STORE_CACHED = 0, FP4_STORE_NT = 1, FP4_STORE_THROUGH = 2 };
 //   neither      64 -> 512 13x13 batch 256 (89) 40.9 / 34.2 / 22.5, batch 64 (22) 10.4 / 10.6 / 9.7; 100 -> 150 31x31 batch 256 (148)
 //                54 / 100 / 48; 512 -> 512 7x7 batch 256 (26) 23.1 / 22.5 / 22.7
 //   (runs of whole 16 bytes: 256 -> 256 14x14 batch 64 (13) 10.0 / 9.2 / 9.6, batch 128 (26) 13.9 / 13.3 / 13.9, batch 256 (51) 30.6 / 23.8 / 22.5)
+// Written through, runs that share lines are the faster ones only where the last-level cache already holds the output: 256 -> 256 14x14 batch 128 after
+// 512 MB of other writes 18.4 / 24.1, batch 64 12.4 / 15.2 (non-temporal / through), so they stay in L2 at every size.
 inline int store_policy(const Geom &g, const void *out)
 {
     const int64_t mb = (4 * g.P * g.C_out) >> 20;
     const uintptr_t pieces = (uintptr_t)out | (uintptr_t)g.HoWo * 4u;
     if ((pieces & 127) == 0) return mb > 96 ? FP4_STORE_NT : FP4_STORE_THROUGH;
     if ((pieces & 63) == 0) return mb > 144 ? FP4_STORE_NT : FP4_STORE_THROUGH;
-    return (pieces & 15) == 0 && mb <= 32 ? FP4_STORE_THROUGH : FP4_STORE_CACHED;
+    return FP4_STORE_CACHED;
 }
 
 }  // namespace snn

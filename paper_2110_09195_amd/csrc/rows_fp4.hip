@@ -149,11 +149,18 @@ __device__ __forceinline__ void words_of_codes(const uint32_t (&code)[8], int d,
 // pixels of the flattened (n, ho, wo) order; for the sign epilogue whole output words (whole rows while they fit 32
 // pixels, else one word of a row), so that the wave that owns a block owns the words it writes.
 // INDEXED: the weight words are made here, from codebook and indices, and kept in LDS behind the expanded pixels.
-// PACED: a divisor of one is a branch, as it once was everywhere.  The start of a workgroup's life is a chain of scalar and vector
-// instructions; without those branches and with 32-bit buffer bounds it is shorter: 1-bit chain of ResNet-18 batch 64 127 -> 123.5 us, 256 -> 256
-// 14x14 batch 128 13.0 -> 12.6, 100 -> 150 37x53 stride 2 batch 12 9.75 -> 9.3, the 32-layer stack at batch 8 51.3 -> 50.1.  Not so several
-// layers whose outputs are past the last-level cache: their workgroups then reach their stores sooner than the memory takes them, the
-// ResNet-18 stack's forward pass at batch 64 179.4 without branches 183.3, with them 180.3; its convolutions from prepared tables 165, 168, 165.5.
+// PACED (several layers whose outputs are past the last-level cache): a divisor of one is a branch, buffers end with the batch, in 64 bits, and
+// stores are non-temporal.  The start of a workgroup's life is a chain of scalar and vector instructions; without those branches and with
+// buffers that end with the tile's images, in 32 bits, it is shorter: 1-bit chain of ResNet-18 batch 64 127 -> 123.5 us, 256 -> 256 14x14
+// batch 128 13.0 -> 12.6, 100 -> 150 37x53 stride 2 batch 12 9.75 -> 9.3, the 32-layer stack at batch 8 51.3 -> 50.1.  Not so here, and it
+// shows on some cards only.  States of rows_fp4_many_kernel, in turn, forward pass of the ResNet-18 stack at batch 64, us on each of five cards, and
+// registers that the compiler keeps in scratch memory:
+//   branches, 64 bits      180.6 180.4 178.8 179.6 179.8   2 (this)
+//   branches, 32 bits      184.3 179.6 179.9 182.6 183.8   none
+//   no branches, 64 bits   184.1 179.9                     none
+//   no branches, 32 bits   197.5                           4
+// At batch 50 the first two are the same (145.6 and 145.5).  With the other policy's store loop beside the non-temporal one 180.3, 178.8, 178.8, 178.9;
+// with the last block's values kept from registers (see there; none in scratch) 182.8, 179.8.  Why is not known, no counter was read.
 template <int PB, int CB, bool SIGN, bool CHANNELS = false, int TASKS = 4, bool INDEXED = false, bool PACED = false>
 __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned char *const smem)
 {
@@ -251,8 +258,18 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     // 14x14 batch 128 14.5 -> 13.6, 100 -> 150 37x53 stride 2 batch 12 12.2 -> 10.0.  Several layers in one launch are bound by memory:
     // two at a time 180.2 us for the ResNet-18 stack's forward pass, four 183.7, one 182.5.
     const uint32_t xplane = (uint32_t)(L.H * L.WW) * 4u;
-    const uint32_t image_bytes = (uint32_t)L.C_in * xplane;    // (of the images that a tile touches: < 2 GiB)
-    const __amdgpu_buffer_rsrc_t xres = make_rsrc((const char *)L.x + (uint64_t)(uint32_t)n0 * image_bytes, (uint32_t)n_images * image_bytes);
+    // the images from the tile's first on, `words` 32-bit words each (of those that a tile touches: < 2 GiB)
+    auto images = [&](const void *base, int C, int words) {
+        if constexpr (PACED) {
+            const int64_t image_words = (int64_t)C * words;
+            const int64_t left = (int64_t)(L.N - n0) * image_words * 4;
+            return make_rsrc((const uint32_t *)base + (int64_t)n0 * image_words, (uint32_t)min(left, (int64_t)0x7fffffff));
+        } else {
+            const uint32_t image_bytes = (uint32_t)(C * words) * 4u;
+            return make_rsrc((const char *)base + (uint64_t)(uint32_t)n0 * image_bytes, (uint32_t)n_images * image_bytes);
+        }
+    };
+    const __amdgpu_buffer_rsrc_t xres = images(L.x, L.C_in, L.H * L.WW);
     const int RW = nrows * L.WW, nk = (RW + 15) >> 4;
     const int grp = lane & 3;
     struct Task {
@@ -336,8 +353,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         }
     };
     // Packed channels [N][H][W][ncb]: a thread takes whole pixels of the tile, zero pixels included, two at a time.
-    const uint32_t cimage_bytes = (uint32_t)(L.H * L.W * L.ncb) * 4u;
-    const __amdgpu_buffer_rsrc_t cres = make_rsrc((const char *)L.x + (uint64_t)(uint32_t)n0 * cimage_bytes, (uint32_t)n_images * cimage_bytes);
+    const __amdgpu_buffer_rsrc_t cres = images(L.x, L.ncb, L.H * L.W);
     auto fill_channels = [&](int cb_first, int ncb) {
         const int n_px = nrows * W1 + 1;
         for (int q0 = tid; q0 < n_px; q0 += 512) {
@@ -802,8 +818,8 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     }
     // ---- y = alpha * S -------------------------------------------------------------------------------------------------
     // Lanes 0..31 of a register are 32 consecutive pixels of one channel; register r is channel 8 (r / 4) + 4 h + r % 4.
-    const uint32_t chan = (uint32_t)L.HoWo * 4u, y_image = (uint32_t)L.C_out * chan;
-    const __amdgpu_buffer_rsrc_t yres = make_rsrc((char *)L.out + (uint64_t)(uint32_t)n0 * y_image, (uint32_t)n_images * y_image);
+    const uint32_t chan = (uint32_t)L.HoWo * 4u;
+    const __amdgpu_buffer_rsrc_t yres = images(L.out, L.C_out, L.HoWo);
     auto store = [&](auto policy) {
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
@@ -824,7 +840,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             }
         }
     };
-    if (L.policy == FP4_STORE_NT) store(std::integral_constant<int, 2>{});
+    if (PACED || L.policy == FP4_STORE_NT) store(std::integral_constant<int, 2>{});
     else if (TASKS == 4 && L.policy == FP4_STORE_THROUGH) store(std::integral_constant<int, 16>{});   // (never in a launch of several layers)
     else store(std::integral_constant<int, 0>{});
 }

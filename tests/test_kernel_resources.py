@@ -42,3 +42,13 @@ def test_rows_kernels_have_no_scratch():
     spilled = {n: k[".vgpr_spill_count"] for n, k in rows.items() if k[".vgpr_spill_count"] > (2 if "rows_fp4_many" in n else 0)}
     scratch = {n: k[".private_segment_fixed_size"] for n, k in rows.items() if k[".private_segment_fixed_size"] and "rows_fp4_many" not in n}
     assert not spilled and not scratch, (spilled, scratch)
+
+
+# Several layers in one launch: outputs past the last-level cache (the instance of template argument true) run faster with two registers in
+# scratch memory than in any state without (rows_fp4.hip, PACED), the others with none.
+@pytest.mark.parametrize("instance, spilled", [("Lb0", 0), ("Lb1", 2)])
+def test_state_of_the_many_layer_kernels(instance, spilled):
+    from paper_2110_09195_amd import binding
+    binding.lib()
+    found = [k[".vgpr_spill_count"] for n, k in kernels(binding.LIB_PATH).items() if "rows_fp4_many" in n and instance in n]
+    assert found == [spilled]

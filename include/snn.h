@@ -25,7 +25,9 @@
  *     what the preparation left there.  Two calls that share a workspace must be ordered
  *     (same stream, or synchronised).
  *   - Return value: SNN_OK (0) or a negative SNN_ERR_* code.  On error nothing has been
- *     enqueued.  No exceptions, no aborts, nothing printed.
+ *     enqueued, but for SNN_ERR_LAUNCH: then part of the call's work may be on the stream (the
+ *     error is read after a launch, and may be that of a second one or of an earlier HIP call
+ *     of the thread), and outputs are not to be used.  No exceptions, no aborts, nothing printed.
  *   - Values of idx[] must be < K and values of codebook[] / w9[] must be < 512; this is
  *     not reported by the device: the table-building kernels read an index >= K as K - 1 and
  *     mask a code to 9 bits, so that only memory inside the library's own tables is ever read

@@ -88,7 +88,7 @@ def _use(L):
     from . import _marshal
     names = ("snn_subbit_conv2d", "snn_subbit_conv2d_prepared", "snn_subbit_conv2d_sign_prepared", "snn_subbit_conv1x1_prepared",
              "snn_bnn_conv2d_prepared", "snn_pack_activations", "snn_packed_bytes", "snn_project_backward", "snn_subset_update")
-    _marshal.use(snn_conv_desc, tuple(ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names))
+    _marshal.use(snn_conv_desc, SnnError, tuple(ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names))
     _lib, _fast = L, _marshal
 
 

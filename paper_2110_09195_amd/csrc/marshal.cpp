@@ -4,8 +4,10 @@
 // descriptor, pointers, the stream's handle and the conversion of nine arguments were the rest.  Here they take 0.3 us.
 //
 // A function here takes the ordinary case alone: plain torch.Tensor objects of the right type and size, on the GPU and contiguous, outputs and
-// workspace given.  It returns true if it has enqueued the call.  For anything else, and after an error status (nothing is enqueued then), it
-// returns false, and the caller goes on with its own checks, which say what is wrong.  Nothing is kept between calls.
+// workspace given.  It returns true if it has enqueued the call.  For anything else, and where the library has refused the arguments (nothing
+// is enqueued then), it returns false, and the caller goes on with its own checks, which say what is wrong.  Any other status raises here and
+// now: after SNN_ERR_LAUNCH some of the call's work may be on the stream (the error can be that of a second launch, or of some earlier
+// call on the thread), and a second call would do it twice.  Nothing is kept between calls.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -33,6 +35,7 @@ struct Library {
 };
 Library lib;
 PyTypeObject *desc_type = nullptr;
+PyObject *error_type = nullptr;              // called with the status and the function's name
 
 // Plain tensors only: subclasses have their own say in Python.
 const at::Tensor *tensor(PyObject *o) { return Py_TYPE(o) == (PyTypeObject *)THPVariableClass ? &THPVariable_Unpack(o) : nullptr; }
@@ -69,15 +72,21 @@ const at::Tensor *output(PyObject *o, const snn_conv_desc &d)
 
 void *stream() { return (void *)c10::hip::getCurrentHIPStreamMasqueradingAsCUDA().stream(); }
 
-// Whether `call` succeeds, without the interpreter's lock.
+// Makes the call, without the interpreter's lock: whether it has been enqueued.
 template <class Call>
-PyObject *enqueued(Call &&call)
+PyObject *enqueued(const char *name, Call &&call)
 {
     int status;
     Py_BEGIN_ALLOW_THREADS
     status = call();
     Py_END_ALLOW_THREADS
-    return PyBool_FromLong(status == SNN_OK);
+    if (status == SNN_OK) Py_RETURN_TRUE;
+    if (status == SNN_ERR_INVALID_ARG || status == SNN_ERR_UNSUPPORTED || status == SNN_ERR_WORKSPACE) Py_RETURN_FALSE;
+    if (PyObject *const args = Py_BuildValue("(is)", status, name)) {
+        PyErr_SetObject(error_type, args);
+        Py_DECREF(args);
+    }
+    return nullptr;
 }
 
 // What raises (a tensor without memory, say) is left to the caller, too.
@@ -102,7 +111,9 @@ PyObject *subbit_conv2d(PyObject *const *a)
     const void *const px = x->data_ptr(), *const pc = codebook->data_ptr(), *const pi = idx->data_ptr(), *const pa = alpha->data_ptr();
     void *const py = y->data_ptr(), *const pw = ws->data_ptr(), *const s = stream();
     const size_t bytes = (size_t)ws->numel();
-    return enqueued([&] { return lib.subbit_conv2d(&d, px, (const uint16_t *)pc, (const uint16_t *)pi, (const float *)pa, (float *)py, pw, bytes, s); });
+    return enqueued("snn_subbit_conv2d", [&] {
+        return lib.subbit_conv2d(&d, px, (const uint16_t *)pc, (const uint16_t *)pi, (const float *)pa, (float *)py, pw, bytes, s);
+    });
 }
 
 PyObject *subbit_conv2d_prepared(PyObject *const *a)
@@ -114,7 +125,7 @@ PyObject *subbit_conv2d_prepared(PyObject *const *a)
     const void *const px = x->data_ptr(), *const pa = alpha->data_ptr();
     void *const py = y->data_ptr(), *const pw = ws->data_ptr(), *const s = stream();
     const size_t bytes = (size_t)ws->numel();
-    return enqueued([&] { return lib.subbit_conv2d_prepared(&d, px, (const float *)pa, (float *)py, pw, bytes, s); });
+    return enqueued("snn_subbit_conv2d_prepared", [&] { return lib.subbit_conv2d_prepared(&d, px, (const float *)pa, (float *)py, pw, bytes, s); });
 }
 
 PyObject *bnn_conv2d_prepared(PyObject *const *a)
@@ -126,7 +137,7 @@ PyObject *bnn_conv2d_prepared(PyObject *const *a)
     const void *const px = x->data_ptr(), *const pa = alpha->data_ptr();
     void *const py = y->data_ptr(), *const pw = ws->data_ptr(), *const s = stream();
     const size_t bytes = (size_t)ws->numel();
-    return enqueued([&] { return lib.bnn_conv2d_prepared(&d, px, (const float *)pa, (float *)py, pw, bytes, s); });
+    return enqueued("snn_bnn_conv2d_prepared", [&] { return lib.bnn_conv2d_prepared(&d, px, (const float *)pa, (float *)py, pw, bytes, s); });
 }
 
 PyObject *subbit_conv2d_sign_prepared(PyObject *const *a)
@@ -139,7 +150,7 @@ PyObject *subbit_conv2d_sign_prepared(PyObject *const *a)
     const void *const px = x->data_ptr();
     void *const po = out->data_ptr(), *const pw = ws->data_ptr(), *const s = stream();
     const size_t bytes = (size_t)ws->numel();
-    return enqueued([&] { return lib.subbit_conv2d_sign_prepared(&d, px, po, pw, bytes, s); });
+    return enqueued("snn_subbit_conv2d_sign_prepared", [&] { return lib.subbit_conv2d_sign_prepared(&d, px, po, pw, bytes, s); });
 }
 
 PyObject *subbit_conv1x1_prepared(PyObject *const *a)
@@ -150,7 +161,7 @@ PyObject *subbit_conv1x1_prepared(PyObject *const *a)
     const void *const px = x->data_ptr();
     void *const py = y->data_ptr(), *const pw = ws->data_ptr(), *const s = stream();
     const size_t bytes = (size_t)ws->numel();
-    return enqueued([&] { return lib.subbit_conv1x1_prepared(&d, px, (float *)py, pw, bytes, s); });
+    return enqueued("snn_subbit_conv1x1_prepared", [&] { return lib.subbit_conv1x1_prepared(&d, px, (float *)py, pw, bytes, s); });
 }
 
 PyObject *pack_activations(PyObject *const *a)
@@ -169,7 +180,7 @@ PyObject *pack_activations(PyObject *const *a)
     if ((size_t)out->numel() * 4 < lib.packed_bytes(N, C, H, W, (int)layout)) Py_RETURN_FALSE;
     const void *const px = x->data_ptr();
     void *const po = out->data_ptr(), *const s = stream();
-    return enqueued([&] { return lib.pack_activations((const float *)px, po, N, C, H, W, (int)layout, s); });
+    return enqueued("snn_pack_activations", [&] { return lib.pack_activations((const float *)px, po, N, C, H, W, (int)layout, s); });
 }
 
 PyObject *project_backward(PyObject *const *a)
@@ -187,7 +198,7 @@ PyObject *project_backward(PyObject *const *a)
     const void *const pw = w->data_ptr(), *const pg = g->data_ptr(), *const pi = idx->data_ptr();
     void *const ow = g_w->data_ptr(), *const op = g_p->data_ptr(), *const pws = ws->data_ptr(), *const s = stream();
     const size_t bytes = (size_t)ws->numel();
-    return enqueued([&] {
+    return enqueued("snn_project_backward", [&] {
         return lib.project_backward((const float *)pw, (const float *)pg, (const uint16_t *)pi, n, (int)K, (float *)ow, (float *)op, pws, bytes, s);
     });
 }
@@ -204,7 +215,9 @@ PyObject *subset_update(PyObject *const *a)
     at::Tensor dup = at::empty({K}, p->options().dtype(at::kByte).requires_grad(false));
     const void *const pp = p->data_ptr();
     void *const pm = m->data_ptr(), *const pc = cb.data_ptr(), *const pd = dup.data_ptr(), *const s = stream();
-    PyObject *const ok = enqueued([&] { return lib.subset_update((const float *)pp, (int8_t *)pm, theta, (int)K, (uint16_t *)pc, (uint8_t *)pd, s); });
+    PyObject *const ok = enqueued("snn_subset_update", [&] {
+        return lib.subset_update((const float *)pp, (int8_t *)pm, theta, (int)K, (uint16_t *)pc, (uint8_t *)pd, s);
+    });
     if (ok != Py_True) return ok;
     Py_DECREF(ok);
     PyObject *const c = THPVariable_Wrap(std::move(cb)), *const u = THPVariable_Wrap(std::move(dup));
@@ -214,17 +227,21 @@ PyObject *subset_update(PyObject *const *a)
     return both;
 }
 
-// use(descriptor type, addresses of the library's functions in the order of Library)
+// use(descriptor type, type of the errors, addresses of the library's functions in the order of Library)
 PyObject *use(PyObject *, PyObject *args)
 {
-    PyObject *type;
+    PyObject *type, *error;
     unsigned long long f[9];
-    if (!PyArg_ParseTuple(args, "O!(KKKKKKKKK)", &PyType_Type, &type, f, f + 1, f + 2, f + 3, f + 4, f + 5, f + 6, f + 7, f + 8)) return nullptr;
+    if (!PyArg_ParseTuple(args, "O!O(KKKKKKKKK)", &PyType_Type, &type, &error, f, f + 1, f + 2, f + 3, f + 4, f + 5, f + 6, f + 7, f + 8))
+        return nullptr;
     static_assert(sizeof(Library) == sizeof f, "one address each");
     std::memcpy(&lib, f, sizeof f);
     Py_INCREF(type);
     Py_XDECREF(desc_type);
     desc_type = (PyTypeObject *)type;
+    Py_INCREF(error);
+    Py_XDECREF(error_type);
+    error_type = error;
     Py_RETURN_NONE;
 }
 

@@ -1,5 +1,7 @@
 """The native part of the binding takes the ordinary case of a call and nothing else: it gives what the general part gives, on the current stream, and what
 that part refuses is refused with the same error."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -103,3 +105,33 @@ def test_the_current_stream():
         got = t["y"].clone()
     side.synchronize()
     assert torch.equal(got, want)
+
+
+# position of the function's address in _marshal.use
+NATIVE = ["snn_subbit_conv2d", "snn_subbit_conv2d_prepared", "snn_subbit_conv2d_sign_prepared", "snn_subbit_conv1x1_prepared",
+          "snn_bnn_conv2d_prepared", "snn_pack_activations", "snn_packed_bytes", "snn_project_backward", "snn_subset_update"]
+
+
+@pytest.mark.parametrize("status, again", [(-4, False), (-77, False), (B.SNN_ERR_INVALID_ARG, True)])
+def test_a_failed_launch_is_reported_and_not_repeated(status, again):
+    """A library whose functions only count and fail (nothing is launched): after a refusal of the arguments the general part has its say, and
+    makes the call with the library proper; after anything else work may be on the stream already, and there is no second call."""
+    made = []
+    stub = ctypes.CFUNCTYPE(ctypes.c_int)(lambda: made.append(1) or status)          # (arguments it does not look at)
+    address = ctypes.cast(stub, ctypes.c_void_p).value
+    calls = list(_calls())
+    real = [ctypes.cast(getattr(B.lib(), n), ctypes.c_void_p).value for n in NATIVE]
+    try:
+        for name, args, _ in calls:
+            B._fast.use(B.snn_conv_desc, B.SnnError, tuple(address if n == name else r for n, r in zip(NATIVE, real)))
+            made.clear()
+            if again:
+                getattr(B, name)(*args)
+            else:
+                with pytest.raises(B.SnnError) as e:
+                    getattr(B, name)(*args)
+                assert e.value.status == status and name in str(e.value)
+            assert made == [1], name
+    finally:
+        B._use(B.lib())
+    torch.cuda.synchronize()

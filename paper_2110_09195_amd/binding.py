@@ -7,12 +7,12 @@ first call raises.
 """
 import ctypes
 import os
+import warnings
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsnn_hip.so")
-MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 
 SNN_OK = 0
 SNN_ERR_INVALID_ARG = -1
@@ -85,7 +85,13 @@ _fast = None            # the module _marshal (csrc/marshal.cpp), which takes th
 def _use(L):
     """Loaded library -> what the calls below go to."""
     global _lib, _fast
-    from . import _marshal
+    try:
+        from . import _marshal
+    except ImportError as e:        # (not built, or for another torch: host code alone, every call goes through the code below)
+        warnings.warn("the native part of the binding does not load (%s): calls of small layers take the longer way from Python; "
+                      "`python -m paper_2110_09195_amd.build` builds it" % e, RuntimeWarning, stacklevel=3)
+        _lib, _fast = L, None
+        return
     names = ("snn_subbit_conv2d", "snn_subbit_conv2d_prepared", "snn_subbit_conv2d_sign_prepared", "snn_subbit_conv1x1_prepared",
              "snn_bnn_conv2d_prepared", "snn_pack_activations", "snn_packed_bytes", "snn_project_backward", "snn_subset_update")
     _marshal.use(snn_conv_desc, SnnError, tuple(ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names))
@@ -95,10 +101,9 @@ def _use(L):
 def lib():
     """Load libsnn_hip.so (built by `python -m paper_2110_09195_amd.build`)."""
     if _lib is None:
-        for path in (LIB_PATH, MARSHAL_PATH):
-            if not os.path.exists(path):
-                raise RuntimeError("HIP library not built: %s is missing; run "
-                                   "`python -m paper_2110_09195_amd.build` (there is no CPU fallback)" % path)
+        if not os.path.exists(LIB_PATH):
+            raise RuntimeError("HIP library not built: %s is missing; run "
+                               "`python -m paper_2110_09195_amd.build` (there is no CPU fallback)" % LIB_PATH)
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
         dp = ctypes.POINTER(snn_conv_desc)

@@ -2,6 +2,7 @@
 import ctypes
 import os
 import re
+import sys
 
 import pytest
 
@@ -207,3 +208,18 @@ def test_a_workspace_holds_the_tables_of_one_form(L):
     d = B.make_desc(1, 1024, 1024, 1, 1, 1, 32, rows)
     assert B.snn_workspace_bytes(d, B.SNN_WS_SUBBIT) > 4 << 20
     assert L.snn_subbit_conv2d_noalloc(ctypes.byref(d), p, p, p, p, p, None) == B.SNN_ERR_WORKSPACE
+
+
+def test_the_binding_loads_without_its_native_part(L, monkeypatch):
+    """Only a shortcut for the host: without it the library serves every call, and a warning says that it is missing."""
+    with monkeypatch.context() as mp:
+        mp.setitem(sys.modules, "paper_2110_09195_amd._marshal", None)
+        mp.delattr("paper_2110_09195_amd._marshal", raising=False)
+        mp.setattr(binding, "_lib", None)
+        mp.setattr(binding, "_fast", binding._fast)
+        with pytest.warns(RuntimeWarning, match="native part of the binding"):
+            assert binding.status_string(0) == "SNN_OK"
+        assert binding._fast is None
+        with pytest.raises(TypeError):
+            binding.snn_subset_update(None, None, 0.0)
+    assert binding._fast is not None

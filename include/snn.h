@@ -358,11 +358,14 @@ int snn_subbit_forward_sign(const snn_conv_desc *desc, const void *x_packed, con
  *   g_w[c][t] = g_wbar[c][t] if -1 < w[c][t] < 1 else 0       (Eq. 3, straight-through estimator, per element)
  *   g_p[k][t] = sum over the kernels c with idx[c] == k of g_wbar[c][t]
  *               (the gradient of the subset tensor p, taken as that of its sign memory m:
- *                backward of Eq. 5 / the p-update of Alg. 1); summed in fp32, per block of 512
- *                kernels in unspecified order (LDS float atomics), the block sums then in a fixed
- *                order: g_p can differ in its last bits from run to run on the same input
+ *                backward of Eq. 5 / the p-update of Alg. 1); summed in fp32.  For K <= 64, and for any K up to
+ *                5120 kernels with outputs apart from inputs, the order is fixed; else kernels of a block are
+ *                added in unspecified order (LDS float atomics) and g_p can differ in its last bits from
+ *                run to run on the same input
  *   w, g_wbar  device, float [n][9];  idx  device, uint16 [n], values < K (as snn_project_kernels wrote them)
  *   g_w        device, float [n][9], fully overwritten;  g_p  device, float [K][9], fully overwritten
+ *              g_w may be g_wbar or w (in place), and g_p may lie over an input; sums of the same values can then be
+ *              added in another order than with outputs apart, and round differently
  *   workspace  device, >= snn_project_backward_workspace_bytes(n, K) bytes, 256-byte aligned (non-decreasing in n
  *              and K: the workspace of a network's largest layer serves every smaller one)
  * n = 0 is allowed (g_p = 0).  Errors: INVALID_ARG; WORKSPACE; LAUNCH.

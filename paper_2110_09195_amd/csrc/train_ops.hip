@@ -369,9 +369,15 @@ int launch_project_backward(const float *w, const float *g_wbar, const uint16_t 
     // instead of four is 4 % faster on large blocks, and its error on skewed indices 1.4 times as large (1.7e-7 for 1.2e-7).
     const bool product = K <= 64 || (K <= 128 && n <= TB_ONE_MAX);
     const bool large = !product && (n > TB_ONE_MAX || n * K > ((int64_t)5 << 20));
-    // (in place, g_w over g_wbar, a block of the one launch would read what another has written)
-    const bool apart = (uintptr_t)g_w + (size_t)n * 36 <= (uintptr_t)g_wbar || (uintptr_t)g_wbar + (size_t)n * 36 <= (uintptr_t)g_w;
-    if (n > 0 && n <= TM_MAX && apart) {
+    // Blocks of the one launch read what others may have written by then if g_w lies over g_wbar (in place) or g_p over an input: the two
+    // launches write g_p when all inputs have been read, and g_w where the same block has read g_wbar.
+    auto apart = [](const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
+        return (uintptr_t)a + a_bytes <= (uintptr_t)b || (uintptr_t)b + b_bytes <= (uintptr_t)a;
+    };
+    const size_t bytes = (size_t)n * 36, p_bytes = (size_t)K * 36;
+    const bool in_order = apart(g_w, bytes, g_wbar, bytes) && apart(g_w, bytes, idx, (size_t)n * 2) && apart(g_p, p_bytes, w, bytes) &&
+                          apart(g_p, p_bytes, g_wbar, bytes) && apart(g_p, p_bytes, idx, (size_t)n * 2);
+    if (n > 0 && n <= TM_MAX && in_order) {
         const bool vec = ((((uintptr_t)w) | ((uintptr_t)g_wbar) | ((uintptr_t)g_w)) & 15u) == 0;
         const unsigned grid = (unsigned)(K + (n * 9 + 4 * TM_THREADS - 1) / (4 * TM_THREADS));
         hipLaunchKernelGGL(project_backward_members_kernel, dim3(grid), dim3(TM_THREADS), 0, s, w, g_wbar, idx, (int)n, K, g_w, g_p, vec ? 1 : 0);

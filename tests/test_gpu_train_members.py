@@ -58,3 +58,20 @@ def test_in_place(oracle, n):
     _, p = B.snn_project_backward(G.dev(w), g, G.dev(idx.astype(np.uint16)), 32, g_w=g)
     assert (g.cpu().numpy() == ref_w).all()
     assert np.abs(p.cpu().numpy() - ref_p).max() <= 1e-4 * np.abs(ref_p).max()
+
+
+@pytest.mark.parametrize("over", ["w", "g_wbar"])
+@pytest.mark.parametrize("n, K", [(200, 32), (4096, 512), (8192, 40)])
+def test_sums_over_an_input(oracle, n, K, over):
+    """g_p in the last rows of an input, which it may take over: every sum is of the values that were there."""
+    w, gw, idx = _inputs(n, K, "geometric")
+    ref_w, ref_p = oracle.project_backward(w, gw, idx, K)
+    t = {"w": G.dev(w), "g_wbar": G.dev(gw)}
+    rows = min(n, K)
+    place = torch.empty((n + K - rows, 9), device="cuda")
+    place[:n] = t[over]
+    t[over] = place[:n]
+    p = place[n - rows:n - rows + K]
+    g_w, _ = B.snn_project_backward(t["w"], t["g_wbar"], G.dev(idx.astype(np.uint16)), K, g_p=p)
+    assert (g_w.cpu().numpy() == ref_w).all()
+    assert np.abs(p.cpu().numpy() - ref_p).max() <= 1e-4 * np.abs(ref_p).max()

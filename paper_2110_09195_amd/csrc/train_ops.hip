@@ -272,7 +272,8 @@ void project_backward_members_kernel(const float *__restrict__ w, const float *_
         if (hit) mine[found + (int)__popcll(hits & ((1ull << lane) - 1ull))] = (uint16_t)(i * TM_THREADS + tid);
         found += (int)__popcll(hits);
     }
-    // (the wave's own piece: what it wrote it reads back in order)
+    // The wave's own piece: LDS gives a wave back in order what it has written.  The compiler knows that of a lane's own words alone.
+    __builtin_amdgcn_wave_barrier();
     float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};                   // four chains: a quarter of the roundings in a row
     if (entry < 7) {
         int e = entry;

@@ -358,7 +358,7 @@ int snn_subbit_forward_sign(const snn_conv_desc *desc, const void *x_packed, con
  *   g_w[c][t] = g_wbar[c][t] if -1 < w[c][t] < 1 else 0       (Eq. 3, straight-through estimator, per element)
  *   g_p[k][t] = sum over the kernels c with idx[c] == k of g_wbar[c][t]
  *               (the gradient of the subset tensor p, taken as that of its sign memory m:
- *                backward of Eq. 5 / the p-update of Alg. 1); summed in fp32.  For K <= 64, and for any K up to
+ *                backward of Eq. 5 / the p-update of Alg. 1); summed in fp32.  For K <= 64 (finite g_wbar), and for any K up to
  *                5120 kernels with outputs apart from inputs, the order is fixed; else kernels of a block are
  *                added in unspecified order (LDS float atomics) and g_p can differ in its last bits from
  *                run to run on the same input

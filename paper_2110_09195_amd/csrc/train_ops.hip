@@ -222,15 +222,24 @@ void project_backward_large_kernel(const float *__restrict__ w, const float *__r
     store_copies(lds, copies, K9, partial + (int64_t)blockIdx.x * K9);
 }
 
-// Both gradients of up to TM_MAX kernels in one launch: block k < K sums the gradients of member k's kernels, the blocks behind them write g_w.
+// Both gradients of few kernels in one launch: block k < K sums the gradients of member k's kernels, the blocks behind them write g_w.
 // A member's block reads all indices, which is what bounds it (a quarter of a microsecond per 1024); a wave keeps the numbers of those that are
 // k in a piece of LDS of its own (in order, so that the sum is the same from run to run) and adds their gradients, seven kernels of
-// nine taps at a time.  No partial sums pass through memory, and no second launch waits for them: per call, two launches -> one, on the
-// GPU alone (and with the host's share), us, K = 32: 144 kernels 5.4 -> 2.8 (9.5 -> 6.5), 4096 5.8 -> 4.2 (9.7 -> 6.6), 8192 6.0 -> 6.1 (9.6 -> 6.6),
-// 16384 6.3 -> 9.9 (9.4 -> 9.5); K = 4 4096 5.2 -> 4.6, 8192 5.3 -> 6.9; K = 512 4096 8.6 -> 4.6, 8192 10.8 -> 6.1.
+// nine taps at a time.  No partial sums pass through memory, and no second launch waits for them.  Two launches -> one, us, replayed from a
+// graph (from Python, call by call), indices even over the members / skewed as in trained layers (Zipf 1.1):
+//   K = 4   1024 kernels 4.5 -> 2.5 (6.0 -> 3.4) / the same       4096 4.8 -> 3.9 (6.3 -> 4.1) / 4.8 -> 4.2 (6.2 -> 4.3)
+//           5120 4.8 -> 4.3 (6.2 -> 4.4) / 4.9 -> 4.9 (6.2 -> 5.0)   8192 5.0 -> 5.6 (6.3 -> 5.7) / 5.1 -> 6.4 (6.2 -> 6.4)
+//   K = 8   4096 4.8 -> 3.4 (6.3 -> 3.6) / 4.8 -> 4.1 (6.3 -> 4.1)   8192 5.1 -> 4.9 (6.3 -> 5.0) / 5.1 -> 6.0 (6.2 -> 6.0)
+//   K = 16  8192 5.2 -> 4.1 (6.3 -> 4.2) / 5.2 -> 5.7 (6.2 -> 5.8)   K = 32  8192 5.6 -> 3.9 (6.3 -> 4.0) / 5.6 -> 5.6 (6.1 -> 5.6)
+//   K = 512 4096 8.0 -> 3.8 (8.4 -> 3.8) / 8.0 -> 4.1 (8.3 -> 4.1)   8192 10.0 -> 4.5 (10.4 -> 4.5) / 10.0 -> 5.5 (10.4 -> 5.5)
+// The block of the most frequent member is the longest.  Hence the lines: 5120 kernels of fewer than eight members, above which
+// skewed indices are slower from Python too, and 8192, what the lanes' indices hold, of more: between 8 and 31 members skewed indices are up to a
+// sixth slower there in a graph (even ones up to a fifth faster) and both are faster from Python.  (All of 8192 kernels in one of
+// 32 members: 5.7 -> 6.5 and 6.3 -> 6.6; 16384 kernels would take 9.9 for 6.3.)  Error of the sums against 64 bits, K = 4 to 32:
+// 8.2e-8 to 1.0e-7 -> 7.8e-8 to 9.8e-8.
 constexpr int TM_THREADS = 1024, TM_WAVES = TM_THREADS / 64;
 constexpr int TM_SCAN = 8;                           // indices that a lane looks at
-constexpr int TM_MAX = TM_THREADS * TM_SCAN;
+constexpr int TM_MAX = TM_THREADS * TM_SCAN, TM_MAX_FEW = 5120;      // kernels; of fewer than eight members
 
 __global__ __launch_bounds__(TM_THREADS)
 void project_backward_members_kernel(const float *__restrict__ w, const float *__restrict__ g_wbar, const uint16_t *__restrict__ idx, int n, int K,
@@ -378,7 +387,7 @@ int launch_project_backward(const float *w, const float *g_wbar, const uint16_t 
     const size_t bytes = (size_t)n * 36, p_bytes = (size_t)K * 36;
     const bool in_order = apart(g_w, bytes, g_wbar, bytes) && apart(g_w, bytes, idx, (size_t)n * 2) && apart(g_p, p_bytes, w, bytes) &&
                           apart(g_p, p_bytes, g_wbar, bytes) && apart(g_p, p_bytes, idx, (size_t)n * 2);
-    if (n > 0 && n <= TM_MAX && in_order) {
+    if (n > 0 && n <= (K < 8 ? TM_MAX_FEW : TM_MAX) && in_order) {
         const bool vec = ((((uintptr_t)w) | ((uintptr_t)g_wbar) | ((uintptr_t)g_w)) & 15u) == 0;
         const unsigned grid = (unsigned)(K + (n * 9 + 4 * TM_THREADS - 1) / (4 * TM_THREADS));
         hipLaunchKernelGGL(project_backward_members_kernel, dim3(grid), dim3(TM_THREADS), 0, s, w, g_wbar, idx, (int)n, K, g_w, g_p, vec ? 1 : 0);

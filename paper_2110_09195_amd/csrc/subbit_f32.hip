@@ -650,31 +650,6 @@ SdPlan sd_plan(const Geom &g)
     return p;
 }
 
-// Whether the pieces are the faster way: rows that fit six loads (two workgroups of a compute unit then have their LDS) and more channels than
-// half of the sixteen that a step takes.  us, fp32 unit -> pieces, K = 32: 12 -> 12 8x8 batch 256 6.7 -> 5.8, 28x28 batch 200 22.6 -> 18.4;
-// 8 -> 32 8x8 batch 256 6.25 -> 5.96, 28x28 batch 200 18.7 -> 19.0, 4 -> 16 14.1 -> 18.3, 1 -> 8 12.4 -> 18.4.  With ten loads (one workgroup to
-// a compute unit) 64 -> 64 56x56 batch 32 100 -> 95, 16 -> 16 batch 64 35 -> 49, 14x53 batch 8 12.3 -> 16.6.
-bool sd_split(const Geom &g) { return g.C_in > 8 && sd_loads(g) <= 6; }
-
-struct SdSplit {
-    int CB;                      // blocks of 32 output channels of a wave
-    bool four;                   // four waves split the channels of a block
-    int64_t blocks;
-};
-
-// Two blocks of output channels read each piece for two products; one, and the channels split over four waves, where that leaves SIMDs
-// without a wave (2 -> 1 blocks, us: 512 -> 21 6x6 batch 231 37.6 -> 27.4, 64 -> 64 8x8 batch 8 7.5 -> 5.7; one wave -> four: 24 -> 64 13x13
-// batch 64 11.4 -> 8.6; of few channels and many blocks four waves have nothing to do).
-SdSplit sd_split_plan(const Geom &g, int n_cob)
-{
-    const int64_t px = (g.P + 31) / 32, octs = (g.C_in + 15) / 16;
-    SdSplit s;
-    s.CB = n_cob >= 2 && px * ((n_cob + 1) / 2) * (octs >= 4 ? 4 : 1) >= 1024 ? 2 : 1;
-    s.blocks = px * ((n_cob + s.CB - 1) / s.CB);
-    s.four = octs >= 4 || (octs >= 2 && s.blocks < 1024);
-    return s;
-}
-
 bool use_dense(const Geom &g)
 {
     if (tuning(SNN_TUNE_F32_WAVES) != SNN_TUNE_AUTO) return false;
@@ -684,18 +659,17 @@ bool use_dense(const Geom &g)
     if (g.C_out > 512 || images * g.C_in * g.H * g.W * 4 >= lim || images * g.C_out * g.HoWo * 4 >= lim || g.P >= lim ||
         sd_plan(g).n_blocks >= lim || (int64_t)sd_plan(g).n_cob * sd_plan(g).quads * 256 >= lim)
         return false;
-    // Nine fp32 multiply-adds per output channel against nine per subset member and a gather: the two-stage form is left the
-    // small subsets with few output channels.  Measured, two-stage (its best workgroup) -> dense, prepared weights, us:
-    // 64 -> 64 8x8 batch 256 K = 4 15.1 -> 20, K = 16 21.0 -> 20.2, K = 32 25.5 -> 20.1, K = 64 49.6 -> 19.4;
-    // 16 -> 16 32x32 batch 128 K = 4 16.8 -> 20.8, K = 16 24.7 -> 20.7; 16 -> 256 56x56 batch 4 K = 4 26.1 -> 20.0;
-    // 512 -> 512 7x7 batch 8 K = 4 217 -> 36, K = 32 323 -> 36.  Relative error of the sums against 64 bits: 1.0e-7 for
-    // 1.6e-7 at 64 channels, 2.2e-7 for 4.1e-7 at 512.
     // In pieces (sd_split) it is the faster one at every K: K = 4 64 -> 64 8x8 batch 256 19.8 -> 11.7 (one call), 16 -> 16 32x32 batch 128 21.9 -> 15.6,
     // 12 -> 12 28x28 batch 200 20.7 -> 18.3.
-    // On the fp32 unit that error is why K >= 16 is the whole rule: where 64 pixels' responses are shared by 33 to 128 output channels and the pixels fill
-    // the chip (16384 and more), the two-stage form is the faster one up to K = 32: 64 -> 128 8x8 batch 256 K = 16 28.8 -> 34.8, 32x32
-    // batch 64 K = 16 89 -> 129, K = 32 104 -> 129; 64 -> 64 32x32 batch 64 K = 16 61 -> 67, K = 24 70 -> 67; also 64 -> 256 K = 16
-    // 212 -> 255, K = 4 189 -> 254.
+    // On the fp32 unit nine multiply-adds per output channel stand against nine per subset member and a gather: the two-stage form is left
+    // the small subsets with few output channels.  Measured on layers that the pieces do not take, two-stage (its best workgroup) -> dense, prepared
+    // weights, us: 8 -> 8 56x56 batch 32 K = 8 11.1 -> 12.7, K = 15 13.0 -> 12.6, K = 32 18.7 -> 12.6; 16 -> 16 56x56 batch 32 K = 8 16.8 -> 18.9,
+    // K = 16 21.5 -> 18.9; 64 -> 64 56x56 batch 32 K = 8 87 -> 99, K = 16 97 -> 99, K = 32 135 -> 99; 512 -> 512 7x7 batch 8 K = 4 217 -> 36 (C_out).
+    // (Eight channels and fewer to 32 and more are faster here at every K, 3 -> 64 56x56 batch 32 K = 8 30 -> 18.)
+    // Relative error of the sums against 64 bits: 1.0e-7 for 1.6e-7 at 64 channels, 2.2e-7 for 4.1e-7 at 512.  That error is why K >= 16 is the
+    // whole rule: where 64 pixels' responses are shared by 33 to 128 output channels and the pixels fill the chip, the two-stage form
+    // is the faster one up to K = 32, 64 -> 128 56x56 batch 32 K = 16 145 -> 190, K = 32 169 -> 189, 14x53 batch 64 K = 16 86 -> 95; so it is for
+    // 128 -> 200, 56x56 batch 32 K = 16 554 -> 585.
     return g.K >= 16 || g.C_out >= 256 || sd_split(g);
 }
 
@@ -714,10 +688,11 @@ int launch_subbit_f32(const Geom &g, const void *x, const uint16_t *codebook, co
 {
     if (use_dense(g)) {
         const SdPlan p = sd_plan(g);
-        const bool split = p.quads >= 4;
+        const bool split = p.quads >= 4, pieces = sd_split(g);
         const int64_t n_wgs = split ? p.n_blocks : (p.n_blocks + 3) / 4;
-        const int staged = sd_staged(g, p.quads, p.n_blocks);
-        const bool look_up = phases == SNN_PHASE_BOTH && sd_looks_up(staged, p.quads, n_wgs);
+        const int staged = sd_staged(g);
+        const SdSplit sp = sd_split_plan(g);
+        const bool look_up = phases == SNN_PHASE_BOTH && (pieces ? sd_pieces_look_up(g, sp) : sd_looks_up(g, staged, p.quads, n_wgs));
         if ((phases & SNN_PHASE_PREPARE) && !look_up) {
             const int words = p.n_cob * p.quads * 256;
             hipLaunchKernelGGL(subbit_f32_dense_prep_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, codebook, idx, g.C_in, g.C_out,
@@ -726,20 +701,18 @@ int launch_subbit_f32(const Geom &g, const void *x, const uint16_t *codebook, co
             if (rc != SNN_OK) return rc;
         }
         if (!(phases & SNN_PHASE_CONVOLVE)) return SNN_OK;
-        if (sd_split(g)) {
-            const SdSplit sp = sd_split_plan(g, p.n_cob);
-            const int64_t loads = sd_loads(g);
+        if (pieces) {
             auto pick_split = [&](auto nl, auto cb) {
                 constexpr int NL = decltype(nl)::value, CB = decltype(cb)::value;
                 if (look_up) return sp.four ? subbit_f32_split_kernel<4, CB, NL, true> : subbit_f32_split_kernel<1, CB, NL, true>;
                 return sp.four ? subbit_f32_split_kernel<4, CB, NL, false> : subbit_f32_split_kernel<1, CB, NL, false>;
             };
             auto pick_loads = [&](auto cb) {
-                return loads <= 3   ? pick_split(std::integral_constant<int, 3>{}, cb)
-                       : loads == 4 ? pick_split(std::integral_constant<int, 4>{}, cb) : pick_split(std::integral_constant<int, 6>{}, cb);
+                return sp.loads == 3   ? pick_split(std::integral_constant<int, 3>{}, cb)
+                       : sp.loads == 4 ? pick_split(std::integral_constant<int, 4>{}, cb) : pick_split(std::integral_constant<int, 6>{}, cb);
             };
             const auto kern = sp.CB == 2 ? pick_loads(std::integral_constant<int, 2>{}) : pick_loads(std::integral_constant<int, 1>{});
-            hipLaunchKernelGGL(kern, dim3((unsigned)(sp.four ? sp.blocks : (sp.blocks + 3) / 4)), dim3(256), 0, s, (const float *)x, (const uint32_t *)ws,
+            hipLaunchKernelGGL(kern, dim3((unsigned)sp.n_wgs), dim3(256), 0, s, (const float *)x, (const uint32_t *)ws,
                                alpha, y, g, p.n_cob, p.quads, (uint32_t)sp.blocks, sd_rows(g), SdIndexed{codebook, idx, g.K});
             return check_launch();
         }

@@ -36,18 +36,22 @@ extern "C" long long bad_pixels(int N, int H, int W, int stride, long long blk)
     }
     return bad;
 }
-extern "C" int staged(int N, int C_in, int C_out, int H, int W, int stride)
+// loads of the instance that runs, or -1 if the rows do not fit them; pieces: 100 more for each block of output channels of a wave, 1000 for four waves
+extern "C" int loads(int N, int C_in, int C_out, int H, int W, int stride)
 {
     const Geom g = make_geom({N, C_in, C_out, H, W, stride, 32, SNN_ACT_F32});
-    const int s = sd_staged(g, (C_in + 7) / 8, (g.P + 31) / 32 * ((C_out + 31) / 32));
-    return s == 0 || s >= sd_loads(g) ? s : -1;
+    const SdSplit s = sd_split_plan(g);
+    const int n = sd_split(g) ? s.loads : sd_staged(g);
+    if (n != 0 && n < sd_loads(g)) return -1;
+    return sd_split(g) ? 1000 * s.four + 100 * s.CB + n : n;
 }
 extern "C" int looks_up(int N, int C_in, int C_out, int H, int W, int stride)
 {
     const Geom g = make_geom({N, C_in, C_out, H, W, stride, 32, SNN_ACT_F32});
+    if (sd_split(g)) return sd_pieces_look_up(g, sd_split_plan(g));
     const int quads = (C_in + 7) / 8;
     const int64_t n_blocks = (g.P + 31) / 32 * ((C_out + 31) / 32);
-    return sd_looks_up(sd_staged(g, quads, n_blocks), quads, quads < 4 ? (n_blocks + 3) / 4 : n_blocks);
+    return sd_looks_up(g, sd_staged(g), quads, quads < 4 ? (n_blocks + 3) / 4 : n_blocks);
 }
 extern "C" long long blocks(int N, int H, int W, int stride)
 {
@@ -72,7 +76,7 @@ def host(tmp_path_factory):
         f.restype = ctypes.c_longlong
     L.bad_pixels.argtypes = [ctypes.c_int] * 4 + [ctypes.c_longlong]
     L.blocks.argtypes = [ctypes.c_int] * 4
-    L.staged.argtypes = L.looks_up.argtypes = [ctypes.c_int] * 6
+    L.loads.argtypes = L.looks_up.argtypes = [ctypes.c_int] * 6
     return L
 
 
@@ -88,21 +92,28 @@ def test_every_tap_is_found(host, case):
         assert host.bad_pixels(N, H, W, stride, blk) == 0, (case, blk)
 
 
-# rows that LDS is the slower way for stay with the loads straight from memory; either side of each line of the rule
-@pytest.mark.parametrize("case, loads", [((256, 64, 64, 8, 8, 1), 3), ((1, 3, 5, 3, 5, 1), 3), ((16, 64, 64, 16, 16, 1), 4), ((64, 64, 64, 16, 16, 1), 4),
-                                         ((65, 64, 64, 16, 16, 1), 0), ((256, 24, 64, 16, 16, 1), 4), ((64, 64, 64, 28, 28, 1), 0),
-                                         ((2, 16, 16, 28, 28, 1), 0), ((256, 64, 64, 10, 25, 1), 0), ((256, 128, 128, 8, 8, 2), 6),
-                                         ((256, 128, 128, 7, 7, 2), 0), ((4, 64, 64, 16, 16, 2), 0), ((1, 512, 512, 56, 56, 1), 0),
-                                         ((1, 512, 64, 32, 32, 1), 6), ((1, 512, 65, 32, 32, 1), 6), ((1, 512, 160, 32, 32, 1), 0),
-                                         ((1, 33, 20, 28, 28, 1), 0), ((64, 512, 64, 1, 1, 1), 0)])
-def test_rows_go_through_lds_only_where_that_is_faster(host, case, loads):
-    assert host.staged(*case) == loads
+# which kernel, and its instance: either side of each line.  Eight channels and fewer: rows through LDS (3, 4, 6) or straight from memory (0); more: in
+# pieces while the rows fit six loads, always through LDS
+@pytest.mark.parametrize("case, loads", [((1, 3, 5, 3, 5, 1), 3), ((256, 8, 64, 8, 8, 1), 3), ((64, 8, 64, 16, 16, 1), 4), ((256, 1, 8, 14, 14, 1), 4),
+                                         ((64, 8, 64, 28, 28, 1), 0), ((256, 8, 128, 8, 8, 2), 6), ((256, 8, 128, 7, 7, 2), 0), ((64, 8, 64, 1, 1, 1), 0),
+                                         ((1, 512, 512, 56, 56, 1), 0), ((32, 16, 16, 56, 56, 1), 0), ((4, 64, 64, 8, 8, 2), 1106), ((4, 64, 64, 16, 16, 2), 0),
+                                         ((9, 9, 32, 35, 35, 1), 106),
+                                         ((9, 9, 32, 39, 39, 1), 0), ((256, 64, 64, 8, 8, 1), 1203), ((127, 64, 64, 8, 8, 1), 1103), ((128, 64, 64, 8, 8, 1), 1203),
+                                         ((1, 16, 5, 3, 5, 1), 103), ((16, 64, 64, 16, 16, 1), 1104), ((256, 24, 64, 16, 16, 1), 204),
+                                         ((64, 24, 64, 13, 13, 1), 1104), ((256, 128, 128, 8, 8, 2), 1206), ((1, 512, 64, 32, 32, 1), 1106)])
+def test_kernel_and_loads(host, case, loads):
+    assert host.loads(*case) == loads
 
 
-@pytest.mark.parametrize("case, yes", [((256, 64, 64, 8, 8, 1), 1), ((257, 64, 64, 8, 8, 1), 0), ((20, 128, 128, 13, 13, 1), 0), ((8, 128, 128, 14, 14, 1), 1),
-                                       ((40, 64, 64, 14, 14, 1), 1), ((8, 64, 64, 28, 28, 1), 1), ((64, 64, 64, 28, 28, 1), 0),
-                                       ((1, 512, 64, 56, 56, 1), 0), ((1, 128, 128, 37, 53, 1), 1), ((1, 256, 256, 32, 32, 1), 1),
-                                       ((2, 256, 256, 32, 32, 1), 0), ((128, 3, 64, 28, 28, 1), 1), ((256, 3, 64, 28, 28, 1), 0),
-                                       ((256, 64, 64, 16, 16, 2), 0)])
+@pytest.mark.parametrize("case, yes", [
+    # pieces: workgroups and steps of a wave, one or two blocks of output channels, rows of indices of whole 32 bytes or others
+    ((64, 64, 64, 8, 8, 1), 1), ((128, 64, 64, 8, 8, 1), 0), ((256, 64, 64, 8, 8, 1), 0), ((256, 32, 32, 8, 8, 1), 1), ((257, 32, 32, 8, 8, 1), 0),
+    ((33, 96, 96, 8, 8, 1), 1), ((50, 128, 64, 8, 8, 1), 1), ((65, 128, 64, 8, 8, 1), 0), ((1, 256, 256, 8, 8, 1), 0),
+    ((133, 40, 96, 8, 8, 1), 1), ((125, 100, 60, 8, 8, 1), 1), ((127, 100, 60, 8, 8, 1), 1), ((129, 100, 60, 8, 8, 1), 0), ((64, 200, 60, 8, 8, 1), 1),
+    ((64, 300, 60, 8, 8, 1), 0), ((2048, 9, 32, 8, 8, 1), 1), ((2049, 9, 32, 8, 8, 1), 0), ((256, 60, 64, 8, 8, 1), 1), ((257, 60, 64, 8, 8, 1), 0),
+    # the fp32 unit
+    ((512, 8, 128, 8, 8, 1), 1), ((513, 8, 128, 8, 8, 1), 0), ((256, 8, 128, 16, 16, 2), 1), ((257, 8, 128, 16, 16, 2), 0), ((167, 3, 64, 28, 28, 1), 1),
+    ((256, 3, 64, 28, 28, 1), 0), ((20, 16, 64, 56, 56, 1), 1), ((21, 16, 64, 56, 56, 1), 0), ((1, 128, 128, 37, 53, 1), 1), ((1, 512, 64, 56, 56, 1), 0),
+    ((1, 256, 256, 37, 53, 1), 0)])
 def test_codes_are_looked_up_only_where_that_is_faster(host, case, yes):
     assert host.looks_up(*case) == yes

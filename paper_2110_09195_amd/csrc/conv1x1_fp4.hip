@@ -175,9 +175,9 @@ void conv1x1_fp4_kernel(const C1Layer L)
         if ((cob0 + CB) * 32 <= L.C_out) store(policy, std::true_type{});
         else store(policy, std::false_type{});
     };
-    if (L.policy == FP4_STORE_NT) store_under(std::integral_constant<int, 2>{});
-    else if (L.policy == FP4_STORE_THROUGH) store_under(std::integral_constant<int, 16>{});
-    else store_under(std::integral_constant<int, 0>{});
+    if (L.policy == FP4_STORE_NT) store_under(std::integral_constant<int, AUX_NT>{});
+    else if (L.policy == FP4_STORE_THROUGH) store_under(std::integral_constant<int, AUX_THROUGH>{});
+    else store_under(std::integral_constant<int, AUX_CACHED>{});
 }
 
 // Indices -> bit planes: a thread makes the word of (output channel, 32 input channels), bit i of which is channel i.

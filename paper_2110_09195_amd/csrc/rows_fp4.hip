@@ -840,9 +840,9 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
             }
         }
     };
-    if (PACED || L.policy == FP4_STORE_NT) store(std::integral_constant<int, 2>{});
-    else if (TASKS == 4 && L.policy == FP4_STORE_THROUGH) store(std::integral_constant<int, 16>{});   // (never in a launch of several layers)
-    else store(std::integral_constant<int, 0>{});
+    if (PACED || L.policy == FP4_STORE_NT) store(std::integral_constant<int, AUX_NT>{});
+    else if (TASKS == 4 && L.policy == FP4_STORE_THROUGH) store(std::integral_constant<int, AUX_THROUGH>{});   // (never in a launch of several layers)
+    else store(std::integral_constant<int, AUX_CACHED>{});
 }
 
 template <int PB, int CB, bool SIGN, bool CHANNELS, bool INDEXED>

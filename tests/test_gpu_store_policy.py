@@ -31,7 +31,7 @@ def same(y, L):
     return bool((got[0::2] == L["want"][0]).all()) and bool((got[1::2] == L["want"][1]).all())
 
 
-# planes of whole lines, half lines, 16 bytes and less; outputs on both sides of 96, 144 and 32 MB
+# planes of whole lines, half lines and neither; outputs of the first two on both sides of 96 and 144 MB
 @pytest.mark.parametrize("case", [(2, 16, 40, 16, 16), (125, 32, 64, 56, 56), (129, 32, 64, 56, 56), (3, 16, 40, 28, 28), (377, 16, 128, 28, 28),
                                   (379, 16, 128, 28, 28), (5, 16, 40, 14, 14), (170, 16, 256, 14, 14), (174, 16, 256, 14, 14), (9, 16, 40, 13, 13),
                                   (65, 16, 40, 3, 5)])

@@ -73,10 +73,11 @@ __host__ __device__ inline uint32_t code_to_window_order(uint32_t code)
     return r;
 }
 
-// Division by a divisor fixed per layer (1 <= d < 2^31) of numerators below 2^31: q = mulhi(n, mul) >> shift with
-// mul = floor(2^(31 + s) / d) + 1, s = ceil(log2 d), shift = s - 1 (exact: mul * d - 2^(31 + s) is in (0, 2^s]);
-// d = 1 is mul = 0.  The kernel's per-tile set-up is a dozen divisions by H_out * W_out, W_out, H and the
-// number of channel tiles; the generic sequence costs forty instructions each.
+// Division by a divisor fixed per layer (1 <= d < 2^31) of numerators below 2^31: q = mulhi(2 n, mul) >> s with
+// s = ceil(log2 d), mul = floor(2^(31 + s) / d) + 1 < 2^32.  Exact: mul * d - 2^(31 + s) is in (0, d], so that n mul / 2^(31 + s) is past
+// n / d by at most n / 2^(31 + s) < 1 / d.  The shift is 0 for d = 1 (mul = 2^31 + 1) and no other.  Of 2 n, which fits 32 bits, so that
+// a divisor of one is no case apart: at the start of a workgroup's life a branch costs more than a shift.  The kernel's per-tile set-up is a
+// dozen divisions by H_out * W_out, W_out, H and the number of channel tiles; the generic sequence costs forty instructions each.
 struct Divisor {
     uint32_t mul, shift;
 };
@@ -84,11 +85,11 @@ struct Divisor {
 inline Divisor make_divisor(uint32_t d)
 {
     uint32_t s = 0;
+    if (d == 0) d = 1;                                         // (nobody's divisor: no trap on the host for it)
     while ((1ull << s) < d) ++s;
     return {(uint32_t)((1ull << (31 + s)) / d) + 1u, s};
 }
 
-// (of 2 n, so that a divisor of one is no case apart: at the start of a workgroup's life a branch costs more than a shift)
 __host__ __device__ inline uint32_t fast_div(uint32_t n, const Divisor &d) { return (uint32_t)(((uint64_t)(2u * n) * d.mul) >> 32) >> d.shift; }
 
 // ---- launchers (each validates nothing: the C entry points did) -----------------------------

@@ -23,6 +23,8 @@ extern "C" long long wrong(unsigned d)
                 if (n <= top && fast_div((unsigned)n, D) != n / d) ++bad;
     return bad + (fast_div((unsigned)top, D) != top / d);
 }
+extern "C" unsigned shift(unsigned d) { return make_divisor(d).shift; }
+extern "C" unsigned by_none(unsigned n) { return fast_div(n, make_divisor(0)); }
 """
 
 
@@ -37,6 +39,10 @@ def test_quotients(tmp_path):
                     "-I", os.path.join(ROOT, "paper_2110_09195_amd", "csrc"), src, "-o", lib], check=True)
     L = ctypes.CDLL(lib)
     L.wrong.argtypes, L.wrong.restype = [ctypes.c_uint], ctypes.c_longlong
+    for f in (L.shift, L.by_none):
+        f.argtypes, f.restype = [ctypes.c_uint], ctypes.c_uint
     around = {v for s in range(31) for v in (2 ** s - 1, 2 ** s, 2 ** s + 1) if 1 <= v < 2 ** 31}
     for d in sorted(around | set(range(1, 2000)) | {3 ** i for i in range(19)}):
         assert L.wrong(d) == 0, d
+        assert (L.shift(d) == 0) == (d == 1), d
+    assert [L.by_none(n) for n in (0, 7, 2 ** 31 - 1)] == [0, 7, 2 ** 31 - 1]        # (a size that does not exist: through, and no trap)

@@ -1552,13 +1552,16 @@ int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, flo
         if (!plans[l].ok) return SNN_ERR_UNSUPPORTED;
         order[l] = l;
     }
-    // Order of the layers.  Outputs that the last-level cache (256 MB) takes up beside what else a pass writes: the layers whose workgroups
-    // run longest from one end and the shortest, which are mostly stores, from the other in turn, so that stores and matrix
-    // work overlap and no long workgroup is left to run alone at the end.  More: the short ones first, the stores that the cache has taken up
-    // drain while the long ones multiply.  Measured, short first / both ends in turn (pack and projection included where they are
-    // part of the call): 32-layer stack batch 4 (43 MB) 41 / 36 us, batch 8 56 / 54, batch 16 (170 MB) 92.8 / 93.8; 16-layer stack batch 16
-    // (84 MB) 77.2 / 74.9, batch 37 (194 MB) 102.5 / 109.1, batch 48 (251 MB) 130 / 138, batch 64 (335 MB) 183 / 193; the long ones first without
-    // the turns: 53.8 -> 56.5 and 193 -> 202; all layers mixed in proportion to their size: 58 and 217 (stores to many tensors at a time).
+    // Order of the layers.  Outputs that the last-level cache (256 MB) takes up: the layers whose workgroups run longest from one end and the
+    // shortest, which are mostly stores, from the other in turn, so that stores and matrix work overlap and no long
+    // workgroup is left to run alone at the end.  More, or so much beside real-valued kernels that the call has projected, which come through that
+    // cache as well: the short ones first, the stores that the cache has taken up drain while the long ones multiply.  Measured, short
+    // first / both ends in turn, with the policy below (pack and projection included where they are part of the call; A: the 16-layer stack,
+    // 43 MB of kernels, B: the 32-layer stack, 76 MB, C: 18 small layers, 1 MB), MB of output in brackets: A batch 16 (92) 65.8 / 60.4, batch 32 (184)
+    // 102 / 96, batch 44 (253) 129 / 125, prepared 63.0 / 59.5, batch 64 (368) 180 / 182; A on 200x200 images batch 45 (212) 160 / 130; B batch 4 (42) 61 / 56,
+    // batch 20 (211) 126 / 122, batch 24 (253) 143 / 146 on two cards, 150 / 146 on another, prepared 72 / 63, batch 32 (337) 181 / 189; C batch 256
+    // (168) 90 / 86, batch 384 (252) 130 / 125, batch 512 (336) 167 / 162.  The long ones first without the turns: B batch 8 53.8 -> 56.5,
+    // A batch 64 193 -> 202; all layers mixed in proportion to their size: 58 and 217 (stores to many tensors at a time).
     // Cache policy: non-temporal, but where the order takes turns the outputs whose runs share lines stay in L2, 16-layer stack batch 16
     // 53.7 -> 51.7, batch 32 95.6 -> 88.8, 32-layer stack batch 8 55.2 -> 53.2, batch 16 93.8 -> 86.7; not below 64 MB (32-layer stack batch 4
     // 36.0 -> 37.5), and where the short ones go first it is 165 -> 179 (batch 64).  Where the call has projected more than 60 MB of
@@ -1570,7 +1573,7 @@ int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, flo
         out_bytes += 4 * gs[l].P * gs[l].C_out;
         if (projected) kernel_bytes += (int64_t)36 * gs[l].C_in * gs[l].C_out;
     }
-    const bool fold = out_bytes <= (int64_t)176 << 20;
+    const bool fold = out_bytes <= (int64_t)256 << 20 && out_bytes + kernel_bytes <= (int64_t)304 << 20;
     const bool cached = fold && out_bytes >= (int64_t)64 << 20 && kernel_bytes <= (int64_t)60 << 20;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return fold ? length(a) > length(b) : length(a) < length(b); });
     for (int at = 0; at < n_layers;) {

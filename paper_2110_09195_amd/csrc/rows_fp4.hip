@@ -1562,11 +1562,12 @@ int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, flo
     // batch 20 (211) 126 / 122, batch 24 (253) 143 / 146 on two cards, 150 / 146 on another, prepared 72 / 63, batch 32 (337) 181 / 189; C batch 256
     // (168) 90 / 86, batch 384 (252) 130 / 125, batch 512 (336) 167 / 162.  The long ones first without the turns: B batch 8 53.8 -> 56.5,
     // A batch 64 193 -> 202; all layers mixed in proportion to their size: 58 and 217 (stores to many tensors at a time).
-    // Cache policy: non-temporal, but where the order takes turns the outputs whose runs share lines stay in L2, 16-layer stack batch 16
-    // 53.7 -> 51.7, batch 32 95.6 -> 88.8, 32-layer stack batch 8 55.2 -> 53.2, batch 16 93.8 -> 86.7; not below 64 MB (32-layer stack batch 4
-    // 36.0 -> 37.5), and where the short ones go first it is 165 -> 179 (batch 64).  Where the call has projected more than 60 MB of
-    // real-valued kernels, which come through L2 as well, it is the slower one: forward pass of the 32-layer stack (76 MB) batch 7 71.6 -> 74.3, batch 10
-    // 80.5 -> 83.0, batch 16 113.8 -> 116.6, of the 16-layer stack (43 MB) batch 16 65.2 -> 61.8, batch 28 96.8 -> 91.6.
+    // Cache policy: non-temporal, but where the order takes turns the outputs whose runs share lines stay in L2, non-temporal -> in L2: A batch 16
+    // 65.0 -> 60.4, batch 32 107 -> 97, prepared 55 -> 46; A on 200x200 images, most of whose planes share lines, batch 12 (56) 55 -> 49, batch 45 150 -> 127,
+    // prepared batch 12 28.7 -> 21.8; B prepared batch 10 34.6 -> 30.7, batch 24 73 -> 67; below 48 MB not, B batch 4 (42) 54.4 -> 55.1, prepared
+    // 19.27 -> 19.35 (A batch 8 (46) 48.3 -> 47.2, prepared 20.0 -> 19.8).  Beside more than 60 MB of projected kernels up to 176 MB alone: B batch 7 68.7 -> 66.6,
+    // batch 10 76.3 -> 73.9, batch 16 (168) 108.5 -> 109.3, 106.6 -> 107.1 and 108.6 -> 106.4 on three cards, batch 20 (211) 122 -> 127; B without its
+    // last layer (67 MB of kernels) batch 7 63.6 -> 61.9, batch 12 90 -> 85, batch 16 105 -> 100.  (Where the short ones go first: A batch 64 165 -> 179.)
     auto length = [&](int l) { return (int64_t)plans[l].ncb * plans[l].PB * plans[l].CB; };
     int64_t out_bytes = 0, kernel_bytes = 0;
     for (int l = 0; l < n_layers; ++l) {
@@ -1574,7 +1575,7 @@ int launch_rows_fp4_many(int n_layers, const Geom *gs, const void *const *x, flo
         if (projected) kernel_bytes += (int64_t)36 * gs[l].C_in * gs[l].C_out;
     }
     const bool fold = out_bytes <= (int64_t)256 << 20 && out_bytes + kernel_bytes <= (int64_t)304 << 20;
-    const bool cached = fold && out_bytes >= (int64_t)64 << 20 && kernel_bytes <= (int64_t)60 << 20;
+    const bool cached = fold && out_bytes >= (int64_t)48 << 20 && (kernel_bytes <= (int64_t)60 << 20 || out_bytes <= (int64_t)176 << 20);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return fold ? length(a) > length(b) : length(a) < length(b); });
     for (int at = 0; at < n_layers;) {
         RfMany m;

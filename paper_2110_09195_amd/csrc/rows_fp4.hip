@@ -258,18 +258,18 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     // 14x14 batch 128 14.5 -> 13.6, 100 -> 150 37x53 stride 2 batch 12 12.2 -> 10.0.  Several layers in one launch are bound by memory:
     // two at a time 180.2 us for the ResNet-18 stack's forward pass, four 183.7, one 182.5.
     const uint32_t xplane = (uint32_t)(L.H * L.WW) * 4u;
-    // the images from the tile's first on, `words` 32-bit words each (of those that a tile touches: < 2 GiB)
-    auto images = [&](const void *base, int C, int words) {
+    // the images from the tile's first on, of C planes each (of those that a tile touches: < 2 GiB)
+    auto images = [&](const void *base, int C, uint32_t plane_bytes) {
         if constexpr (PACED) {
-            const int64_t image_words = (int64_t)C * words;
+            const int64_t image_words = (int64_t)C * (int)(plane_bytes >> 2);
             const int64_t left = (int64_t)(L.N - n0) * image_words * 4;
             return make_rsrc((const uint32_t *)base + (int64_t)n0 * image_words, (uint32_t)min(left, (int64_t)0x7fffffff));
         } else {
-            const uint32_t image_bytes = (uint32_t)(C * words) * 4u;
+            const uint32_t image_bytes = (uint32_t)C * plane_bytes;
             return make_rsrc((const char *)base + (uint64_t)(uint32_t)n0 * image_bytes, (uint32_t)n_images * image_bytes);
         }
     };
-    const __amdgpu_buffer_rsrc_t xres = images(L.x, L.C_in, L.H * L.WW);
+    const __amdgpu_buffer_rsrc_t xres = images(L.x, L.C_in, xplane);
     const int RW = nrows * L.WW, nk = (RW + 15) >> 4;
     const int grp = lane & 3;
     struct Task {
@@ -353,7 +353,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
         }
     };
     // Packed channels [N][H][W][ncb]: a thread takes whole pixels of the tile, zero pixels included, two at a time.
-    const __amdgpu_buffer_rsrc_t cres = images(L.x, L.ncb, L.H * L.W);
+    const __amdgpu_buffer_rsrc_t cres = images(L.x, 1, (uint32_t)(L.H * L.W * L.ncb) * 4u);
     auto fill_channels = [&](int cb_first, int ncb) {
         const int n_px = nrows * W1 + 1;
         for (int q0 = tid; q0 < n_px; q0 += 512) {
@@ -819,7 +819,7 @@ __device__ __forceinline__ void rf_tile(const RfLayer &L, uint32_t wg, unsigned 
     // ---- y = alpha * S -------------------------------------------------------------------------------------------------
     // Lanes 0..31 of a register are 32 consecutive pixels of one channel; register r is channel 8 (r / 4) + 4 h + r % 4.
     const uint32_t chan = (uint32_t)L.HoWo * 4u;
-    const __amdgpu_buffer_rsrc_t yres = images(L.out, L.C_out, L.HoWo);
+    const __amdgpu_buffer_rsrc_t yres = images(L.out, L.C_out, chan);
     auto store = [&](auto policy) {
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {

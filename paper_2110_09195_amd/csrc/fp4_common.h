@@ -30,6 +30,8 @@ constexpr int AUX_CACHED = 0, AUX_NT = 2 /* nt */, AUX_THROUGH = 16 /* sc1 */;  
 //                13.0 / 13.6 / 12.4, 16.8 / 17.2 / 24.1, batch 256 (49) 20.3 / 29.8 / 21.9, 25.1 / 29.4 / 39.3; 64 -> 512 13x13 batch 64 (21)
 //                9.4 / 10.2 / 10.2, 13.1 / 13.2 / 20.6, batch 256 (84) 21.6 / 39.5 / 39.1, 27.5 / 41.2 / 59.7; 100 -> 150 31x31 batch 256 (141)
 //                46.7 / 53.4 / 100.8, 49.3 / 55.2 / 106.6
+// Written to memory (WRITE_SIZE, MiB, in the same order): half lines, batch 128 (49.0) 49.1 / 53.7 / 49.0; neither, 256 -> 256 batch 128 (24.5) 24.6 / 26.2 /
+// 28.0, 64 -> 512 batch 256 (84.5) 85.7 / 109.0 / 106.4: lines that two tiles share are written once from L2.
 // Runs that share lines stay in L2 at every size: through is up to a tenth faster warm and half as slow again after other writes.  Non-temporal
 // is the faster one of two after other writes up to some 18 MB, by 1 to 9 % (at the 9 to 18 MB that fill part of L2 most), and warm
 // there on some cards (12 MB above, by 2 %) but not on others (the same layer 9.0 / 9.5, 128 -> 300 7.3 / 7.9, 1x1 256 -> 1024 6.1 / 7.0).

@@ -9,7 +9,7 @@ import collections
 import csv
 import sys
 
-WANTED = ("rows_fp4", "subbit_", "bnn_", "pack_", "dense_", "copy_kernel", "project")
+WANTED = ("rows_fp4", "subbit_", "bnn_", "pack_", "dense_", "copy_kernel", "project", "conv1x1_fp4")
 
 
 def short(name):
